@@ -39,7 +39,7 @@ LINK_FLAGS = [f"--offload-arch={ARCH}", "-shared", "-fPIC"]
 # one-face-per-lane adjoint ran 18-24 % slower under it and keeps the default, as do the
 # other sources (some lose occupancy under it).
 FILE_FLAGS = {
-    name: ["-mllvm", "--amdgpu-sched-strategy=max-ilp"] for name in ("wn_fwd.hip", "wn_batched.hip", "wn_bwd_pairs.hip")
+    name: ["-mllvm", "--amdgpu-sched-strategy=max-ilp"] for name in ("wn_fwd.hip", "wn_batched.hip", "wn_bwd_pairs.hip", "wn_cycle.hip")
 }
 
 

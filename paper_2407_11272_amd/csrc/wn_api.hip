@@ -9,7 +9,7 @@
 #include <string>
 #include <vector>
 
-#include "wn_internal.hpp"
+#include "wn_cycle.hpp"
 
 using namespace wn;
 
@@ -50,6 +50,11 @@ size_t voxelize_ws(int64_t nR, int64_t nQ) {
     return b;
 }
 
+// The boundary path's table and scratch, after the all-pairs workspace.
+size_t cycle_ws(int64_t nV, int64_t nF, int64_t nQ) {
+    return cyc_wanted(nV, nF, nQ) ? kCycTable + cyc_bytes(nV, nF, nQ) : 0;
+}
+
 size_t loss_ws(int64_t n) { return kWsHeader + align_up((size_t)loss_blocks(n) * sizeof(float)); }
 
 // Morphing workspace: one region shared in turn by the forward, the loss and the
@@ -81,7 +86,7 @@ size_t wn_workspace_size(int32_t op, int64_t nV, int64_t nF, int64_t nQ) {
     if (nV < 0 || nF < 0 || nQ < 0) return 0;
     switch (op) {
         case WN_OP_VOXELIZE:
-            return voxelize_ws(3 * nF, nQ);
+            return voxelize_ws(3 * nF, nQ) + cycle_ws(nV, nF, nQ);
         case WN_OP_BACKWARD:
             return bwd_workspace(nV, nF, nQ);
         case WN_OP_LOSS:
@@ -117,7 +122,8 @@ namespace wn {
 
 wn_status voxelize_impl(const float *V, int64_t nV, const int32_t *F, int64_t nF, const int32_t *R, int64_t nR,
                         const wn_grid *grid, const float *Q, int64_t nQ, float *W, int32_t occ_mode, float tau,
-                        float k, void *occ, void *ws, size_t ws_bytes, void *stream, const TuneConfig *force) {
+                        float k, void *occ, void *ws, size_t ws_bytes, void *stream, const TuneConfig *force,
+                        bool all_pairs) {
     if (!mesh_ok(V, nV, F, nF)) return WN_ERR_INVALID_ARG;
     if (R == nullptr) {
         if (nR != 0) return WN_ERR_INVALID_ARG;
@@ -147,14 +153,50 @@ wn_status voxelize_impl(const float *V, int64_t nV, const int32_t *F, int64_t nF
     OccParams op{occ, occ_mode, tau, k};
 
     const TuneConfig cfg = force ? *force : lookup_config(WN_OP_VOXELIZE, nF, P);
+    const PointSrc ps = make_point_src(grid, Q);
+    // The boundary path needs a grid, room after the all-pairs workspace, and, with a strip
+    // stream, room in the allocation-free entry point's array too (that entry point's
+    // results are bit-identical to this one's).
+    const size_t extra = cycle_ws(nV, nF, P);
+    const bool fits = R == nullptr || need > WN_NOALLOC_SCRATCH_BYTES || need + extra <= WN_NOALLOC_SCRATCH_BYTES;
+    const bool cyc = !all_pairs && grid != nullptr && extra > 0 && need + extra <= ws_bytes && fits &&
+                     cyc_grid_ok(*grid);
     hipError_t e = launch_ws_reset(hdr, s);
-    if (e == hipSuccess) e = launch_pack_records(V, nV, F, nF, R, nR, recs, hdr, s);
+    if (!cyc) {
+        if (e == hipSuccess) e = launch_pack_records(V, nV, F, nF, R, nR, recs, hdr, nullptr, nullptr, s);
+        if (e == hipSuccess) e = launch_fwd(recs, nR, ps, P, split, W, partials, op, cfg.ppl, cfg.depth, nullptr, nullptr,
+                           s);
+        return hip_status(e);
+    }
+    char *table = base + need;
+    CycMesh m{};
+    m.V = V;
+    m.F = F;
+    m.recs = recs;
+    m.nV = nV;
+    m.nF = nF;
+    m.nR = nR;
+    m.chunk = fwd_split_chunk(nR, split);
+    m.ps = ps;
+    m.n0 = grid->n[0];
+    m.strips = R != nullptr;
+    m.P = P;
+    m.W = W;
+    m.occ = op;
+    cyc_place(m, table + kCycTable);
+    CycHead h{};
+    h.meshes = sizeof(CycHead);
+    h.ppl = cfg.ppl;
+    cyc_units(m, h);
+    if (e == hipSuccess) e = launch_cyc_begin(m, h, table, s);
     if (e == hipSuccess)
-        e = launch_fwd(recs, nR, make_point_src(grid, Q), P, split, W, partials, op, cfg.ppl, cfg.depth, s);
+        e = launch_pack_records(V, nV, F, nF, R, nR, recs, hdr, R ? m.count : nullptr, &m.st->go, s);
+    if (e == hipSuccess) e = launch_cyc(h, table, false, s);
+    if (e == hipSuccess)
+        e = launch_fwd(recs, nR, ps, P, split, W, partials, op, cfg.ppl, cfg.depth, m.st, m.mark, s);
+    if (e == hipSuccess) e = launch_cyc_near(table, s);
     return hip_status(e);
 }
-
-size_t voxelize_workspace(int64_t nR, int64_t nQ) { return voxelize_ws(nR, nQ); }
 
 }  // namespace wn
 
@@ -503,8 +545,10 @@ wn_status wn_morph_step(float *V, int64_t nV, const int32_t *F, int64_t nF, cons
                 OccParams none{nullptr, WN_OCC_NONE, tau, k};
                 st = hip_status(launch_naive_fwd(V, nV, F, nF, ps, P, W, none, sub, ppl, s));
             } else {
+                // all pairs: Adam turns the rounding of vanishing gradients into whole steps, so
+                // a morph keeps one arithmetic
                 st = voxelize_impl(V, nV, F, nF, nullptr, 0, grid, nullptr, 0, W, WN_OCC_NONE, tau, k, nullptr, sub,
-                                   sub_bytes, stream, nullptr);
+                                   sub_bytes, stream, nullptr, true);
             }
             if (st != WN_OK) return st;
         }

@@ -22,7 +22,7 @@
 #include <tuple>
 #include <vector>
 
-#include "wn_internal.hpp"
+#include "wn_cycle.hpp"
 
 namespace wn {
 
@@ -42,6 +42,9 @@ struct BMesh {
     int64_t rec_off;    // first record of this mesh in the batch stream
     int64_t part_off;   // first partial-sum float of this mesh (chunks > 1)
     PointSrc ps;
+    CycState *st;       // boundary path (wn_cycle.hpp), or nullptr
+    uint32_t *mark;
+    int32_t *count;
     int32_t nF;
     int32_t chunks;
     int32_t pblocks;
@@ -61,11 +64,18 @@ struct BatchHeader {
     int64_t total_records;
     int64_t total_reduce_points;
     int64_t off_meshes, off_groups, off_face_prefix, off_reduce_ids, off_reduce_prefix, off_soup, off_part;
+    int64_t off_cyc, off_active_groups, off_active_ids, off_active_prefix;
     int32_t n_meshes;
     int32_t n_groups;
     int32_t n_reduce;
     int32_t ppl;
+    // of the groups and multi-chunk meshes that the all-pairs kernels are left with
+    int64_t active_units, active_points;
+    int32_t active_groups, active_reduce;
 };
+
+// The boundary path's table: its head at this place in every batch's tables.
+constexpr size_t kCycHeadAt = kWsHeader + (sizeof(BatchHeader) + 63) / 64 * 64;
 
 __device__ __forceinline__ const BatchHeader *bheader(const char *ws) {
     return reinterpret_cast<const BatchHeader *>(ws + kWsHeader);
@@ -114,7 +124,8 @@ __global__ __launch_bounds__(kBlock) void k_batched_pack(char *ws) {
         if (mh.R) {
             vid = mh.R[2 * r];
             fid = mh.R[2 * r + 1];
-            check_strip_record(mh.R, r, mh.F, mh.nF, fid, hdr);
+            check_strip_record(mh.R, r, mh.F, mh.nF, fid, hdr, mh.st ? &mh.st->go : nullptr);
+            if (mh.st && fid >= 0 && fid < mh.nF) atomicAdd(&mh.count[fid], 1);
         } else {
             const int64_t f = r / 3;
             const int j = (int)(r - 3 * f);
@@ -125,6 +136,67 @@ __global__ __launch_bounds__(kBlock) void k_batched_pack(char *ws) {
     }
 }
 
+// The groups and multi-chunk meshes that the all-pairs kernels have to run for, in order,
+// with their units and points renumbered.  One workgroup; a thread takes a consecutive
+// share of the items.
+constexpr int kActiveThreads = 1024;
+
+__global__ __launch_bounds__(kActiveThreads) void k_batched_active(char *ws) {
+    __shared__ int64_t sums[2][kActiveThreads];
+    BatchHeader *bh = reinterpret_cast<BatchHeader *>(ws + kWsHeader);
+    const BMesh *meshes = reinterpret_cast<const BMesh *>(ws + bh->off_meshes);
+    const int tid = threadIdx.x;
+    auto runs = [&](int32_t m) { return meshes[m].st == nullptr || meshes[m].st->go != 0; };
+    // size(i): units of item i where it runs, else -1; put(place, units before, i)
+    auto compact = [&](int32_t n, auto size, auto put, int32_t &kept, int64_t &total) {
+        const int32_t per = (n + kActiveThreads - 1) / kActiveThreads;
+        const int32_t i0 = min(n, tid * per), i1 = min(n, i0 + per);
+        int64_t items = 0, units = 0;
+        for (int32_t i = i0; i < i1; ++i) {
+            const int64_t x = size(i);
+            if (x >= 0) ++items, units += x;
+        }
+        sums[0][tid] = items;
+        sums[1][tid] = units;
+        __syncthreads();
+        for (int o = 1; o < kActiveThreads; o <<= 1) {
+            const int64_t a = tid >= o ? sums[0][tid - o] : 0, b = tid >= o ? sums[1][tid - o] : 0;
+            __syncthreads();
+            sums[0][tid] += a;
+            sums[1][tid] += b;
+            __syncthreads();
+        }
+        int64_t at = sums[0][tid] - items, before = sums[1][tid] - units;
+        for (int32_t i = i0; i < i1; ++i) {
+            const int64_t x = size(i);
+            if (x < 0) continue;
+            put((int32_t)at++, before, i);
+            before += x;
+        }
+        if (tid == 0) {
+            kept = (int32_t)sums[0][kActiveThreads - 1];
+            total = sums[1][kActiveThreads - 1];
+        }
+        __syncthreads();
+    };
+    const BGroup *groups = reinterpret_cast<const BGroup *>(ws + bh->off_groups);
+    BGroup *active = reinterpret_cast<BGroup *>(ws + bh->off_active_groups);
+    compact(
+        bh->n_groups, [&](int32_t i) { return runs(groups[i].mesh) ? (int64_t)meshes[groups[i].mesh].pblocks : -1; },
+        [&](int32_t at, int64_t before, int32_t i) { active[at] = BGroup{before, groups[i].mesh, groups[i].chunk}; },
+        bh->active_groups, bh->active_units);
+    const int32_t *rids = reinterpret_cast<const int32_t *>(ws + bh->off_reduce_ids);
+    int32_t *arids = reinterpret_cast<int32_t *>(ws + bh->off_active_ids);
+    int64_t *arpre = reinterpret_cast<int64_t *>(ws + bh->off_active_prefix);
+    compact(
+        bh->n_reduce, [&](int32_t i) { return runs(rids[i]) ? meshes[rids[i]].P : (int64_t)-1; },
+        [&](int32_t at, int64_t before, int32_t i) {
+            arids[at] = rids[i];
+            arpre[at] = before;
+        },
+        bh->active_reduce, bh->active_points);
+}
+
 // Persistent workgroups: take units from the cursor until the list is exhausted.
 template <int PPL, int DEPTH>
 __global__ __launch_bounds__(kBlock) void k_batched_persistent(char *ws) {
@@ -133,12 +205,12 @@ __global__ __launch_bounds__(kBlock) void k_batched_persistent(char *ws) {
     __shared__ int32_t s_group;
     const BatchHeader *bh = bheader(ws);
     const BMesh *meshes = reinterpret_cast<const BMesh *>(ws + bh->off_meshes);
-    const BGroup *groups = reinterpret_cast<const BGroup *>(ws + bh->off_groups);
+    const BGroup *groups = reinterpret_cast<const BGroup *>(ws + bh->off_active_groups);
     const float4 *recs = reinterpret_cast<const float4 *>(ws + bh->off_soup);
     float *part = reinterpret_cast<float *>(ws + bh->off_part);
     WsHeader *hdr = reinterpret_cast<WsHeader *>(ws);
-    const int64_t n_units = bh->n_units;
-    const int32_t n_groups = bh->n_groups;
+    const int64_t n_units = bh->active_units;
+    const int32_t n_groups = bh->active_groups;
     const int tid = threadIdx.x;
     for (;;) {
         __syncthreads();  // the previous unit's tile reads and s_* reads are done
@@ -173,7 +245,7 @@ __global__ __launch_bounds__(kBlock) void k_batched_persistent(char *ws) {
             const float tot = s[p] + c[p];
             if (mh.chunks > 1) {
                 part[mh.part_off + (int64_t)gr.chunk * mh.P + idx] = tot;
-            } else {
+            } else if (go_writes(mh.st, mh.mark, idx)) {
                 const float w = tot * kInv2Pi;
                 mh.W[mh.p0 + idx] = w;
                 write_occ(OccParams{mh.occ, mh.occ_mode, mh.tau, mh.k}, mh.p0 + idx, w);
@@ -186,15 +258,16 @@ __global__ __launch_bounds__(kBlock) void k_batched_persistent(char *ws) {
 __global__ __launch_bounds__(kBlock) void k_batched_reduce(char *ws) {
     const BatchHeader *bh = bheader(ws);
     const BMesh *meshes = reinterpret_cast<const BMesh *>(ws + bh->off_meshes);
-    const int32_t *rids = reinterpret_cast<const int32_t *>(ws + bh->off_reduce_ids);
-    const int64_t *rpre = reinterpret_cast<const int64_t *>(ws + bh->off_reduce_prefix);
+    const int32_t *rids = reinterpret_cast<const int32_t *>(ws + bh->off_active_ids);
+    const int64_t *rpre = reinterpret_cast<const int64_t *>(ws + bh->off_active_prefix);
     const float *part = reinterpret_cast<const float *>(ws + bh->off_part);
-    const int64_t total = bh->total_reduce_points;
+    const int64_t total = bh->active_points;
     for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < total;
          g += (int64_t)gridDim.x * blockDim.x) {
-        const int32_t r = upper_index(rpre, bh->n_reduce, g);
+        const int32_t r = upper_index(rpre, bh->active_reduce, g);
         const BMesh &mh = meshes[rids[r]];
         const int64_t idx = g - rpre[r];
+        if (!go_writes(mh.st, mh.mark, idx)) continue;
         float s = 0.0f, c = 0.0f;
         for (int32_t k = 0; k < mh.chunks; ++k) neumaier_add(s, c, part[mh.part_off + (int64_t)k * mh.P + idx]);
         const float w = (s + c) * kInv2Pi;
@@ -213,6 +286,7 @@ struct Plan {
     int64_t n_units = 0;
     int64_t total_faces = 0;
     int64_t total_reduce = 0;
+    CycHead cyc{};             // meshes on the boundary path (cyc.n of them)
 };
 
 bool desc_ok(const wn_mesh_desc &d) {
@@ -237,8 +311,11 @@ bool desc_ok(const wn_mesh_desc &d) {
     return true;
 }
 
-size_t tables_layout(int32_t n, int32_t n_groups, int32_t n_reduce, BatchHeader &h) {
-    size_t o = align_up(sizeof(BatchHeader), 64);
+size_t tables_layout(int32_t n, int32_t n_groups, int32_t n_reduce, int32_t n_cyc, BatchHeader &h) {
+    size_t o = kCycHeadAt - kWsHeader;
+    o += align_up(sizeof(CycHead), 64);
+    h.off_cyc = kWsHeader + o;
+    o += align_up(sizeof(CycMesh) * (size_t)n_cyc, 64);
     h.off_meshes = kWsHeader + o;
     o += align_up(sizeof(BMesh) * (size_t)n, 64);
     h.off_groups = kWsHeader + o;
@@ -256,8 +333,9 @@ int64_t mesh_records(const wn_mesh_desc &d) { return d.strips ? d.n_strip_record
 
 int32_t mesh_chunks(int64_t nR) { return nR > 0 ? (int32_t)((nR + kChunkRecords - 1) / kChunkRecords) : 1; }
 
-// Build the tables; ppl only changes the unit count, not any result.
-bool make_plan(const wn_mesh_desc *d, int32_t n, int32_t ppl, Plan &plan) {
+// Build the tables for workspace ws (without it, sizes alone); ppl only changes the unit
+// count, not any result.
+bool make_plan(const wn_mesh_desc *d, int32_t n, int32_t ppl, char *ws, Plan &plan) {
     std::vector<BMesh> meshes((size_t)n);
     struct G {
         int32_t faces, mesh, chunk;
@@ -301,6 +379,13 @@ bool make_plan(const wn_mesh_desc *d, int32_t n, int32_t ppl, Plan &plan) {
             gs.push_back(G{faces, m, c, b.pblocks});
         }
     }
+    // Meshes on the boundary path, largest first.
+    std::vector<int32_t> cyc_ids;
+    for (int32_t m = 0; m < n; ++m)
+        if (cyc_wanted(d[m].nV, d[m].nF, (int64_t)d[m].grid.n[0] * d[m].grid.n[1] * d[m].grid.n[2]) &&
+            cyc_grid_ok(d[m].grid))
+            cyc_ids.push_back(m);
+    std::stable_sort(cyc_ids.begin(), cyc_ids.end(), [&](int32_t a, int32_t b) { return d[a].nF > d[b].nF; });
     // Largest units first (longest-processing-time order); ties in table order.
     std::stable_sort(gs.begin(), gs.end(), [](const G &a, const G &b) { return a.faces > b.faces; });
     std::vector<BGroup> groups(gs.size());
@@ -313,7 +398,7 @@ bool make_plan(const wn_mesh_desc *d, int32_t n, int32_t ppl, Plan &plan) {
     BatchHeader h;
     memset(&h, 0, sizeof h);
     const int32_t n_reduce = (int32_t)rpre.size() - 1;
-    const size_t tbytes = tables_layout(n, (int32_t)groups.size(), n_reduce, h);
+    const size_t tbytes = tables_layout(n, (int32_t)groups.size(), n_reduce, (int32_t)cyc_ids.size(), h);
     h.n_units = units;
     h.total_records = fpre[(size_t)n];
     h.total_reduce_points = rpre.back();
@@ -323,13 +408,52 @@ bool make_plan(const wn_mesh_desc *d, int32_t n, int32_t ppl, Plan &plan) {
     h.ppl = ppl;
     h.off_soup = (int64_t)align_up(kWsHeader + tbytes);
     h.off_part = h.off_soup + (int64_t)align_up((size_t)h.total_records * sizeof(VRec));
-    plan.total_bytes = (size_t)h.off_part + align_up((size_t)part * sizeof(float));
+    size_t end = (size_t)h.off_part + align_up((size_t)part * sizeof(float));
+    h.off_active_groups = (int64_t)end;
+    end += align_up(sizeof(BGroup) * groups.size());
+    h.off_active_ids = (int64_t)end;
+    end += align_up(sizeof(int32_t) * (size_t)(n_reduce + 1));
+    h.off_active_prefix = (int64_t)end;
+    end += align_up(sizeof(int64_t) * (size_t)(n_reduce + 1));
+    std::vector<CycMesh> cyc(cyc_ids.size());
+    plan.cyc.meshes = h.off_cyc - (int64_t)kCycHeadAt;
+    plan.cyc.ppl = ppl;
+    for (size_t i = 0; i < cyc_ids.size(); ++i) {
+        BMesh &b = meshes[(size_t)cyc_ids[i]];
+        CycMesh &m = cyc[i];
+        memset(&m, 0, sizeof m);
+        m.V = b.V;
+        m.F = b.F;
+        m.nV = b.nV;
+        m.nF = b.nF;
+        m.nR = b.nR;
+        m.chunk = kChunkRecords;
+        m.ps = b.ps;
+        m.n0 = d[cyc_ids[i]].grid.n[0];
+        m.strips = b.R != nullptr;
+        m.p0 = b.p0;
+        m.P = b.P;
+        m.W = b.W;
+        m.occ = OccParams{b.occ, b.occ_mode, b.tau, b.k};
+        if (ws) {
+            m.recs = reinterpret_cast<const VRec *>(ws + h.off_soup) + b.rec_off;
+            cyc_place(m, ws + end);
+            b.st = m.st;
+            b.mark = m.mark;
+            b.count = m.count;
+            cyc_units(m, plan.cyc);
+        }
+        end += cyc_bytes(b.nV, b.nF, b.P);
+    }
+    plan.total_bytes = end;
     plan.n_units = units;
     plan.total_faces = h.total_records;
     plan.total_reduce = h.total_reduce_points;
     plan.tables.assign(tbytes, 0);
     char *t = plan.tables.data();
     memcpy(t, &h, sizeof h);
+    memcpy(t + (kCycHeadAt - kWsHeader), &plan.cyc, sizeof plan.cyc);
+    memcpy(t + (h.off_cyc - kWsHeader), cyc.data(), sizeof(CycMesh) * cyc.size());
     memcpy(t + (h.off_meshes - kWsHeader), meshes.data(), sizeof(BMesh) * meshes.size());
     memcpy(t + (h.off_groups - kWsHeader), groups.data(), sizeof(BGroup) * groups.size());
     memcpy(t + (h.off_face_prefix - kWsHeader), fpre.data(), sizeof(int64_t) * fpre.size());
@@ -350,7 +474,7 @@ struct Staging {
 
 struct WsState {
     std::vector<Staging> ring;
-    std::map<std::tuple<int, int, int, int>, hipGraphExec_t> graphs;  // (ppl, depth, persistent grid, device)
+    std::map<std::tuple<int, int, int, int, bool>, hipGraphExec_t> graphs;  // (ppl, depth, persistent grid, device, boundary path)
 };
 
 constexpr size_t kMaxStaging = 64;  // buffers per workspace ring
@@ -372,10 +496,17 @@ int persistent_grid(int ppl, int depth, int wg_per_cu) {
     return cus * per;
 }
 
-hipError_t enqueue_kernels(char *ws, int ppl, int depth, int grid, hipStream_t s) {
+hipError_t enqueue_kernels(char *ws, int ppl, int depth, int grid, bool cyc, hipStream_t s) {
+    char *table = ws + kCycHeadAt;
     hipError_t e = launch_ws_reset(reinterpret_cast<WsHeader *>(ws), s);
+    if (e == hipSuccess && cyc) e = launch_cyc_clear(table, s);
     if (e != hipSuccess) return e;
     k_batched_pack<<<1024, kBlock, 0, s>>>(ws);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    CycHead h{};
+    h.ppl = ppl;
+    if (cyc && (e = launch_cyc(h, table, true, s)) != hipSuccess) return e;
+    k_batched_active<<<1, kActiveThreads, 0, s>>>(ws);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     e = with_config(ppl, depth, [&](auto P, auto D) {
         k_batched_persistent<decltype(P)::value, decltype(D)::value><<<grid, kBlock, 0, s>>>(ws);
@@ -383,7 +514,8 @@ hipError_t enqueue_kernels(char *ws, int ppl, int depth, int grid, hipStream_t s
     });
     if (e != hipSuccess) return e;
     k_batched_reduce<<<2048, kBlock, 0, s>>>(ws);
-    return hipGetLastError();
+    if ((e = hipGetLastError()) != hipSuccess || !cyc) return e;
+    return launch_cyc_near(table, s);
 }
 
 }  // namespace
@@ -391,7 +523,7 @@ hipError_t enqueue_kernels(char *ws, int ppl, int depth, int grid, hipStream_t s
 size_t batched_workspace(const wn_mesh_desc *d, int32_t n) {
     Plan p;
     if (n <= 0 || d == nullptr) return kWsHeader;
-    if (!make_plan(d, n, 1, p)) return 0;
+    if (!make_plan(d, n, 1, nullptr, p)) return 0;
     return p.total_bytes;
 }
 
@@ -406,7 +538,7 @@ wn_status run_batched(const wn_mesh_desc *d, int32_t n, int32_t flags, char *ws,
     const int ppl = valid_ppl(cfg.ppl) ? cfg.ppl : 1;
     const int depth = valid_depth(cfg.depth) ? cfg.depth : 1;
     Plan plan;
-    if (!make_plan(d, n, ppl, plan)) return WN_ERR_INVALID_ARG;
+    if (!make_plan(d, n, ppl, ws, plan)) return WN_ERR_INVALID_ARG;
     if (ws_bytes < plan.total_bytes) return WN_ERR_WORKSPACE;
     if (plan.n_units > (int64_t)1 << 40) return WN_ERR_UNSUPPORTED;
     const int grid = persistent_grid(ppl, depth, cfg.wg_per_cu);
@@ -417,6 +549,7 @@ wn_status run_batched(const wn_mesh_desc *d, int32_t n, int32_t flags, char *ws,
     std::lock_guard<std::mutex> lk(g_mu);
     WsState &st = g_state[ws];
     const size_t tb = plan.tables.size();
+    const bool cyc = plan.cyc.n > 0;
     // a staging buffer whose previous copy has finished, else a new one in the ring
     Staging *sb = nullptr;
     for (Staging &x : st.ring) {
@@ -452,14 +585,14 @@ wn_status run_batched(const wn_mesh_desc *d, int32_t n, int32_t flags, char *ws,
     if (hipMemcpyAsync(ws + kWsHeader, sb->buf, tb, hipMemcpyHostToDevice, s) != hipSuccess) return WN_ERR_HIP;
     if (hipEventRecord(sb->copied, s) != hipSuccess) return WN_ERR_HIP;
 
-    if (flags & WN_BATCH_NO_GRAPH) return enqueue_kernels(ws, ppl, depth, grid, s) == hipSuccess ? WN_OK : WN_ERR_HIP;
+    if (flags & WN_BATCH_NO_GRAPH) return enqueue_kernels(ws, ppl, depth, grid, cyc, s) == hipSuccess ? WN_OK : WN_ERR_HIP;
 
-    auto key = std::make_tuple(ppl, depth, grid, dev);
+    auto key = std::make_tuple(ppl, depth, grid, dev, cyc);
     auto it = st.graphs.find(key);
     if (it == st.graphs.end()) {
         if (!g_capture && hipStreamCreateWithFlags(&g_capture, hipStreamNonBlocking) != hipSuccess) return WN_ERR_HIP;
         if (hipStreamBeginCapture(g_capture, hipStreamCaptureModeRelaxed) != hipSuccess) return WN_ERR_HIP;
-        hipError_t e = enqueue_kernels(ws, ppl, depth, grid, g_capture);
+        hipError_t e = enqueue_kernels(ws, ppl, depth, grid, cyc, g_capture);
         hipGraph_t graph = nullptr;
         hipError_t e2 = hipStreamEndCapture(g_capture, &graph);
         if (e != hipSuccess || e2 != hipSuccess || !graph) {

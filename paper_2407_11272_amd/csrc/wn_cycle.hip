@@ -1,0 +1,1078 @@
+// Forward by the boundary of the mesh; see wn_cycle.hpp for the identity.
+//
+// Steps, each a launch over all meshes of a call:
+//   begin   clear the chains and the crossing counts (kept in W);
+//   faces   chain every half-edge by its undirected edge; crossings of the small faces
+//           with the columns of voxels, and the voxels close to them;
+//   mark    half-edges whose undirected edge does not cancel: the mesh's boundary;
+//   caps    (one workgroup per mesh) join the boundary edges to loops, fill each loop with
+//           a zigzag strip of triangles;
+//   slabs   crossings of the large faces and the caps;
+//   columns winding number of M - C at every voxel from the crossings above it, and the
+//           list of voxels close to a face;
+//   sum     solid angles of the caps at every voxel, W and occupancy;
+//   near    the direct sum at the listed voxels.
+// A mesh that the path does not suit (an edge used three times the same way, a
+// boundary longer than the face count, coordinates out of range, a strip stream that
+// does not name every face once) sets `go` and the all-pairs kernels, launched after
+// `sum`, run for it; otherwise they leave at once.  More voxels than the list holds are
+// marked, and the all-pairs kernels run for the marked ones.
+#include "wn_cycle.hpp"
+
+#include <algorithm>
+#include <cmath>
+
+namespace wn {
+
+namespace {
+
+constexpr int kChainLimit = 1024;   // half-edges looked at per chain before giving up
+constexpr int kDegreeLimit = 1024;  // boundary edges looked at per vertex
+constexpr float kCoordMax = 1.0e9f; // coordinates beyond this (or not finite) go direct
+
+__device__ __forceinline__ const CycMesh *meshes_of(const char *table) {
+    return reinterpret_cast<const CycMesh *>(table + reinterpret_cast<const CycHead *>(table)->meshes);
+}
+
+template <int64_t CycMesh::*First>
+__device__ __forceinline__ const CycMesh *find_mesh(const char *table, int64_t u) {
+    const CycHead *h = reinterpret_cast<const CycHead *>(table);
+    const CycMesh *m = meshes_of(table);
+    int lo = 0, hi = h->n - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (m[mid].*First <= u)
+            lo = mid;
+        else
+            hi = mid - 1;
+    }
+    return m + lo;
+}
+
+__device__ __forceinline__ int32_t face_vertex(const CycMesh &m, int64_t h) {
+    const int32_t v = m.F[h];
+    return (v < 0 || (int64_t)v >= m.nV) ? 0 : v;  // as the packs replace them
+}
+
+// Half-edge h = 3 f + j runs from corner j to corner j + 1 of face f.
+__device__ __forceinline__ void half_edge(const CycMesh &m, int64_t h, int32_t &u, int32_t &v) {
+    const int64_t f = h / 3;
+    const int j = (int)(h - 3 * f);
+    u = face_vertex(m, h);
+    v = face_vertex(m, 3 * f + (j == 2 ? 0 : j + 1));
+}
+
+// Crossing counts live in the W array until the columns are summed: a bias that keeps them
+// positive, and the top bit for "close to a face".
+constexpr uint32_t kCountBias = 0x40000000u, kCloseBit = 0x80000000u;
+
+__device__ void clear_unit(const CycMesh &m, int64_t u) {
+    for (int64_t i = u * kCycClear + threadIdx.x; i < (u + 1) * kCycClear; i += kCycUnit) {
+        if (i < m.buckets) m.head[i] = -1;
+        if (i < m.nV) m.hout[i] = m.hin[i] = -1;
+        if (m.strips && i < m.nF) m.count[i] = 0;
+        if (i < m.P) reinterpret_cast<uint32_t *>(m.W)[m.p0 + i] = kCountBias;
+        if (32 * i < m.P) m.mark[i] = 0u;
+        if (i == 0) *m.st = CycState{};
+    }
+}
+
+__global__ __launch_bounds__(kCycUnit) void k_cyc_begin_one(CycMesh m, CycHead h, char *table) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        *reinterpret_cast<CycHead *>(table) = h;
+        *reinterpret_cast<CycMesh *>(table + h.meshes) = m;
+    }
+    clear_unit(m, blockIdx.x);
+}
+
+__global__ __launch_bounds__(kCycUnit) void k_cyc_clear(char *table) {
+    CycHead *h = reinterpret_cast<CycHead *>(table);
+    if (blockIdx.x == 0 && threadIdx.x == 0) h->cursor = 0ull;
+    for (int64_t u = blockIdx.x; u < h->u_clear; u += gridDim.x) {
+        const CycMesh &m = *find_mesh<&CycMesh::u_clear>(table, u);
+        clear_unit(m, u - m.u_clear);
+    }
+}
+
+// ------------------------------------------------------------------ crossings
+
+// Voxels closer to a triangle than this share of its extent are listed: there
+// the side of the triangle, and with it the jump of its solid angle, is near the rounding
+// of FP32 (about 4e-7 of the extent), and the all-pairs sum's own error grows as 1e-7
+// extent / distance.
+constexpr double kClose = 2.0e-4;
+
+// What edge (p, q) adds to the winding of its triangle's projection about (x, y): the
+// signed crossing with the ray towards +x.  The same for every face that uses the edge but
+// for the sign, so the windings of a closed surface's faces cancel exactly, whatever the
+// rounding.
+__device__ __forceinline__ int edge_crossing(double px, double py, double qx, double qy, double x, double y) {
+    const bool up = py <= y && qy > y, down = qy <= y && py > y;
+    if (!(up || down)) return 0;
+    const double lx = up ? px : qx, ly = up ? py : qy, ux = up ? qx : px, uy = up ? qy : py;
+    const double t = (x - lx) * (uy - ly);
+    return __builtin_fma(ux - lx, y - ly, -t) > 0.0 ? (up ? 1 : -1) : 0;
+}
+
+__device__ __forceinline__ float axis_centre(const PointSrc &ps, int d, int i) {
+    return __builtin_fmaf((float)i + 0.5f, ps.h[d], ps.lo[d]);
+}
+
+// Cells [a, b] of an axis whose centres may lie in [lo, hi] (all of them, and perhaps a
+// neighbour: the slack covers the rounding of the centres), within [first, last].
+__device__ __forceinline__ void cell_range(const CycMesh &m, int d, double lo, double hi, int first, int last, int &a,
+                                           int &b) {
+    const double z = m.ps.lo[d], inv = m.inv_h[d], slack = m.slack[d];
+    a = (int)fmin(fmax(ceil((lo - z) * inv - 0.5 - slack), (double)first), (double)last + 1.0);
+    b = (int)fmax(fmin(floor((hi - z) * inv - 0.5 + slack), (double)last), (double)first - 1.0);
+}
+
+// A triangle (a, b, c) for the columns of voxels: N, its range, and the cells it may meet.
+struct RasterFace {
+    double ax, ay, az, bx, by, bz, cx, cy, cz, nx, ny, nz, inv, zmin, zmax, eps, nn;
+    float lab, lbc, lca;  // eps times the edges' lengths in the x-y plane
+    int i0, i1, j0, j1;
+
+    __device__ __forceinline__ void set(const CycMesh &m, const float *a, const float *b, const float *c) {
+        ax = a[0], ay = a[1], az = a[2], bx = b[0], by = b[1], bz = b[2], cx = c[0], cy = c[1], cz = c[2];
+        const double e1x = bx - ax, e1y = by - ay, e1z = bz - az, e2x = cx - ax, e2y = cy - ay, e2z = cz - az;
+        nx = e1y * e2z - e1z * e2y, ny = e1z * e2x - e1x * e2z, nz = e1x * e2y - e1y * e2x;
+        inv = 1.0 / nz;
+        zmin = fmin(fmin(az, bz), cz), zmax = fmax(fmax(az, bz), cz);
+        const double x0 = fmin(fmin(ax, bx), cx), x1 = fmax(fmax(ax, bx), cx);
+        const double y0 = fmin(fmin(ay, by), cy), y1 = fmax(fmax(ay, by), cy);
+        eps = kClose * sqrt((x1 - x0) * (x1 - x0) + (y1 - y0) * (y1 - y0) + (zmax - zmin) * (zmax - zmin));
+        nn = sqrt(nx * nx + ny * ny + nz * nz) * eps;
+        const float e = (float)eps * 1.01f;
+        lab = e * length(bx - ax, by - ay), lbc = e * length(cx - bx, cy - by), lca = e * length(ax - cx, ay - cy);
+        cell_range(m, 0, x0 - eps, x1 + eps, m.i_first, m.i_last, i0, i1);
+        cell_range(m, 1, y0 - eps, y1 + eps, 0, m.ps.n1 - 1, j0, j1);
+    }
+    static __device__ __forceinline__ float length(double x, double y) { return fast_sqrt((float)(x * x + y * y)); }
+    // Whether (x, y) is inside, or within eps of, the triangle's projection (a superset near
+    // its corners; a projection that is a mere line keeps its own strip).
+    __device__ __forceinline__ bool over(double x, double y) const {
+        const double t = nz < 0.0 ? -1.0 : 1.0;
+        return t * ((bx - ax) * (y - ay) - (x - ax) * (by - ay)) >= -lab &&
+               t * ((cx - bx) * (y - by) - (x - bx) * (cy - by)) >= -lbc &&
+               t * ((ax - cx) * (y - cy) - (x - cx) * (ay - cy)) >= -lca;
+    }
+    __device__ __forceinline__ int64_t columns() const {
+        return i1 < i0 || j1 < j0 ? 0 : (int64_t)(i1 - i0 + 1) * (j1 - j0 + 1);
+    }
+    // Column (i, j): the crossing is counted at the last voxel below it (a column is summed
+    // from the top), and the voxels within eps are marked.
+    __device__ __forceinline__ void column(const CycMesh &m, int sign, int i, int j) const {
+        const int n2 = m.ps.n2;
+        const int64_t base = ((int64_t)i * m.ps.n1 + j) * n2;
+        const int first = base >= m.p0 ? 0 : (int)(m.p0 - base < n2 ? m.p0 - base : n2);  // voxels of this slice
+        const int last = (int)(m.p0 + m.P - base < n2 ? m.p0 + m.P - base : n2) - 1;
+        if (first > last) return;
+        uint32_t *count = reinterpret_cast<uint32_t *>(m.W) + base;
+        const double x = axis_centre(m.ps, 0, i), y = axis_centre(m.ps, 1, j);
+        const double off = nx * (ax - x) + ny * (ay - y);  // N . (a - (x, y, a.z))
+        const int w = edge_crossing(ax, ay, bx, by, x, y) + edge_crossing(bx, by, cx, cy, x, y) +
+                      edge_crossing(cx, cy, ax, ay, x, y);
+        if (w != 0) {
+            const double zf = fmin(fmax(az + off * inv, zmin), zmax);  // also a vertical sliver's NaN
+            int k = (int)fmin(fmax((zf - m.ps.lo[2]) * m.inv_h[2] - 0.5, 0.0), (double)n2);
+            while (k < n2 && (double)axis_centre(m.ps, 2, k) < zf) ++k;
+            while (k > 0 && !((double)axis_centre(m.ps, 2, k - 1) < zf)) --k;
+            k = min(k - 1, last);
+            if (k >= first) atomicAdd(&count[k], (uint32_t)(sign * w));
+        }
+        if (!over(x, y)) return;
+        double lo = zmin - eps, hi = zmax + eps;
+        if (fabs(nz) * (hi - lo) > 2.0e-3 * nn) {  // |N . (a - q)| <= |N| eps
+            const double zc = az + off * inv, dz = nn * fabs(inv);
+            lo = fmax(lo, zc - dz);
+            hi = fmin(hi, zc + dz);
+        } else if (fabs(off + nz * (az - lo)) > 1.01 * nn) {
+            return;
+        }
+        int ka, kb;
+        cell_range(m, 2, lo, hi, first, last, ka, kb);
+        for (int k = ka; k <= kb; ++k) atomicOr(&count[k], kCloseBit);
+    }
+};
+
+// Columns that a face's own lanes take; more are left to the slab list, 64 per entry.
+constexpr int kOwnColumns = 64;
+
+// Room for the columns on the raster list; false where there is none.
+__device__ __forceinline__ bool add_slabs(const CycMesh &m, int32_t id, int64_t columns) {
+    const int64_t n = (columns + 63) / 64;
+    if (n > m.slab_cap) return false;
+    const unsigned long long at = atomicAdd(&m.st->n_slab, (unsigned long long)n);
+    if (at + n > (unsigned long long)m.slab_cap) {
+        for (int64_t k = at; k < m.slab_cap; ++k) m.slab[k] = make_int2(-1, 0);  // what was left of it
+        return false;
+    }
+    for (int32_t k = 0; k < (int32_t)n; ++k) m.slab[at + k] = make_int2(id, k);
+    return true;
+}
+
+// The bucket of an undirected edge (l < u): a multiplicative hash.
+__device__ __forceinline__ int64_t edge_bucket(const CycMesh &m, int32_t l, int32_t u) {
+    const uint64_t x = ((uint64_t)(uint32_t)l << 32 | (uint32_t)u) * 0x9E3779B97F4A7C15ull;
+    return (int64_t)((x >> 32) & (uint64_t)(m.buckets - 1));
+}
+
+// Eight lanes per face: three chain its half-edges, all share its columns.  Bound by the
+// latency of the loads and of the FP64 chain per column, so the lanes go to more faces and
+// columns at a time rather than to a face's whole range.
+__global__ __launch_bounds__(kCycUnit) void k_cyc_faces(const char *table) {
+    constexpr int kFaces = kCycUnit / kCycFaceLanes;
+    const CycHead *h = reinterpret_cast<const CycHead *>(table);
+    const int part = threadIdx.x % kCycFaceLanes;
+    for (int64_t u = blockIdx.x; u < h->u_face; u += gridDim.x) {
+        const CycMesh &m = *find_mesh<&CycMesh::u_face>(table, u);
+        const int64_t f = (u - m.u_face) * kFaces + threadIdx.x / kCycFaceLanes;
+        uint32_t bits = 0;
+        if (f < m.nF) {
+            int32_t id[3];
+            float p[3][3];
+            for (int j = 0; j < 3; ++j) {
+                id[j] = face_vertex(m, 3 * f + j);
+                for (int c = 0; c < 3; ++c) {
+                    p[j][c] = m.V[3 * (int64_t)id[j] + c];
+                    bits = max(bits, __float_as_uint(__builtin_fabsf(p[j][c])));
+                }
+            }
+            if (part < 3) {
+                const int32_t a = part == 0 ? id[0] : part == 1 ? id[1] : id[2];
+                const int32_t b = part == 0 ? id[1] : part == 1 ? id[2] : id[0];
+                int4 x = make_int4(-1, -1, -1, 0);  // a degenerate edge bounds nothing
+                if (a != b) {
+                    x.y = min(a, b);
+                    x.z = max(a, b);
+                    x.w = a > b;
+                    x.x = atomicExch(&m.head[edge_bucket(m, x.y, x.z)], (int32_t)(3 * f + part));
+                }
+                m.ent[3 * f + part] = x;
+            }
+            if (bits <= __float_as_uint(kCoordMax)) {  // else the mesh goes direct
+                RasterFace r;
+                r.set(m, p[0], p[1], p[2]);
+                const int64_t n = r.columns();
+                int own = n <= kOwnColumns;
+                if (!own) {
+                    if (part == 0) own = !add_slabs(m, (int32_t)f, n);
+                    own = __shfl(own, (threadIdx.x & 63) - part);
+                }
+                if (own) {
+                    const int nj = r.j1 - r.j0 + 1;
+                    for (int c = part; c < (int)n; c += kCycFaceLanes) {
+                        const int i = c / nj;
+                        r.column(m, 1, r.i0 + i, r.j0 + c - i * nj);
+                    }
+                }
+            }
+        }
+        for (int o = 32; o > 0; o >>= 1) bits = max(bits, (uint32_t)__shfl_xor((int)bits, o));
+        if ((threadIdx.x & 63) == 0 && bits) atomicMax(&m.st->max_bits, bits);
+    }
+}
+
+// One thread per half-edge: the uses of an undirected edge in its two directions cancel; the first
+// half-edge of the direction that is left over stands for it.
+__global__ __launch_bounds__(kCycUnit) void k_cyc_mark(const char *table) {
+    __shared__ int32_t wave_n[kCycUnit / 64];
+    const CycHead *h = reinterpret_cast<const CycHead *>(table);
+    for (int64_t u = blockIdx.x; u < h->u_half; u += gridDim.x) {
+        const CycMesh &m = *find_mesh<&CycMesh::u_half>(table, u);
+        const int64_t unit = u - m.u_half, e = unit * kCycUnit + threadIdx.x;
+        bool keep = false;
+        if (e < 3 * m.nF) {
+            const int4 x = m.ent[e];
+            if (x.y != -1) {
+                int net = 0, steps = 0;
+                bool first = true;
+                for (int32_t k = m.head[edge_bucket(m, x.y, x.z)]; k >= 0; ++steps) {
+                    if (steps == kChainLimit) {
+                        atomicMax(&m.st->go, 2);
+                        break;
+                    }
+                    const int4 y = m.ent[k];
+                    if (y.y == x.y && y.z == x.z) {  // the same edge
+                        const bool same = y.w == x.w;
+                        net += same ? 1 : -1;
+                        first = first && !(same && k < (int32_t)e);
+                    }
+                    k = y.x;
+                }
+                keep = net > 0 && first;
+                if (net > 1) atomicMax(&m.st->go, 2);
+            }
+            if (m.strips && e < m.nF && m.count[e] != 1) atomicMax(&m.st->go, 2);
+        }
+        const unsigned long long mask = __builtin_amdgcn_ballot_w64(keep);
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        if (lane == 0) wave_n[wave] = __popcll(mask);
+        __syncthreads();
+        int base = 0, total = 0;
+        for (int w = 0; w < kCycUnit / 64; ++w) {
+            if (w < wave) base += wave_n[w];
+            total += wave_n[w];
+        }
+        if (keep) m.list[unit * kCycUnit + base + __popcll(mask & ((1ull << lane) - 1ull))] = (int32_t)e;
+        if (threadIdx.x == 0) m.blk[2 * unit] = total;
+        __syncthreads();
+    }
+}
+
+// Points at least this many times the longer of the edges v_0 v_1 and v_0 v_2 away from
+// v_0 use a triangle's far forms: there the squares differ by less than half, so the
+// differences lose no digits, and |angle| < 1 / 50.
+constexpr float kFar = 5.0f;
+
+__device__ TriRec tri_record(const RasterFace &f) {
+    TriRec t;
+    const double d1[3] = {f.bx - f.ax, f.by - f.ay, f.bz - f.az}, d2[3] = {f.cx - f.ax, f.cy - f.ay, f.cz - f.az};
+    auto dot = [](const double *x, const double *y) { return x[0] * y[0] + x[1] * y[1] + x[2] * y[2]; };
+    t.v[0] = (float)f.ax, t.v[1] = (float)f.ay, t.v[2] = (float)f.az;
+    for (int k = 0; k < 3; ++k) {
+        t.d[0][k] = (float)(2.0 * d1[k]);
+        t.d[1][k] = (float)(2.0 * d2[k]);
+    }
+    t.d[0][3] = (float)dot(d1, d1);
+    t.d[1][3] = (float)dot(d2, d2);
+    t.n[0] = (float)f.nx, t.n[1] = (float)f.ny, t.n[2] = (float)f.nz;
+    t.g = (float)dot(d1, d2);
+    t.far = kFar * kFar * fmaxf(t.d[0][3], t.d[1][3]);
+    return t;
+}
+
+constexpr int kCapThreads = 1024;
+constexpr int kCapLds = 4096;  // a boundary of at most so many edges is worked on in LDS
+
+// Exclusive sum over the workgroup; `total` gets the sum of all.
+__device__ __forceinline__ unsigned long long block_scan(unsigned long long x, unsigned long long *red,
+                                                         unsigned long long &total) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    unsigned long long s = x;
+    for (int o = 1; o < 64; o <<= 1) {
+        const unsigned long long y = __shfl_up(s, o);
+        if (lane >= o) s += y;
+    }
+    if (lane == 63) red[wave] = s;
+    __syncthreads();
+    unsigned long long before = 0;
+    total = 0;
+    for (int w = 0; w < kCapThreads / 64; ++w) {
+        if (w < wave) before += red[w];
+        total += red[w];
+    }
+    __syncthreads();
+    return before + s - x;
+}
+
+// Place of a loop's vertex r (of k) in its zigzag strip p0, p1, p(k-1), p2, p(k-2), ...
+__device__ __forceinline__ int zigzag(int r, int k) { return r == 0 ? 0 : (r <= k / 2 ? 2 * r - 1 : 2 * (k - r)); }
+
+// Loops by kind: triangles, other short loops, long loops; three counts of 21 bits.
+__device__ __forceinline__ int loop_kind(int k) { return k == 3 ? 0 : k <= kCycShortLoop ? 1 : 2; }
+__device__ __forceinline__ int count_of(unsigned long long x, int kind) { return (int)(x >> (21 * kind)) & 0x1fffff; }
+
+// One workgroup per mesh.  Boundary edges are numbered in half-edge order.  Three edges that
+// form a triangle are taken as a loop first (two missing faces that touch at a vertex would
+// otherwise become one loop of six); then an edge entering a vertex continues with the
+// leaving edge of the same rank there.  A loop starts at its lowest edge, so the cap stream
+// depends on F alone.  A loop of k edges becomes a strip of k records and k - 2 triangles.
+__global__ __launch_bounds__(kCapThreads) void k_cyc_caps(const char *table) {
+    __shared__ unsigned long long red[kCapThreads / 64];
+    __shared__ int2 s_edge[kCapLds];
+    __shared__ int32_t s_work[4][kCapLds];
+    __shared__ int32_t s_bad;
+    const CycHead *h = reinterpret_cast<const CycHead *>(table);
+    const CycMesh *meshes = meshes_of(table);
+    const int tid = threadIdx.x;
+    for (int mi = blockIdx.x; mi < h->n; mi += gridDim.x) {
+        const CycMesh &m = meshes[mi];
+        __syncthreads();
+        if (tid == 0) s_bad = 0;
+        const int64_t units = (3 * m.nF + kCycUnit - 1) / kCycUnit;
+        unsigned long long B64 = 0;
+        for (int64_t u0 = 0; u0 < units; u0 += kCapThreads) {
+            const int64_t u = u0 + tid;
+            const int n = u < units ? m.blk[2 * u] : 0;
+            unsigned long long all;
+            const unsigned long long at = block_scan((unsigned long long)n, red, all);
+            if (u < units) m.blk[2 * u + 1] = (int32_t)(B64 + at);
+            B64 += all;
+        }
+        const bool range = m.st->max_bits > __float_as_uint(kCoordMax);  // NaN bits are larger still
+        if (m.st->go || range || (int64_t)B64 > m.nF ||
+            (int64_t)B64 > kCycMaxEdges) {
+            if (tid == 0) atomicMax(&m.st->go, 2);
+            continue;
+        }
+        const int B = (int)B64;
+        if (B == 0) continue;
+        int n_tri = 0, n_short = 0;
+        // (a lambda's two instances, so that LDS is addressed as LDS)
+        auto join = [&](int2 *edge, int32_t *nout, int32_t *nin, int32_t *rank, int32_t *next) -> int {
+            __syncthreads();
+            for (int64_t u = tid >> 6; u < units; u += kCapThreads / 64) {
+                const int n = m.blk[2 * u], at = m.blk[2 * u + 1];
+                for (int x = tid & 63; x < n; x += 64) {
+                    int32_t a, b;
+                    half_edge(m, m.list[u * kCycUnit + x], a, b);
+                    edge[at + x] = make_int2(a, b);
+                }
+            }
+            __syncthreads();
+            for (int i = tid; i < B; i += kCapThreads) {
+                const int2 e = edge[i];
+                nout[i] = atomicExch(&m.hout[e.x], i);
+                nin[i] = atomicExch(&m.hin[e.y], i);
+            }
+            __syncthreads();
+            // the lowest triangle (by its edges in increasing order) that edge i is part of
+            auto triangle = [&](int i, int &to) -> unsigned long long {
+                const int2 e = edge[i];
+                unsigned long long best = ~0ull;
+                int steps = 0;
+                for (int j = m.hout[e.y]; j >= 0; j = nout[j])
+                    for (int k = m.hout[edge[j].y]; k >= 0; k = nout[k]) {
+                        if (++steps > kDegreeLimit) {
+                            s_bad = 1;
+                            return best;
+                        }
+                        if (edge[k].y != e.x) continue;
+                        const int lo = min(i, min(j, k)), hi = max(i, max(j, k)), mid = i + j + k - lo - hi;
+                        const unsigned long long id = (unsigned long long)lo << 40 | (unsigned long long)mid << 20 | hi;
+                        if (id < best) {
+                            best = id;
+                            to = j;
+                        }
+                    }
+                return best;
+            };
+            for (int i = tid; i < B; i += kCapThreads) {
+                int j = -1, k = -1, x = -1;
+                const unsigned long long id = triangle(i, j);
+                // a loop if its other two edges choose it as well
+                const bool loop = id != ~0ull && triangle(j, k) == id && triangle(k, x) == id;
+                next[i] = loop ? j : -1;
+            }
+            __syncthreads();
+            for (int i = tid; i < B; i += kCapThreads) {
+                const int2 e = edge[i];
+                int ro = 0, ri = 0, steps = 0;
+                for (int k = m.hout[e.x]; k >= 0 && steps < kDegreeLimit; k = nout[k], ++steps)
+                    ro += k < i && next[k] < 0;
+                for (int k = m.hin[e.y]; k >= 0 && steps < kDegreeLimit; k = nin[k], ++steps)
+                    ri += k < i && next[k] < 0;
+                if (steps >= kDegreeLimit) s_bad = 1;
+                rank[i] = ro | (ri << 16);
+            }
+            __syncthreads();
+            int32_t *len = nin;
+            for (int i = tid; i < B; i += kCapThreads) {
+                int to = next[i];
+                if (to < 0) {
+                    const int want = rank[i] >> 16;
+                    int steps = 0;
+                    for (int k = m.hout[edge[i].y]; k >= 0 && steps < kDegreeLimit; k = nout[k], ++steps)
+                        if (next[k] < 0 && (rank[k] & 0xffff) == want) to = k;
+                    if (to < 0) s_bad = 1;
+                }
+                len[i] = to;  // the others still read next[]
+            }
+            __syncthreads();
+            for (int i = tid; i < B; i += kCapThreads) next[i] = len[i];
+            __syncthreads();
+            if (s_bad) return -1;
+            // a loop's length at its lowest edge, 0 at the others
+            int32_t *off = rank;
+            for (int i = tid; i < B; i += kCapThreads) {
+                int n = 1;
+                for (int j = next[i]; j != i; j = next[j]) {
+                    if (j < i || n >= B) {
+                        n = 0;
+                        break;
+                    }
+                    ++n;
+                }
+                len[i] = n;
+            }
+            __syncthreads();
+            unsigned long long done = 0;  // records of each kind
+            for (int i0 = 0; i0 < B; i0 += kCapThreads) {
+                const int i = i0 + tid;
+                const int n = i < B ? len[i] : 0, kind = loop_kind(n);
+                unsigned long long all;
+                const unsigned long long at = done + block_scan((unsigned long long)n << (21 * kind), red, all);
+                if (n) off[i] = count_of(at, kind);
+                done += all;
+            }
+            const int first[3] = {0, count_of(done, 0), count_of(done, 0) + count_of(done, 1)};
+            if (first[2] + count_of(done, 2) != B) return -1;  // not a permutation (cannot be)
+            for (int i = tid; i < B; i += kCapThreads) {
+                const int k = len[i];
+                if (k == 0) continue;
+                const int at = off[i] + first[loop_kind(k)];
+                int j = i;
+                for (int r = 0; r < k; ++r) {
+                    const int pos = zigzag(r, k);
+                    m.cvid[at + pos] = edge[j].x;
+                    m.cpos[at + pos] = pos;
+                    j = next[j];
+                }
+            }
+            n_tri = first[1] / 3;
+            n_short = first[2];
+            return 0;
+        };
+        const int bad = B <= kCapLds ? join(s_edge, s_work[0], s_work[1], s_work[2], s_work[3])
+                                     : join(m.edge, m.nout, m.nin, m.rank, m.next);
+        if (bad) {
+            if (tid == 0) atomicMax(&m.st->go, 2);
+            continue;
+        }
+        __syncthreads();
+        for (int x = tid; x < B; x += kCapThreads) {
+            const int pos = m.cpos[x];
+            const int32_t c = m.cvid[x];
+            VRec r;
+            r.p = make_float4(m.V[3 * (int64_t)c], m.V[3 * (int64_t)c + 1], m.V[3 * (int64_t)c + 2], 0.0f);
+            r.n = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            if (pos >= 2) {
+                const int32_t a = m.cvid[x - 2], b = m.cvid[x - 1];
+                if (a != b && b != c && c != a) {
+                    RasterFace f;
+                    f.set(m, m.V + 3 * (int64_t)a, m.V + 3 * (int64_t)b, m.V + 3 * (int64_t)c);
+                    const double s = (pos & 1) ? -1.0 : 1.0;  // the zigzag turns every second triangle
+                    r.n = make_float4((float)(s * f.nx), (float)(s * f.ny), (float)(s * f.nz), 0.0f);
+                    r.p.w = 1.0f;
+                    if (!add_slabs(m, (int32_t)(m.nF + x), f.columns()))
+                        for (int i = f.i0; i <= f.i1; ++i)
+                            for (int j = f.j0; j <= f.j1; ++j) f.column(m, -1, i, j);
+                    if (x < 3 * n_tri) m.tri[x / 3] = tri_record(f);
+                }
+            }
+            m.caps[x] = r;
+        }
+        if (tid == 0) {
+            m.st->n_rec = B;
+            m.st->n_tri = n_tri;
+            m.st->n_short = n_short;
+        }
+    }
+}
+
+// One wave per entry of the raster list, one column per lane.
+__global__ __launch_bounds__(kCycUnit) void k_cyc_slabs(const char *table) {
+    const CycHead *h = reinterpret_cast<const CycHead *>(table);
+    const CycMesh *meshes = meshes_of(table);
+    const int lane = threadIdx.x & 63;
+    const int64_t waves = (int64_t)gridDim.x * (kCycUnit / 64);
+    const int64_t wave = __builtin_amdgcn_readfirstlane((int)blockIdx.x * (kCycUnit / 64) + (int)(threadIdx.x >> 6));
+    int64_t before = 0;
+    for (int mi = 0; mi < h->n; ++mi) {
+        const CycMesh &m = meshes[mi];
+        const unsigned long long asked = m.st->n_slab;
+        const int64_t n = asked < (unsigned long long)m.slab_cap ? (int64_t)asked : m.slab_cap;
+        if (m.st->go) continue;
+        for (int64_t x = (wave + waves - before % waves) % waves; x < n; x += waves) {
+            const int2 e = m.slab[x];
+            if (e.x < 0) continue;
+            RasterFace r;
+            int sign = 1;
+            if (e.x >= m.nF) {
+                const int32_t at = (int32_t)(e.x - m.nF);
+                const VRec *c = m.caps + at;
+                const bool turn = m.cpos[at] & 1;
+                r.set(m, &c[-2].p.x, turn ? &c[0].p.x : &c[-1].p.x, turn ? &c[-1].p.x : &c[0].p.x);
+                sign = -1;
+            } else {
+                const int64_t f = e.x;
+                r.set(m, m.V + 3 * (int64_t)face_vertex(m, 3 * f), m.V + 3 * (int64_t)face_vertex(m, 3 * f + 1),
+                      m.V + 3 * (int64_t)face_vertex(m, 3 * f + 2));
+            }
+            const int64_t c = (int64_t)e.y * 64 + lane;
+            if (c < r.columns()) {
+                const int nj = r.j1 - r.j0 + 1;
+                const int i = (int)(c / nj);
+                r.column(m, sign, r.i0 + i, r.j0 + (int)(c - (int64_t)i * nj));
+            }
+        }
+        before += n;
+    }
+}
+
+__device__ __forceinline__ void list_near(const CycMesh &m, int64_t idx) {
+    const int32_t x = (int32_t)(idx - m.p0);
+    const uint32_t bit = 1u << (x & 31);
+    if (atomicOr(&m.mark[x >> 5], bit) & bit) return;
+    const int32_t at = atomicAdd(&m.st->n_near, 1);
+    if (at < m.near_cap)
+        m.near[at] = x;
+    else
+        atomicMax(&m.st->go, 1);
+}
+
+// Close enough to the threshold for rounding to decide: the direct sum decides.
+__device__ __forceinline__ bool near_threshold(const OccParams &o, float w) {
+    return o.mode == WN_OCC_THRESHOLD && __builtin_fabsf(w - o.tau) < 1.0e-5f;
+}
+
+// One wave per column, from the top: W is the sum of the crossings at and above a voxel.
+__global__ __launch_bounds__(kCycColumns * 64) void k_cyc_columns(const char *table) {
+    const CycHead *h = reinterpret_cast<const CycHead *>(table);
+    const int lane = threadIdx.x & 63;
+    for (int64_t u = blockIdx.x; u < h->u_col; u += gridDim.x) {
+        const CycMesh &m = *find_mesh<&CycMesh::u_col>(table, u);
+        const int n2 = m.ps.n2;
+        const int64_t base = (m.p0 / n2 + (u - m.u_col) * kCycColumns + (threadIdx.x >> 6)) * n2;
+        const int64_t lo = base > m.p0 ? base : m.p0;
+        const int64_t hi = base + n2 < m.p0 + m.P ? base + n2 : m.p0 + m.P;
+        const bool last = m.st->n_rec == 0;  // no caps to add
+        int carry = 0;
+        for (int64_t top = hi; top > lo; top -= 64) {
+            const int64_t idx = top - 1 - lane;  // lane 0 is the highest voxel
+            const bool live = idx >= lo;
+            const uint32_t x = live ? reinterpret_cast<const uint32_t *>(m.W)[idx] : kCountBias;
+            int s = (int)(x & ~kCloseBit) - (int)kCountBias;
+            for (int o = 1; o < 64; o <<= 1) {
+                const int y = __shfl_up(s, o);
+                if (lane >= o) s += y;
+            }
+            s += carry;
+            carry = __shfl(s, 63);
+            if (!live) continue;
+            const float w = (float)s;
+            m.W[idx] = w;
+            bool near = (x & kCloseBit) != 0u;
+            if (last) {
+                write_occ(m.occ, idx, w);
+                near = near || near_threshold(m.occ, w);
+            }
+            if (near) list_near(m, idx);
+        }
+    }
+}
+
+// ------------------------------------------------------------------ caps' solid angles
+
+struct Slot64 {
+    double x, y, z, r, dprev, rprev;
+};
+
+__device__ __forceinline__ void enter64(const float4 v, const Slot64 &B, Slot64 &C, double qx, double qy, double qz) {
+    C.x = (double)v.x - qx;
+    C.y = (double)v.y - qy;
+    C.z = (double)v.z - qz;
+    const double d = C.x * C.x + C.y * C.y + C.z * C.z;
+    const double y = __builtin_amdgcn_rsq(d), g = d * y;  // one Newton step on the hardware's estimate
+    C.r = d > 0.0 ? __builtin_fma(g, __builtin_fma(-0.5 * y, g, 0.5), g) : 0.0;
+    C.dprev = B.x * C.x + B.y * C.y + B.z * C.z;
+    C.rprev = B.r * C.r;
+}
+
+__device__ __forceinline__ float half_angle64(const float4 n, const Slot64 &A, const Slot64 &B, const Slot64 &C) {
+    const double dca = C.x * A.x + C.y * A.y + C.z * A.z;
+    const double pr = B.rprev * C.r;
+    const double be = pr + B.dprev * C.r + C.dprev * A.r + dca * B.r;
+    const double al = A.x * n.x + A.y * n.y + A.z * n.z;
+    // any positive factor common to both will do: the approximate reciprocal keeps them in FP32's range
+    const double scale = pr > 0.0 ? __builtin_amdgcn_rcp(pr) : 0.0;
+    return atan2_eq8((float)(al * scale), (float)(be * scale));
+}
+
+// Long loops: the strips of a long loop hold thin triangles as long as the loop is wide, whose
+// terms near their two long edges lose half their digits in FP32 (beta cancels
+// to the product of two small angles); they are formed in FP64.  Every record completes a triangle, so this
+// costs about twice an FP32 strip record; boundaries are a small part of a mesh.
+__device__ __forceinline__ void sum_long(const VRec *__restrict__ recs, int n, float qx, float qy, float qz, float &s,
+                                         float &c) {
+    Slot64 A{}, B{}, C{};
+    const double x = qx, y = qy, z = qz;
+    float ts = 0.0f;
+    for (int i = 0; i < n; ++i) {
+        const float4 p = recs[i].p, nn = recs[i].n;
+        A = B;
+        B = C;
+        enter64(p, B, C, x, y, z);
+        if (p.w != 0.0f) ts += half_angle64(nn, A, B, C);
+        if ((i & 31) == 31 || i + 1 == n) {
+            neumaier_add(s, c, ts);
+            ts = 0.0f;
+        }
+    }
+}
+
+// Half solid angle of the triangle of records r[0..2] at (qx, qy, qz), as the all-pairs
+// kernel forms a lone face.
+__device__ __forceinline__ float tri_near(const VRec *__restrict__ r, float x, float y, float z) {
+    const float qx[1] = {x}, qy[1] = {y}, qz[1] = {z};
+    Slot<1> A, B, C;
+    C.x[0] = C.y[0] = C.z[0] = C.r[0] = 0.0f;
+    float ts[1] = {0.0f};
+    push_record<1>(r[0].p, false, r[0].n, B, C, A, qx, qy, qz, ts);
+    push_record<1>(r[1].p, false, r[1].n, C, A, B, qx, qy, qz, ts);
+    push_record<1>(r[2].p, true, r[2].n, A, B, C, qx, qy, qz, ts);
+    return ts[0];
+}
+
+// Sum over the n triangles.  A triangle's 64 bytes come through the scalar cache
+// and are used as scalar operands: 33 VALU and 4 transcendentals per far pair, against 52
+// and 3.5 for a face of three records (the edge vectors replace two of the three
+// subtractions and norms, and a small angle t needs t - t^3 / 3 alone).  A point that is
+// near uses the exact forms, whatever the points of its wave do, so that its
+// value does not depend on them.
+template <int PPL>
+__device__ __forceinline__ void sum_triangles(const TriRec *tri, const VRec *caps, int n, const float (&qx)[PPL],
+                                              const float (&qy)[PPL], const float (&qz)[PPL], float (&s)[PPL],
+                                              float (&c)[PPL]) {
+    typedef float Rec __attribute__((ext_vector_type(16)));
+    typedef const __attribute__((address_space(4))) Rec *ConstPtr;
+    static_assert(sizeof(Rec) == sizeof(TriRec), "one scalar load");
+    ConstPtr rec = (ConstPtr)(uintptr_t)tri;
+    Rec next = *rec;  // one ahead; the array holds one more than it has triangles
+    for (int i0 = 0; i0 < n; i0 += 32) {
+        float ts[PPL];
+#pragma unroll
+        for (int p = 0; p < PPL; ++p) ts[p] = 0.0f;
+        const int i1 = min(n, i0 + 32);
+#pragma unroll 1
+        for (int i = i0; i < i1; ++i) {
+            const Rec r = next;
+            next = *++rec;
+            float v[PPL];
+            bool near[PPL], any = false;
+#pragma unroll
+            for (int p = 0; p < PPL; ++p) {
+                const float x = r[0] - qx[p], y = r[1] - qy[p], z = r[2] - qz[p];
+                const float q = __builtin_fmaf(z, z, __builtin_fmaf(y, y, x * x));
+                const float s1 = __builtin_fmaf(z, r[6], __builtin_fmaf(y, r[5], x * r[4]));
+                const float s2 = __builtin_fmaf(z, r[10], __builtin_fmaf(y, r[9], x * r[8]));
+                const float al = __builtin_fmaf(z, r[14], __builtin_fmaf(y, r[13], x * r[12]));
+                const float r0 = fast_sqrt(q), r1 = fast_sqrt((q + r[7]) + s1), r2 = fast_sqrt((q + r[11]) + s2);
+                const float d01 = __builtin_fmaf(0.5f, s1, q), d02 = __builtin_fmaf(0.5f, s2, q);
+                const float d12 = d01 + __builtin_fmaf(0.5f, s2, r[15]);
+                const float be =
+                    __builtin_fmaf(d12, r0, __builtin_fmaf(d02, r1, __builtin_fmaf(d01, r2, (r0 * r1) * r2)));
+                const float t = al * __builtin_amdgcn_rcpf(be);
+                v[p] = t * __builtin_fmaf(t * t, -0.333333333f, 1.0f);
+                near[p] = q < r[3];
+                any = any || near[p];
+            }
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(any) != 0ull, 0)) {
+#pragma unroll
+                for (int p = 0; p < PPL; ++p)
+                    if (near[p]) v[p] = tri_near(caps + 3 * i, qx[p], qy[p], qz[p]);
+            }
+#pragma unroll
+            for (int p = 0; p < PPL; ++p) ts[p] += v[p];
+        }
+#pragma unroll
+        for (int p = 0; p < PPL; ++p) neumaier_add(s[p], c[p], ts[p]);
+    }
+}
+
+// A value that is the same in every lane, as a scalar.
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+template <typename T>
+__device__ __forceinline__ T *uniform(T *p) {
+    const uint64_t a = reinterpret_cast<uint64_t>(p);
+    const uint32_t lo = (uint32_t)uniform((int)(uint32_t)a), hi = (uint32_t)uniform((int)(uint32_t)(a >> 32));
+    return reinterpret_cast<T *>((uint64_t)hi << 32 | lo);
+}
+
+template <int PPL>
+__global__ __launch_bounds__(kBlock) void k_cyc_sum(const char *table) {
+    __shared__ float4 tile[kRecTile * 4];
+    __shared__ unsigned long long s_unit;
+    __shared__ int32_t s_go;
+    CycHead *h = reinterpret_cast<CycHead *>(const_cast<char *>(table));
+    const int tid = threadIdx.x;
+    const int64_t units = h->u_sum;
+    for (int64_t u = blockIdx.x; u < units;) {
+        const CycMesh &m = *uniform(find_mesh<&CycMesh::u_sum>(table, u));
+        const int n_rec = uniform(m.st->n_rec), n_tri = uniform(m.st->n_tri), n_short = uniform(m.st->n_short);
+        const VRec *caps = uniform(m.caps);
+        if (tid == 0) s_go = m.st->go;  // other workgroups may set it meanwhile
+        __syncthreads();
+        if (s_go < 2 && n_rec > 0) {
+            const int64_t base = (u - m.u_sum) * (kBlock * PPL) + tid;
+            float qx[PPL], qy[PPL], qz[PPL], s[PPL], c[PPL];
+#pragma unroll
+            for (int p = 0; p < PPL; ++p) {
+                int64_t idx = base + (int64_t)p * kBlock;
+                idx = idx < m.P ? idx : m.P - 1;
+                m.ps.get(m.p0 + idx, qx[p], qy[p], qz[p]);
+                s[p] = c[p] = 0.0f;
+            }
+            sum_triangles<PPL>(uniform(m.tri), caps, n_tri, qx, qy, qz, s, c);
+            sum_records<PPL, 2>(reinterpret_cast<const float4 *>(caps + 3 * n_tri), 0, n_short - 3 * n_tri, tile,
+                                qx, qy, qz, s, c);
+            if (n_rec > n_short) {
+#pragma unroll
+                for (int p = 0; p < PPL; ++p)
+                    sum_long(caps + n_short, n_rec - n_short, qx[p], qy[p], qz[p], s[p], c[p]);
+            }
+#pragma unroll
+            for (int p = 0; p < PPL; ++p) {
+                const int64_t idx = base + (int64_t)p * kBlock;
+                if (idx >= m.P) continue;
+                const int64_t at = m.p0 + idx;
+                const float w = m.W[at] + (s[p] + c[p]) * kInv2Pi;
+                m.W[at] = w;
+                write_occ(m.occ, at, w);
+                if (near_threshold(m.occ, w)) list_near(m, at);
+            }
+        }
+        if (units <= gridDim.x) break;
+        __syncthreads();
+        if (tid == 0) s_unit = atomicAdd(&h->cursor, 1ull) + gridDim.x;
+        __syncthreads();
+        u = (int64_t)s_unit;
+    }
+}
+
+// ------------------------------------------------------------------ direct sums
+
+// One workgroup per listed voxel, 32 lanes per tile of the record stream, a lane per two
+// records: what sum_tile does one record after another (a tile took 25 us that way), with
+// the same pairing of faces and the same order of the sums.  A tile of whole six-record
+// steps pairs the faces of records 2 l and 2 l + 1, and lone faces two at a time; the
+// records after its last whole step (in the stream's last tile) count one by one.
+constexpr int kNearThreads = 1024, kNearTiles = kNearThreads / 32;
+
+__global__ __launch_bounds__(kNearThreads) void k_cyc_near(const char *table) {
+    __shared__ float2 s_face[kNearTiles][32];    // (alpha, beta) of a lane's lone face
+    __shared__ float s_part[kNearTiles][36];     // a tile's terms in order: 30 lanes, the last lone face, 5 tail records
+    __shared__ float s_tile[kNearTiles];
+    const CycHead *h = reinterpret_cast<const CycHead *>(table);
+    const CycMesh *meshes = meshes_of(table);
+    const int tid = threadIdx.x, tl = tid >> 5, l = tid & 31;
+    const int64_t g = gridDim.x;
+    int64_t before = 0;
+    for (int mi = 0; mi < h->n; ++mi) {
+        const CycMesh &m = meshes[mi];
+        if (m.st->go) continue;
+        const int64_t n = m.st->n_near;
+        const float4 *src = reinterpret_cast<const float4 *>(m.recs);
+        const int64_t tiles = (m.nR + kRecTile - 1) / kRecTile, per = m.chunk / kRecTile;
+        for (int64_t x = (blockIdx.x + g - before % g) % g; x < n; x += g) {
+            const int64_t at = m.p0 + m.near[x];
+            float qx[1], qy[1], qz[1];
+            m.ps.get(at, qx[0], qy[0], qz[0]);
+            float s = 0.0f, c = 0.0f, cs = 0.0f, cc = 0.0f;  // chunks so far, this chunk's tiles
+            for (int64_t t0 = 0; t0 < tiles; t0 += kNearTiles) {
+                const int64_t t = t0 + tl;
+                const int nt = t < tiles ? (int)min((int64_t)kRecTile, m.nR - t * kRecTile) : 0;
+                const int full = nt / 6 * 6;
+                const bool in_step = 2 * l < full;
+                Slot<1> S0, S1, S2;
+                float a0[1], b0[1], a1[1], b1[1];
+                unsigned bits = 0;
+                if (2 * l < nt) {
+                    const int64_t r = t * kRecTile + 2 * l;
+                    const bool second = 2 * l + 1 < nt;
+                    const float4 vx = src[2 * r], nx = src[2 * r + 1];
+                    const float4 vy = second ? src[2 * r + 2] : vx, ny = second ? src[2 * r + 3] : nx;
+                    prime_window<1>(src, r, S0, S1, S2, qx, qy, qz);
+                    bits = (vx.w != 0.0f ? 1u : 0u) | (second && vy.w != 0.0f ? 2u : 0u);
+                    enter_vertex<1>(vx, S2, S0, qx, qy, qz);
+                    if (bits & 1u) face_terms<1>(nx, S1, S2, S0, a0, b0);
+                    enter_vertex<1>(vy, S0, S1, qx, qy, qz);
+                    if (bits & 2u) {
+                        if (in_step)
+                            face_terms<1, true>(ny, S2, S0, S1, a1, b1);
+                        else
+                            face_terms<1>(ny, S2, S0, S1, a1, b1);
+                    }
+                }
+                const bool lone = in_step && (bits == 1u || bits == 2u);
+                const unsigned all = (unsigned)(__builtin_amdgcn_ballot_w64(lone) >> (tid & 32));
+                const unsigned lower = all & ((1u << l) - 1u);
+                if (lone) s_face[tl][l] = bits & 1u ? make_float2(a0[0], b0[0]) : make_float2(a1[0], b1[0]);
+                float *part = s_part[tl];
+                if (l < 6) part[30 + l] = 0.0f;  // (the same wave writes and reads these)
+                __builtin_amdgcn_wave_barrier();
+                float term = 0.0f;
+                if (in_step && bits == 3u) {
+                    term = pair_angle(a0[0], b0[0], a1[0], b1[0]);
+                } else if (lone) {
+                    const float2 f = s_face[tl][l];
+                    if (__popc(lower) & 1) {
+                        const float2 e = s_face[tl][31 - __clz((int)lower)];
+                        term = pair_angle(e.x, e.y, f.x, f.y);
+                    } else if ((all >> l) == 1u) {  // the tile's last, without a partner
+                        part[30] = atan2_eq8(f.x, f.y);
+                    }
+                } else if (!in_step && 2 * l < nt) {
+                    const int k = 31 + 2 * l - full;
+                    if (bits & 1u) part[k] = atan2_eq8(a0[0], b0[0]);
+                    if (bits & 2u) part[k + 1] = atan2_eq8(a1[0], b1[0]);
+                }
+                if (l < 30) part[l] = term;
+                __syncthreads();
+                if (l == 0) {
+                    float ts = 0.0f;
+#pragma unroll
+                    for (int k = 0; k < 36; ++k) ts += part[k];
+                    s_tile[tl] = ts;
+                }
+                __syncthreads();
+                if (tid == 0) {
+                    const int here = (int)min((int64_t)kNearTiles, tiles - t0);
+                    for (int i = 0; i < here; ++i) {
+                        neumaier_add(cs, cc, s_tile[i]);
+                        if ((t0 + i + 1) % per == 0 || t0 + i + 1 == tiles) {
+                            neumaier_add(s, c, cs + cc);
+                            cs = cc = 0.0f;
+                        }
+                    }
+                }
+            }
+            if (tid == 0) {
+                const float w = (s + c) * kInv2Pi;
+                m.W[at] = w;
+                write_occ(m.occ, at, w);
+            }
+        }
+        before += n;
+    }
+}
+
+}  // namespace
+
+// ------------------------------------------------------------------ host
+
+// The path costs about ten short launches; the all-pairs sum reaches that at about 5e7
+// pairs.  A few large faces are better summed: their close voxels are many.
+bool cyc_wanted(int64_t nV, int64_t nF, int64_t P) {
+    return nF >= 128 && nV > 0 && nV < ((int64_t)1 << 30) && nF < ((int64_t)1 << 28) && P > 0 &&
+           (double)nF * (double)P >= 5.0e7;
+}
+
+bool cyc_grid_ok(const wn_grid &g) {
+    for (int d = 0; d < 3; ++d) {
+        const float h = (g.hi[d] - g.lo[d]) / (float)g.n[d];
+        if (!(__builtin_fabsf(g.lo[d]) <= kCoordMax && __builtin_fabsf(g.hi[d]) <= kCoordMax && h > 1.0e-30f)) return false;
+    }
+    return true;
+}
+
+namespace {
+
+int64_t edge_buckets(int64_t nF) {
+    int64_t b = 64;
+    while (b < 2 * nF) b *= 2;
+    return b;
+}
+
+int64_t slab_capacity(int64_t nF) { return nF + 65536; }
+
+int64_t near_capacity(int64_t P) { return P < kCycNear ? P : kCycNear; }
+
+// Calls take(field, bytes) for every scratch array of a mesh, in layout order.
+template <typename Fn>
+void cyc_arrays(CycMesh &m, Fn &&take) {
+    const size_t nV = (size_t)m.nV, nF = (size_t)m.nF, units = (3 * nF + kCycUnit - 1) / kCycUnit;
+    take(m.st, sizeof(CycState));
+    take(m.ent, 16 * 3 * nF);
+    take(m.head, 4 * (size_t)edge_buckets(m.nF));
+    take(m.hout, 4 * nV);
+    take(m.hin, 4 * nV);
+    take(m.count, 4 * nF);
+    take(m.list, 4 * units * kCycUnit);
+    take(m.blk, 8 * units);
+    take(m.edge, 8 * nF);
+    take(m.nout, 4 * nF);
+    take(m.nin, 4 * nF);
+    take(m.rank, 4 * nF);
+    take(m.next, 4 * nF);
+    take(m.cvid, 4 * nF);
+    take(m.cpos, 4 * nF);
+    take(m.caps, sizeof(VRec) * nF);
+    take(m.tri, sizeof(TriRec) * (nF / 3 + 2));
+    take(m.slab, 8 * (size_t)slab_capacity(m.nF));
+    take(m.near, 4 * (size_t)near_capacity(m.P));
+    take(m.mark, 4 * (((size_t)m.P + 31) / 32));
+}
+
+}  // namespace
+
+size_t cyc_bytes(int64_t nV, int64_t nF, int64_t P) {
+    CycMesh m{};
+    m.nV = nV;
+    m.nF = nF;
+    m.P = P;
+    size_t o = 0;
+    cyc_arrays(m, [&](auto *&, size_t bytes) { o += align_up(bytes); });
+    return o;
+}
+
+void cyc_place(CycMesh &m, char *base) {
+    size_t o = 0;
+    cyc_arrays(m, [&](auto *&p, size_t bytes) {
+        p = reinterpret_cast<std::remove_reference_t<decltype(p)>>(base + o);
+        o += align_up(bytes);
+    });
+    m.buckets = edge_buckets(m.nF);
+    m.near_cap = (int32_t)near_capacity(m.P);
+    m.slab_cap = (int32_t)slab_capacity(m.nF);
+}
+
+void cyc_units(CycMesh &m, CycHead &h) {
+    auto units = [](int64_t n, int64_t per) { return (n + per - 1) / per; };
+    const int64_t columns = (m.p0 + m.P - 1) / m.ps.n2 - m.p0 / m.ps.n2 + 1;
+    m.u_clear = h.u_clear;
+    m.u_face = h.u_face;
+    m.u_half = h.u_half;
+    m.u_col = h.u_col;
+    m.u_sum = h.u_sum;
+    const int32_t n[3] = {m.n0, m.ps.n1, m.ps.n2};
+    for (int d = 0; d < 3; ++d) {
+        const double l = m.ps.lo[d], c = m.ps.h[d];
+        m.inv_h[d] = 1.0 / c;
+        m.slack[d] = 1.0e-3 + 2.4e-7 * std::max(std::fabs(l), std::fabs(l + n[d] * c)) / c;
+    }
+    const int64_t yz = (int64_t)m.ps.n1 * m.ps.n2;
+    m.i_first = (int32_t)(m.p0 / yz);
+    m.i_last = (int32_t)((m.p0 + m.P - 1) / yz);
+    h.u_clear += units(std::max(std::max(m.buckets, m.nV), std::max(m.nF, m.P)), kCycClear);
+    h.u_face += units(m.nF, kCycUnit / kCycFaceLanes);
+    h.u_half += units(3 * m.nF, kCycUnit);
+    h.u_col += units(columns, kCycColumns);
+    h.u_sum += units(m.P, (int64_t)kBlock * h.ppl);
+    h.n += 1;
+}
+
+hipError_t launch_cyc_begin(const CycMesh &m, const CycHead &h, char *table, hipStream_t s) {
+    k_cyc_begin_one<<<dim3((unsigned)h.u_clear), kCycUnit, 0, s>>>(m, h, table);
+    return hipGetLastError();
+}
+
+hipError_t launch_cyc_clear(char *table, hipStream_t s) {
+    k_cyc_clear<<<2048, kCycUnit, 0, s>>>(table);
+    return hipGetLastError();
+}
+
+hipError_t launch_cyc(const CycHead &h, char *table, bool fixed, hipStream_t s) {
+    auto grid = [&](int64_t units) { return dim3((unsigned)(fixed ? 2048 : units)); };
+    k_cyc_faces<<<grid(h.u_face), kCycUnit, 0, s>>>(table);
+    k_cyc_mark<<<grid(h.u_half), kCycUnit, 0, s>>>(table);
+    k_cyc_caps<<<fixed ? 256 : h.n, kCapThreads, 0, s>>>(table);
+    k_cyc_slabs<<<1024, kCycUnit, 0, s>>>(table);
+    k_cyc_columns<<<grid(h.u_col), kCycColumns * 64, 0, s>>>(table);
+    if (h.ppl == 1)
+        k_cyc_sum<1><<<grid(h.u_sum), kBlock, 0, s>>>(table);
+    else if (h.ppl == 2)
+        k_cyc_sum<2><<<grid(h.u_sum), kBlock, 0, s>>>(table);
+    else
+        k_cyc_sum<4><<<grid(h.u_sum), kBlock, 0, s>>>(table);
+    return hipGetLastError();
+}
+
+hipError_t launch_cyc_near(char *table, hipStream_t s) {
+    k_cyc_near<<<512, kNearThreads, 0, s>>>(table);
+    return hipGetLastError();
+}
+
+}  // namespace wn

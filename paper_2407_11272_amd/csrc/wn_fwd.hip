@@ -10,7 +10,7 @@
 //   * each tile's per-point sum is folded into a Neumaier-compensated total;
 //   * when the point count alone cannot fill the GPU, the faces are split over
 //     workgroups and the partial sums are added in a fixed order afterwards.
-#include "wn_internal.hpp"
+#include "wn_cycle.hpp"
 
 namespace wn {
 
@@ -59,14 +59,16 @@ __global__ __launch_bounds__(kBlock) void k_pack(const float *__restrict__ V, in
 __global__ __launch_bounds__(kBlock) void k_pack_records(const float *__restrict__ V, int64_t nV,
                                                          const int32_t *__restrict__ F, int64_t nF,
                                                          const int32_t *__restrict__ R, int64_t nR,
-                                                         VRec *__restrict__ recs, WsHeader *hdr) {
+                                                         VRec *__restrict__ recs, WsHeader *hdr, int32_t *counts,
+                                                         int32_t *go) {
     const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (r >= nR) return;
     int32_t vid, fid;
     if (R) {
         vid = R[2 * r];
         fid = R[2 * r + 1];
-        check_strip_record(R, r, F, nF, fid, hdr);
+        check_strip_record(R, r, F, nF, fid, hdr, go);
+        if (counts && fid >= 0 && (int64_t)fid < nF) atomicAdd(&counts[fid], 1);
     } else {
         const int64_t f = r / 3;
         const int j = (int)(r - 3 * f);
@@ -76,17 +78,17 @@ __global__ __launch_bounds__(kBlock) void k_pack_records(const float *__restrict
     recs[r] = make_record(V, nV, F, nF, vid, fid, hdr);
 }
 
-// All-pairs forward.  Grid: x = point blocks of kBlock * PPL points, y = record splits.
-// With split == 1 the kernel writes W (scaled by 1 / 2 pi) and the occupancy map;
-// otherwise it writes the unscaled partial sum of split y to partials[y * nQ + idx].
+// One point block against one record split of the all-pairs forward.  With one split it
+// writes W (scaled by 1 / 2 pi) and the occupancy map; otherwise the unscaled partial sum of
+// split y to partials[y * nQ + idx].
 template <int PPL, int DEPTH>
-__global__ __launch_bounds__(kBlock) void k_wn_fwd(const VRec *__restrict__ recs, int64_t nR, int64_t chunk,
-                                                   PointSrc ps, int64_t nQ, float *__restrict__ W,
-                                                   float *__restrict__ partials, OccParams occ) {
-    __shared__ float4 tile[kRecTile * 2 * DEPTH];
+__device__ __forceinline__ void fwd_unit(int64_t pblock, int64_t y, float4 *tile, const VRec *__restrict__ recs,
+                                         int64_t nR, int64_t chunk, const PointSrc &ps, int64_t nQ,
+                                         float *__restrict__ W, float *__restrict__ partials, const OccParams &occ,
+                                         const CycState *st, const uint32_t *mark) {
     const int tid = threadIdx.x;
-    const int64_t base = (int64_t)blockIdx.x * (kBlock * PPL) + tid;
-    const int64_t r0 = (int64_t)blockIdx.y * chunk;
+    const int64_t base = pblock * (kBlock * PPL) + tid;
+    const int64_t r0 = y * chunk;
     const int64_t r1 = min(nR, r0 + chunk);
 
     float qx[PPL], qy[PPL], qz[PPL], s[PPL], c[PPL];
@@ -105,8 +107,8 @@ __global__ __launch_bounds__(kBlock) void k_wn_fwd(const VRec *__restrict__ recs
         if (idx >= nQ) continue;
         const float tot = s[p] + c[p];
         if (partials) {
-            partials[(int64_t)blockIdx.y * nQ + idx] = tot;
-        } else {
+            partials[y * nQ + idx] = tot;
+        } else if (go_writes(st, mark, idx)) {
             const float w = tot * kInv2Pi;
             W[idx] = w;
             write_occ(occ, idx, w);
@@ -114,16 +116,41 @@ __global__ __launch_bounds__(kBlock) void k_wn_fwd(const VRec *__restrict__ recs
     }
 }
 
-// Fixed-order sum of the split partials, scale to W, occupancy.
+// All-pairs forward.  Grid: x = point blocks of kBlock * PPL points, y = record splits.
+template <int PPL, int DEPTH>
+__global__ __launch_bounds__(kBlock) void k_wn_fwd(const VRec *__restrict__ recs, int64_t nR, int64_t chunk,
+                                                   PointSrc ps, int64_t nQ, float *__restrict__ W,
+                                                   float *__restrict__ partials, OccParams occ) {
+    __shared__ float4 tile[kRecTile * 2 * DEPTH];
+    fwd_unit<PPL, DEPTH>(blockIdx.x, blockIdx.y, tile, recs, nR, chunk, ps, nQ, W, partials, occ, nullptr, nullptr);
+}
+
+// The same where st asks for it; a bounded number of workgroups, so that leaving costs little.
+template <int PPL, int DEPTH>
+__global__ __launch_bounds__(kBlock) void k_wn_fwd_if(const CycState *st, const uint32_t *mark, int64_t pblocks, int64_t units,
+                                                      const VRec *__restrict__ recs, int64_t nR, int64_t chunk,
+                                                      PointSrc ps, int64_t nQ, float *__restrict__ W,
+                                                      float *__restrict__ partials, OccParams occ) {
+    __shared__ float4 tile[kRecTile * 2 * DEPTH];
+    if (st->go == 0) return;
+    for (int64_t u = blockIdx.x; u < units; u += gridDim.x)
+        fwd_unit<PPL, DEPTH>(u % pblocks, u / pblocks, tile, recs, nR, chunk, ps, nQ, W, partials, occ, st, mark);
+}
+
+// Fixed-order sum of the split partials, scale to W, occupancy (where st is null or asks for it).
 __global__ __launch_bounds__(kBlock) void k_wn_reduce(const float *__restrict__ partials, int32_t split,
-                                                      int64_t nQ, float scale, float *__restrict__ W, OccParams occ) {
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= nQ) return;
-    float s = 0.0f, c = 0.0f;
-    for (int32_t k = 0; k < split; ++k) neumaier_add(s, c, partials[(int64_t)k * nQ + idx]);
-    const float w = (s + c) * scale;
-    W[idx] = w;
-    write_occ(occ, idx, w);
+                                                      int64_t nQ, float scale, float *__restrict__ W, OccParams occ,
+                                                      const CycState *st, const uint32_t *mark) {
+    if (st && st->go == 0) return;
+    for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < nQ;
+         idx += (int64_t)gridDim.x * blockDim.x) {
+        if (!go_writes(st, mark, idx)) continue;
+        float s = 0.0f, c = 0.0f;
+        for (int32_t k = 0; k < split; ++k) neumaier_add(s, c, partials[(int64_t)k * nQ + idx]);
+        const float w = (s + c) * scale;
+        W[idx] = w;
+        write_occ(occ, idx, w);
+    }
 }
 
 __global__ __launch_bounds__(kBlock) void k_occ(const float *__restrict__ W, int64_t n, OccParams occ) {
@@ -182,6 +209,8 @@ __global__ __launch_bounds__(kBlock) void k_loss_final(const float *__restrict__
 
 // ---------------------------------------------------------------- launchers
 
+constexpr int64_t kGoBlocks = 8192;  // workgroups of a launch that may have nothing to do
+
 int fwd_split_count(int64_t nR, int64_t nQ) {
     // Aim for about 131072 wave64s of (point block, record split) units, about 16
     // rounds of resident workgroups, so that the last, partly filled round costs little
@@ -231,27 +260,34 @@ hipError_t launch_pack(const float *V, int64_t nV, const int32_t *F, int64_t nF,
 }
 
 hipError_t launch_pack_records(const float *V, int64_t nV, const int32_t *F, int64_t nF, const int32_t *R,
-                               int64_t nR, VRec *recs, WsHeader *hdr, hipStream_t s) {
+                               int64_t nR, VRec *recs, WsHeader *hdr, int32_t *counts, int32_t *go,
+                               hipStream_t s) {
     if (nR <= 0) return hipSuccess;
     const int64_t blocks = (nR + kBlock - 1) / kBlock;
-    k_pack_records<<<dim3((unsigned)blocks), kBlock, 0, s>>>(V, nV, F, nF, R, nR, recs, hdr);
+    k_pack_records<<<dim3((unsigned)blocks), kBlock, 0, s>>>(V, nV, F, nF, R, nR, recs, hdr, counts, go);
     return hipGetLastError();
 }
 
 hipError_t launch_fwd(const VRec *recs, int64_t nR, const PointSrc &ps, int64_t nQ, int split, float *W,
-                      float *partials, const OccParams &occ, int ppl, int depth, hipStream_t s) {
+                      float *partials, const OccParams &occ, int ppl, int depth, const CycState *st, const uint32_t *mark, hipStream_t s) {
     if (nQ <= 0) return hipSuccess;
     const int64_t chunk = fwd_split_chunk(nR, split);
+    float *part = split > 1 ? partials : nullptr;
     hipError_t e = with_config(ppl, depth, [&](auto P, auto D) {
         constexpr int kP = decltype(P)::value, kD = decltype(D)::value;
-        const int64_t pblocks = (nQ + kBlock * kP - 1) / (kBlock * kP);
-        k_wn_fwd<kP, kD><<<dim3((unsigned)pblocks, (unsigned)split), kBlock, 0, s>>>(
-            recs, nR, chunk, ps, nQ, W, split > 1 ? partials : nullptr, occ);
+        const int64_t pblocks = (nQ + kBlock * kP - 1) / (kBlock * kP), units = pblocks * split;
+        if (st)
+            k_wn_fwd_if<kP, kD><<<(unsigned)(units < kGoBlocks ? units : kGoBlocks), kBlock, 0, s>>>(
+                st, mark, pblocks, units, recs, nR, chunk, ps, nQ, W, part, occ);
+        else
+            k_wn_fwd<kP, kD><<<dim3((unsigned)pblocks, (unsigned)split), kBlock, 0, s>>>(recs, nR, chunk, ps, nQ, W,
+                                                                                       part, occ);
         return hipGetLastError();
     });
     if (e != hipSuccess || split <= 1) return e;
-    const int64_t rblocks = (nQ + kBlock - 1) / kBlock;
-    k_wn_reduce<<<dim3((unsigned)rblocks), kBlock, 0, s>>>(partials, split, nQ, kInv2Pi, W, occ);
+    int64_t rblocks = (nQ + kBlock - 1) / kBlock;
+    if (st && rblocks > kGoBlocks) rblocks = kGoBlocks;
+    k_wn_reduce<<<dim3((unsigned)rblocks), kBlock, 0, s>>>(partials, split, nQ, kInv2Pi, W, occ, st, mark);
     return hipGetLastError();
 }
 
@@ -276,7 +312,7 @@ hipError_t launch_checksum(const float *x, int64_t n, WsHeader *hdr, bool reset,
 hipError_t launch_split_reduce(const float *partials, int split, int64_t nQ, float scale, float *W,
                                const OccParams &occ, hipStream_t s) {
     const int64_t rblocks = (nQ + kBlock - 1) / kBlock;
-    k_wn_reduce<<<dim3((unsigned)rblocks), kBlock, 0, s>>>(partials, split, nQ, scale, W, occ);
+    k_wn_reduce<<<dim3((unsigned)rblocks), kBlock, 0, s>>>(partials, split, nQ, scale, W, occ, nullptr, nullptr);
     return hipGetLastError();
 }
 

@@ -67,13 +67,13 @@ static_assert(sizeof(WsHeader) == kWsHeader, "header size");
 
 // ---------------------------------------------------------------- device math
 
-// atan(t) for t in [0, 1] as t P(t^2): minimax in relative error (Remez exchange,
+// P in atan(t) = t P(t^2) for t in [0, 1]: minimax in relative error (Remez exchange,
 // degree 6 in t^2; coefficients from gen_atan_poly.py, max relative error 7.6e-7 and
 // absolute error 5.9e-7 when evaluated in FP32).  The polynomial's share of the error in
 // W is at most 7.6e-7 times the sum of |angle| / 2 pi over a point's faces: about 8e-7
 // per closed surface around the point, 6e-6 inside eight stacked shells even with every
 // error of one sign, against the 1e-4 bar.  Degree 7 (2.2e-7) cost one more FMA per ATAN2.
-__device__ __forceinline__ float atan_unit(float t) {
+__device__ __forceinline__ float atan_ratio(float t) {
     const float x = t * t;
     float p = 0.007863377f;
     p = __builtin_fmaf(p, x, -0.037013f);
@@ -82,7 +82,7 @@ __device__ __forceinline__ float atan_unit(float t) {
     p = __builtin_fmaf(p, x, 0.19881482f);
     p = __builtin_fmaf(p, x, -0.33326516f);
     p = __builtin_fmaf(p, x, 0.99999934f);
-    return p * t;
+    return p;
 }
 
 // |ATAN2(y, x)|: the angle of (|y|, x), in [0, pi].
@@ -91,8 +91,8 @@ __device__ __forceinline__ float atan2_mag(float y, float x) {
     const float mn = __builtin_fminf(ax, ay);
     const float mx = __builtin_fmaxf(ax, ay);
     const float t = mn * __builtin_amdgcn_rcpf(__builtin_fmaxf(mx, kFltMin));
-    float a = atan_unit(t);
-    a = (ay > ax) ? (kHalfPi - a) : a;
+    const float p = atan_ratio(t);
+    const float a = (ay > ax) ? __builtin_fmaf(-t, p, kHalfPi) : t * p;
     return (x < 0.0f) ? (kPi - a) : a;
 }
 
@@ -139,6 +139,12 @@ struct PointSrc {
     }
 };
 
+// a . b with its rounding fixed, whatever block the compiler places the products in: a point
+// close to the surface gets the same bits from every kernel.
+__device__ __forceinline__ float dot3(float ax, float ay, float az, float bx, float by, float bz) {
+    return __builtin_fmaf(az, bz, __builtin_fmaf(ax, bx, ay * by));
+}
+
 // One vertex of the record window, per query point: R = v - q, r = |R|, and the dot
 // product and length product with the previous record's vertex.
 template <int PPL>
@@ -156,24 +162,27 @@ __device__ __forceinline__ void enter_vertex(const float4 v, const Slot<PPL> &B,
         C.x[p] = v.x - qx[p];
         C.y[p] = v.y - qy[p];
         C.z[p] = v.z - qz[p];
-        C.r[p] = fast_sqrt(C.x[p] * C.x[p] + C.y[p] * C.y[p] + C.z[p] * C.z[p]);
-        C.dprev[p] = B.x[p] * C.x[p] + B.y[p] * C.y[p] + B.z[p] * C.z[p];
+        C.r[p] = fast_sqrt(dot3(C.x[p], C.y[p], C.z[p], C.x[p], C.y[p], C.z[p]));
+        C.dprev[p] = dot3(B.x[p], B.y[p], B.z[p], C.x[p], C.y[p], C.z[p]);
         C.rprev[p] = B.r[p] * C.r[p];
     }
 }
 
 // Scale-free Eq. 7 terms of the face (A, B, C) with normal n: alpha' = R_A . N and
 // beta' = r_A r_B r_C + (R_A.R_B) r_C + (R_B.R_C) r_A + (R_C.R_A) r_B; alpha' = 0 when a
-// vertex coincides with the point.
-template <int PPL>
+// vertex coincides with the point.  kSecond (the second record of a pair) starts alpha's
+// sum with the other product.
+template <int PPL, bool kSecond = false>
 __device__ __forceinline__ void face_terms(const float4 n, const Slot<PPL> &A, const Slot<PPL> &B, const Slot<PPL> &C,
                                            float (&al)[PPL], float (&be)[PPL]) {
 #pragma unroll
     for (int p = 0; p < PPL; ++p) {
-        const float dca = C.x[p] * A.x[p] + C.y[p] * A.y[p] + C.z[p] * A.z[p];
+        const float dca = dot3(C.x[p], C.y[p], C.z[p], A.x[p], A.y[p], A.z[p]);
         const float pr = B.rprev[p] * C.r[p];  // r_A r_B r_C
-        be[p] = pr + B.dprev[p] * C.r[p] + C.dprev[p] * A.r[p] + dca * B.r[p];
-        const float alpha = A.x[p] * n.x + A.y[p] * n.y + A.z[p] * n.z;
+        be[p] = __builtin_fmaf(dca, B.r[p],
+                               __builtin_fmaf(C.dprev[p], A.r[p], __builtin_fmaf(B.dprev[p], C.r[p], pr)));
+        const float alpha = kSecond ? dot3(A.x[p], A.y[p], A.z[p], n.x, n.y, n.z)
+                                    : dot3(A.y[p], A.x[p], A.z[p], n.y, n.x, n.z);
         al[p] = (pr == 0.0f) ? 0.0f : alpha;
     }
 }
@@ -188,7 +197,7 @@ __device__ __forceinline__ void face_terms(const float4 n, const Slot<PPL> &A, c
 __device__ __forceinline__ float pair_angle(float a0, float b0, float a1, float b1) {
     const float a01 = a0 * a1;
     const float pre = __builtin_fmaf(b0, b1, -a01);
-    const float pim = a0 * b1 + b0 * a1;
+    const float pim = __builtin_fmaf(b0, a1, a0 * b1);
     // Same sign: a01 > 0 (where it is not, |a01| < FLT_MIN or a zero angle, the two ATAN2s
     // are taken below).  A wrap has the angles' sign opposite to pim's, so the corrected
     // sum is the ATAN2's sign applied to (|angle| - 2 pi): one subtraction and one select,
@@ -231,7 +240,7 @@ __device__ __forceinline__ void push_pair(const float4 vx, const float4 nx, cons
     enter_vertex<PPL>(vx, X1, X2, qx, qy, qz);
     if (bits & 1u) face_terms<PPL>(nx, X0, X1, X2, a0, b0);
     enter_vertex<PPL>(vy, X2, X0, qx, qy, qz);
-    if (bits & 2u) face_terms<PPL>(ny, X1, X2, X0, a1, b1);
+    if (bits & 2u) face_terms<PPL, true>(ny, X1, X2, X0, a1, b1);
     if ((bits & 3u) == 3u) {
 #pragma unroll
         for (int p = 0; p < PPL; ++p) ts[p] += pair_angle(a0[p], b0[p], a1[p], b1[p]);
@@ -265,14 +274,64 @@ __device__ __forceinline__ unsigned long long tile_face_mask(const float4 *tile,
     return __builtin_amdgcn_ballot_w64(flag != 0.0f);
 }
 
+// The window before record r0: the two records before it (if any) in slots S0 and S1.
+template <int PPL>
+__device__ __forceinline__ void prime_window(const float4 *__restrict__ src, int64_t r0, Slot<PPL> &S0, Slot<PPL> &S1,
+                                             Slot<PPL> &S2, const float (&qx)[PPL], const float (&qy)[PPL],
+                                             const float (&qz)[PPL]) {
+#pragma unroll
+    for (int p = 0; p < PPL; ++p) {
+        S0.x[p] = S0.y[p] = S0.z[p] = S0.r[p] = S0.dprev[p] = S0.rprev[p] = 0.0f;
+        S1.x[p] = S1.y[p] = S1.z[p] = S1.r[p] = S1.dprev[p] = S1.rprev[p] = 0.0f;
+        S2.x[p] = S2.y[p] = S2.z[p] = S2.r[p] = S2.dprev[p] = S2.rprev[p] = 0.0f;
+    }
+    float ts[PPL];
+    const float4 zero = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (r0 >= 2) push_record<PPL>(src[2 * (r0 - 2)], false, zero, S2, S0, S1, qx, qy, qz, ts);
+    if (r0 >= 1) push_record<PPL>(src[2 * (r0 - 1)], false, zero, S0, S1, S2, qx, qy, qz, ts);
+}
+
+// Adds to ts the faces completed by the nt <= kRecTile records of a tile (face flags in
+// fmask).  The window's three slots rotate statically (records are taken six at a time;
+// kRecTile is a multiple of six), so no register moves are needed.
+template <int PPL>
+__device__ __forceinline__ void sum_tile(const float4 *tile_s, int nt, unsigned long long fmask, Slot<PPL> &S0,
+                                         Slot<PPL> &S1, Slot<PPL> &S2, const float (&qx)[PPL], const float (&qy)[PPL],
+                                         const float (&qz)[PPL], float (&ts)[PPL]) {
+    int i = 0;
+    // six records per step: the window's slots return to their places after six
+    float pa[PPL], pb[PPL];
+    bool pending = false;
+    for (; i + 6 <= nt; i += 6) {
+        const float4 *g = tile_s + 2 * i;
+        const unsigned bits = (unsigned)(fmask >> i);
+        push_pair<PPL>(g[0], g[1], g[2], g[3], bits, S1, S2, S0, qx, qy, qz, ts, pa, pb, pending);
+        push_pair<PPL>(g[4], g[5], g[6], g[7], bits >> 2, S0, S1, S2, qx, qy, qz, ts, pa, pb, pending);
+        push_pair<PPL>(g[8], g[9], g[10], g[11], bits >> 4, S2, S0, S1, qx, qy, qz, ts, pa, pb, pending);
+    }
+    if (pending) {
+#pragma unroll
+        for (int p = 0; p < PPL; ++p) ts[p] += atan2_eq8(pa[p], pb[p]);
+    }
+    // a partial step only occurs in the last tile of the range
+    if (i < nt) {
+        const float4 *g = tile_s + 2 * i;
+        const unsigned bits = (unsigned)(fmask >> i);
+        const int m = nt - i;
+        push_record<PPL>(g[0], bits & 1u, g[1], S1, S2, S0, qx, qy, qz, ts);
+        if (m > 1) push_record<PPL>(g[2], bits & 2u, g[3], S2, S0, S1, qx, qy, qz, ts);
+        if (m > 2) push_record<PPL>(g[4], bits & 4u, g[5], S0, S1, S2, qx, qy, qz, ts);
+        if (m > 3) push_record<PPL>(g[6], bits & 8u, g[7], S1, S2, S0, qx, qy, qz, ts);
+        if (m > 4) push_record<PPL>(g[8], bits & 16u, g[9], S2, S0, S1, qx, qy, qz, ts);
+    }
+}
+
 // Sum of the half solid angles of the faces completed by records [r0, r1), at PPL
 // points per lane.  The two records before r0 (if any) prime the vertex window, so a
 // range may start anywhere in the stream.  Records are staged through `tile` (LDS,
 // 2 * kRecTile * DEPTH float4: DEPTH tiles per barrier) by the whole workgroup; each
 // tile's per-point sum is folded into the Neumaier pair (s, c).  The result depends only
-// on the record stream and the kRecTile boundaries, not on DEPTH.  The window's three
-// slots rotate statically (records are taken six at a time; kRecTile is a multiple of
-// six), so no register moves are needed.
+// on the record stream and the kRecTile boundaries, not on DEPTH.
 template <int PPL, int DEPTH>
 __device__ __forceinline__ void sum_records(const float4 *__restrict__ src, int64_t r0, int64_t r1, float4 *tile,
                                             const float (&qx)[PPL], const float (&qy)[PPL], const float (&qz)[PPL],
@@ -280,18 +339,7 @@ __device__ __forceinline__ void sum_records(const float4 *__restrict__ src, int6
     if (r0 >= r1) return;  // empty range: nothing to prime or sum (uniform)
     const int tid = threadIdx.x;
     Slot<PPL> S0, S1, S2;
-#pragma unroll
-    for (int p = 0; p < PPL; ++p) {
-        S0.x[p] = S0.y[p] = S0.z[p] = S0.r[p] = S0.dprev[p] = S0.rprev[p] = 0.0f;
-        S1.x[p] = S1.y[p] = S1.z[p] = S1.r[p] = S1.dprev[p] = S1.rprev[p] = 0.0f;
-        S2.x[p] = S2.y[p] = S2.z[p] = S2.r[p] = S2.dprev[p] = S2.rprev[p] = 0.0f;
-    }
-    {
-        float ts[PPL];
-        const float4 zero = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        if (r0 >= 2) push_record<PPL>(src[2 * (r0 - 2)], false, zero, S2, S0, S1, qx, qy, qz, ts);
-        if (r0 >= 1) push_record<PPL>(src[2 * (r0 - 1)], false, zero, S0, S1, S2, qx, qy, qz, ts);
-    }
+    prime_window<PPL>(src, r0, S0, S1, S2, qx, qy, qz);
     // window now: A = S1, B = S2
     for (int64_t t0 = r0; t0 < r1; t0 += kRecTile * DEPTH) {
         const int nst = (int)min((int64_t)kRecTile * DEPTH, r1 - t0);
@@ -300,40 +348,14 @@ __device__ __forceinline__ void sum_records(const float4 *__restrict__ src, int6
         __syncthreads();
 #pragma unroll 1
         for (int sub = 0; sub < DEPTH && sub * kRecTile < nst; ++sub) {
-        const float4 *tile_s = tile + 2 * sub * kRecTile;
-        const int nt = min(kRecTile, nst - sub * kRecTile);
-        const unsigned long long fmask = tile_face_mask(tile_s, nt);
-        float ts[PPL];
+            const float4 *tile_s = tile + 2 * sub * kRecTile;
+            const int nt = min(kRecTile, nst - sub * kRecTile);
+            float ts[PPL];
 #pragma unroll
-        for (int p = 0; p < PPL; ++p) ts[p] = 0.0f;
-        int i = 0;
-        // six records per step: the window's slots return to their places after six
-        float pa[PPL], pb[PPL];
-        bool pending = false;
-        for (; i + 6 <= nt; i += 6) {
-            const float4 *g = tile_s + 2 * i;
-            const unsigned bits = (unsigned)(fmask >> i);
-            push_pair<PPL>(g[0], g[1], g[2], g[3], bits, S1, S2, S0, qx, qy, qz, ts, pa, pb, pending);
-            push_pair<PPL>(g[4], g[5], g[6], g[7], bits >> 2, S0, S1, S2, qx, qy, qz, ts, pa, pb, pending);
-            push_pair<PPL>(g[8], g[9], g[10], g[11], bits >> 4, S2, S0, S1, qx, qy, qz, ts, pa, pb, pending);
-        }
-        if (pending) {
+            for (int p = 0; p < PPL; ++p) ts[p] = 0.0f;
+            sum_tile<PPL>(tile_s, nt, tile_face_mask(tile_s, nt), S0, S1, S2, qx, qy, qz, ts);
 #pragma unroll
-            for (int p = 0; p < PPL; ++p) ts[p] += atan2_eq8(pa[p], pb[p]);
-        }
-        // a partial step only occurs in the last tile of the range
-        if (i < nt) {
-            const float4 *g = tile_s + 2 * i;
-            const unsigned bits = (unsigned)(fmask >> i);
-            const int m = nt - i;
-            push_record<PPL>(g[0], bits & 1u, g[1], S1, S2, S0, qx, qy, qz, ts);
-            if (m > 1) push_record<PPL>(g[2], bits & 2u, g[3], S2, S0, S1, qx, qy, qz, ts);
-            if (m > 2) push_record<PPL>(g[4], bits & 4u, g[5], S0, S1, S2, qx, qy, qz, ts);
-            if (m > 3) push_record<PPL>(g[6], bits & 8u, g[7], S1, S2, S0, qx, qy, qz, ts);
-            if (m > 4) push_record<PPL>(g[8], bits & 16u, g[9], S2, S0, S1, qx, qy, qz, ts);
-        }
-#pragma unroll
-        for (int p = 0; p < PPL; ++p) neumaier_add(s[p], c[p], ts[p]);
+            for (int p = 0; p < PPL; ++p) neumaier_add(s[p], c[p], ts[p]);
         }
     }
 }
@@ -398,14 +420,16 @@ __device__ __forceinline__ bool strip_window_ok(const int32_t *__restrict__ R, i
 }
 
 // Strip record r (vertex vid, face fid) checked against F before it is packed: a face
-// whose window is not F[fid] is recorded as a bad index, and a face flag on record 0 or
-// 1 is also dropped (its window would reach before the stream).
+// whose window is not F[fid] is recorded as a bad index (and in *go, if given: the stream
+// does not stand for F, and the all-pairs sum over the stream is wanted), and a face flag on record 0 or 1 is also dropped (its
+// window would reach before the stream).
 __device__ __forceinline__ void check_strip_record(const int32_t *__restrict__ R, int64_t r,
                                                    const int32_t *__restrict__ F, int64_t nF, int32_t &fid,
-                                                   WsHeader *hdr) {
+                                                   WsHeader *hdr, int32_t *go = nullptr) {
     if (fid < 0 || (int64_t)fid >= nF) return;  // no face, or out of range (make_record records it)
     if (!strip_window_ok(R, r, F, fid)) {
         atomicOr(&hdr->bad_index, 1);
+        if (go) atomicMax(go, 2);
         if (r < 2) fid = -1;
     }
 }
@@ -448,10 +472,15 @@ hipError_t launch_pack(const float *V, int64_t nV, const int32_t *F, int64_t nF,
                        WsHeader *hdr, hipStream_t s);
 // Vertex records from (V, F) and an optional strip stream R ([nR][2] = vertex, face or
 // -1); with R == nullptr the stream is three records per face (nR = 3 nF).
+// counts / go (optional): the times a strip stream names each face, and a flag raised to 2
+// where the stream does not stand for F.
 hipError_t launch_pack_records(const float *V, int64_t nV, const int32_t *F, int64_t nF, const int32_t *R,
-                               int64_t nR, VRec *recs, WsHeader *hdr, hipStream_t s);
+                               int64_t nR, VRec *recs, WsHeader *hdr, int32_t *counts, int32_t *go,
+                               hipStream_t s);
+// st, mark (optional, device; wn_cycle.hpp): the launch does what the state asks for.
 hipError_t launch_fwd(const VRec *recs, int64_t nR, const PointSrc &ps, int64_t nQ, int split,
-                      float *W, float *partials, const OccParams &occ, int ppl, int depth, hipStream_t s);
+                      float *W, float *partials, const OccParams &occ, int ppl, int depth, const struct CycState *st,
+                      const uint32_t *mark, hipStream_t s);
 // Order-free checksum (sum of the bit patterns) of n floats into hdr->checksum.
 hipError_t launch_checksum(const float *x, int64_t n, WsHeader *hdr, bool reset, hipStream_t s);
 hipError_t launch_occ(const float *W, int64_t n, const OccParams &occ, hipStream_t s);
@@ -555,13 +584,13 @@ wn_status run_flip(const float *V, int64_t nV, const int32_t *F, int64_t nF, flo
                    char *ws, size_t ws_bytes, hipStream_t s);
 
 // The forward entry point's checks and launch sequence (wn_api.hip): R == nullptr for
-// three records per face; `force` overrides the tuned launch configuration.  The
-// workspace of a stream of nR records over nQ points is voxelize_workspace(nR, nQ).
+// three records per face; `force` overrides the tuned launch configuration, `all_pairs`
+// keeps the call on the all-pairs kernel.
 struct TuneConfig;
 wn_status voxelize_impl(const float *V, int64_t nV, const int32_t *F, int64_t nF, const int32_t *R, int64_t nR,
                         const wn_grid *grid, const float *Q, int64_t nQ, float *W, int32_t occ_mode, float tau,
-                        float k, void *occ, void *ws, size_t ws_bytes, void *stream, const TuneConfig *force);
-size_t voxelize_workspace(int64_t nR, int64_t nQ);
+                        float k, void *occ, void *ws, size_t ws_bytes, void *stream, const TuneConfig *force,
+                        bool all_pairs = false);
 // Device address of the allocation-free entry point's scratch array on the current
 // device (wn_noalloc.hip); its header carries that entry point's device error record.
 wn_status noalloc_header(void **out);
