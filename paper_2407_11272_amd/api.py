@@ -372,9 +372,10 @@ def wn_backward(V, F, dLdW: torch.Tensor, grid: Grid | None = None, Q: torch.Ten
                 want_dLdT: bool = False, dLdV: torch.Tensor | None = None, dLdT: torch.Tensor | None = None,
                 _entry: str = "wn_backward", pairs: torch.Tensor | None = None, vertex_sums: bool | None = None):
     """dL/dV [nV, 3] (and dL/dT [nF, 3, 3] if requested) for the given dL/dW.  With
-    ``pairs`` (a device copy of :func:`wn_build_face_pairs`) two faces per lane, through
-    one wn_backward_range call; ``vertex_sums`` (default: when dL/dT is not wanted) lets
-    the two faces of a pair share their sums at their common vertices."""
+    ``pairs`` (a device copy of :func:`wn_build_face_pairs`) two faces per lane;
+    ``vertex_sums`` (default: when dL/dT is not wanted) lets faces share their sums at
+    common vertices: the two of a pair, or, for a grid's points, all of them, which leaves
+    the mesh's boundary edges."""
     lib = L.load()
     _check_mesh(V, F)
     if (grid is None) == (Q is None):
@@ -399,11 +400,11 @@ def wn_backward(V, F, dLdW: torch.Tensor, grid: Grid | None = None, Q: torch.Ten
         vertex_sums = not want_dLdT
     if vertex_sums and want_dLdT:
         raise ValueError("dL/dT is not available with vertex_sums")
-    if pairs is not None:   # the whole range in one wn_backward_range call
+    if pairs is not None or (vertex_sums and _entry == "wn_backward"):   # the whole range in one call
         pairs = _check_pairs(pairs, F)
         flags = L.WN_BWD_BEGIN | L.WN_BWD_END | (L.WN_BWD_VERTEX_SUMS if vertex_sums else 0)
-        st = lib.wn_backward_range(_ptr(V), V.shape[0], _ptr(F), F.shape[0], _ptr(pairs), pairs.shape[0], gptr, qptr,
-                                   nQ, _ptr(dLdW), 0, P, flags, _ptr(dLdV),
+        st = lib.wn_backward_range(_ptr(V), V.shape[0], _ptr(F), F.shape[0], _ptr(pairs), 0 if pairs is None else pairs.shape[0],
+                                   gptr, qptr, nQ, _ptr(dLdW), 0, P, flags, _ptr(dLdV),
                                    _ptr(dLdT if want_dLdT else None), ws, wsb, _stream_handle(dev))
         L.check("wn_backward_range", st)
         return (dLdV, dLdT) if want_dLdT else dLdV

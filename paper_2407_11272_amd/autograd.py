@@ -14,22 +14,26 @@ class WindingNumber(torch.autograd.Function):
     point x face matrix) and returns dL/dV.  Optional device ``strips`` (from
     ``wn_build_strips``) select the strip-order forward, and ``pairs`` (from
     ``wn_build_face_pairs``) the adjoint with two faces per lane and shared vertex sums;
-    both depend only on F, so a loop over vertex positions builds them once."""
+    both depend only on F, so a loop over vertex positions builds them once.  ``soft`` =
+    (tau, k) of a sigmoid that follows: W is that of a call with this occupancy."""
 
     @staticmethod
-    def forward(ctx, V, F, grid=None, Q=None, strips=None, pairs=None):
+    def forward(ctx, V, F, grid=None, Q=None, strips=None, pairs=None, soft=None):
         ctx.save_for_backward(V, F, Q, pairs)
         ctx.grid = grid
+        kw = {} if soft is None else dict(occupancy="sigmoid", tau=soft[0], k=soft[1])
         if strips is not None:
-            return api.wn_voxelize_strips(V, F, strips, grid=grid, Q=Q)
-        return api.wn_voxelize(V, F, grid=grid, Q=Q)
+            out = api.wn_voxelize_strips(V, F, strips, grid=grid, Q=Q, **kw)
+        else:
+            out = api.wn_voxelize(V, F, grid=grid, Q=Q, **kw)
+        return out if soft is None else out[0]
 
     @staticmethod
     def backward(ctx, gW):
         V, F, Q, pairs = ctx.saved_tensors
         g = gW.contiguous().reshape(-1).to(torch.float32)
         dLdV = api.wn_backward(V, F, g, grid=ctx.grid, Q=Q, pairs=pairs)
-        return dLdV, None, None, None, None, None
+        return dLdV, None, None, None, None, None, None
 
 
 class NaiveWindingNumber(torch.autograd.Function):
@@ -77,4 +81,4 @@ def naive_winding_number(V, F, grid=None, Q=None):
 
 
 def soft_occupancy(V, F, grid=None, Q=None, tau: float = 0.5, k: float = 50.0, strips=None, pairs=None):
-    return SigmoidOccupancy.apply(WindingNumber.apply(V, F, grid, Q, strips, pairs), tau, k)
+    return SigmoidOccupancy.apply(WindingNumber.apply(V, F, grid, Q, strips, pairs, (tau, k)), tau, k)

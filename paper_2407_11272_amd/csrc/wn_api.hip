@@ -67,7 +67,7 @@ MorphLayout morph_layout(int64_t nV, int64_t nF, int64_t P) {
     MorphLayout l;
     size_t sub = voxelize_ws(3 * nF, P);
     sub = std::max(sub, naive_fwd_workspace(nF, P));
-    sub = std::max(sub, bwd_workspace(nV, nF, P));
+    sub = std::max(sub, bwd_workspace_min(nV, nF, P));
     sub = std::max(sub, loss_ws(P));
     l.sub = 0;
     l.w = align_up(sub);
@@ -301,7 +301,7 @@ wn_status wn_backward_range(const float *V, int64_t nV, const int32_t *F, int64_
     if (grid)
         for (int d = 0; d < 3; ++d)
             if (grid->n[d] > 0 && !(grid->hi[d] > grid->lo[d])) return WN_ERR_INVALID_ARG;
-    const size_t need = bwd_workspace(nV, nF, P);
+    const size_t need = bwd_workspace_min(nV, nF, P);
     if (ws == nullptr || !aligned256(ws) || ws_bytes < need) return WN_ERR_WORKSPACE;
     return run_backward(V, nV, F, nF, pairs, n_pairs, make_point_src(grid, Q), P, dLdW, p0, n, flags, dLdV, dLdT,
                         static_cast<char *>(ws), ws_bytes, static_cast<hipStream_t>(stream));
@@ -366,7 +366,7 @@ wn_status wn_backward_naive(const float *V, int64_t nV, const int32_t *F, int64_
     if (grid)
         for (int d = 0; d < 3; ++d)
             if (grid->n[d] > 0 && !(grid->hi[d] > grid->lo[d])) return WN_ERR_INVALID_ARG;
-    const size_t need = bwd_workspace(nV, nF, P);
+    const size_t need = bwd_workspace_min(nV, nF, P);
     if (ws == nullptr || !aligned256(ws) || ws_bytes < need) return WN_ERR_WORKSPACE;
     return run_backward(V, nV, F, nF, make_point_src(grid, Q), P, dLdW, dLdV, dLdT, static_cast<char *>(ws),
                         ws_bytes, static_cast<hipStream_t>(stream), true);

@@ -29,7 +29,7 @@
 
 #include <rocprim/device/device_radix_sort.hpp>
 
-#include "wn_internal.hpp"
+#include "wn_cycle.hpp"
 
 namespace wn {
 
@@ -48,10 +48,15 @@ static_assert(kBwdTile == kBlock && kBwdTile == WN_BWD_TILE, "one point per thre
 // R_k x R_l = C_j + D_j x R_0 with D_j = v_k - v_l, C_0 = N = (v_1 - v_0) x (v_2 - v_0)
 // and C_1 = C_2 = 0, so over a tile of points it is C_j sum(w) + D_j x sum(w R_0): four
 // sums per pair instead of nine products.  alpha = (R_0 . N) / (r_0 r_1 r_2) (Eq. 7).
+//
+// kIf: it leaves at once unless st asks for the all-pairs sum.
+template <bool kIf>
 __global__ __launch_bounds__(kBlock) void k_wn_bwd(const FaceRec *__restrict__ soup, int32_t nF, PointSrc ps,
                                                    int64_t nQ, int32_t S, int64_t t0, int64_t t1,
-                                                   const float *__restrict__ dLdW, float2 *__restrict__ state) {
+                                                   const float *__restrict__ dLdW, float2 *__restrict__ state,
+                                                   const CycState *st) {
     __shared__ float4 pts[kPointTile];
+    if (kIf && st->go == 0) return;
     const int tid = threadIdx.x;
     const int64_t tfirst = t0 + blockIdx.y;       // this block's first tile
     const int64_t sy = tfirst % S;                // its split
@@ -139,9 +144,9 @@ __global__ __launch_bounds__(kBlock) void k_wn_bwd(const FaceRec *__restrict__ s
 // T[f][i] = sum over splits (fixed order) of each split's total, * scale (1/(2 pi) for
 // the exact field, 1/(8 pi) for Eq. 4).
 __global__ __launch_bounds__(kBlock) void k_bwd_reduce(const float2 *__restrict__ state, int32_t split, int32_t nF,
-                                                       float scale, float *__restrict__ T) {
+                                                       float scale, float *__restrict__ T, const CycState *st) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (int64_t)nF * 9) return;
+    if (t >= (int64_t)nF * 9 || (st && st->go == 0)) return;
     const int32_t i = (int32_t)(t / nF);
     const int32_t f = (int32_t)(t - (int64_t)i * nF);
     const float2 *p = state + (int64_t)i * nF + f;
@@ -336,6 +341,12 @@ BwdPlan plan_backward(int64_t nV, int64_t nF, int64_t nQ) {
     o += align_up((size_t)p.split * 9 * (size_t)nF * sizeof(float2) * (p.wide ? 2 : 1));
     p.off_T = o;
     o += align_up((size_t)nF * 9 * sizeof(float));
+    p.off_prec = o;
+    o += align_up((size_t)nF * kPairRecBytes);
+    p.off_pmeta = o;
+    o += align_up((size_t)nF * kPairMetaBytes);
+    p.off_pcount = o;
+    o += align_up((size_t)nF * 4);
     p.off_keys = o;
     o += align_up((size_t)nC * 4);
     p.off_vals = o;
@@ -350,21 +361,39 @@ BwdPlan plan_backward(int64_t nV, int64_t nF, int64_t nQ) {
     o += align_up((size_t)nV * 4);
     p.off_ve = o;
     o += align_up((size_t)nV * 4);
-    p.off_prec = o;
-    o += align_up((size_t)nF * kPairRecBytes);
-    p.off_pmeta = o;
-    o += align_up((size_t)nF * kPairMetaBytes);
-    p.off_pcount = o;
-    o += align_up((size_t)nF * 4);
     p.total = o;
     return p;
+}
+
+// Workspace with the boundary-edge adjoint's table and scratch, which take the place of the
+// corner sort's outputs (it does not sort); p.total without.  It has about ten short launches
+// more, which the all-pairs sum reaches at about 2e7 pairs.
+size_t edge_total(const BwdPlan &p, int64_t nV, int64_t nF, int64_t nQ) {
+    if (!cyc_wanted(nV, nF, nQ, 2.0e7)) return 0;
+    return std::max(p.total, p.off_keys2 + kCycTable + cyc_bytes(nV, nF, 0));
+}
+
+bool grid_ok(const PointSrc &ps, int64_t nQ) {
+    wn_grid g;
+    const int64_t n[3] = {nQ / ((int64_t)ps.n1 * ps.n2), ps.n1, ps.n2};
+    for (int d = 0; d < 3; ++d) {
+        g.lo[d] = ps.lo[d];
+        g.n[d] = (int32_t)n[d];
+        g.hi[d] = ps.lo[d] + ps.h[d] * (float)n[d];
+    }
+    return cyc_grid_ok(g);
 }
 
 unsigned blocks_for(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
 
 }  // namespace
 
-size_t bwd_workspace(int64_t nV, int64_t nF, int64_t nQ) { return plan_backward(nV, nF, nQ).total; }
+size_t bwd_workspace(int64_t nV, int64_t nF, int64_t nQ) {
+    const BwdPlan p = plan_backward(nV, nF, nQ);
+    return std::max(p.total, edge_total(p, nV, nF, nQ));
+}
+
+size_t bwd_workspace_min(int64_t nV, int64_t nF, int64_t nQ) { return plan_backward(nV, nF, nQ).total; }
 
 // The flip reuses the adjoint's layout with no points: the corner sort buffers, vertex
 // bounds, and the face-normal table in place of the per-split partials.
@@ -411,6 +440,32 @@ wn_status run_backward(const float *V, int64_t nV, const int32_t *F, int64_t nF,
                        float *dLdV, float *dLdT, char *ws, size_t ws_bytes, hipStream_t s, bool naive) {
     const BwdPlan p = plan_backward(nV, nF, nQ);
     if (ws_bytes < p.total) return WN_ERR_WORKSPACE;
+    // dL/dV alone of a grid's points: from the boundary edges (wn_edge_bwd.hip).  The
+    // all-pairs kernels below then run only for a mesh that the edges do not suit, which is
+    // known on the device.
+    char *table = ws + p.off_keys2;
+    const size_t with_edges = edge_total(p, nV, nF, nQ);
+    const CycState *st = nullptr;
+    if ((flags & kBwdVertexSums) && !naive && with_edges > 0 && ws_bytes >= with_edges && ps.Q == nullptr &&
+        grid_ok(ps, nQ)) {
+        CycMesh m{};
+        m.V = V;
+        m.F = F;
+        m.nV = nV;
+        m.nF = nF;
+        m.ps = ps;
+        m.n0 = (int32_t)(nQ / ((int64_t)ps.n1 * ps.n2));
+        cyc_place(m, table + kCycTable);
+        st = m.st;
+        if (flags & kBwdBegin) {
+            CycHead h{};
+            h.meshes = sizeof(CycHead);
+            h.ppl = 1;
+            cyc_units(m, h);
+            if (launch_cyc_begin(m, h, table, s) != hipSuccess || launch_cyc_edges(h, table, s) != hipSuccess)
+                return WN_ERR_HIP;
+        }
+    }
     WsHeader *hdr = reinterpret_cast<WsHeader *>(ws);
     FaceRec *soup = reinterpret_cast<FaceRec *>(ws + p.off_soup);
     float2 *state = reinterpret_cast<float2 *>(ws + p.off_part);
@@ -443,14 +498,15 @@ wn_status run_backward(const float *V, int64_t nV, const int32_t *F, int64_t nF,
     if (n > 0 && nV > 0 && nF > 0) {
         const int64_t t0 = p0 / kPointTile, t1 = (p0 + n + kPointTile - 1) / kPointTile;
         const int64_t rows = min((int64_t)S, t1 - t0);
+        if (st && launch_edge_bwd(table, nQ, t0, t1, dLdW, state, s) != hipSuccess) return WN_ERR_HIP;
         if (naive) {
             e = launch_naive_bwd(soup, (int32_t)nF, ps, nQ, p.split, t0, t1, (int32_t)rows, dLdW, state, s);
         } else if (use_pairs) {
-            e = launch_bwd_pairs(prec, pmeta, (int32_t)nP, (int32_t)nF, ps, nQ, S, t0, t1, (int32_t)rows, dLdW, state,
-                                 merged, s);
+            e = launch_bwd_pairs(prec, pmeta, (int32_t)nP, ps, nQ, S, t0, t1, (int32_t)rows, dLdW, state,
+                                 merged, st, s);
         } else {
-            k_wn_bwd<<<dim3(blocks_for(nF), (unsigned)rows), kBlock, 0, s>>>(soup, (int32_t)nF, ps, nQ, p.split, t0,
-                                                                              t1, dLdW, state);
+            (st ? k_wn_bwd<true> : k_wn_bwd<false>)<<<dim3(blocks_for(nF), (unsigned)rows), kBlock, 0, s>>>(
+                soup, (int32_t)nF, ps, nQ, p.split, t0, t1, dLdW, state, st);
             e = hipGetLastError();
         }
         if (e != hipSuccess) return WN_ERR_HIP;
@@ -470,15 +526,24 @@ wn_status run_backward(const float *V, int64_t nV, const int32_t *F, int64_t nF,
     int32_t *vs = reinterpret_cast<int32_t *>(ws + p.off_vs);
     int32_t *ve = reinterpret_cast<int32_t *>(ws + p.off_ve);
     if (nQ > 0 && use_pairs) {
-        if ((e = launch_reduce_pairs(state, S, (int32_t)nP, pmeta, kInv2Pi, T, merged, s)) != hipSuccess)
+        if ((e = launch_reduce_pairs(state, S, (int32_t)nP, pmeta, kInv2Pi, T, merged, st, s)) != hipSuccess)
             return WN_ERR_HIP;
     } else if (nQ > 0) {
-        k_bwd_reduce<<<blocks_for(9 * nF), kBlock, 0, s>>>(state, p.split, (int32_t)nF, naive ? kInv8Pi : kInv2Pi, T);
+        k_bwd_reduce<<<blocks_for(9 * nF), kBlock, 0, s>>>(state, p.split, (int32_t)nF, naive ? kInv8Pi : kInv2Pi, T,
+                                                       st);
     } else {
         k_fill_i32<<<blocks_for(9 * nF), kBlock, 0, s>>>(reinterpret_cast<int32_t *>(T), 9 * nF, 0);
     }
     if ((e = hipGetLastError()) != hipSuccess) return WN_ERR_HIP;
 
+    if (st) {
+        // the edges' gradients lie behind T (9 nF floats), in the sort's first two arrays (6 nF)
+        float *G = reinterpret_cast<float *>(keys);
+        if (launch_edge_reduce(table, nQ, state, G, s) != hipSuccess ||
+            launch_edge_gather(table, nV, G, T, dLdV, s) != hipSuccess)
+            return WN_ERR_HIP;
+        return WN_OK;
+    }
     const int64_t nC = 3 * nF;
     k_corner_keys<<<blocks_for(nC), kBlock, 0, s>>>(F, nC, nV, keys, vals);
     if ((e = hipGetLastError()) != hipSuccess) return WN_ERR_HIP;

@@ -3,7 +3,7 @@
 // lane adjoint (the chain rule through Eq. 7/8 for dW/dv, Section 2.4 of arXiv
 // 2407.11272); this file is compiled with the backend's ILP-first scheduler, which
 // orders this kernel's point loop better (and the one-face kernel's worse).
-#include "wn_internal.hpp"
+#include "wn_cycle.hpp"
 
 namespace wn {
 
@@ -147,13 +147,15 @@ __global__ __launch_bounds__(kBlock) void k_check_counts(const int32_t *__restri
 // corner terms are exactly zero; its tile sums of w (the beta u_j terms) are dropped.
 // kThreads: lanes per workgroup, 256 or 64 (one wave); every wave stages the whole point
 // tile, so the per-lane arithmetic and the bits do not depend on it.
-template <bool kMerge, int kThreads>
+// kIf: it leaves at once unless st asks for the all-pairs sum.
+template <bool kMerge, int kThreads, bool kIf>
 __global__ __launch_bounds__(kThreads) void k_wn_bwd_pairs(const PairRec *__restrict__ recs,
-                                                         const PairMeta *__restrict__ meta, int32_t nP, int32_t nF,
-                                                         PointSrc ps, int64_t nQ, int32_t S, int64_t t0, int64_t t1,
-                                                         const float *__restrict__ dLdW,
-                                                         float2 *__restrict__ state) {
+                                                           const PairMeta *__restrict__ meta, int32_t nP, PointSrc ps,
+                                                           int64_t nQ, int32_t S, int64_t t0, int64_t t1,
+                                                           const float *__restrict__ dLdW,
+                                                           float2 *__restrict__ state, const CycState *st) {
     __shared__ float4 pts[kPointTile];
+    if (kIf && st->go == 0) return;
     const int tid = threadIdx.x;
     const int64_t tfirst = t0 + blockIdx.y;
     const int64_t sy = tfirst % S;
@@ -361,9 +363,9 @@ __global__ __launch_bounds__(kThreads) void k_wn_bwd_pairs(const PairRec *__rest
 __global__ __launch_bounds__(kBlock) void k_bwd_reduce_pairs(const float2 *__restrict__ state, int32_t split,
                                                              int32_t nP, int32_t rows,
                                                              const PairMeta *__restrict__ meta, float scale,
-                                                             float *__restrict__ T) {
+                                                             float *__restrict__ T, const CycState *st) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= (int64_t)nP * rows) return;
+    if (t >= (int64_t)nP * rows || (st && st->go == 0)) return;
     const int32_t i = (int32_t)(t / nP);
     const int32_t p = (int32_t)(t - (int64_t)i * nP);
     const PairMeta m = meta[p];
@@ -421,9 +423,9 @@ hipError_t launch_pack_pairs(const float *V, int64_t nV, const int32_t *F, int64
     return hipGetLastError();
 }
 
-hipError_t launch_bwd_pairs(const char *recs, const char *meta, int32_t nP, int32_t nF, const PointSrc &ps, int64_t nQ,
+hipError_t launch_bwd_pairs(const char *recs, const char *meta, int32_t nP, const PointSrc &ps, int64_t nQ,
                             int32_t S, int64_t t0, int64_t t1, int32_t rows, const float *dLdW, float2 *state,
-                            bool merged, hipStream_t s) {
+                            bool merged, const CycState *st, hipStream_t s) {
     static_assert(kPointTile % 64 == 0 && kBlock % 64 == 0, "whole waves");
     // One-wave workgroups avoid the idle waves of a last, mostly empty column of 256-lane
     // workgroups (C3: 2576 pairs, 44 waves for 41 of work); they cost about 2.5 % more per
@@ -433,27 +435,20 @@ hipError_t launch_bwd_pairs(const char *recs, const char *meta, int32_t nP, int3
     const bool narrow = waves_wide * 40 > waves_narrow * 41;
     const auto *r = reinterpret_cast<const PairRec *>(recs);
     const auto *m = reinterpret_cast<const PairMeta *>(meta);
-    if (narrow) {
-        const dim3 grid((unsigned)waves_narrow, (unsigned)rows);
-        if (merged)
-            k_wn_bwd_pairs<true, 64><<<grid, 64, 0, s>>>(r, m, nP, nF, ps, nQ, S, t0, t1, dLdW, state);
-        else
-            k_wn_bwd_pairs<false, 64><<<grid, 64, 0, s>>>(r, m, nP, nF, ps, nQ, S, t0, t1, dLdW, state);
-    } else {
-        const dim3 grid(blocks_of(nP), (unsigned)rows);
-        if (merged)
-            k_wn_bwd_pairs<true, kBlock><<<grid, kBlock, 0, s>>>(r, m, nP, nF, ps, nQ, S, t0, t1, dLdW, state);
-        else
-            k_wn_bwd_pairs<false, kBlock><<<grid, kBlock, 0, s>>>(r, m, nP, nF, ps, nQ, S, t0, t1, dLdW, state);
-    }
+    const dim3 grid((unsigned)(narrow ? waves_narrow : blocks_of(nP)), (unsigned)rows);
+    auto *k = narrow ? (st ? k_wn_bwd_pairs<true, 64, true>
+                           : (merged ? k_wn_bwd_pairs<true, 64, false> : k_wn_bwd_pairs<false, 64, false>))
+                     : (st ? k_wn_bwd_pairs<true, kBlock, true>
+                           : (merged ? k_wn_bwd_pairs<true, kBlock, false> : k_wn_bwd_pairs<false, kBlock, false>));
+    k<<<grid, narrow ? 64 : kBlock, 0, s>>>(r, m, nP, ps, nQ, S, t0, t1, dLdW, state, st);  // st: merged
     return hipGetLastError();
 }
 
 hipError_t launch_reduce_pairs(const float2 *state, int32_t S, int32_t nP, const char *meta, float scale, float *T,
-                               bool merged, hipStream_t s) {
+                               bool merged, const CycState *st, hipStream_t s) {
     const int32_t rows = merged ? 12 : 18;
     k_bwd_reduce_pairs<<<blocks_of((int64_t)rows * nP), kBlock, 0, s>>>(
-        state, S, nP, rows, reinterpret_cast<const PairMeta *>(meta), scale, T);
+        state, S, nP, rows, reinterpret_cast<const PairMeta *>(meta), scale, T, st);
     return hipGetLastError();
 }
 

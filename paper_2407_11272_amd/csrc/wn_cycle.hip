@@ -69,10 +69,12 @@ constexpr uint32_t kCountBias = 0x40000000u, kCloseBit = 0x80000000u;
 __device__ void clear_unit(const CycMesh &m, int64_t u) {
     for (int64_t i = u * kCycClear + threadIdx.x; i < (u + 1) * kCycClear; i += kCycUnit) {
         if (i < m.buckets) m.head[i] = -1;
-        if (i < m.nV) m.hout[i] = m.hin[i] = -1;
+        if (m.W && i < m.nV) m.hout[i] = m.hin[i] = -1;
         if (m.strips && i < m.nF) m.count[i] = 0;
-        if (i < m.P) reinterpret_cast<uint32_t *>(m.W)[m.p0 + i] = kCountBias;
-        if (32 * i < m.P) m.mark[i] = 0u;
+        if (m.W && i < m.P) reinterpret_cast<uint32_t *>(m.W)[m.p0 + i] = kCountBias;
+        if (m.W && 32 * i < m.P) m.mark[i] = 0u;
+        if (!m.W && i < m.nV) m.used[i] = 0;
+        if (!m.W && i < 3 * m.nV) m.grad[i] = 0;
         if (i == 0) *m.st = CycState{};
     }
 }
@@ -251,7 +253,24 @@ __global__ __launch_bounds__(kCycUnit) void k_cyc_faces(const char *table) {
                 }
                 m.ent[3 * f + part] = x;
             }
-            if (bits <= __float_as_uint(kCoordMax)) {  // else the mesh goes direct
+            if (!m.W) {
+                // a face whose vertex is a query point contributes nothing there, so its
+                // edges do not cancel its neighbours': the all-pairs sum takes such a mesh
+                if (part < 3) {
+                    const int32_t v = part == 0 ? id[0] : part == 1 ? id[1] : id[2];
+                    m.used[v] = 1;
+                    bool same = true;
+                    for (int d = 0; d < 3; ++d) {
+                        const float x = part == 0 ? p[0][d] : part == 1 ? p[1][d] : p[2][d];
+                        int a, b;
+                        cell_range(m, d, x, x, 0, (d == 0 ? m.n0 : d == 1 ? m.ps.n1 : m.ps.n2) - 1, a, b);
+                        bool hit = false;
+                        for (int k = a - 1; k <= b + 1; ++k) hit = hit || axis_centre(m.ps, d, k) == x;
+                        same = same && hit;
+                    }
+                    if (same) atomicMax(&m.st->go, 2);
+                }
+            } else if (bits <= __float_as_uint(kCoordMax)) {  // else the mesh goes direct
                 RasterFace r;
                 r.set(m, p[0], p[1], p[2]);
                 const int64_t n = r.columns();
@@ -409,6 +428,19 @@ __global__ __launch_bounds__(kCapThreads) void k_cyc_caps(const char *table) {
         }
         const int B = (int)B64;
         if (B == 0) continue;
+        if (!m.W) {  // the edges are all that is wanted
+            __syncthreads();
+            for (int64_t u = tid >> 6; u < units; u += kCapThreads / 64) {
+                const int n = m.blk[2 * u], at = m.blk[2 * u + 1];
+                for (int x = tid & 63; x < n; x += 64) {
+                    int32_t a, b;
+                    half_edge(m, m.list[u * kCycUnit + x], a, b);
+                    m.edge[at + x] = make_int2(a, b);
+                }
+            }
+            if (tid == 0) m.st->n_rec = B;
+            continue;
+        }
         int n_tri = 0, n_short = 0;
         // (a lambda's two instances, so that LDS is addressed as LDS)
         auto join = [&](int2 *edge, int32_t *nout, int32_t *nin, int32_t *rank, int32_t *next) -> int {
@@ -613,9 +645,14 @@ __device__ __forceinline__ void list_near(const CycMesh &m, int64_t idx) {
         atomicMax(&m.st->go, 1);
 }
 
-// Close enough to the threshold for rounding to decide: the direct sum decides.
+// Where the occupancy map amplifies the rounding of W: within rounding of a threshold, and
+// on the slope of a steep sigmoid (k |dW| there, in the loss gradients that follow as
+// well, against W's own 1e-6).  Such voxels take the direct sum, so that the map's outcome does not depend
+// on the path.  They lie around the holes: 0.2 % of the voxels of a mesh with 5 % of its faces missing.
 __device__ __forceinline__ bool near_threshold(const OccParams &o, float w) {
-    return o.mode == WN_OCC_THRESHOLD && __builtin_fabsf(w - o.tau) < 1.0e-5f;
+    const float d = __builtin_fabsf(w - o.tau);
+    if (o.mode == WN_OCC_THRESHOLD) return d < 1.0e-5f;
+    return o.mode == WN_OCC_SIGMOID && o.k > 10.0f && d < fminf(10.0f / o.k, 0.25f);
 }
 
 // One wave per column, from the top: W is the sum of the crossings at and above a voxel.
@@ -945,9 +982,9 @@ __global__ __launch_bounds__(kNearThreads) void k_cyc_near(const char *table) {
 
 // The path costs about ten short launches; the all-pairs sum reaches that at about 5e7
 // pairs.  A few large faces are better summed: their close voxels are many.
-bool cyc_wanted(int64_t nV, int64_t nF, int64_t P) {
+bool cyc_wanted(int64_t nV, int64_t nF, int64_t P, double min_pairs) {
     return nF >= 128 && nV > 0 && nV < ((int64_t)1 << 30) && nF < ((int64_t)1 << 28) && P > 0 &&
-           (double)nF * (double)P >= 5.0e7;
+           (double)nF * (double)P >= min_pairs;
 }
 
 bool cyc_grid_ok(const wn_grid &g) {
@@ -977,12 +1014,17 @@ void cyc_arrays(CycMesh &m, Fn &&take) {
     take(m.st, sizeof(CycState));
     take(m.ent, 16 * 3 * nF);
     take(m.head, 4 * (size_t)edge_buckets(m.nF));
-    take(m.hout, 4 * nV);
-    take(m.hin, 4 * nV);
     take(m.count, 4 * nF);
     take(m.list, 4 * units * kCycUnit);
     take(m.blk, 8 * units);
     take(m.edge, 8 * nF);
+    if (m.P == 0) {
+        take(m.used, 4 * nV);
+        take(m.grad, 24 * nV);
+        return;
+    }
+    take(m.hout, 4 * nV);
+    take(m.hin, 4 * nV);
     take(m.nout, 4 * nF);
     take(m.nin, 4 * nF);
     take(m.rank, 4 * nF);
@@ -1036,7 +1078,7 @@ void cyc_units(CycMesh &m, CycHead &h) {
     const int64_t yz = (int64_t)m.ps.n1 * m.ps.n2;
     m.i_first = (int32_t)(m.p0 / yz);
     m.i_last = (int32_t)((m.p0 + m.P - 1) / yz);
-    h.u_clear += units(std::max(std::max(m.buckets, m.nV), std::max(m.nF, m.P)), kCycClear);
+    h.u_clear += units(std::max(std::max(m.buckets, 3 * m.nV), std::max(m.nF, m.P)), kCycClear);
     h.u_face += units(m.nF, kCycUnit / kCycFaceLanes);
     h.u_half += units(3 * m.nF, kCycUnit);
     h.u_col += units(columns, kCycColumns);
@@ -1067,6 +1109,13 @@ hipError_t launch_cyc(const CycHead &h, char *table, bool fixed, hipStream_t s) 
         k_cyc_sum<2><<<grid(h.u_sum), kBlock, 0, s>>>(table);
     else
         k_cyc_sum<4><<<grid(h.u_sum), kBlock, 0, s>>>(table);
+    return hipGetLastError();
+}
+
+hipError_t launch_cyc_edges(const CycHead &h, char *table, hipStream_t s) {
+    k_cyc_faces<<<dim3((unsigned)h.u_face), kCycUnit, 0, s>>>(table);
+    k_cyc_mark<<<dim3((unsigned)h.u_half), kCycUnit, 0, s>>>(table);
+    k_cyc_caps<<<1, kCapThreads, 0, s>>>(table);
     return hipGetLastError();
 }
 

@@ -42,7 +42,9 @@ struct CycState {
     int32_t n_tri;      // triangles (three records each)
     int32_t n_short;    // records of the triangles and the other short loops
     int32_t n_near;     // points on the list of direct sums
+    int32_t odd;        // adjoint: dL/dW holds a value that is not finite
     uint32_t max_bits;  // bits of the largest |coordinate| of a face corner
+    uint32_t grad_bits; // adjoint: bits of the largest |term|
     unsigned long long n_slab;  // entries asked of the raster list
 };
 
@@ -58,7 +60,7 @@ struct CycMesh {
     int32_t strips;       // the stream has to name every face once
     int64_t p0, P;        // the voxels [p0, p0 + P)
     int32_t i_first, i_last;  // their range along x
-    float *W;
+    float *W;             // null: the boundary edges alone (the adjoint)
     OccParams occ;
     CycState *st;
     double inv_h[3], slack[3];  // cells per length, and the rounding of a voxel centre in cells
@@ -66,6 +68,8 @@ struct CycMesh {
     int32_t *head;        // [buckets] first half-edge of a bucket
     int64_t buckets;      // a power of two
     int32_t *hout, *hin;  // [nV] first boundary edge leaving / entering a vertex
+    int32_t *used;        // [nV] adjoint: 1 for a vertex of a face
+    int64_t *grad;        // [nV][3] adjoint: sums of its terms
     int32_t *count;       // [nF] times the stream names a face
     int32_t *list, *blk;  // boundary half-edges of each unit, and their number and offset
     int2 *edge;           // [nF] boundary edges (start, end)
@@ -90,10 +94,11 @@ struct CycHead {
 
 // Whether sizes make the boundary path worth its fixed cost (see wn_cycle.hip); P is the
 // whole grid, so that a slice takes the path of the grid.
-bool cyc_wanted(int64_t nV, int64_t nF, int64_t P);
+bool cyc_wanted(int64_t nV, int64_t nF, int64_t P, double min_pairs = 5.0e7);
 // Whether the grid's extent is finite and in the range of the path.
 bool cyc_grid_ok(const wn_grid &g);
-// Scratch bytes of one mesh with P voxels in its slice, and its pointers laid out from `base`.
+// Scratch bytes of one mesh with P voxels in its slice (0: for the boundary edges alone), and
+// its pointers laid out from `base`.
 size_t cyc_bytes(int64_t nV, int64_t nF, int64_t P);
 void cyc_place(CycMesh &m, char *base);
 // Unit numbers of mesh m, after what `h` holds already.
@@ -108,6 +113,19 @@ hipError_t launch_cyc_begin(const CycMesh &m, const CycHead &h, char *table, hip
 hipError_t launch_cyc_clear(char *table, hipStream_t s);
 hipError_t launch_cyc(const CycHead &h, char *table, bool fixed, hipStream_t s);
 hipError_t launch_cyc_near(char *table, hipStream_t s);
+
+// The boundary edges alone, after `begin`.
+hipError_t launch_cyc_edges(const CycHead &h, char *table, hipStream_t s);
+
+// Adjoint over the boundary edges (wn_edge_bwd.hip) for one mesh's table: the points of the
+// tiles [t0, t1), the gradients of each edge's ends (G, float [B][6]), and dL/dV from
+// them, or from the corners' gradients T where the state asks for the all-pairs sum.
+// state: as much as the all-pairs adjoint's.
+hipError_t launch_edge_bwd(const char *table, int64_t nQ, int64_t t0, int64_t t1, const float *dLdW, float2 *state,
+                           hipStream_t s);
+hipError_t launch_edge_reduce(const char *table, int64_t nQ, const float2 *state, float *G, hipStream_t s);
+hipError_t launch_edge_gather(const char *table, int64_t nV, const float *G, const float *T, float *dLdV,
+                              hipStream_t s);
 
 // Whether the all-pairs kernels write voxel idx (counted from the slice's first): go is
 // the state's, or null where the mesh has no boundary path.

@@ -1,0 +1,278 @@
+// Adjoint for dL/dV from the mesh's boundary edges.
+//
+// The solid angle of a face depends on its edges alone: moving a vertex changes it by
+// line integrals along the face's edges (the Biot-Savart form of dOmega), and the two
+// faces at an inner edge run along it in opposite directions.  So in
+//     dL/dV = sum over faces of dL/dT
+// the inner edges cancel, and what is left is the sum over the boundary edges of
+// wn_cycle.hip: for an edge from u to v, with A = u - q, B = v - q, E = v - u,
+//     dW/du = -(A x E) / (4 pi |A| (|A| |B| + A . B)),
+//     dW/dv = -(A x E) / (4 pi |B| (|A| |B| + A . B)).
+// A closed mesh has no such edge and no gradient (Section 2.4 of arXiv 2407.11272 notes
+// that it vanishes).
+//
+// One lane owns an edge and keeps six sums, sum(g J P) for either end: A x E = P x E with P the
+// part of A at right angles to E, so the cross product waits until the sums are complete.  Points come
+// through LDS, 256 to a tile, tiles dealt to S splits in turn, as in the all-pairs adjoint (the same
+// calls on point ranges give the same bits as one call).
+//
+// The all-pairs adjoint is bound by its arithmetic over all faces; here the arithmetic of 42 VALU
+// instructions and 3 transcendentals per (edge, point) bounds the point kernel.  Measured, whole
+// adjoint: 7706 faces with 1154 boundary edges on 96 x 88 x 97 points, 10.0 -> 1.08 ms (point kernel
+// 1.02 ms); 9140 faces, 2.6 % of them missing, on 43 x 32 x 17 points, 519 -> 118 us.  The error
+// against 64 bits falls too (1.3e-6 -> 1e-7 in the first): fewer terms, and none that cancel.
+#include "wn_cycle.hpp"
+
+namespace wn {
+
+namespace {
+
+constexpr int kEdgeWaves = 16384;  // one-wave workgroups of the point kernel
+constexpr int kTile = kBwdTile;
+
+// Splits of B edges over the tiles of the points, a pure function of the sizes: about
+// kEdgeWaves waves of (64 edges, split), all with the same number of tiles.
+__device__ __forceinline__ int edge_splits(int B, int tiles) {
+    const int64_t blocks = B > 64 ? (B + 63) / 64 : 1;
+    const int per = max((int)((tiles * blocks + kEdgeWaves - 1) / kEdgeWaves), (tiles + 4095) / 4096);
+    return max(1, (tiles + per - 1) / max(1, per));
+}
+
+// state: float2 (sum, compensation) [S][6][B].  Grid: waves; wave w takes edge block
+// w mod blocks of the split w / blocks.  dL/dW that is not finite is noted (with
+// no edge at all the points are only looked at): every vertex gets NaN then, as from the
+// all-pairs sum.
+__global__ __launch_bounds__(64) void k_edge_bwd(const char *table, int64_t nQ, int64_t t0, int64_t t1,
+                                                 const float *__restrict__ dLdW, float2 *__restrict__ state) {
+    __shared__ float4 pts[kTile];
+    const CycMesh &m = *reinterpret_cast<const CycMesh *>(table + reinterpret_cast<const CycHead *>(table)->meshes);
+    if (m.st->go) return;
+    const int B = __builtin_amdgcn_readfirstlane(m.st->n_rec);
+    const int blocks = B > 64 ? (B + 63) / 64 : 1;
+    const int tiles = (int)((nQ + kTile - 1) / kTile), S = edge_splits(B, tiles);
+    const int lane = threadIdx.x;
+    const PointSrc ps = m.ps;
+    bool odd = false;
+    for (int w = blockIdx.x; w < blocks * S; w += gridDim.x) {
+        const int s = w / blocks, block = w - s * blocks;
+        // the split's first tile in the range
+        int t = (int)t0 - (int)t0 % S + s;
+        if (t < (int)t0) t += S;
+        if (t >= (int)t1) continue;
+        const int e = block * 64 + lane;
+        const bool live = e < B;
+        const int2 id = B > 0 ? m.edge[live ? e : B - 1] : make_int2(0, 0);
+        const float *pu = m.V + 3 * (int64_t)id.x, *pv = m.V + 3 * (int64_t)id.y;
+        const float ux = pu[0], uy = pu[1], uz = pu[2];
+        const double ex = (double)pv[0] - ux, ey = (double)pv[1] - uy, ez = (double)pv[2] - uz;
+        const double l2 = ex * ex + ey * ey + ez * ez, inv = l2 > 0.0 ? 1.0 / l2 : 0.0;
+        const float Ex = (float)ex, Ey = (float)ey, Ez = (float)ez, L2 = (float)l2, L = (float)sqrt(l2);
+        const float tiny = (float)(1.0e-24 * l2 * l2);
+        const float Fx = (float)(ex * inv), Fy = (float)(ey * inv), Fz = (float)(ez * inv);  // E / |E|^2
+        for (; t < (int)t1; t += S) {
+            const int q0 = t * kTile;
+            const int nt = (int)min((int64_t)kTile, nQ - q0);
+            __syncthreads();
+#pragma unroll 1
+            for (int k = 0; k < kTile / 64; ++k) {
+                const int j = lane + 64 * k;
+                float x, y, z, g = 0.0f;  // past the last point: that point again, without weight
+                ps.get(q0 + min(j, nt - 1), x, y, z);
+                if (j < nt) g = dLdW[q0 + j];
+                odd = odd || !(__builtin_fabsf(g) < INFINITY);
+                pts[j] = make_float4(x, y, z, g);
+            }
+            __syncthreads();
+            if (B == 0) continue;
+            float su[3] = {0.0f, 0.0f, 0.0f}, sv[3] = {0.0f, 0.0f, 0.0f};
+#pragma unroll 4
+            for (int i = 0; i < kTile; ++i) {
+                const float4 q = pts[i];
+                const float x = ux - q.x, y = uy - q.y, z = uz - q.z;
+                const float a = x * Fx + y * Fy + z * Fz;  // A = a E + P
+                const float px = x - a * Ex, py = y - a * Ey, pz = z - a * Ez;
+                const float d2 = px * px + py * py + pz * pz;
+                const float ul = a * L, vl = ul + L;
+                const float A2 = ul * ul + d2, B2 = vl * vl + d2, AB = ul * vl + d2;
+                // (no point is at a vertex: such a mesh took the all-pairs sum)
+                const float ia = __builtin_amdgcn_rsqf(A2), ib = __builtin_amdgcn_rsqf(B2);
+                const float mn = (A2 * ia) * (B2 * ib) + __builtin_fabsf(AB);
+                // 1 / (|A| |B| + A . B); between the ends, where that cancels, through
+                // (|A| |B|)^2 - (A . B)^2 = |P|^2 |E|^2 (on the edge itself P = 0 and so is the term)
+                const bool between = AB < 0.0f;
+                const float den = between ? __builtin_fmaf(d2, L2, tiny) : mn;
+                const float k = (between ? mn * q.w : q.w) * __builtin_amdgcn_rcpf(den);
+                const float ku = k * ia, kv = k * ib;
+                su[0] += ku * px, su[1] += ku * py, su[2] += ku * pz;
+                sv[0] += kv * px, sv[1] += kv * py, sv[2] += kv * pz;
+            }
+            if (live) {
+                float2 *row = state + (int64_t)s * 6 * B + e;
+                const float ts[6] = {su[0], su[1], su[2], sv[0], sv[1], sv[2]};
+                float2 x[6];
+#pragma unroll
+                for (int i = 0; i < 6; ++i) x[i] = t < S ? make_float2(0.0f, 0.0f) : row[(int64_t)i * B];
+#pragma unroll
+                for (int i = 0; i < 6; ++i) {
+                    neumaier_add(x[i].x, x[i].y, ts[i]);
+                    row[(int64_t)i * B] = x[i];
+                }
+            }
+        }
+    }
+    if (__builtin_amdgcn_ballot_w64(odd) && lane == 0) atomicOr(&m.st->odd, 1);
+}
+
+// One wave per edge: its six sums over the splits (lane l the splits l, l + 64, ... in
+// order, then the lanes in pairs), and the gradients of its two ends.
+__global__ __launch_bounds__(kBlock) void k_edge_reduce(const char *table, int64_t nQ, const float2 *__restrict__ state,
+                                                        float *__restrict__ G) {
+    const CycMesh &m = *reinterpret_cast<const CycMesh *>(table + reinterpret_cast<const CycHead *>(table)->meshes);
+    if (m.st->go) return;
+    const int64_t B = m.st->n_rec, S = edge_splits((int)B, (int)((nQ + kTile - 1) / kTile));
+    const int lane = threadIdx.x & 63;
+    uint32_t bits = 0;
+    for (int64_t e = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6); e < B;
+         e += (int64_t)gridDim.x * (kBlock / 64)) {
+        float s[6], c[6];
+#pragma unroll
+        for (int i = 0; i < 6; ++i) s[i] = c[i] = 0.0f;
+        for (int64_t k = lane; k < S; k += 64) {
+            float2 x[6];
+#pragma unroll
+            for (int i = 0; i < 6; ++i) x[i] = state[(k * 6 + i) * B + e];
+#pragma unroll
+            for (int i = 0; i < 6; ++i) {
+                neumaier_add(s[i], c[i], x[i].x);
+                c[i] += x[i].y;
+            }
+        }
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1)
+#pragma unroll
+            for (int i = 0; i < 6; ++i) {
+                const float os = __shfl_xor(s[i], o), oc = __shfl_xor(c[i], o);
+                const float a = (lane & o) ? os : s[i], b = (lane & o) ? s[i] : os;  // lower lane first
+                const float t = a + b;
+                const float big = __builtin_fabsf(a) >= __builtin_fabsf(b) ? a : b;
+                const float small = __builtin_fabsf(a) >= __builtin_fabsf(b) ? b : a;
+                c[i] = (c[i] + oc) + ((big - t) + small);
+                s[i] = t;
+            }
+        if (lane == 0) {
+            const int2 id = m.edge[e];
+            const float *pu = m.V + 3 * (int64_t)id.x, *pv = m.V + 3 * (int64_t)id.y;
+            const double E[3] = {(double)pv[0] - pu[0], (double)pv[1] - pu[1], (double)pv[2] - pu[2]};
+            const double f = -0.07957747154594767;  // -1 / (4 pi)
+#pragma unroll
+            for (int end = 0; end < 2; ++end) {
+                const double P[3] = {(double)s[3 * end] + c[3 * end], (double)s[3 * end + 1] + c[3 * end + 1],
+                                     (double)s[3 * end + 2] + c[3 * end + 2]};
+                G[6 * e + 3 * end + 0] = (float)(f * (P[1] * E[2] - P[2] * E[1]));
+                G[6 * e + 3 * end + 1] = (float)(f * (P[2] * E[0] - P[0] * E[2]));
+                G[6 * e + 3 * end + 2] = (float)(f * (P[0] * E[1] - P[1] * E[0]));
+                for (int d = 0; d < 3; ++d) {
+                    const float x = __builtin_fabsf(G[6 * e + 3 * end + d]);
+                    if (x < INFINITY) bits = max(bits, __float_as_uint(x));
+                }
+            }
+        }
+    }
+    if (lane == 0 && bits) atomicMax(&m.st->grad_bits, bits);
+}
+
+// The terms of dL/dV: the two ends of each boundary edge (G), or, for a mesh that took the
+// all-pairs sum, every corner (T).  They are added per vertex as 64-bit integers on one
+// scale, so that the sum does not depend on the order: with n terms of at most 2^e the
+// unit is 2^(e - 61) n, rounded up to a power of two, 1e-13 of the largest term for 1e5
+// terms.
+struct Terms {
+    const float *x;  // three floats per term
+    int64_t n;
+    bool edges;
+};
+
+__device__ __forceinline__ Terms terms_of(const CycMesh &m, const float *G, const float *T) {
+    if (m.st->go) return Terms{T, 3 * m.nF, false};
+    return Terms{G, 2 * (int64_t)m.st->n_rec, true};
+}
+
+// Power of two that a term is multiplied by.
+__device__ __forceinline__ int term_shift(const CycMesh &m, int64_t n) {
+    int bits = 0;
+    while (bits < 40 && ((int64_t)1 << bits) < n) ++bits;
+    int e = (int)(m.st->grad_bits >> 23) - 126;  // |term| < 2^e
+    return 61 - bits - e;
+}
+
+// Largest corner gradient (the edges' is noted as they are formed).
+__global__ __launch_bounds__(kBlock) void k_corner_max(const char *table, const float *__restrict__ T) {
+    const CycMesh &m = *reinterpret_cast<const CycMesh *>(table + reinterpret_cast<const CycHead *>(table)->meshes);
+    if (m.st->go == 0) return;
+    uint32_t bits = 0;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < 9 * m.nF; i += (int64_t)gridDim.x * blockDim.x) {
+        const float x = __builtin_fabsf(T[i]);
+        if (x < INFINITY) bits = max(bits, __float_as_uint(x));
+    }
+    for (int o = 32; o > 0; o >>= 1) bits = max(bits, (uint32_t)__shfl_xor((int)bits, o));
+    if ((threadIdx.x & 63) == 0 && bits) atomicMax(&m.st->grad_bits, bits);
+}
+
+__global__ __launch_bounds__(kBlock) void k_add_terms(const char *table, const float *__restrict__ G,
+                                                      const float *__restrict__ T) {
+    const CycMesh &m = *reinterpret_cast<const CycMesh *>(table + reinterpret_cast<const CycHead *>(table)->meshes);
+    const Terms t = terms_of(m, G, T);
+    const int shift = term_shift(m, t.n);
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < t.n; i += (int64_t)gridDim.x * blockDim.x) {
+        int32_t v;
+        if (t.edges) {
+            const int2 e = m.edge[i >> 1];
+            v = (i & 1) ? e.y : e.x;
+        } else {
+            v = m.F[i];
+            if (v < 0 || (int64_t)v >= m.nV) v = 0;
+        }
+        for (int d = 0; d < 3; ++d) {
+            const float x = t.x[3 * i + d];
+            if (__builtin_fabsf(x) < INFINITY)
+                atomicAdd(reinterpret_cast<unsigned long long *>(&m.grad[3 * (int64_t)v + d]),
+                          (unsigned long long)__double2ll_rn(ldexp((double)x, shift)));
+            else
+                m.used[v] = 2;
+        }
+    }
+}
+
+__global__ __launch_bounds__(kBlock) void k_write_grad(const char *table, float *__restrict__ dLdV) {
+    const CycMesh &m = *reinterpret_cast<const CycMesh *>(table + reinterpret_cast<const CycHead *>(table)->meshes);
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= 3 * m.nV) return;
+    const int32_t used = m.used[i / 3];
+    const int shift = term_shift(m, m.st->go ? 3 * m.nF : 2 * (int64_t)m.st->n_rec);
+    // dL/dW that is not finite reaches every vertex of a face
+    const bool odd = used == 2 || (used == 1 && m.st->go == 0 && m.st->odd);
+    dLdV[i] = odd ? NAN : (float)ldexp((double)m.grad[i], -shift);
+}
+
+}  // namespace
+
+hipError_t launch_edge_bwd(const char *table, int64_t nQ, int64_t t0, int64_t t1, const float *dLdW, float2 *state,
+                           hipStream_t s) {
+    k_edge_bwd<<<kEdgeWaves, 64, 0, s>>>(table, nQ, t0, t1, dLdW, state);
+    return hipGetLastError();
+}
+
+hipError_t launch_edge_reduce(const char *table, int64_t nQ, const float2 *state, float *G, hipStream_t s) {
+    k_edge_reduce<<<1024, kBlock, 0, s>>>(table, nQ, state, G);
+    return hipGetLastError();
+}
+
+hipError_t launch_edge_gather(const char *table, int64_t nV, const float *G, const float *T, float *dLdV,
+                              hipStream_t s) {
+    k_corner_max<<<256, kBlock, 0, s>>>(table, T);
+    k_add_terms<<<256, kBlock, 0, s>>>(table, G, T);
+    k_write_grad<<<(unsigned)((3 * nV + kBlock - 1) / kBlock), kBlock, 0, s>>>(table, dLdV);
+    return hipGetLastError();
+}
+
+}  // namespace wn

@@ -127,14 +127,13 @@ struct PointSrc {
             y = Q[3 * idx + 1];
             z = Q[3 * idx + 2];
         } else {
-            const int64_t yz = (int64_t)n1 * n2;
-            const int32_t i = (int32_t)(idx / yz);
-            const int32_t rem = (int32_t)(idx - (int64_t)i * yz);
-            const int32_t j = rem / n2;
-            const int32_t k = rem - j * n2;
-            x = __builtin_fmaf((float)i + 0.5f, h[0], lo[0]);
-            y = __builtin_fmaf((float)j + 0.5f, h[1], lo[1]);
-            z = __builtin_fmaf((float)k + 0.5f, h[2], lo[2]);
+            // flat indices are below 2^31: 32-bit divisions
+            const uint32_t yz = (uint32_t)n1 * (uint32_t)n2, u = (uint32_t)idx;
+            const uint32_t i = u / yz, rem = u - i * yz;
+            const uint32_t j = rem / (uint32_t)n2, k = rem - j * (uint32_t)n2;
+            x = __builtin_fmaf((float)(int32_t)i + 0.5f, h[0], lo[0]);
+            y = __builtin_fmaf((float)(int32_t)j + 0.5f, h[1], lo[1]);
+            z = __builtin_fmaf((float)(int32_t)k + 0.5f, h[2], lo[2]);
         }
     }
 };
@@ -507,11 +506,11 @@ int loss_blocks(int64_t n);
 constexpr size_t kPairRecBytes = 80, kPairMetaBytes = 16;
 hipError_t launch_pack_pairs(const float *V, int64_t nV, const int32_t *F, int64_t nF, const int32_t *pairs, int64_t nP,
                              char *recs, char *meta, int32_t *counts, WsHeader *hdr, hipStream_t s);
-hipError_t launch_bwd_pairs(const char *recs, const char *meta, int32_t nP, int32_t nF, const PointSrc &ps, int64_t nQ,
+hipError_t launch_bwd_pairs(const char *recs, const char *meta, int32_t nP, const PointSrc &ps, int64_t nQ,
                             int32_t S, int64_t t0, int64_t t1, int32_t rows, const float *dLdW, float2 *state,
-                            bool merged, hipStream_t s);
+                            bool merged, const struct CycState *st, hipStream_t s);
 hipError_t launch_reduce_pairs(const float2 *state, int32_t S, int32_t nP, const char *meta, float scale, float *T,
-                               bool merged, hipStream_t s);
+                               bool merged, const struct CycState *st, hipStream_t s);
 constexpr int kBwdBegin = 1, kBwdEnd = 2, kBwdVertexSums = 4;
 // Loads in flight per thread in the reductions over the splits (each thread's loop over
 // several hundred splits is bound by memory latency, not bandwidth).
@@ -519,6 +518,8 @@ constexpr int kReduceBatch = 32;
 constexpr int kBwdTile = 256;
 int bwd_splits(int64_t nF, int64_t nQ);
 size_t bwd_workspace(int64_t nV, int64_t nF, int64_t nQ);
+// Without the boundary-edge adjoint's part (a smaller workspace keeps to all pairs).
+size_t bwd_workspace_min(int64_t nV, int64_t nF, int64_t nQ);
 // `pairs` (device int32 [nP][2], optional): faces two per lane, each pair sharing an
 // edge (wn_build_face_pairs); the exact adjoint only.
 wn_status run_backward(const float *V, int64_t nV, const int32_t *F, int64_t nF, const int32_t *pairs, int64_t nP,

@@ -113,7 +113,7 @@ def test_boundary_path_vs_oracle_and_all_pairs(dev, orc, kind):
         def call(**kw):
             return wn.wn_voxelize(Vt, Ft, **kw) if strips is None else wn.wn_voxelize_strips(Vt, Ft, strips, **kw)
         W, occ = call(grid=GRID, occupancy="threshold")
-        _, soft = call(grid=GRID, occupancy="sigmoid", k=20.0)
+        Ws, soft = call(grid=GRID, occupancy="sigmoid", k=20.0)
         P = call(Q=Qt)
         assert wn.wn_get_device_error() == 0
         Wg = W.cpu().numpy().reshape(-1)
@@ -123,7 +123,9 @@ def test_boundary_path_vs_oracle_and_all_pairs(dev, orc, kind):
         assert err[~guard].max() <= 1e-4
         m = ~guard & (np.abs(Wr - 0.5) > 1e-3)
         np.testing.assert_array_equal(occ.cpu().numpy().reshape(-1)[m], orc.occupancy_threshold(Wr)[m])
-        torch.testing.assert_close(soft, wn.wn_occupancy(W, "sigmoid", 0.5, 20.0), rtol=0, atol=0)
+        # on the sigmoid's slope this call's field is the all-pairs sum
+        torch.testing.assert_close(soft, wn.wn_occupancy(Ws, "sigmoid", 0.5, 20.0), rtol=0, atol=0)
+        assert np.abs(Ws.cpu().numpy().reshape(-1) - Wr)[~guard].max() <= 1e-4
         if kind in ("closed", "two shells, one reversed"):
             exact = Wg == np.round(Wg)
             assert exact.mean() > 0.99 and np.abs(Wg - np.round(Wr))[exact].max() == 0.0

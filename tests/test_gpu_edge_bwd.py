@@ -1,0 +1,162 @@
+"""dL/dV from the mesh's boundary edges (wn_edge_bwd.hip) against the FP64 oracle.
+
+Above the rule's line (128 faces, 2e7 pairs) a grid's wn_backward without dL/dT takes this
+path, with or without face pairs.  Tolerance: FP32 terms with a relative rounding of a few
+1e-7, whose vertex sums are exact integers: 1e-5 of the largest component (the per-face
+kernels are held to 1e-3 of a vertex's corner terms), and exactly 0 where no boundary edge
+ends."""
+import numpy as np
+import pytest
+
+import wn_inputs as wi
+from .test_gpu_cycle import GRID, _centres, _dev, _mesh
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dev():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2407_11272_amd as wn
+    wn.wn_version()
+    return torch.device("cuda", 0)
+
+
+def _weights(P, seed=2):
+    import torch
+    return torch.randn(P, device="cuda", generator=torch.Generator("cuda").manual_seed(seed))
+
+
+def _pairs(V, F):
+    import torch
+    import paper_2407_11272_amd as wn
+    return torch.as_tensor(wn.wn_build_face_pairs(np.ascontiguousarray(F), len(V))).cuda()
+
+
+def _oracle(orc, V, F, grid, g):
+    Q = _centres(grid).astype(np.float64)
+    return orc.grad(np.asarray(V, np.float32).astype(np.float64), F, Q, g.cpu().numpy().astype(np.float64))
+
+
+@pytest.mark.parametrize("kind", ["closed", "holes", "loop of 4", "loop of 7", "open end", "sheet",
+                                  "two shells, one reversed", "repeated", "reversed faces"])
+def test_boundary_edges_vs_oracle(dev, orc, kind):
+    import paper_2407_11272_amd as wn
+    V, F = _mesh(kind)
+    Vt, Ft = _dev(V, F)
+    g = _weights(GRID.size)
+    Tr, Dr = _oracle(orc, V, F, GRID, g)
+    corner = np.abs(Tr).sum(axis=(0, 1)).max() / len(V)
+    for pairs in (None, _pairs(V, F)):
+        D = wn.wn_backward(Vt, Ft, g, grid=GRID, pairs=pairs).cpu().numpy().astype(np.float64)
+        assert wn.wn_get_device_error() == 0
+        print(f"[{kind}] |d dL/dV| {np.abs(D - Dr).max():.2e} of {np.abs(Dr).max():.2e}", flush=True)
+        if kind in ("closed", "two shells, one reversed"):
+            assert not D.any()
+        elif kind in ("repeated", "reversed faces"):   # edges that do not suit the path: the per-face kernels
+            assert np.abs(D - Dr).max() <= 1e-3 * max(np.abs(Dr).max(), corner)
+        else:
+            assert np.abs(D - Dr).max() <= 1e-5 * np.abs(Dr).max()
+            assert not D[np.abs(Dr).max(1) < 1e-12 * np.abs(Dr).max()].any()
+
+
+@pytest.mark.parametrize("res", [(25, 23, 27), (40, 33, 64)])
+def test_point_ranges_give_the_bits_of_one_call(dev, res):
+    """Ranges shorter and longer than a round over the splits, with and without pairs."""
+    import torch
+    import paper_2407_11272_amd as wn
+    V, F = _mesh("holes")
+    Vt, Ft = _dev(V, F)
+    grid = wn.Grid((-0.5,) * 3, (0.5,) * 3, res)
+    P = grid.size
+    g = _weights(P)
+    for pairs in (None, _pairs(V, F)):
+        D = wn.wn_backward(Vt, Ft, g, grid=grid, pairs=pairs)
+        tiles = -(-P // 256)
+        for cuts in ([1, 2, tiles // 2], [tiles - 1], list(range(1, tiles, 3))):
+            sb = wn.SlicedBackward(Vt, Ft, grid=grid, pairs=pairs, vertex_sums=True)
+            sb.begin()
+            at = [0] + [256 * c for c in cuts] + [P]
+            for a, b in zip(at[:-1], at[1:]):
+                sb.points(a, b - a, g)
+            assert torch.equal(sb.end(), D)
+
+
+def test_fan_of_faces_at_one_vertex(dev, orc):
+    """1000 triangles that share one vertex only, beside a closed mesh: a vertex where 2000
+    boundary edges end.  Voxels as near as 1e-4 of edges 0.5 long leave FP32 few digits, so
+    the bar here is the per-face kernels' own error."""
+    import paper_2407_11272_amd as wn
+    V, F = _mesh("closed")
+    rng = np.random.default_rng(9)
+    n, base = 1000, len(V)
+    P = rng.uniform(-0.45, 0.45, (n, 3))
+    V = np.concatenate([V, [[0.0117, 0.0039, -0.0071]], P, P + 0.02 * rng.standard_normal((n, 3))])
+    a = base + 1 + np.arange(n)
+    F = np.concatenate([F, np.stack([np.full(n, base), a, a + n], -1)])
+    Vt, Ft = _dev(V, F)
+    g = _weights(GRID.size)
+    _, Dr = _oracle(orc, V, F, GRID, g)
+    D = wn.wn_backward(Vt, Ft, g, grid=GRID).cpu().numpy().astype(np.float64)
+    A = wn.wn_backward(Vt, Ft, g, grid=GRID, want_dLdT=True)[0].cpu().numpy().astype(np.float64)
+    assert np.abs(D - Dr).max() <= np.abs(A - Dr).max()
+    assert not D[:base].any()
+
+
+def test_vertex_on_a_query_point_takes_the_per_face_sum(dev, orc):
+    """A face with a vertex at q contributes nothing there, so its edges do not cancel its
+    neighbours': the mesh takes the per-face kernels."""
+    import paper_2407_11272_amd as wn
+    V, F = _mesh("holes")
+    V = np.asarray(V, np.float32).copy()
+    V[100] = _centres(GRID)[7001]
+    Vt, Ft = _dev(V, F)
+    g = _weights(GRID.size)
+    Tr, Dr = _oracle(orc, V, F, GRID, g)
+    scale = np.zeros_like(Dr)
+    np.add.at(scale, F.reshape(-1), np.abs(Tr.reshape(-1, 3)))
+    D = wn.wn_backward(Vt, Ft, g, grid=GRID).cpu().numpy().astype(np.float64)
+    far = np.setdiff1d(np.arange(len(V)), F[(F == 100).any(1)])
+    assert np.all(np.abs(D - Dr)[far] <= 1e-3 * scale[far] + 1e-12)
+
+
+@pytest.mark.parametrize("kind", ["closed", "holes"])
+def test_values_that_are_not_finite_reach_every_vertex(dev, kind):
+    import torch
+    import paper_2407_11272_amd as wn
+    V, F = _mesh(kind)
+    V = np.concatenate([V, [[0.3, 0.3, 0.3]]])      # a vertex that no face uses
+    Vt, Ft = _dev(V, F)
+    for bad in (float("nan"), float("inf")):
+        g = _weights(GRID.size)
+        g[1234] = bad
+        D = wn.wn_backward(Vt, Ft, g, grid=GRID)
+        assert torch.isnan(D[:-1]).all() and not D[-1].any()
+    Vt[3, 1] = float("nan")
+    D = wn.wn_backward(Vt, Ft, _weights(GRID.size), grid=GRID)
+    used = (Ft == 3).any(1)
+    assert torch.isnan(D[3]).any() and used.any()
+
+
+def test_fitting_step_follows_the_all_pairs_field(dev):
+    """soft_occupancy: on the sigmoid's slope W is the all-pairs kernel's bit for bit, so the
+    gradient that a steep sigmoid sends back does not depend on the path."""
+    import torch
+    import paper_2407_11272_amd as wn
+    V, F = _mesh("holes")
+    Vt, Ft = _dev(V, F)
+    Q = torch.as_tensor(_centres(GRID)).cuda()
+    W = wn.WindingNumber.apply(Vt, Ft, wn.Grid.of(GRID), None, None, None, (0.5, 50.0)).reshape(-1)
+    P = wn.wn_voxelize(Vt, Ft, Q=Q)
+    slope = (P - 0.5).abs() < 0.19
+    assert slope.any()
+    assert torch.equal(W[slope], P[slope])
+    x = Vt.clone().requires_grad_(True)
+    occ = wn.soft_occupancy(x, Ft, grid=wn.Grid.of(GRID), tau=0.5, k=50.0)
+    (occ ** 2).mean().backward()
+    y = Vt.clone().requires_grad_(True)
+    occ2 = wn.soft_occupancy(y, Ft, Q=Q, tau=0.5, k=50.0)
+    (occ2 ** 2).mean().backward()
+    assert float((x.grad - y.grad).norm()) <= 1e-4 * float(y.grad.norm())
