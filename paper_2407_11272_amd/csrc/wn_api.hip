@@ -186,7 +186,7 @@ wn_status voxelize_impl(const float *V, int64_t nV, const int32_t *F, int64_t nF
     cyc_place(m, table + kCycTable);
     CycHead h{};
     h.meshes = sizeof(CycHead);
-    h.ppl = cfg.ppl;
+    h.ppl = cyc_ppl(P, cfg.ppl);
     cyc_units(m, h);
     if (e == hipSuccess) e = launch_cyc_begin(m, h, table, s);
     if (e == hipSuccess)

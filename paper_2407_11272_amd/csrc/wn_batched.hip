@@ -417,7 +417,9 @@ bool make_plan(const wn_mesh_desc *d, int32_t n, int32_t ppl, char *ws, Plan &pl
     end += align_up(sizeof(int64_t) * (size_t)(n_reduce + 1));
     std::vector<CycMesh> cyc(cyc_ids.size());
     plan.cyc.meshes = h.off_cyc - (int64_t)kCycHeadAt;
-    plan.cyc.ppl = ppl;
+    int64_t cyc_points = 0;
+    for (int32_t id : cyc_ids) cyc_points += meshes[(size_t)id].P;
+    plan.cyc.ppl = cyc_ppl(cyc_points, ppl);
     for (size_t i = 0; i < cyc_ids.size(); ++i) {
         BMesh &b = meshes[(size_t)cyc_ids[i]];
         CycMesh &m = cyc[i];
@@ -474,7 +476,7 @@ struct Staging {
 
 struct WsState {
     std::vector<Staging> ring;
-    std::map<std::tuple<int, int, int, int, bool>, hipGraphExec_t> graphs;  // (ppl, depth, persistent grid, device, boundary path)
+    std::map<std::tuple<int, int, int, int, int>, hipGraphExec_t> graphs;  // (ppl, depth, persistent grid, device, cyc)
 };
 
 constexpr size_t kMaxStaging = 64;  // buffers per workspace ring
@@ -496,16 +498,17 @@ int persistent_grid(int ppl, int depth, int wg_per_cu) {
     return cus * per;
 }
 
-hipError_t enqueue_kernels(char *ws, int ppl, int depth, int grid, bool cyc, hipStream_t s) {
+// cyc: CycHead::ppl of the boundary path, 0 without it.
+hipError_t enqueue_kernels(char *ws, int ppl, int depth, int grid, int cyc, hipStream_t s) {
     char *table = ws + kCycHeadAt;
     hipError_t e = launch_ws_reset(reinterpret_cast<WsHeader *>(ws), s);
-    if (e == hipSuccess && cyc) e = launch_cyc_clear(table, s);
+    if (e == hipSuccess && cyc != 0) e = launch_cyc_clear(table, s);
     if (e != hipSuccess) return e;
     k_batched_pack<<<1024, kBlock, 0, s>>>(ws);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     CycHead h{};
-    h.ppl = ppl;
-    if (cyc && (e = launch_cyc(h, table, true, s)) != hipSuccess) return e;
+    h.ppl = cyc;
+    if (cyc != 0 && (e = launch_cyc(h, table, true, s)) != hipSuccess) return e;
     k_batched_active<<<1, kActiveThreads, 0, s>>>(ws);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     e = with_config(ppl, depth, [&](auto P, auto D) {
@@ -514,7 +517,7 @@ hipError_t enqueue_kernels(char *ws, int ppl, int depth, int grid, bool cyc, hip
     });
     if (e != hipSuccess) return e;
     k_batched_reduce<<<2048, kBlock, 0, s>>>(ws);
-    if ((e = hipGetLastError()) != hipSuccess || !cyc) return e;
+    if ((e = hipGetLastError()) != hipSuccess || cyc == 0) return e;
     return launch_cyc_near(table, s);
 }
 
@@ -549,7 +552,7 @@ wn_status run_batched(const wn_mesh_desc *d, int32_t n, int32_t flags, char *ws,
     std::lock_guard<std::mutex> lk(g_mu);
     WsState &st = g_state[ws];
     const size_t tb = plan.tables.size();
-    const bool cyc = plan.cyc.n > 0;
+    const int cyc = plan.cyc.n > 0 ? plan.cyc.ppl : 0;
     // a staging buffer whose previous copy has finished, else a new one in the ring
     Staging *sb = nullptr;
     for (Staging &x : st.ring) {

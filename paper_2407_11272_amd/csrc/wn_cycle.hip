@@ -693,6 +693,9 @@ __global__ __launch_bounds__(kCycColumns * 64) void k_cyc_columns(const char *ta
 
 // ------------------------------------------------------------------ caps' solid angles
 
+constexpr int kTriBlock = 16;   // triangles per compensated sum
+constexpr int kLongBlock = 8;  // records of long loops per compensated sum
+
 struct Slot64 {
     double x, y, z, r, dprev, rprev;
 };
@@ -722,9 +725,8 @@ __device__ __forceinline__ float half_angle64(const float4 n, const Slot64 &A, c
 // terms near their two long edges lose half their digits in FP32 (beta cancels
 // to the product of two small angles); they are formed in FP64.  Every record completes a triangle, so this
 // costs about twice an FP32 strip record; boundaries are a small part of a mesh.
-__device__ __forceinline__ void sum_long(const VRec *__restrict__ recs, int n, float qx, float qy, float qz, float &s,
-                                         float &c) {
-    Slot64 A{}, B{}, C{};
+__device__ __forceinline__ float add_long(const VRec *__restrict__ recs, int n, Slot64 &A, Slot64 &B, Slot64 &C,
+                                          float qx, float qy, float qz) {
     const double x = qx, y = qy, z = qz;
     float ts = 0.0f;
     for (int i = 0; i < n; ++i) {
@@ -733,11 +735,15 @@ __device__ __forceinline__ void sum_long(const VRec *__restrict__ recs, int n, f
         B = C;
         enter64(p, B, C, x, y, z);
         if (p.w != 0.0f) ts += half_angle64(nn, A, B, C);
-        if ((i & 31) == 31 || i + 1 == n) {
-            neumaier_add(s, c, ts);
-            ts = 0.0f;
-        }
     }
+    return ts;
+}
+
+__device__ __forceinline__ void sum_long(const VRec *__restrict__ recs, int n, float qx, float qy, float qz, float &s,
+                                         float &c) {
+    Slot64 A{}, B{}, C{};
+    for (int i = 0; i < n; i += kLongBlock)
+        neumaier_add(s, c, add_long(recs + i, min(n - i, kLongBlock), A, B, C, qx, qy, qz));
 }
 
 // Half solid angle of the triangle of records r[0..2] at (qx, qy, qz), as the all-pairs
@@ -759,51 +765,59 @@ __device__ __forceinline__ float tri_near(const VRec *__restrict__ r, float x, f
 // subtractions and norms, and a small angle t needs t - t^3 / 3 alone).  A point that is
 // near uses the exact forms, whatever the points of its wave do, so that its
 // value does not depend on them.
+// Adds the triangles [0, n) from rec on, their records at caps.  rec moves on; next is one ahead.
+typedef float TriVec __attribute__((ext_vector_type(16)));
+typedef const __attribute__((address_space(4))) TriVec *ConstTri;
+static_assert(sizeof(TriVec) == sizeof(TriRec), "one scalar load");
+
+template <int PPL>
+__device__ __forceinline__ void add_triangles(ConstTri &rec, TriVec &next, const VRec *caps, int n,
+                                              const float (&qx)[PPL], const float (&qy)[PPL], const float (&qz)[PPL],
+                                              float (&ts)[PPL]) {
+#pragma unroll 1
+    for (int i = 0; i < n; ++i) {
+        const TriVec r = next;
+        next = *++rec;
+        float v[PPL];
+        bool near[PPL], any = false;
+#pragma unroll
+        for (int p = 0; p < PPL; ++p) {
+            const float x = r[0] - qx[p], y = r[1] - qy[p], z = r[2] - qz[p];
+            const float q = __builtin_fmaf(z, z, __builtin_fmaf(y, y, x * x));
+            const float s1 = __builtin_fmaf(z, r[6], __builtin_fmaf(y, r[5], x * r[4]));
+            const float s2 = __builtin_fmaf(z, r[10], __builtin_fmaf(y, r[9], x * r[8]));
+            const float al = __builtin_fmaf(z, r[14], __builtin_fmaf(y, r[13], x * r[12]));
+            const float r0 = fast_sqrt(q), r1 = fast_sqrt((q + r[7]) + s1), r2 = fast_sqrt((q + r[11]) + s2);
+            const float d01 = __builtin_fmaf(0.5f, s1, q), d02 = __builtin_fmaf(0.5f, s2, q);
+            const float d12 = d01 + __builtin_fmaf(0.5f, s2, r[15]);
+            const float be =
+                __builtin_fmaf(d12, r0, __builtin_fmaf(d02, r1, __builtin_fmaf(d01, r2, (r0 * r1) * r2)));
+            const float t = al * __builtin_amdgcn_rcpf(be);
+            v[p] = t * __builtin_fmaf(t * t, -0.333333333f, 1.0f);
+            near[p] = q < r[3];
+            any = any || near[p];
+        }
+        if (__builtin_expect(__builtin_amdgcn_ballot_w64(any) != 0ull, 0)) {
+#pragma unroll
+            for (int p = 0; p < PPL; ++p)
+                if (near[p]) v[p] = tri_near(caps + 3 * i, qx[p], qy[p], qz[p]);
+        }
+#pragma unroll
+        for (int p = 0; p < PPL; ++p) ts[p] += v[p];
+    }
+}
+
 template <int PPL>
 __device__ __forceinline__ void sum_triangles(const TriRec *tri, const VRec *caps, int n, const float (&qx)[PPL],
                                               const float (&qy)[PPL], const float (&qz)[PPL], float (&s)[PPL],
                                               float (&c)[PPL]) {
-    typedef float Rec __attribute__((ext_vector_type(16)));
-    typedef const __attribute__((address_space(4))) Rec *ConstPtr;
-    static_assert(sizeof(Rec) == sizeof(TriRec), "one scalar load");
-    ConstPtr rec = (ConstPtr)(uintptr_t)tri;
-    Rec next = *rec;  // one ahead; the array holds one more than it has triangles
-    for (int i0 = 0; i0 < n; i0 += 32) {
+    ConstTri rec = (ConstTri)(uintptr_t)tri;
+    TriVec next = *rec;  // one ahead; the array holds one more than it has triangles
+    for (int i0 = 0; i0 < n; i0 += kTriBlock) {
         float ts[PPL];
 #pragma unroll
         for (int p = 0; p < PPL; ++p) ts[p] = 0.0f;
-        const int i1 = min(n, i0 + 32);
-#pragma unroll 1
-        for (int i = i0; i < i1; ++i) {
-            const Rec r = next;
-            next = *++rec;
-            float v[PPL];
-            bool near[PPL], any = false;
-#pragma unroll
-            for (int p = 0; p < PPL; ++p) {
-                const float x = r[0] - qx[p], y = r[1] - qy[p], z = r[2] - qz[p];
-                const float q = __builtin_fmaf(z, z, __builtin_fmaf(y, y, x * x));
-                const float s1 = __builtin_fmaf(z, r[6], __builtin_fmaf(y, r[5], x * r[4]));
-                const float s2 = __builtin_fmaf(z, r[10], __builtin_fmaf(y, r[9], x * r[8]));
-                const float al = __builtin_fmaf(z, r[14], __builtin_fmaf(y, r[13], x * r[12]));
-                const float r0 = fast_sqrt(q), r1 = fast_sqrt((q + r[7]) + s1), r2 = fast_sqrt((q + r[11]) + s2);
-                const float d01 = __builtin_fmaf(0.5f, s1, q), d02 = __builtin_fmaf(0.5f, s2, q);
-                const float d12 = d01 + __builtin_fmaf(0.5f, s2, r[15]);
-                const float be =
-                    __builtin_fmaf(d12, r0, __builtin_fmaf(d02, r1, __builtin_fmaf(d01, r2, (r0 * r1) * r2)));
-                const float t = al * __builtin_amdgcn_rcpf(be);
-                v[p] = t * __builtin_fmaf(t * t, -0.333333333f, 1.0f);
-                near[p] = q < r[3];
-                any = any || near[p];
-            }
-            if (__builtin_expect(__builtin_amdgcn_ballot_w64(any) != 0ull, 0)) {
-#pragma unroll
-                for (int p = 0; p < PPL; ++p)
-                    if (near[p]) v[p] = tri_near(caps + 3 * i, qx[p], qy[p], qz[p]);
-            }
-#pragma unroll
-            for (int p = 0; p < PPL; ++p) ts[p] += v[p];
-        }
+        add_triangles<PPL>(rec, next, caps + 3 * i0, min(n - i0, kTriBlock), qx, qy, qz, ts);
 #pragma unroll
         for (int p = 0; p < PPL; ++p) neumaier_add(s[p], c[p], ts[p]);
     }
@@ -816,6 +830,13 @@ __device__ __forceinline__ T *uniform(T *p) {
     const uint64_t a = reinterpret_cast<uint64_t>(p);
     const uint32_t lo = (uint32_t)uniform((int)(uint32_t)a), hi = (uint32_t)uniform((int)(uint32_t)(a >> 32));
     return reinterpret_cast<T *>((uint64_t)hi << 32 | lo);
+}
+
+__device__ __forceinline__ void add_caps(const CycMesh &m, int64_t at, float sum) {
+    const float w = m.W[at] + sum * kInv2Pi;
+    m.W[at] = w;
+    write_occ(m.occ, at, w);
+    if (near_threshold(m.occ, w)) list_near(m, at);
 }
 
 template <int PPL>
@@ -854,11 +875,7 @@ __global__ __launch_bounds__(kBlock) void k_cyc_sum(const char *table) {
             for (int p = 0; p < PPL; ++p) {
                 const int64_t idx = base + (int64_t)p * kBlock;
                 if (idx >= m.P) continue;
-                const int64_t at = m.p0 + idx;
-                const float w = m.W[at] + (s[p] + c[p]) * kInv2Pi;
-                m.W[at] = w;
-                write_occ(m.occ, at, w);
-                if (near_threshold(m.occ, w)) list_near(m, at);
+                add_caps(m, m.p0 + idx, s[p] + c[p]);
             }
         }
         if (units <= gridDim.x) break;
@@ -866,6 +883,74 @@ __global__ __launch_bounds__(kBlock) void k_cyc_sum(const char *table) {
         if (tid == 0) s_unit = atomicAdd(&h->cursor, 1ull) + gridDim.x;
         __syncthreads();
         u = (int64_t)s_unit;
+    }
+}
+
+// The same for few points: one workgroup per 64 points, its waves a block of the caps each
+// (16 triangles, a tile of records, or 8 records of long loops).  The blocks' sums meet in
+// LDS and are added in the caps' order, so the bits are k_cyc_sum's.  There, 12818 points
+// are 200 waves with all caps in turn: 171 us for 8300 faces of which 6 % are missing, 27 here.
+constexpr int kSplitRounds = 8;  // blocks per wave between two barriers
+
+template <int kSplitWaves>
+__global__ __launch_bounds__(kSplitWaves * 64) void k_cyc_sum_split(const char *table) {
+    __shared__ float4 tiles[kSplitWaves][2 * kRecTile];
+    __shared__ float s_block[kSplitWaves * kSplitRounds][64];
+    __shared__ int32_t s_go;
+    const int64_t units = reinterpret_cast<const CycHead *>(table)->u_sum;
+    const int wave = uniform((int)threadIdx.x >> 6), lane = threadIdx.x & 63;
+    for (int64_t u = blockIdx.x; u < units; u += gridDim.x) {
+        const CycMesh &m = *uniform(find_mesh<&CycMesh::u_sum>(table, u));
+        const int n_rec = uniform(m.st->n_rec), n_tri = uniform(m.st->n_tri), n_short = uniform(m.st->n_short);
+        const VRec *caps = uniform(m.caps);
+        __syncthreads();
+        if (threadIdx.x == 0) s_go = m.st->go;  // other workgroups may set it meanwhile
+        __syncthreads();
+        if (s_go >= 2 || n_rec == 0) continue;
+        const int64_t idx = (u - m.u_sum) * 64 + lane;
+        float qx[1], qy[1], qz[1], s = 0.0f, c = 0.0f;
+        m.ps.get(m.p0 + (idx < m.P ? idx : m.P - 1), qx[0], qy[0], qz[0]);
+        const float4 *strips = reinterpret_cast<const float4 *>(caps + 3 * n_tri);
+        const int n_strip = n_short - 3 * n_tri, n_long = n_rec - n_short;
+        const int b_tri = (n_tri + kTriBlock - 1) / kTriBlock, b_strip = b_tri + (n_strip + kRecTile - 1) / kRecTile;
+        const int blocks = b_strip + (n_long + kLongBlock - 1) / kLongBlock;
+        for (int b0 = 0; b0 < blocks; b0 += kSplitWaves * kSplitRounds) {
+            const int b1 = min(blocks - b0, kSplitWaves * kSplitRounds);
+            for (int k = wave; k < b1; k += kSplitWaves) {
+                const int b = b0 + k;
+                float ts[1] = {0.0f};
+                if (b < b_tri) {
+                    const int i = b * kTriBlock;
+                    ConstTri rec = (ConstTri)(uintptr_t)uniform(m.tri + i);
+                    TriVec next = *rec;
+                    add_triangles<1>(rec, next, caps + 3 * i, min(n_tri - i, kTriBlock), qx, qy, qz, ts);
+                } else if (b < b_strip) {
+                    const int r = (b - b_tri) * kRecTile, nt = min(n_strip - r, kRecTile);
+                    float4 *tile = tiles[wave];
+                    __builtin_amdgcn_wave_barrier();
+                    for (int x = lane; x < 2 * nt; x += 64) tile[x] = strips[2 * r + x];
+                    __builtin_amdgcn_wave_barrier();
+                    Slot<1> S0, S1, S2;
+                    prime_window<1>(strips, r, S0, S1, S2, qx, qy, qz);
+                    sum_tile<1>(tile, nt, tile_face_mask(tile, nt), S0, S1, S2, qx, qy, qz, ts);
+                } else {
+                    const int r = (b - b_strip) * kLongBlock;
+                    const VRec *recs = caps + n_short;
+                    Slot64 A{}, B{}, C{};
+                    if (r > 0) {
+                        enter64(recs[r - 2].p, A, B, (double)qx[0], (double)qy[0], (double)qz[0]);
+                        enter64(recs[r - 1].p, B, C, (double)qx[0], (double)qy[0], (double)qz[0]);
+                    }
+                    ts[0] = add_long(recs + r, min(n_long - r, kLongBlock), A, B, C, qx[0], qy[0], qz[0]);
+                }
+                s_block[k][lane] = ts[0];
+            }
+            __syncthreads();
+            if (wave == 0)
+                for (int k = 0; k < b1; ++k) neumaier_add(s, c, s_block[k][lane]);
+            __syncthreads();
+        }
+        if (wave == 0 && idx < m.P) add_caps(m, m.p0 + idx, s + c);
     }
 }
 
@@ -987,6 +1072,15 @@ bool cyc_wanted(int64_t nV, int64_t nF, int64_t P, double min_pairs) {
            (double)nF * (double)P >= min_pairs;
 }
 
+// Below 2^18 points a lane with all caps in turn leaves the chip idle: the caps are split over
+// the least number of waves that gives 3000 in all.  Measured (us, k_cyc_sum | 4, 8, 16 waves):
+// 12818 points 171 | 54 34 27, 59276 points 33 | 17 18 28, 97336 points 52 | 29 30 47,
+// 262144 points 62 | 62 72 115 and, with twice the caps, 101 | 102 113 217.
+int cyc_ppl(int64_t points, int ppl) {
+    if (points >= ((int64_t)1 << 18)) return ppl;
+    return points >= 48000 ? -4 : points >= 24000 ? -8 : -16;
+}
+
 bool cyc_grid_ok(const wn_grid &g) {
     for (int d = 0; d < 3; ++d) {
         const float h = (g.hi[d] - g.lo[d]) / (float)g.n[d];
@@ -1082,7 +1176,7 @@ void cyc_units(CycMesh &m, CycHead &h) {
     h.u_face += units(m.nF, kCycUnit / kCycFaceLanes);
     h.u_half += units(3 * m.nF, kCycUnit);
     h.u_col += units(columns, kCycColumns);
-    h.u_sum += units(m.P, (int64_t)kBlock * h.ppl);
+    h.u_sum += units(m.P, h.ppl > 0 ? (int64_t)kBlock * h.ppl : 64);
     h.n += 1;
 }
 
@@ -1103,7 +1197,13 @@ hipError_t launch_cyc(const CycHead &h, char *table, bool fixed, hipStream_t s) 
     k_cyc_caps<<<fixed ? 256 : h.n, kCapThreads, 0, s>>>(table);
     k_cyc_slabs<<<1024, kCycUnit, 0, s>>>(table);
     k_cyc_columns<<<grid(h.u_col), kCycColumns * 64, 0, s>>>(table);
-    if (h.ppl == 1)
+    if (h.ppl == -16)
+        k_cyc_sum_split<16><<<grid(h.u_sum), 16 * 64, 0, s>>>(table);
+    else if (h.ppl == -8)
+        k_cyc_sum_split<8><<<grid(h.u_sum), 8 * 64, 0, s>>>(table);
+    else if (h.ppl == -4)
+        k_cyc_sum_split<4><<<grid(h.u_sum), 4 * 64, 0, s>>>(table);
+    else if (h.ppl == 1)
         k_cyc_sum<1><<<grid(h.u_sum), kBlock, 0, s>>>(table);
     else if (h.ppl == 2)
         k_cyc_sum<2><<<grid(h.u_sum), kBlock, 0, s>>>(table);

@@ -87,7 +87,7 @@ struct CycMesh {
 struct CycHead {
     int64_t meshes;  // offset of the meshes from the table
     int32_t n;
-    int32_t ppl;
+    int32_t ppl;  // points per lane of the caps' sum; -n: the caps split over n waves
     int64_t u_clear, u_face, u_half, u_col, u_sum;  // units of all meshes
     unsigned long long cursor;
 };
@@ -96,6 +96,7 @@ struct CycHead {
 // whole grid, so that a slice takes the path of the grid.
 bool cyc_wanted(int64_t nV, int64_t nF, int64_t P, double min_pairs = 5.0e7);
 // Whether the grid's extent is finite and in the range of the path.
+int cyc_ppl(int64_t points, int ppl);
 bool cyc_grid_ok(const wn_grid &g);
 // Scratch bytes of one mesh with P voxels in its slice (0: for the boundary edges alone), and
 // its pointers laid out from `base`.
