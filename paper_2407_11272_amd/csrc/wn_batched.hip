@@ -418,7 +418,8 @@ bool make_plan(const wn_mesh_desc *d, int32_t n, int32_t ppl, char *ws, Plan &pl
     std::vector<CycMesh> cyc(cyc_ids.size());
     plan.cyc.meshes = h.off_cyc - (int64_t)kCycHeadAt;
     int64_t cyc_points = 0;
-    for (int32_t id : cyc_ids) cyc_points += meshes[(size_t)id].P;
+    for (int32_t id : cyc_ids)
+        if (cyc_blocks(d[id].grid.n, d[id].nF).order == 0) cyc_points += meshes[(size_t)id].P;
     plan.cyc.ppl = cyc_ppl(cyc_points, ppl);
     for (size_t i = 0; i < cyc_ids.size(); ++i) {
         BMesh &b = meshes[(size_t)cyc_ids[i]];
@@ -445,7 +446,13 @@ bool make_plan(const wn_mesh_desc *d, int32_t n, int32_t ppl, char *ws, Plan &pl
             b.count = m.count;
             cyc_units(m, plan.cyc);
         }
-        end += cyc_bytes(b.nV, b.nF, b.P);
+        const CycBlocks blocks = cyc_blocks(d[cyc_ids[i]].grid.n, b.nF);
+        int64_t x_blocks = 0;
+        if (blocks.order) {
+            const int64_t plane = (int64_t)b.ps.n1 * b.ps.n2;
+            x_blocks = (b.p0 + b.P - 1) / plane / blocks.size[0] - b.p0 / plane / blocks.size[0] + 1;
+        }
+        end += cyc_bytes(b.nV, b.nF, b.P, cyc_node_floats(blocks, x_blocks));
     }
     plan.total_bytes = end;
     plan.n_units = units;
@@ -498,7 +505,7 @@ int persistent_grid(int ppl, int depth, int wg_per_cu) {
     return cus * per;
 }
 
-// cyc: CycHead::ppl of the boundary path, 0 without it.
+// cyc: of the boundary path, CycHead::ppl and which kernels for the caps are needed; 0 without it.
 hipError_t enqueue_kernels(char *ws, int ppl, int depth, int grid, int cyc, hipStream_t s) {
     char *table = ws + kCycHeadAt;
     hipError_t e = launch_ws_reset(reinterpret_cast<WsHeader *>(ws), s);
@@ -507,7 +514,9 @@ hipError_t enqueue_kernels(char *ws, int ppl, int depth, int grid, int cyc, hipS
     k_batched_pack<<<1024, kBlock, 0, s>>>(ws);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     CycHead h{};
-    h.ppl = cyc;
+    h.ppl = cyc >> 2;
+    h.u_sum = cyc & 1;
+    h.u_node = h.u_blk = cyc >> 1 & 1;
     if (cyc != 0 && (e = launch_cyc(h, table, true, s)) != hipSuccess) return e;
     k_batched_active<<<1, kActiveThreads, 0, s>>>(ws);
     if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -552,7 +561,7 @@ wn_status run_batched(const wn_mesh_desc *d, int32_t n, int32_t flags, char *ws,
     std::lock_guard<std::mutex> lk(g_mu);
     WsState &st = g_state[ws];
     const size_t tb = plan.tables.size();
-    const int cyc = plan.cyc.n > 0 ? plan.cyc.ppl : 0;
+    const int cyc = plan.cyc.n > 0 ? plan.cyc.ppl * 4 + (plan.cyc.u_node > 0 ? 2 : 0) + (plan.cyc.u_sum > 0 ? 1 : 0) : 0;
     // a staging buffer whose previous copy has finished, else a new one in the ring
     Staging *sb = nullptr;
     for (Staging &x : st.ring) {

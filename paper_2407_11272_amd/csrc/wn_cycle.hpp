@@ -35,6 +35,16 @@ struct alignas(64) TriRec {
     float n[3], g;        // (v_1 - v_0) x (v_2 - v_0); d_1 . d_2
 };
 
+// The grid cut into blocks of voxels, for the caps' far field (wn_cycle.hip).
+struct CycBlocks {
+    int32_t order;      // 0: no blocks
+    int32_t size[3];    // voxels per block
+    int32_t n[3];       // blocks
+    int32_t coarse[3];  // coarse nodes per block: min(kCoarse, size)
+    int32_t fine[3];    // fine nodes: min(kFine, size)
+    int32_t splits;     // of the caps over waves
+};
+
 // What the kernels find out about a mesh.
 struct CycState {
     int32_t go;         // all-pairs sum: 0 none, 1 at the marked voxels, 2 at all voxels
@@ -76,19 +86,24 @@ struct CycMesh {
     int32_t *nout, *nin, *rank, *next;  // [nF] each
     int32_t *cvid, *cpos; // [nF] cap records: vertex, place in its loop's strip
     VRec *caps;           // [nF] cap records
-    TriRec *tri;          // [nF / 3 + 2] the triangles among them
+    TriRec *tri;          // [nF + 2] the triangles of the loops of three, then one slot per other record
+    float4 *tri0;         // [nF + 2] their v and far
+    CycBlocks grid;
+    int32_t xb0, xb1;     // the slice's blocks along x
+    float *weight;        // weights of the blocks' nodes
+    float *node;          // [splits][blocks of the slice][coarse, fine nodes] far field at the nodes
     int2 *slab;           // raster list: (face, or nF + cap record; 64 columns of its range)
     int32_t *near;        // voxels for the direct sum, counted from p0
     uint32_t *mark;       // a bit for each such voxel, also those that the list had no room for
     int32_t near_cap, slab_cap;
-    int64_t u_clear, u_face, u_half, u_col, u_sum;  // first units of this mesh
+    int64_t u_clear, u_face, u_half, u_col, u_sum, u_node, u_blk;  // first units of this mesh
 };
 
 struct CycHead {
     int64_t meshes;  // offset of the meshes from the table
     int32_t n;
     int32_t ppl;  // points per lane of the caps' sum; -n: the caps split over n waves
-    int64_t u_clear, u_face, u_half, u_col, u_sum;  // units of all meshes
+    int64_t u_clear, u_face, u_half, u_col, u_sum, u_node, u_blk;  // units of all meshes
     unsigned long long cursor;
 };
 
@@ -96,11 +111,14 @@ struct CycHead {
 // whole grid, so that a slice takes the path of the grid.
 bool cyc_wanted(int64_t nV, int64_t nF, int64_t P, double min_pairs = 5.0e7);
 // Whether the grid's extent is finite and in the range of the path.
-int cyc_ppl(int64_t points, int ppl);
 bool cyc_grid_ok(const wn_grid &g);
-// Scratch bytes of one mesh with P voxels in its slice (0: for the boundary edges alone), and
-// its pointers laid out from `base`.
-size_t cyc_bytes(int64_t nV, int64_t nF, int64_t P);
+int cyc_ppl(int64_t points, int ppl);
+CycBlocks cyc_blocks(const int32_t *n, int64_t nF);
+int64_t cyc_node_floats(const CycBlocks &b, int64_t x_blocks);
+// Scratch bytes of one mesh with P voxels in its slice (0: for the boundary edges alone) and
+// `nodes` floats for the blocks (-1: as many as any grid of P voxels needs), and its
+// pointers laid out from `base`.
+size_t cyc_bytes(int64_t nV, int64_t nF, int64_t P, int64_t nodes = -1);
 void cyc_place(CycMesh &m, char *base);
 // Unit numbers of mesh m, after what `h` holds already.
 void cyc_units(CycMesh &m, CycHead &h);

@@ -235,3 +235,45 @@ def test_voxels_on_the_surface(dev, orc):
     assert on.sum() > 500
     np.testing.assert_array_equal(W[on], P[on])
     np.testing.assert_array_equal(W[~on], (np.abs(Q).max(1) < 0.25)[~on].astype(np.float32))
+
+
+@pytest.mark.parametrize("n", [(78, 74, 83), (213, 6, 370), (450, 3, 350)])
+@pytest.mark.parametrize("kind", ["holes", "open end", "sheet", "two shells, one reversed"])
+def test_blocks_of_voxels(dev, orc, kind, n):
+    """Grids above the blocks' line (2^18 voxels, 1.5e9 pairs): the caps' far field comes from
+    nodes.  Ragged last blocks, and axes with fewer voxels than fine and than coarse nodes.
+
+    Tolerance: the rule takes at most 10 x 4e-8 per far triangle, of either sign; the 300
+    triangles here add up to 10 x 4e-8 x sqrt(300) = 7e-6 at most.  Off the surface the FP32
+    forms add less than 3e-6 (as at the other sizes of this file)."""
+    import torch
+    import paper_2407_11272_amd as wn
+    V, F = _mesh(kind)
+    grid = wi.Grid((-0.5, -0.45, -0.5), (0.5, 0.5, 0.47), n)
+    assert grid.size >= 1 << 18 and len(F) * grid.size >= 1.5e9
+    Vt, Ft = _dev(V, F)
+    W, occ = wn.wn_voxelize(Vt, Ft, grid=grid, occupancy="threshold")
+    Q = _centres(grid)
+    pick = np.random.default_rng(5).choice(grid.size, 4000, replace=False)
+    V64 = np.asarray(V, np.float32).astype(np.float64)
+    Wr = orc.winding(V64, F, Q[pick].astype(np.float64))
+    guard = orc.guard_mask(V64, F, Q[pick].astype(np.float64))
+    Wg = W.cpu().numpy().reshape(-1)[pick]
+    err = np.abs(Wg - Wr)[~guard]
+    print(f"[{kind} {n}] max |dW| {err.max():.2e}, rms {np.sqrt((err ** 2).mean()):.2e}", flush=True)
+    assert err.max() <= 1e-5
+    m = ~guard & (np.abs(Wr - 0.5) > 1e-4)
+    np.testing.assert_array_equal(occ.cpu().numpy().reshape(-1)[pick][m], orc.occupancy_threshold(Wr)[m])
+    # a call without occupancy, a batch and slices of it: the same bits, but at voxels near the
+    # threshold, which only a call with one lists, and listed voxels of the batch (its own chunks)
+    again = wn.wn_voxelize(Vt, Ft, grid=grid)
+    assert bool(((again == W) | ((W - 0.5).abs() < 2e-5)).all())
+    g = wn.Grid.of(grid)
+    whole = wn.MeshJob(Vt, Ft, g, "threshold")
+    S = torch.full(n, float("nan"), device="cuda")
+    cuts = [0, 5, n[1] * n[2] * 17 + 31, grid.size]
+    parts = [wn.MeshJob(Vt, Ft, g, "none", W=S, point_begin=a, point_count=b - a) for a, b in zip(cuts[:-1], cuts[1:])]
+    wn.wn_voxelize_batched(parts + [whole])
+    torch.cuda.synchronize()
+    assert float((W - whole.W).abs().max()) <= 2e-6 and float((W != whole.W).float().mean()) < 0.01
+    assert bool(((S == whole.W) | ((whole.W - 0.5).abs() < 2e-5)).all())
