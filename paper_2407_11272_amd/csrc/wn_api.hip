@@ -160,12 +160,10 @@ wn_status voxelize_impl(const float *V, int64_t nV, const int32_t *F, int64_t nF
     const size_t extra = cycle_ws(nV, nF, P);
     const bool fits = R == nullptr || need > WN_NOALLOC_SCRATCH_BYTES || need + extra <= WN_NOALLOC_SCRATCH_BYTES;
     const bool cyc = !all_pairs && grid != nullptr && extra > 0 && need + extra <= ws_bytes && fits &&
-                     cyc_grid_ok(*grid);
-    hipError_t e = launch_ws_reset(hdr, s);
+                     cyc_wanted(nV, nF, P, R ? kCycStripPairs : kCycPairs) && cyc_grid_ok(*grid);
     if (!cyc) {
-        if (e == hipSuccess) e = launch_pack_records(V, nV, F, nF, R, nR, recs, hdr, nullptr, nullptr, s);
-        if (e == hipSuccess) e = launch_fwd(recs, nR, ps, P, split, W, partials, op, cfg.ppl, cfg.depth, nullptr, nullptr,
-                           s);
+        hipError_t e = launch_pack_records(V, nV, F, nF, R, nR, recs, hdr, s);
+        if (e == hipSuccess) e = launch_fwd(recs, nR, ps, P, split, W, partials, op, cfg.ppl, cfg.depth, nullptr, nullptr, s);
         return hip_status(e);
     }
     char *table = base + need;
@@ -180,6 +178,10 @@ wn_status voxelize_impl(const float *V, int64_t nV, const int32_t *F, int64_t nF
     m.ps = ps;
     m.n0 = grid->n[0];
     m.strips = R != nullptr;
+    m.R = R;
+    m.hdr = hdr;
+    m.partials = split > 1 ? partials : nullptr;
+    m.split = split;
     m.P = P;
     m.W = W;
     m.occ = op;
@@ -188,10 +190,8 @@ wn_status voxelize_impl(const float *V, int64_t nV, const int32_t *F, int64_t nF
     h.meshes = sizeof(CycHead);
     h.ppl = cyc_ppl(P, cfg.ppl);
     cyc_units(m, h);
-    if (e == hipSuccess) e = launch_cyc_begin(m, h, table, s);
-    if (e == hipSuccess)
-        e = launch_pack_records(V, nV, F, nF, R, nR, recs, hdr, R ? m.count : nullptr, &m.st->go, s);
-    if (e == hipSuccess) e = launch_cyc(h, table, false, s);
+    hipError_t e = launch_cyc_begin(m, h, table, s);
+    if (e == hipSuccess) e = launch_cyc(h, table, false, nR, s);
     if (e == hipSuccess)
         e = launch_fwd(recs, nR, ps, P, split, W, partials, op, cfg.ppl, cfg.depth, m.st, m.mark, s);
     if (e == hipSuccess) e = launch_cyc_near(table, s);

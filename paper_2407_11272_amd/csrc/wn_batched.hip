@@ -382,7 +382,8 @@ bool make_plan(const wn_mesh_desc *d, int32_t n, int32_t ppl, char *ws, Plan &pl
     // Meshes on the boundary path, largest first.
     std::vector<int32_t> cyc_ids;
     for (int32_t m = 0; m < n; ++m)
-        if (cyc_wanted(d[m].nV, d[m].nF, (int64_t)d[m].grid.n[0] * d[m].grid.n[1] * d[m].grid.n[2]) &&
+        if (cyc_wanted(d[m].nV, d[m].nF, (int64_t)d[m].grid.n[0] * d[m].grid.n[1] * d[m].grid.n[2],
+                       d[m].strips ? kCycStripPairs : kCycPairs) &&
             cyc_grid_ok(d[m].grid))
             cyc_ids.push_back(m);
     std::stable_sort(cyc_ids.begin(), cyc_ids.end(), [&](int32_t a, int32_t b) { return d[a].nF > d[b].nF; });
@@ -439,7 +440,7 @@ bool make_plan(const wn_mesh_desc *d, int32_t n, int32_t ppl, char *ws, Plan &pl
         m.W = b.W;
         m.occ = OccParams{b.occ, b.occ_mode, b.tau, b.k};
         if (ws) {
-            m.recs = reinterpret_cast<const VRec *>(ws + h.off_soup) + b.rec_off;
+            m.recs = reinterpret_cast<VRec *>(ws + h.off_soup) + b.rec_off;
             cyc_place(m, ws + end);
             b.st = m.st;
             b.mark = m.mark;
@@ -517,7 +518,7 @@ hipError_t enqueue_kernels(char *ws, int ppl, int depth, int grid, int cyc, hipS
     h.ppl = cyc >> 2;
     h.u_sum = cyc & 1;
     h.u_node = h.u_blk = cyc >> 1 & 1;
-    if (cyc != 0 && (e = launch_cyc(h, table, true, s)) != hipSuccess) return e;
+    if (cyc != 0 && (e = launch_cyc(h, table, true, 0, s)) != hipSuccess) return e;
     k_batched_active<<<1, kActiveThreads, 0, s>>>(ws);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     e = with_config(ppl, depth, [&](auto P, auto D) {

@@ -83,6 +83,10 @@ __global__ __launch_bounds__(kCycUnit) void k_cyc_begin_one(CycMesh m, CycHead h
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         *reinterpret_cast<CycHead *>(table) = h;
         *reinterpret_cast<CycMesh *>(table + h.meshes) = m;
+        if (m.hdr) {
+            m.hdr->bad_index = 0;
+            m.hdr->cursor = 0ull;
+        }
     }
     clear_unit(m, blockIdx.x);
 }
@@ -223,9 +227,18 @@ __device__ __forceinline__ int64_t edge_bucket(const CycMesh &m, int32_t l, int3
 // Eight lanes per face: three chain its half-edges, all share its columns.  Bound by the
 // latency of the loads and of the FP64 chain per column, so the lanes go to more faces and
 // columns at a time rather than to a face's whole range.
+// kPack: workgroups beyond the faces' pack the record stream.
+template <bool kPack>
 __global__ __launch_bounds__(kCycUnit) void k_cyc_faces(const char *table) {
     constexpr int kFaces = kCycUnit / kCycFaceLanes;
     const CycHead *h = reinterpret_cast<const CycHead *>(table);
+    if (kPack && blockIdx.x >= h->u_face) {
+        const CycMesh &m = *meshes_of(table);
+        const int64_t r = ((int64_t)blockIdx.x - h->u_face) * kCycUnit + threadIdx.x;
+        if (r < m.nR)
+            pack_record(r, m.V, m.nV, m.F, m.nF, m.R, m.recs, m.hdr, m.R ? m.count : nullptr, &m.st->go);
+        return;
+    }
     const int part = threadIdx.x % kCycFaceLanes;
     for (int64_t u = blockIdx.x; u < h->u_face; u += gridDim.x) {
         const CycMesh &m = *find_mesh<&CycMesh::u_face>(table, u);
@@ -1328,12 +1341,13 @@ __global__ __launch_bounds__(kBlock) void k_cyc_blocks(const char *table) {
 // the same pairing of faces and the same order of the sums.  A tile of whole six-record
 // steps pairs the faces of records 2 l and 2 l + 1, and lone faces two at a time; the
 // records after its last whole step (in the stream's last tile) count one by one.
-constexpr int kNearThreads = 1024, kNearTiles = kNearThreads / 32;
+constexpr int kNearThreads = 1024, kNearTiles = kNearThreads / 32, kNearSums = 1024;
 
 __global__ __launch_bounds__(kNearThreads) void k_cyc_near(const char *table) {
     __shared__ float2 s_face[kNearTiles][32];    // (alpha, beta) of a lane's lone face
     __shared__ float s_part[kNearTiles][36];     // a tile's terms in order: 30 lanes, the last lone face, 5 tail records
-    __shared__ float s_tile[kNearTiles];
+    __shared__ float s_tile[kNearSums];          // tiles' sums
+    __shared__ float s_chunk[kNearSums];         // chunks' sums
     const CycHead *h = reinterpret_cast<const CycHead *>(table);
     const CycMesh *meshes = meshes_of(table);
     const int tid = threadIdx.x, tl = tid >> 5, l = tid & 31;
@@ -1341,7 +1355,16 @@ __global__ __launch_bounds__(kNearThreads) void k_cyc_near(const char *table) {
     int64_t before = 0;
     for (int mi = 0; mi < h->n; ++mi) {
         const CycMesh &m = meshes[mi];
-        if (m.st->go) continue;
+        if (m.st->go) {
+            if (m.partials)  // of the all-pairs kernel, which went before
+                for (int64_t idx = blockIdx.x * (int64_t)kNearThreads + tid; idx < m.P; idx += g * kNearThreads) {
+                    if (!go_writes(m.st, m.mark, idx)) continue;
+                    const float w = split_sum(m.partials, m.split, m.P, idx) * kInv2Pi;
+                    m.W[idx] = w;
+                    write_occ(m.occ, idx, w);
+                }
+            continue;
+        }
         const int64_t n = m.st->n_near;
         const float4 *src = reinterpret_cast<const float4 *>(m.recs);
         const int64_t tiles = (m.nR + kRecTile - 1) / kRecTile, per = m.chunk / kRecTile;
@@ -1350,9 +1373,13 @@ __global__ __launch_bounds__(kNearThreads) void k_cyc_near(const char *table) {
             float qx[1], qy[1], qz[1];
             m.ps.get(at, qx[0], qy[0], qz[0]);
             float s = 0.0f, c = 0.0f, cs = 0.0f, cc = 0.0f;  // chunks so far, this chunk's tiles
-            for (int64_t t0 = 0; t0 < tiles; t0 += kNearTiles) {
-                const int64_t t = t0 + tl;
-                const int nt = t < tiles ? (int)min((int64_t)kRecTile, m.nR - t * kRecTile) : 0;
+            // whole chunks at a time where they fit, else parts of one
+            const int64_t pass = per <= kNearSums ? kNearSums / per * per : kNearSums;
+            for (int64_t t0 = 0; t0 < tiles; t0 += pass) {
+              const int here = (int)min(pass, tiles - t0);
+              for (int k = tl; k < here; k += kNearTiles) {
+                const int64_t t = t0 + k;
+                const int nt = (int)min((int64_t)kRecTile, m.nR - t * kRecTile);
                 const int full = nt / 6 * 6;
                 const bool in_step = 2 * l < full;
                 Slot<1> S0, S1, S2;
@@ -1399,24 +1426,36 @@ __global__ __launch_bounds__(kNearThreads) void k_cyc_near(const char *table) {
                     if (bits & 2u) part[k + 1] = atan2_eq8(a1[0], b1[0]);
                 }
                 if (l < 30) part[l] = term;
-                __syncthreads();
+                __builtin_amdgcn_wave_barrier();
                 if (l == 0) {
                     float ts = 0.0f;
 #pragma unroll
-                    for (int k = 0; k < 36; ++k) ts += part[k];
-                    s_tile[tl] = ts;
+                    for (int i = 0; i < 36; ++i) ts += part[i];
+                    s_tile[k] = ts;
+                }
+                __builtin_amdgcn_wave_barrier();
+              }
+              __syncthreads();
+              if (per <= kNearSums) {
+                const int chunks = (int)((here + per - 1) / per);
+                for (int i = tid; i < chunks; i += kNearThreads) {
+                    float a = 0.0f, b = 0.0f;
+                    for (int k = i * (int)per; k < min(here, (i + 1) * (int)per); ++k) neumaier_add(a, b, s_tile[k]);
+                    s_chunk[i] = a + b;
                 }
                 __syncthreads();
-                if (tid == 0) {
-                    const int here = (int)min((int64_t)kNearTiles, tiles - t0);
-                    for (int i = 0; i < here; ++i) {
-                        neumaier_add(cs, cc, s_tile[i]);
-                        if ((t0 + i + 1) % per == 0 || t0 + i + 1 == tiles) {
-                            neumaier_add(s, c, cs + cc);
-                            cs = cc = 0.0f;
-                        }
+                if (tid == 0)
+                    for (int i = 0; i < chunks; ++i) neumaier_add(s, c, s_chunk[i]);
+              } else if (tid == 0) {
+                for (int i = 0; i < here; ++i) {
+                    neumaier_add(cs, cc, s_tile[i]);
+                    if ((t0 + i + 1) % per == 0 || t0 + i + 1 == tiles) {
+                        neumaier_add(s, c, cs + cc);
+                        cs = cc = 0.0f;
                     }
                 }
+              }
+              __syncthreads();
             }
             if (tid == 0) {
                 const float w = (s + c) * kInv2Pi;
@@ -1432,8 +1471,10 @@ __global__ __launch_bounds__(kNearThreads) void k_cyc_near(const char *table) {
 
 // ------------------------------------------------------------------ host
 
-// The path costs about ten short launches; the all-pairs sum reaches that at about 5e7
-// pairs.  A few large faces are better summed: their close voxels are many.
+// The path's nine short launches take 45 to 55 us for a closed mesh and up to 120 us for many
+// holes; the all-pairs sum took (us) 77 at 3.8e7 pairs without strips, and with them 50 at 4.3e7, 60
+// at 4.8e7 (here 46, closed), 69 at 7.1e7 (here 75, 7 % missing), 103 at 9.2e7 (here 68).
+// A few large faces are better summed: their close voxels are many.
 bool cyc_wanted(int64_t nV, int64_t nF, int64_t P, double min_pairs) {
     return nF >= 128 && nV > 0 && nV < ((int64_t)1 << 30) && nF < ((int64_t)1 << 28) && P > 0 &&
            (double)nF * (double)P >= min_pairs;
@@ -1615,9 +1656,12 @@ hipError_t launch_cyc_clear(char *table, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_cyc(const CycHead &h, char *table, bool fixed, hipStream_t s) {
+hipError_t launch_cyc(const CycHead &h, char *table, bool fixed, int64_t pack, hipStream_t s) {
     auto grid = [&](int64_t units) { return dim3((unsigned)(fixed ? 2048 : units)); };
-    k_cyc_faces<<<grid(h.u_face), kCycUnit, 0, s>>>(table);
+    if (pack > 0)
+        k_cyc_faces<true><<<dim3((unsigned)(h.u_face + (pack + kCycUnit - 1) / kCycUnit)), kCycUnit, 0, s>>>(table);
+    else
+        k_cyc_faces<false><<<grid(h.u_face), kCycUnit, 0, s>>>(table);
     k_cyc_mark<<<grid(h.u_half), kCycUnit, 0, s>>>(table);
     k_cyc_caps<<<fixed ? 256 : h.n, kCapThreads, 0, s>>>(table);
     k_cyc_slabs<<<1024, kCycUnit, 0, s>>>(table);
@@ -1643,7 +1687,7 @@ hipError_t launch_cyc(const CycHead &h, char *table, bool fixed, hipStream_t s) 
 }
 
 hipError_t launch_cyc_edges(const CycHead &h, char *table, hipStream_t s) {
-    k_cyc_faces<<<dim3((unsigned)h.u_face), kCycUnit, 0, s>>>(table);
+    k_cyc_faces<false><<<dim3((unsigned)h.u_face), kCycUnit, 0, s>>>(table);
     k_cyc_mark<<<dim3((unsigned)h.u_half), kCycUnit, 0, s>>>(table);
     k_cyc_caps<<<1, kCapThreads, 0, s>>>(table);
     return hipGetLastError();

@@ -62,7 +62,11 @@ struct CycState {
 struct CycMesh {
     const float *V;
     const int32_t *F;
-    const VRec *recs;     // the all-pairs record stream
+    VRec *recs;           // the all-pairs record stream
+    const int32_t *R;     // its order (plain calls), or null: three records per face
+    WsHeader *hdr;        // reset by the begin kernel (plain calls)
+    const float *partials;  // sums of the all-pairs kernel's splits, if it has more than one (plain calls)
+    int32_t split;
     int64_t nV, nF, nR;
     int64_t chunk;        // records per partial sum of the all-pairs kernel
     PointSrc ps;
@@ -109,7 +113,8 @@ struct CycHead {
 
 // Whether sizes make the boundary path worth its fixed cost (see wn_cycle.hip); P is the
 // whole grid, so that a slice takes the path of the grid.
-bool cyc_wanted(int64_t nV, int64_t nF, int64_t P, double min_pairs = 5.0e7);
+constexpr double kCycPairs = 3.0e7, kCycStripPairs = 7.0e7;  // without and with a strip order
+bool cyc_wanted(int64_t nV, int64_t nF, int64_t P, double min_pairs = kCycPairs);
 // Whether the grid's extent is finite and in the range of the path.
 bool cyc_grid_ok(const wn_grid &g);
 int cyc_ppl(int64_t points, int ppl);
@@ -125,12 +130,13 @@ void cyc_units(CycMesh &m, CycHead &h);
 // The path in launch order: `begin` (one mesh: it also writes the table) or `clear` (a
 // table that is in place), the packing of the record streams, `launch_cyc`, the all-pairs
 // kernels for the meshes whose state asks for them, and `near` for the listed voxels.
-// fixed: launches of fixed size, for a captured graph.
+// fixed: launches of fixed size, for a captured graph.  pack: records that are packed with
+// the first kernel (one mesh).  `near` also adds up the all-pairs kernel's splits.
 constexpr size_t kCycTable = 1024;
 static_assert(sizeof(CycHead) + sizeof(CycMesh) <= kCycTable, "table size");
 hipError_t launch_cyc_begin(const CycMesh &m, const CycHead &h, char *table, hipStream_t s);
 hipError_t launch_cyc_clear(char *table, hipStream_t s);
-hipError_t launch_cyc(const CycHead &h, char *table, bool fixed, hipStream_t s);
+hipError_t launch_cyc(const CycHead &h, char *table, bool fixed, int64_t pack, hipStream_t s);
 hipError_t launch_cyc_near(char *table, hipStream_t s);
 
 // The boundary edges alone, after `begin`.

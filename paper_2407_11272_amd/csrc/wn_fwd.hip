@@ -16,6 +16,8 @@ namespace wn {
 
 // ------------------------------------------------------------------ kernels
 
+constexpr int kPackThreads = 1024;
+
 __global__ void k_ws_reset(WsHeader *hdr) {
     if (threadIdx.x == 0 && blockIdx.x == 0) {
         hdr->bad_index = 0;
@@ -56,26 +58,21 @@ __global__ __launch_bounds__(kBlock) void k_pack(const float *__restrict__ V, in
     soup[f] = r;
 }
 
-__global__ __launch_bounds__(kBlock) void k_pack_records(const float *__restrict__ V, int64_t nV,
-                                                         const int32_t *__restrict__ F, int64_t nF,
-                                                         const int32_t *__restrict__ R, int64_t nR,
-                                                         VRec *__restrict__ recs, WsHeader *hdr, int32_t *counts,
-                                                         int32_t *go) {
-    const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (r >= nR) return;
-    int32_t vid, fid;
-    if (R) {
-        vid = R[2 * r];
-        fid = R[2 * r + 1];
-        check_strip_record(R, r, F, nF, fid, hdr, go);
-        if (counts && fid >= 0 && (int64_t)fid < nF) atomicAdd(&counts[fid], 1);
-    } else {
-        const int64_t f = r / 3;
-        const int j = (int)(r - 3 * f);
-        vid = F[3 * f + j];
-        fid = j == 2 ? (int32_t)f : -1;
+// Forward record stream: one thread per record.  With kReset one workgroup takes the whole stream and
+// resets the header first, which saves the reset's launch.
+template <bool kReset>
+__global__ __launch_bounds__(kReset ? kPackThreads : kBlock) void k_pack_records(
+    const float *__restrict__ V, int64_t nV, const int32_t *__restrict__ F, int64_t nF, const int32_t *__restrict__ R,
+    int64_t nR, VRec *__restrict__ recs, WsHeader *hdr) {
+    if (kReset) {
+        if (threadIdx.x == 0) {
+            hdr->bad_index = 0;
+            hdr->cursor = 0ull;
+        }
+        __syncthreads();
     }
-    recs[r] = make_record(V, nV, F, nF, vid, fid, hdr);
+    for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < nR; r += (int64_t)gridDim.x * blockDim.x)
+        pack_record(r, V, nV, F, nF, R, recs, hdr, nullptr, nullptr);
 }
 
 // One point block against one record split of the all-pairs forward.  With one split it
@@ -137,17 +134,12 @@ __global__ __launch_bounds__(kBlock) void k_wn_fwd_if(const CycState *st, const 
         fwd_unit<PPL, DEPTH>(u % pblocks, u / pblocks, tile, recs, nR, chunk, ps, nQ, W, partials, occ, st, mark);
 }
 
-// Fixed-order sum of the split partials, scale to W, occupancy (where st is null or asks for it).
+// Fixed-order sum of the split partials, scale to W, occupancy.
 __global__ __launch_bounds__(kBlock) void k_wn_reduce(const float *__restrict__ partials, int32_t split,
-                                                      int64_t nQ, float scale, float *__restrict__ W, OccParams occ,
-                                                      const CycState *st, const uint32_t *mark) {
-    if (st && st->go == 0) return;
+                                                      int64_t nQ, float scale, float *__restrict__ W, OccParams occ) {
     for (int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; idx < nQ;
          idx += (int64_t)gridDim.x * blockDim.x) {
-        if (!go_writes(st, mark, idx)) continue;
-        float s = 0.0f, c = 0.0f;
-        for (int32_t k = 0; k < split; ++k) neumaier_add(s, c, partials[(int64_t)k * nQ + idx]);
-        const float w = (s + c) * scale;
+        const float w = split_sum(partials, split, nQ, idx) * scale;
         W[idx] = w;
         write_occ(occ, idx, w);
     }
@@ -215,11 +207,14 @@ int fwd_split_count(int64_t nR, int64_t nQ) {
     // Aim for about 131072 wave64s of (point block, record split) units, about 16
     // rounds of resident workgroups, so that the last, partly filled round costs little
     // (one round of 8192 point blocks left the GPU 5-10 % idle at the end); never give a
-    // split fewer than 2 tiles of records.  Depends only on (nR, nQ), so results do not
-    // depend on the launch configuration.
-    const int64_t waves = (nQ + 63) / 64;
+    // split fewer than 2 tiles of records, but 1 where that leaves most of the chip idle: with less than
+    // 700 workgroups (320 faces on 16^3 points, 128 of them: 17 -> 11 us; 646 faces on 37 x 38 x 19, 630:
+    // a call 37 -> 34 us; with 800 to 2100 from 3 % faster to 8 % slower, more partial sums).
+    // Depends only on (nR, nQ), so results do not depend on the launch configuration.
+    const int64_t waves = (nQ + 63) / 64, blocks = (nQ + kBlock - 1) / kBlock;
     int64_t s = (131072 + waves - 1) / (waves > 0 ? waves : 1);
-    const int64_t max_by_faces = (nR + 2 * kRecTile - 1) / (2 * kRecTile);
+    int64_t max_by_faces = (nR + 2 * kRecTile - 1) / (2 * kRecTile);
+    if (blocks * max_by_faces < 700) max_by_faces = (nR + kRecTile - 1) / kRecTile;
     if (s > max_by_faces) s = max_by_faces;
     if (s > 64) s = 64;
     if (s < 1) s = 1;
@@ -260,11 +255,15 @@ hipError_t launch_pack(const float *V, int64_t nV, const int32_t *F, int64_t nF,
 }
 
 hipError_t launch_pack_records(const float *V, int64_t nV, const int32_t *F, int64_t nF, const int32_t *R,
-                               int64_t nR, VRec *recs, WsHeader *hdr, int32_t *counts, int32_t *go,
-                               hipStream_t s) {
-    if (nR <= 0) return hipSuccess;
+                               int64_t nR, VRec *recs, WsHeader *hdr, hipStream_t s) {
+    if (nR <= 2 * kPackThreads) {
+        k_pack_records<true><<<1, kPackThreads, 0, s>>>(V, nV, F, nF, R, nR, recs, hdr);
+        return hipGetLastError();
+    }
+    const hipError_t e = launch_ws_reset(hdr, s);
+    if (e != hipSuccess) return e;
     const int64_t blocks = (nR + kBlock - 1) / kBlock;
-    k_pack_records<<<dim3((unsigned)blocks), kBlock, 0, s>>>(V, nV, F, nF, R, nR, recs, hdr, counts, go);
+    k_pack_records<false><<<dim3((unsigned)blocks), kBlock, 0, s>>>(V, nV, F, nF, R, nR, recs, hdr);
     return hipGetLastError();
 }
 
@@ -284,10 +283,9 @@ hipError_t launch_fwd(const VRec *recs, int64_t nR, const PointSrc &ps, int64_t 
                                                                                        part, occ);
         return hipGetLastError();
     });
-    if (e != hipSuccess || split <= 1) return e;
-    int64_t rblocks = (nQ + kBlock - 1) / kBlock;
-    if (st && rblocks > kGoBlocks) rblocks = kGoBlocks;
-    k_wn_reduce<<<dim3((unsigned)rblocks), kBlock, 0, s>>>(partials, split, nQ, kInv2Pi, W, occ, st, mark);
+    if (e != hipSuccess || split <= 1 || st) return e;  // (with st, k_cyc_near adds up)
+    const int64_t rblocks = (nQ + kBlock - 1) / kBlock;
+    k_wn_reduce<<<dim3((unsigned)rblocks), kBlock, 0, s>>>(partials, split, nQ, kInv2Pi, W, occ);
     return hipGetLastError();
 }
 
@@ -312,7 +310,7 @@ hipError_t launch_checksum(const float *x, int64_t n, WsHeader *hdr, bool reset,
 hipError_t launch_split_reduce(const float *partials, int split, int64_t nQ, float scale, float *W,
                                const OccParams &occ, hipStream_t s) {
     const int64_t rblocks = (nQ + kBlock - 1) / kBlock;
-    k_wn_reduce<<<dim3((unsigned)rblocks), kBlock, 0, s>>>(partials, split, nQ, scale, W, occ, nullptr, nullptr);
+    k_wn_reduce<<<dim3((unsigned)rblocks), kBlock, 0, s>>>(partials, split, nQ, scale, W, occ);
     return hipGetLastError();
 }
 

@@ -114,6 +114,13 @@ __device__ __forceinline__ void neumaier_add(float &s, float &c, float x) {
     s = t;
 }
 
+// Sum of the splits' partial sums of a point, in order.
+__device__ __forceinline__ float split_sum(const float *__restrict__ partials, int32_t split, int64_t nQ, int64_t idx) {
+    float s = 0.0f, c = 0.0f;
+    for (int32_t k = 0; k < split; ++k) neumaier_add(s, c, partials[(int64_t)k * nQ + idx]);
+    return s + c;
+}
+
 // Where the query points come from: an explicit list or the voxel centres of a grid.
 struct PointSrc {
     const float *Q;      // [n][3] or nullptr for grid mode
@@ -433,6 +440,25 @@ __device__ __forceinline__ void check_strip_record(const int32_t *__restrict__ R
     }
 }
 
+// Record r of the forward stream, by the strip order R or, without one, three per face.
+__device__ __forceinline__ void pack_record(int64_t r, const float *__restrict__ V, int64_t nV,
+                                            const int32_t *__restrict__ F, int64_t nF, const int32_t *__restrict__ R,
+                                            VRec *__restrict__ recs, WsHeader *hdr, int32_t *counts, int32_t *go) {
+    int32_t vid, fid;
+    if (R) {
+        vid = R[2 * r];
+        fid = R[2 * r + 1];
+        check_strip_record(R, r, F, nF, fid, hdr, go);
+        if (counts && fid >= 0 && (int64_t)fid < nF) atomicAdd(&counts[fid], 1);
+    } else {
+        const int64_t f = r / 3;
+        const int j = (int)(r - 3 * f);
+        vid = F[3 * f + j];
+        fid = j == 2 ? (int32_t)f : -1;
+    }
+    recs[r] = make_record(V, nV, F, nF, vid, fid, hdr);
+}
+
 struct OccParams {
     void *occ;
     int32_t mode;
@@ -474,8 +500,7 @@ hipError_t launch_pack(const float *V, int64_t nV, const int32_t *F, int64_t nF,
 // counts / go (optional): the times a strip stream names each face, and a flag raised to 2
 // where the stream does not stand for F.
 hipError_t launch_pack_records(const float *V, int64_t nV, const int32_t *F, int64_t nF, const int32_t *R,
-                               int64_t nR, VRec *recs, WsHeader *hdr, int32_t *counts, int32_t *go,
-                               hipStream_t s);
+                               int64_t nR, VRec *recs, WsHeader *hdr, hipStream_t s);
 // st, mark (optional, device; wn_cycle.hpp): the launch does what the state asks for.
 hipError_t launch_fwd(const VRec *recs, int64_t nR, const PointSrc &ps, int64_t nQ, int split,
                       float *W, float *partials, const OccParams &occ, int ppl, int depth, const struct CycState *st,
