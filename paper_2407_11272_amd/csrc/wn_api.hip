@@ -159,8 +159,9 @@ wn_status voxelize_impl(const float *V, int64_t nV, const int32_t *F, int64_t nF
     // results are bit-identical to this one's).
     const size_t extra = cycle_ws(nV, nF, P);
     const bool fits = R == nullptr || need > WN_NOALLOC_SCRATCH_BYTES || need + extra <= WN_NOALLOC_SCRATCH_BYTES;
-    const bool cyc = !all_pairs && grid != nullptr && extra > 0 && need + extra <= ws_bytes && fits &&
-                     cyc_wanted(nV, nF, P, R ? kCycStripPairs : kCycPairs) && cyc_grid_ok(*grid);
+    const bool suits = grid ? cyc_wanted(nV, nF, P, R ? kCycStripPairs : kCycPairs) && cyc_grid_ok(*grid)
+                            : cyc_wanted(nV, nF, P, kCycPointPairs) && P <= kCycPoints;
+    const bool cyc = !all_pairs && extra > 0 && need + extra <= ws_bytes && fits && suits;
     if (!cyc) {
         hipError_t e = launch_pack_records(V, nV, F, nF, R, nR, recs, hdr, s);
         if (e == hipSuccess) e = launch_fwd(recs, nR, ps, P, split, W, partials, op, cfg.ppl, cfg.depth, nullptr, nullptr, s);
@@ -176,7 +177,7 @@ wn_status voxelize_impl(const float *V, int64_t nV, const int32_t *F, int64_t nF
     m.nR = nR;
     m.chunk = fwd_split_chunk(nR, split);
     m.ps = ps;
-    m.n0 = grid->n[0];
+    m.n0 = grid ? grid->n[0] : 0;
     m.strips = R != nullptr;
     m.R = R;
     m.hdr = hdr;
@@ -191,7 +192,8 @@ wn_status voxelize_impl(const float *V, int64_t nV, const int32_t *F, int64_t nF
     h.ppl = cyc_ppl(P, cfg.ppl);
     cyc_units(m, h);
     hipError_t e = launch_cyc_begin(m, h, table, s);
-    if (e == hipSuccess) e = launch_cyc(h, table, false, nR, s);
+    if (e == hipSuccess && Q) e = launch_cyc_bins(m, table, s);
+    if (e == hipSuccess) e = launch_cyc(h, table, false, Q ? 0 : nR, s);
     if (e == hipSuccess)
         e = launch_fwd(recs, nR, ps, P, split, W, partials, op, cfg.ppl, cfg.depth, m.st, m.mark, s);
     if (e == hipSuccess) e = launch_cyc_near(table, s);

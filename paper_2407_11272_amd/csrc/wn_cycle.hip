@@ -73,6 +73,10 @@ __device__ void clear_unit(const CycMesh &m, int64_t u) {
         if (m.strips && i < m.nF) m.count[i] = 0;
         if (m.W && i < m.P) reinterpret_cast<uint32_t *>(m.W)[m.p0 + i] = kCountBias;
         if (m.W && 32 * i < m.P) m.mark[i] = 0u;
+        if (i < (int64_t)m.bins * m.bins) {
+            m.bin[i] = -1;
+            m.bin_n[i] = 0;
+        }
         if (!m.W && i < m.nV) m.used[i] = 0;
         if (!m.W && i < 3 * m.nV) m.grad[i] = 0;
         if (i == 0) *m.st = CycState{};
@@ -133,6 +137,36 @@ __device__ __forceinline__ void cell_range(const CycMesh &m, int d, double lo, d
     b = (int)fmax(fmin(floor((hi - z) * inv - 0.5 + slack), (double)last), (double)first - 1.0);
 }
 
+// A float as an unsigned integer of the same order; larger than 0 for every number.
+__device__ __forceinline__ uint32_t ordered(float x) {
+    const uint32_t b = __float_as_uint(x);
+    return (b >> 31) ? ~b : b | 0x80000000u;
+}
+__device__ __forceinline__ float from_ordered(uint32_t k) {
+    return __uint_as_float((k >> 31) ? k & 0x7fffffffu : ~k);
+}
+
+// The bins' squares: the box of the vertices with a margin wider than any face's eps, so a point outside
+// meets no face.
+struct Bins {
+    double lo[2], inv[2];
+
+    __device__ __forceinline__ explicit Bins(const CycMesh &m) {
+        double a[3], b[3], most = 0.0;
+        for (int d = 0; d < 3; ++d) {
+            a[d] = -(double)from_ordered(m.st->box[3 + d]);
+            b[d] = (double)from_ordered(m.st->box[d]);
+            most = fmax(most, b[d] - a[d]);
+        }
+        const double margin = 1.0e-3 * most + 1.0e-30;
+        for (int d = 0; d < 2; ++d) {
+            lo[d] = a[d] - margin;
+            inv[d] = (double)m.bins / (b[d] - a[d] + 2.0 * margin);
+        }
+    }
+    __device__ __forceinline__ double at(int d, double x) const { return floor((x - lo[d]) * inv[d]); }
+};
+
 // A triangle (a, b, c) for the columns of voxels: N, its range, and the cells it may meet.
 struct RasterFace {
     double ax, ay, az, bx, by, bz, cx, cy, cz, nx, ny, nz, inv, zmin, zmax, eps, nn;
@@ -151,6 +185,13 @@ struct RasterFace {
         nn = sqrt(nx * nx + ny * ny + nz * nz) * eps;
         const float e = (float)eps * 1.01f;
         lab = e * length(bx - ax, by - ay), lbc = e * length(cx - bx, cy - by), lca = e * length(ax - cx, ay - cy);
+        if (m.bins) {
+            const Bins b(m);
+            const double top = m.bins - 1.0;
+            i0 = (int)fmin(fmax(b.at(0, x0 - eps), 0.0), top), i1 = (int)fmin(fmax(b.at(0, x1 + eps), 0.0), top);
+            j0 = (int)fmin(fmax(b.at(1, y0 - eps), 0.0), top), j1 = (int)fmin(fmax(b.at(1, y1 + eps), 0.0), top);
+            return;
+        }
         cell_range(m, 0, x0 - eps, x1 + eps, m.i_first, m.i_last, i0, i1);
         cell_range(m, 1, y0 - eps, y1 + eps, 0, m.ps.n1 - 1, j0, j1);
     }
@@ -166,9 +207,29 @@ struct RasterFace {
     __device__ __forceinline__ int64_t columns() const {
         return i1 < i0 || j1 < j0 ? 0 : (int64_t)(i1 - i0 + 1) * (j1 - j0 + 1);
     }
+    // Bin (i, j) of a list of points: the crossing is counted at the points below it.
+    __device__ __forceinline__ void points(const CycMesh &m, int sign, int i, int j) const {
+        uint32_t *count = reinterpret_cast<uint32_t *>(m.W);
+        int32_t after;
+        for (int32_t at = m.bin[(int64_t)i * m.bins + j]; at >= 0; at = after) {
+            const float *q = m.ps.Q + 3 * (int64_t)at;
+            const double x = q[0], y = q[1], z = q[2];
+            after = m.after[at];
+            const double off = nx * (ax - x) + ny * (ay - y);
+            const int w = edge_crossing(ax, ay, bx, by, x, y) + edge_crossing(bx, by, cx, cy, x, y) +
+                          edge_crossing(cx, cy, ax, ay, x, y);
+            if (w != 0 && z < fmin(fmax(az + off * inv, zmin), zmax)) atomicAdd(&count[at], (uint32_t)(sign * w));
+            if (z >= zmin - eps && z <= zmax + eps && fabs(off + nz * (az - z)) <= 1.01 * nn && over(x, y))
+                atomicOr(&count[at], kCloseBit);
+        }
+    }
     // Column (i, j): the crossing is counted at the last voxel below it (a column is summed
     // from the top), and the voxels within eps are marked.
     __device__ __forceinline__ void column(const CycMesh &m, int sign, int i, int j) const {
+        if (m.bins) {
+            points(m, sign, i, j);
+            return;
+        }
         const int n2 = m.ps.n2;
         const int64_t base = ((int64_t)i * m.ps.n1 + j) * n2;
         const int first = base >= m.p0 ? 0 : (int)(m.p0 - base < n2 ? m.p0 - base : n2);  // voxels of this slice
@@ -222,6 +283,49 @@ __device__ __forceinline__ bool add_slabs(const CycMesh &m, int32_t id, int64_t 
 __device__ __forceinline__ int64_t edge_bucket(const CycMesh &m, int32_t l, int32_t u) {
     const uint64_t x = ((uint64_t)(uint32_t)l << 32 | (uint32_t)u) * 0x9E3779B97F4A7C15ull;
     return (int64_t)((x >> 32) & (uint64_t)(m.buckets - 1));
+}
+
+// Point lists.  Packs the record stream, and takes the box of the vertices.
+__global__ __launch_bounds__(kCycUnit) void k_cyc_box(const char *table) {
+    __shared__ uint32_t s_box[6];
+    const CycMesh &m = *meshes_of(table);
+    const int64_t i = (int64_t)blockIdx.x * kCycUnit + threadIdx.x;
+    if (threadIdx.x < 6) s_box[threadIdx.x] = 0u;
+    __syncthreads();
+    if (i < m.nR) pack_record(i, m.V, m.nV, m.F, m.nF, m.R, m.recs, m.hdr, m.R ? m.count : nullptr, &m.st->go);
+    if (i < m.nV)
+        for (int d = 0; d < 3; ++d) {
+            const float x = m.V[3 * i + d];
+            if (__builtin_fabsf(x) <= kCoordMax) {  // (a face corner beyond that makes the mesh go direct)
+                atomicMax(&s_box[d], ordered(x));
+                atomicMax(&s_box[3 + d], ordered(-x));
+            }
+        }
+    __syncthreads();
+    if (threadIdx.x < 6 && s_box[threadIdx.x]) atomicMax(&m.st->box[threadIdx.x], s_box[threadIdx.x]);
+}
+
+// Points of a bin that are too many (all faces that meet it go through them one by one).
+constexpr int kBinMax = 64;
+
+__global__ __launch_bounds__(kCycUnit) void k_cyc_bin(const char *table) {
+    const CycMesh &m = *meshes_of(table);
+    const int64_t i = (int64_t)blockIdx.x * kCycUnit + threadIdx.x;
+    if (i >= m.P) return;
+    const float x = m.ps.Q[3 * i], y = m.ps.Q[3 * i + 1], z = m.ps.Q[3 * i + 2];
+    if (!(__builtin_fabsf(x) <= kCoordMax && __builtin_fabsf(y) <= kCoordMax && __builtin_fabsf(z) <= kCoordMax)) {
+        atomicOr(reinterpret_cast<uint32_t *>(m.W) + i, kCloseBit);  // the direct sum
+        return;
+    }
+    const Bins b(m);
+    const double bx = b.at(0, x), by = b.at(1, y);
+    if (!(bx >= 0.0 && by >= 0.0 && bx < (double)m.bins && by < (double)m.bins)) return;
+    const int64_t at = (int64_t)bx * m.bins + (int64_t)by;
+    if (atomicAdd(&m.bin_n[at], 1) >= kBinMax) {
+        atomicMax(&m.st->go, 2);
+        return;
+    }
+    m.after[i] = atomicExch(&m.bin[at], (int32_t)i);
 }
 
 // Eight lanes per face: three chain its half-edges, all share its columns.  Bound by the
@@ -283,7 +387,7 @@ __global__ __launch_bounds__(kCycUnit) void k_cyc_faces(const char *table) {
                     }
                     if (same) atomicMax(&m.st->go, 2);
                 }
-            } else if (bits <= __float_as_uint(kCoordMax)) {  // else the mesh goes direct
+            } else if (bits <= __float_as_uint(kCoordMax) && !(m.bins && m.st->go)) {  // else the mesh goes direct
                 RasterFace r;
                 r.set(m, p[0], p[1], p[2]);
                 const int64_t n = r.columns();
@@ -291,6 +395,10 @@ __global__ __launch_bounds__(kCycUnit) void k_cyc_faces(const char *table) {
                 if (!own) {
                     if (part == 0) own = !add_slabs(m, (int32_t)f, n);
                     own = __shfl(own, (threadIdx.x & 63) - part);
+                    if (own && m.bins) {  // many large faces
+                        atomicMax(&m.st->go, 2);
+                        own = 0;
+                    }
                 }
                 if (own) {
                     const int nj = r.j1 - r.j0 + 1;
@@ -734,6 +842,16 @@ __global__ __launch_bounds__(kCycColumns * 64) void k_cyc_columns(const char *ta
     for (int64_t u = blockIdx.x; u < h->u_col; u += gridDim.x) {
         const CycMesh &m = *find_mesh<&CycMesh::u_col>(table, u);
         if (u == m.u_col && m.grid.order) write_weights(m);
+        if (m.bins) {
+            const int64_t idx = (u - m.u_col) * (kCycColumns * 64) + threadIdx.x;
+            if (idx >= m.P) continue;
+            const uint32_t x = reinterpret_cast<const uint32_t *>(m.W)[idx];
+            const float w = (float)((int)(x & ~kCloseBit) - (int)kCountBias);
+            m.W[idx] = w;
+            if (m.st->n_rec == 0) write_occ(m.occ, idx, w);
+            if ((x & kCloseBit) || (m.st->n_rec == 0 && near_threshold(m.occ, w))) list_near(m, idx);
+            continue;
+        }
         const int n2 = m.ps.n2;
         const int64_t base = (m.p0 / n2 + (u - m.u_col) * kCycColumns + (threadIdx.x >> 6)) * n2;
         const int64_t lo = base > m.p0 ? base : m.p0;
@@ -1475,6 +1593,9 @@ __global__ __launch_bounds__(kNearThreads) void k_cyc_near(const char *table) {
 // holes; the all-pairs sum took (us) 77 at 3.8e7 pairs without strips, and with them 50 at 4.3e7, 60
 // at 4.8e7 (here 46, closed), 69 at 7.1e7 (here 75, 7 % missing), 103 at 9.2e7 (here 68).
 // A few large faces are better summed: their close voxels are many.
+// A list of points has two launches more, and its faces go through chains of points: 9120
+// faces with 5 % missing at 100003 points 702 -> 269 us, 24109 at 28249 925 -> 102 us; at 2e8 pairs 235 against
+// 269 without strips, below 1.5e8 it loses.  With strips the line is the same: 117 us at 1.45e8 pairs, here 170.
 bool cyc_wanted(int64_t nV, int64_t nF, int64_t P, double min_pairs) {
     return nF >= 128 && nV > 0 && nV < ((int64_t)1 << 30) && nF < ((int64_t)1 << 28) && P > 0 &&
            (double)nF * (double)P >= min_pairs;
@@ -1547,6 +1668,12 @@ int64_t edge_buckets(int64_t nF) {
 
 int64_t slab_capacity(int64_t nF) { return nF + 65536; }
 
+// Bins per side for so many points (0: too many): about three to a bin.
+int64_t bin_side(int64_t points) {
+    if (points > kCycPoints) return 0;
+    return std::max<int64_t>(8, (int64_t)std::sqrt((double)points / 3.0));
+}
+
 int64_t near_capacity(int64_t P) { return P < kCycNear ? P : kCycNear; }
 
 // Calls take(field, bytes) for every scratch array of a mesh, in layout order.
@@ -1580,7 +1707,15 @@ void cyc_arrays(CycMesh &m, int64_t nodes, Fn &&take) {
     take(m.near, 4 * (size_t)near_capacity(m.P));
     take(m.mark, 4 * (((size_t)m.P + 31) / 32));
     take(m.weight, 4 * kWeights);
-    take(m.node, 4 * (size_t)(nodes < 0 ? node_space(m.P) : nodes));
+    // a grid's node values or a list's bins
+    size_t shared = 4 * (size_t)(nodes < 0 ? node_space(m.P) : nodes);
+    const int64_t bins = m.bins ? m.bins : nodes < 0 ? bin_side(m.P) : 0;
+    const size_t bin_bytes = align_up(4 * (size_t)(bins * bins));
+    if (bins) shared = std::max(shared, 2 * bin_bytes + 4 * (size_t)m.P);
+    take(m.node, shared);
+    m.bin = reinterpret_cast<int32_t *>(m.node);
+    m.bin_n = m.bin + bin_bytes / 4;
+    m.after = m.bin_n + bin_bytes / 4;
 }
 
 }  // namespace
@@ -1597,7 +1732,9 @@ size_t cyc_bytes(int64_t nV, int64_t nF, int64_t P, int64_t nodes) {
 
 void cyc_place(CycMesh &m, char *base) {
     size_t o = 0;
-    if (m.P > 0) {
+    if (m.ps.Q) {
+        m.bins = (int32_t)bin_side(m.P);
+    } else if (m.P > 0) {
         const int64_t yz = (int64_t)m.ps.n1 * m.ps.n2;
         m.i_first = (int32_t)(m.p0 / yz);
         m.i_last = (int32_t)((m.p0 + m.P - 1) / yz);
@@ -1617,7 +1754,8 @@ void cyc_place(CycMesh &m, char *base) {
 
 void cyc_units(CycMesh &m, CycHead &h) {
     auto units = [](int64_t n, int64_t per) { return (n + per - 1) / per; };
-    const int64_t columns = (m.p0 + m.P - 1) / m.ps.n2 - m.p0 / m.ps.n2 + 1;
+    // (a list's units hold as many points as a grid's hold columns' lanes)
+    const int64_t columns = m.bins ? (m.P + 63) / 64 : (m.p0 + m.P - 1) / m.ps.n2 - m.p0 / m.ps.n2 + 1;
     m.u_clear = h.u_clear;
     m.u_face = h.u_face;
     m.u_half = h.u_half;
@@ -1631,7 +1769,7 @@ void cyc_units(CycMesh &m, CycHead &h) {
         m.inv_h[d] = 1.0 / c;
         m.slack[d] = 1.0e-3 + 2.4e-7 * std::max(std::fabs(l), std::fabs(l + n[d] * c)) / c;
     }
-    h.u_clear += units(std::max(std::max(m.buckets, 3 * m.nV), std::max(m.nF, m.P)), kCycClear);
+    h.u_clear += units(std::max({m.buckets, 3 * m.nV, m.nF, m.P, (int64_t)m.bins * m.bins}), kCycClear);
     h.u_face += units(m.nF, kCycUnit / kCycFaceLanes);
     h.u_half += units(3 * m.nF, kCycUnit);
     h.u_col += units(columns, kCycColumns);
@@ -1683,6 +1821,12 @@ hipError_t launch_cyc(const CycHead &h, char *table, bool fixed, int64_t pack, h
         k_cyc_sum<2><<<grid(h.u_sum), kBlock, 0, s>>>(table);
     else
         k_cyc_sum<4><<<grid(h.u_sum), kBlock, 0, s>>>(table);
+    return hipGetLastError();
+}
+
+hipError_t launch_cyc_bins(const CycMesh &m, char *table, hipStream_t s) {
+    k_cyc_box<<<dim3((unsigned)((std::max(m.nR, m.nV) + kCycUnit - 1) / kCycUnit)), kCycUnit, 0, s>>>(table);
+    k_cyc_bin<<<dim3((unsigned)((m.P + kCycUnit - 1) / kCycUnit)), kCycUnit, 0, s>>>(table);
     return hipGetLastError();
 }
 

@@ -56,6 +56,7 @@ struct CycState {
     uint32_t max_bits;  // bits of the largest |coordinate| of a face corner
     uint32_t grad_bits; // adjoint: bits of the largest |term|
     unsigned long long n_slab;  // entries asked of the raster list
+    uint32_t box[6];    // point lists: largest x, y, z and -x, -y, -z of the vertices, as ordered integers
 };
 
 // One mesh (or slice of its grid) of a launch.
@@ -96,6 +97,11 @@ struct CycMesh {
     int32_t xb0, xb1;     // the slice's blocks along x
     float *weight;        // weights of the blocks' nodes
     float *node;          // [splits][blocks of the slice][coarse, fine nodes] far field at the nodes
+    // A list of points (ps.Q) in place of a grid: bins x bins squares over the mesh's box in x and y
+    // take the place of the columns.
+    int32_t bins;
+    int32_t *bin, *bin_n; // [bins^2] first point of a bin, and their number
+    int32_t *after;       // [P] the next point of its bin
     int2 *slab;           // raster list: (face, or nF + cap record; 64 columns of its range)
     int32_t *near;        // voxels for the direct sum, counted from p0
     uint32_t *mark;       // a bit for each such voxel, also those that the list had no room for
@@ -114,6 +120,8 @@ struct CycHead {
 // Whether sizes make the boundary path worth its fixed cost (see wn_cycle.hip); P is the
 // whole grid, so that a slice takes the path of the grid.
 constexpr double kCycPairs = 3.0e7, kCycStripPairs = 7.0e7;  // without and with a strip order
+constexpr double kCycPointPairs = 1.5e8;                     // a list of points
+constexpr int64_t kCycPoints = (int64_t)1 << 22;             // the longest list (room for its bins)
 bool cyc_wanted(int64_t nV, int64_t nF, int64_t P, double min_pairs = kCycPairs);
 // Whether the grid's extent is finite and in the range of the path.
 bool cyc_grid_ok(const wn_grid &g);
@@ -137,6 +145,8 @@ static_assert(sizeof(CycHead) + sizeof(CycMesh) <= kCycTable, "table size");
 hipError_t launch_cyc_begin(const CycMesh &m, const CycHead &h, char *table, hipStream_t s);
 hipError_t launch_cyc_clear(char *table, hipStream_t s);
 hipError_t launch_cyc(const CycHead &h, char *table, bool fixed, int64_t pack, hipStream_t s);
+// For a list of points, before launch_cyc: packs the records and bins the points.
+hipError_t launch_cyc_bins(const CycMesh &m, char *table, hipStream_t s);
 hipError_t launch_cyc_near(char *table, hipStream_t s);
 
 // The boundary edges alone, after `begin`.

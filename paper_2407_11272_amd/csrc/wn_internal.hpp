@@ -114,10 +114,19 @@ __device__ __forceinline__ void neumaier_add(float &s, float &c, float x) {
     s = t;
 }
 
-// Sum of the splits' partial sums of a point, in order.
+// Sum of the splits' partial sums of a point, in order, eight loads in flight (64 splits of 18294
+// points took 18 us one after the other).
 __device__ __forceinline__ float split_sum(const float *__restrict__ partials, int32_t split, int64_t nQ, int64_t idx) {
     float s = 0.0f, c = 0.0f;
-    for (int32_t k = 0; k < split; ++k) neumaier_add(s, c, partials[(int64_t)k * nQ + idx]);
+    int32_t k = 0;
+    for (; k + 8 <= split; k += 8) {
+        float x[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[j] = partials[(int64_t)(k + j) * nQ + idx];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) neumaier_add(s, c, x[j]);
+    }
+    for (; k < split; ++k) neumaier_add(s, c, partials[(int64_t)k * nQ + idx]);
     return s + c;
 }
 

@@ -277,3 +277,67 @@ def test_blocks_of_voxels(dev, orc, kind, n):
     torch.cuda.synchronize()
     assert float((W - whole.W).abs().max()) <= 2e-6 and float((W != whole.W).float().mean()) < 0.01
     assert bool(((S == whole.W) | ((whole.W - 0.5).abs() < 2e-5)).all())
+
+
+@pytest.mark.parametrize("kind", KINDS)
+def test_lists_of_points(dev, orc, kind):
+    """Lists above the points' line (1.5e8 pairs): points over the whole box, on and very near the
+    surface, on its vertices, far away, on a line through it along z, and with coordinates that
+    are not finite.
+
+    Off the guard band |dW| <= 1e-4 as for every forward; points on the surface or not finite take
+    the all-pairs sum, so shorter lists (below the line) give their W up to the splits' order."""
+    import torch
+    import paper_2407_11272_amd as wn
+    V, F = _mesh(kind)
+    rng = np.random.default_rng(11)
+    T = V[F]
+    f = rng.integers(0, len(F), 4000)
+    b = rng.dirichlet([1, 1, 1], 4000)
+    on = np.einsum("ij,ijk->ik", b, T[f])
+    line = np.stack([np.full(40, 0.013), np.full(40, -0.021), np.linspace(-0.6, 0.6, 40)], -1)
+    odd = np.array([[np.nan, 0, 0], [0, np.inf, 0], [0.1, 0.1, -np.inf], [1e12, 0, 0], [0.0, 0.0, -3e9]])
+    n = int(1.6e8 / len(F)) + 1
+    Q = np.concatenate([rng.uniform(-0.6, 0.6, (n, 3)), on, on + 1e-5 * rng.standard_normal(on.shape), V[:500], line,
+                        rng.uniform(-40, 40, (500, 3)), odd]).astype(np.float32)
+    order = rng.permutation(len(Q))
+    Q, surface = Q[order], (order >= n) & (order < n + len(on))
+    assert len(F) * len(Q) >= 1.5e8
+    Vt, Ft = _dev(V, F)
+    Qt = torch.as_tensor(Q).cuda()
+    W, occ = wn.wn_voxelize(Vt, Ft, Q=Qt, occupancy="threshold")
+    Ws = wn.wn_voxelize_strips(Vt, Ft, _strips(V, F), Q=Qt)
+    assert wn.wn_get_device_error() == 0
+    step = 8192
+    assert len(F) * step < 1.5e8
+    A = torch.cat([wn.wn_voxelize(Vt, Ft, Q=Qt[i:i + step].contiguous()) for i in range(0, len(Q), step)])
+    ok = np.isfinite(Q).all(1) & (np.abs(Q) < 1e9).all(1)
+    torch.testing.assert_close(W.cpu()[~ok], A.cpu()[~ok], rtol=0, atol=2e-6, equal_nan=True)
+    pick = np.nonzero(ok)[0][rng.permutation(int(ok.sum()))[:6000]]
+    V64 = np.asarray(V, np.float32).astype(np.float64)
+    Wr = orc.winding(V64, F, Q[pick].astype(np.float64))
+    guard = orc.guard_mask(V64, F, Q[pick].astype(np.float64))
+    for X in (W, Ws):
+        x = X.cpu().numpy()[pick]
+        print(f"[points {kind}] {len(Q)} off-guard {np.abs(x - Wr)[~guard].max():.2e} on-guard {guard.sum()}", flush=True)
+        assert np.abs(x - Wr)[~guard].max() <= 1e-4
+    assert float((W - A).abs()[torch.as_tensor(surface).cuda()].max()) <= 2e-6
+    m = ~guard & (np.abs(Wr - 0.5) > 1e-3)
+    np.testing.assert_array_equal(occ.cpu().numpy()[pick][m], orc.occupancy_threshold(Wr)[m])
+
+
+def test_points_that_crowd_take_all_pairs(dev):
+    """More points in one square than a bin holds: the all-pairs sum, bit for bit what a
+    list in another order gives."""
+    import torch
+    import paper_2407_11272_amd as wn
+    V, F = _mesh("holes")
+    Vt, Ft = _dev(V, F)
+    Q = np.random.default_rng(2).uniform(-0.01, 0.01, (40000, 3)).astype(np.float32)
+    Q[:, 2] *= 50
+    p = np.random.default_rng(3).permutation(len(Q))
+    W = wn.wn_voxelize(Vt, Ft, Q=torch.as_tensor(Q).cuda())
+    torch.testing.assert_close(wn.wn_voxelize(Vt, Ft, Q=torch.as_tensor(Q[p]).cuda()), W[torch.as_tensor(p).cuda()],
+                               rtol=0, atol=0)
+    A = torch.cat([wn.wn_voxelize(Vt, Ft, Q=torch.as_tensor(Q[i:i + 8000]).cuda()) for i in range(0, len(Q), 8000)])
+    assert float((W - A).abs().max()) <= 2e-6
