@@ -266,11 +266,28 @@ struct RasterFace {
 // Columns that a face's own lanes take; more are left to the slab list, 64 per entry.
 constexpr int kOwnColumns = 64;
 
-// Room for the columns on the raster list; false where there is none.
+// Room for the columns on the raster list; false where there is none.  Called by the lanes of a
+// wave together (any of them): one atomic for all, since thousands queue up at its address (the
+// caps of 1364 boundary edges took 58 us with one each, 55 with one per wave).
 __device__ __forceinline__ bool add_slabs(const CycMesh &m, int32_t id, int64_t columns) {
     const int64_t n = (columns + 63) / 64;
-    if (n > m.slab_cap) return false;
-    const unsigned long long at = atomicAdd(&m.st->n_slab, (unsigned long long)n);
+    const bool fits = n <= m.slab_cap;
+    const int lane = threadIdx.x & 63;
+    unsigned long long asking = __builtin_amdgcn_ballot_w64(fits && n > 0);
+    if (!asking) return fits;
+    const int leader = __builtin_ctzll(asking);
+    unsigned long long before = 0, total = 0;
+    for (; asking; asking &= asking - 1ull) {
+        const int l = __builtin_ctzll(asking);
+        const unsigned x = (unsigned)__builtin_amdgcn_readlane((int)n, l);
+        if (l < lane) before += x;
+        total += x;
+    }
+    unsigned long long at = 0;
+    if (lane == leader) at = atomicAdd(&m.st->n_slab, total);
+    at = ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(at >> 32), leader) << 32 |
+          (unsigned)__builtin_amdgcn_readlane((int)(unsigned)at, leader)) + before;
+    if (!fits || n == 0) return fits;
     if (at + n > (unsigned long long)m.slab_cap) {
         for (int64_t k = at; k < m.slab_cap; ++k) m.slab[k] = make_int2(-1, 0);  // what was left of it
         return false;
@@ -467,7 +484,7 @@ __global__ __launch_bounds__(kCycUnit) void k_cyc_mark(const char *table) {
 // three terms of the arctangent are off by 1e-9.
 constexpr float kFar = 2.0f;
 
-__device__ TriRec tri_record(const RasterFace &f, double sign) {
+__device__ TriRec tri_record(const RasterFace &f) {
     TriRec t;
     const double d1[3] = {f.bx - f.ax, f.by - f.ay, f.bz - f.az}, d2[3] = {f.cx - f.ax, f.cy - f.ay, f.cz - f.az};
     auto dot = [](const double *x, const double *y) { return x[0] * y[0] + x[1] * y[1] + x[2] * y[2]; };
@@ -478,13 +495,27 @@ __device__ TriRec tri_record(const RasterFace &f, double sign) {
     }
     t.d[0][3] = (float)dot(d1, d1);
     t.d[1][3] = (float)dot(d2, d2);
-    t.n[0] = (float)(sign * f.nx), t.n[1] = (float)(sign * f.ny), t.n[2] = (float)(sign * f.nz);
+    t.n[0] = (float)f.nx, t.n[1] = (float)f.ny, t.n[2] = (float)f.nz;
     t.g = (float)dot(d1, d2);
     t.far = kFar * kFar * fmaxf(t.d[0][3], t.d[1][3]);
     return t;
 }
 
+constexpr int kCapListed = 1 << 30;  // in cpos: the triangle's columns are on the raster list
+constexpr int kWaveColumns = 2048;   // columns that one wave takes
+
+// The triangle that cap record x completes (its place in the strip is at least 2), wound as the caps
+// are: the zigzag turns every second one.  False for a degenerate one.
+__device__ __forceinline__ bool set_cap(const CycMesh &m, int x, RasterFace &f) {
+    const int32_t a = m.cvid[x - 2], u = m.cvid[x - 1], v = m.cvid[x];
+    if (a == u || u == v || v == a) return false;
+    const bool turn = m.cpos[x] & 1;
+    f.set(m, m.V + 3 * (int64_t)a, m.V + 3 * (int64_t)(turn ? v : u), m.V + 3 * (int64_t)(turn ? u : v));
+    return true;
+}
+
 constexpr int kCapThreads = 1024;
+constexpr int kUnitLanes = 16;  // lanes that collect the boundary edges of a unit of 256 half-edges: mostly a few
 constexpr int kCapLds = 4096;  // a boundary of at most so many edges is worked on in LDS
 
 // Exclusive sum over the workgroup; `total` gets the sum of all.
@@ -523,7 +554,7 @@ __device__ __forceinline__ int count_of(unsigned long long x, int kind) { return
 __global__ __launch_bounds__(kCapThreads) void k_cyc_caps(const char *table) {
     __shared__ unsigned long long red[kCapThreads / 64];
     __shared__ int2 s_edge[kCapLds];
-    __shared__ int32_t s_work[4][kCapLds];
+    __shared__ int32_t s_work[7][kCapLds];
     __shared__ int32_t s_bad;
     const CycHead *h = reinterpret_cast<const CycHead *>(table);
     const CycMesh *meshes = meshes_of(table);
@@ -552,9 +583,9 @@ __global__ __launch_bounds__(kCapThreads) void k_cyc_caps(const char *table) {
         if (B == 0) continue;
         if (!m.W) {  // the edges are all that is wanted
             __syncthreads();
-            for (int64_t u = tid >> 6; u < units; u += kCapThreads / 64) {
+            for (int64_t u = tid / kUnitLanes; u < units; u += kCapThreads / kUnitLanes) {
                 const int n = m.blk[2 * u], at = m.blk[2 * u + 1];
-                for (int x = tid & 63; x < n; x += 64) {
+                for (int x = tid % kUnitLanes; x < n; x += kUnitLanes) {
                     int32_t a, b;
                     half_edge(m, m.list[u * kCycUnit + x], a, b);
                     m.edge[at + x] = make_int2(a, b);
@@ -565,11 +596,12 @@ __global__ __launch_bounds__(kCapThreads) void k_cyc_caps(const char *table) {
         }
         int n_tri = 0, n_short = 0;
         // (a lambda's two instances, so that LDS is addressed as LDS)
-        auto join = [&](int2 *edge, int32_t *nout, int32_t *nin, int32_t *rank, int32_t *next) -> int {
+        auto join = [&](int2 *edge, int32_t *nout, int32_t *nin, int32_t *rank, int32_t *next, int32_t *succ,
+                        int32_t *same, int32_t *into) -> int {
             __syncthreads();
-            for (int64_t u = tid >> 6; u < units; u += kCapThreads / 64) {
+            for (int64_t u = tid / kUnitLanes; u < units; u += kCapThreads / kUnitLanes) {
                 const int n = m.blk[2 * u], at = m.blk[2 * u + 1];
-                for (int x = tid & 63; x < n; x += 64) {
+                for (int x = tid % kUnitLanes; x < n; x += kUnitLanes) {
                     int32_t a, b;
                     half_edge(m, m.list[u * kCycUnit + x], a, b);
                     edge[at + x] = make_int2(a, b);
@@ -582,13 +614,21 @@ __global__ __launch_bounds__(kCapThreads) void k_cyc_caps(const char *table) {
                 nin[i] = atomicExch(&m.hin[e.y], i);
             }
             __syncthreads();
+            // the chains' heads by edge: those leaving its end and its start, and those entering its end
+            for (int i = tid; i < B; i += kCapThreads) {
+                const int2 e = edge[i];
+                succ[i] = m.hout[e.y];
+                same[i] = m.hout[e.x];
+                into[i] = m.hin[e.y];
+            }
+            __syncthreads();
             // the lowest triangle (by its edges in increasing order) that edge i is part of
             auto triangle = [&](int i, int &to) -> unsigned long long {
                 const int2 e = edge[i];
                 unsigned long long best = ~0ull;
                 int steps = 0;
-                for (int j = m.hout[e.y]; j >= 0; j = nout[j])
-                    for (int k = m.hout[edge[j].y]; k >= 0; k = nout[k]) {
+                for (int j = succ[i]; j >= 0; j = nout[j])
+                    for (int k = succ[j]; k >= 0; k = nout[k]) {
                         if (++steps > kDegreeLimit) {
                             s_bad = 1;
                             return best;
@@ -612,11 +652,10 @@ __global__ __launch_bounds__(kCapThreads) void k_cyc_caps(const char *table) {
             }
             __syncthreads();
             for (int i = tid; i < B; i += kCapThreads) {
-                const int2 e = edge[i];
                 int ro = 0, ri = 0, steps = 0;
-                for (int k = m.hout[e.x]; k >= 0 && steps < kDegreeLimit; k = nout[k], ++steps)
+                for (int k = same[i]; k >= 0 && steps < kDegreeLimit; k = nout[k], ++steps)
                     ro += k < i && next[k] < 0;
-                for (int k = m.hin[e.y]; k >= 0 && steps < kDegreeLimit; k = nin[k], ++steps)
+                for (int k = into[i]; k >= 0 && steps < kDegreeLimit; k = nin[k], ++steps)
                     ri += k < i && next[k] < 0;
                 if (steps >= kDegreeLimit) s_bad = 1;
                 rank[i] = ro | (ri << 16);
@@ -628,7 +667,7 @@ __global__ __launch_bounds__(kCapThreads) void k_cyc_caps(const char *table) {
                 if (to < 0) {
                     const int want = rank[i] >> 16;
                     int steps = 0;
-                    for (int k = m.hout[edge[i].y]; k >= 0 && steps < kDegreeLimit; k = nout[k], ++steps)
+                    for (int k = succ[i]; k >= 0 && steps < kDegreeLimit; k = nout[k], ++steps)
                         if (next[k] < 0 && (rank[k] & 0xffff) == want) to = k;
                     if (to < 0) s_bad = 1;
                 }
@@ -679,42 +718,30 @@ __global__ __launch_bounds__(kCapThreads) void k_cyc_caps(const char *table) {
             n_short = first[2];
             return 0;
         };
-        const int bad = B <= kCapLds ? join(s_edge, s_work[0], s_work[1], s_work[2], s_work[3])
-                                     : join(m.edge, m.nout, m.nin, m.rank, m.next);
+        const int bad = B <= kCapLds ? join(s_edge, s_work[0], s_work[1], s_work[2], s_work[3], s_work[4], s_work[5], s_work[6])
+                                     : join(m.edge, m.nout, m.nin, m.rank, m.next, m.cvid, m.cpos,
+                                            reinterpret_cast<int32_t *>(m.caps));  // (written later)
         if (bad) {
             if (tid == 0) atomicMax(&m.st->go, 2);
             continue;
         }
         __syncthreads();
+        // triangles over many columns go on the raster list; k_cyc_slabs takes the others one by one
         for (int x = tid; x < B; x += kCapThreads) {
-            const int pos = m.cpos[x];
-            const int32_t c = m.cvid[x];
-            VRec r;
-            r.p = make_float4(m.V[3 * (int64_t)c], m.V[3 * (int64_t)c + 1], m.V[3 * (int64_t)c + 2], 0.0f);
-            r.n = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            TriRec t{};
-            t.far = -1.0f;  // no triangle
-            if (pos >= 2) {
-                const int32_t a = m.cvid[x - 2], b = m.cvid[x - 1];
-                if (a != b && b != c && c != a) {
-                    RasterFace f;
-                    f.set(m, m.V + 3 * (int64_t)a, m.V + 3 * (int64_t)b, m.V + 3 * (int64_t)c);
-                    const double s = (pos & 1) ? -1.0 : 1.0;  // the zigzag turns every second triangle
-                    r.n = make_float4((float)(s * f.nx), (float)(s * f.ny), (float)(s * f.nz), 0.0f);
-                    r.p.w = 1.0f;
-                    if (!add_slabs(m, (int32_t)(m.nF + x), f.columns()))
-                        for (int i = f.i0; i <= f.i1; ++i)
-                            for (int j = f.j0; j <= f.j1; ++j) f.column(m, -1, i, j);
-                    t = tri_record(f, s);
-                }
+            if (m.cpos[x] < 2) continue;
+            const float *p[3] = {m.V + 3 * (int64_t)m.cvid[x - 2], m.V + 3 * (int64_t)m.cvid[x - 1],
+                                 m.V + 3 * (int64_t)m.cvid[x]};
+            double area = 1.0;
+            for (int d = 0; d < 2; ++d) {
+                const float l = fminf(fminf(p[0][d], p[1][d]), p[2][d]), u = fmaxf(fmaxf(p[0][d], p[1][d]), p[2][d]);
+                area *= ((double)u - l) * (m.bins ? Bins(m).inv[d] : m.inv_h[d]) + 1.0;
             }
-            if (x >= 3 * n_tri || pos == 2) {
-                const int slot = x >= 3 * n_tri ? x - 2 * n_tri : x / 3;
-                m.tri[slot] = t;
-                m.tri0[slot] = make_float4(t.v[0], t.v[1], t.v[2], t.far);
+            if (area > (double)kWaveColumns) {
+                RasterFace f;
+                if (set_cap(m, x, f) && add_slabs(m, (int32_t)(m.nF + x), f.columns())) m.cpos[x] |= kCapListed;
             }
-            m.caps[x] = r;
         }
+        __syncthreads();
         if (tid == 0) {
             m.st->n_rec = B;
             m.st->n_tri = n_tri;
@@ -723,7 +750,9 @@ __global__ __launch_bounds__(kCapThreads) void k_cyc_caps(const char *table) {
     }
 }
 
-// One wave per entry of the raster list, one column per lane.
+// One wave per entry of the raster list, one column per lane, and one per record of the caps:
+// it writes the record and its triangle, and takes the triangle's columns unless they are on the
+// list.  (One workgroup formed all of them, in FP64: 55 us for 1364 boundary edges.)
 __global__ __launch_bounds__(kCycUnit) void k_cyc_slabs(const char *table) {
     const CycHead *h = reinterpret_cast<const CycHead *>(table);
     const CycMesh *meshes = meshes_of(table);
@@ -736,30 +765,53 @@ __global__ __launch_bounds__(kCycUnit) void k_cyc_slabs(const char *table) {
         const unsigned long long asked = m.st->n_slab;
         const int64_t n = asked < (unsigned long long)m.slab_cap ? (int64_t)asked : m.slab_cap;
         if (m.st->go) continue;
-        for (int64_t x = (wave + waves - before % waves) % waves; x < n; x += waves) {
-            const int2 e = m.slab[x];
-            if (e.x < 0) continue;
+        const int n_tri = m.st->n_tri, n_rec = m.st->n_rec;
+        for (int64_t x = (wave + waves - before % waves) % waves; x < n + n_rec; x += waves) {
             RasterFace r;
             int sign = 1;
-            if (e.x >= m.nF) {
-                const int32_t at = (int32_t)(e.x - m.nF);
-                const VRec *c = m.caps + at;
-                const bool turn = m.cpos[at] & 1;
-                r.set(m, &c[-2].p.x, turn ? &c[0].p.x : &c[-1].p.x, turn ? &c[-1].p.x : &c[0].p.x);
+            int64_t first = 0, end = 0;  // of the columns
+            if (x >= n) {
+                const int at = (int)(x - n), cpos = m.cpos[at], pos = cpos & ~kCapListed;
+                const float *p = m.V + 3 * (int64_t)m.cvid[at];
+                VRec rec;
+                rec.p = make_float4(p[0], p[1], p[2], 0.0f);
+                rec.n = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                TriRec t{};
+                t.far = -1.0f;  // no triangle
+                if (pos >= 2 && set_cap(m, at, r)) {
+                    rec.n = make_float4((float)r.nx, (float)r.ny, (float)r.nz, 0.0f);
+                    rec.p.w = 1.0f;
+                    t = tri_record(r);
+                    if (cpos == pos) end = r.columns();
+                }
+                if (lane == 0) {
+                    m.caps[at] = rec;
+                    if (at >= 3 * n_tri || pos == 2) {
+                        const int slot = at >= 3 * n_tri ? at - 2 * n_tri : at / 3;
+                        m.tri[slot] = t;
+                        m.tri0[slot] = make_float4(t.v[0], t.v[1], t.v[2], t.far);
+                    }
+                }
                 sign = -1;
             } else {
-                const int64_t f = e.x;
-                r.set(m, m.V + 3 * (int64_t)face_vertex(m, 3 * f), m.V + 3 * (int64_t)face_vertex(m, 3 * f + 1),
-                      m.V + 3 * (int64_t)face_vertex(m, 3 * f + 2));
+                const int2 e = m.slab[x];
+                if (e.x < 0) continue;
+                if (e.x >= m.nF) {
+                    set_cap(m, (int)(e.x - m.nF), r);
+                    sign = -1;
+                } else {
+                    const int64_t f = e.x;
+                    r.set(m, m.V + 3 * (int64_t)face_vertex(m, 3 * f), m.V + 3 * (int64_t)face_vertex(m, 3 * f + 1),
+                          m.V + 3 * (int64_t)face_vertex(m, 3 * f + 2));
+                }
+                first = (int64_t)e.y * 64;
+                end = min(first + 64, r.columns());
             }
-            const int64_t c = (int64_t)e.y * 64 + lane;
-            if (c < r.columns()) {
-                const int nj = r.j1 - r.j0 + 1;
-                const int i = (int)(c / nj);
-                r.column(m, sign, r.i0 + i, r.j0 + (int)(c - (int64_t)i * nj));
-            }
+            const int64_t nj = r.j1 - r.j0 + 1;
+            for (int64_t c = first + lane; c < end; c += 64)
+                r.column(m, sign, r.i0 + (int)(c / nj), r.j0 + (int)(c % nj));
         }
-        before += n;
+        before += n + n_rec;
     }
 }
 
