@@ -42,7 +42,11 @@ from dataclasses import dataclass
 import numpy as np
 
 POINT_QUANTUM = 2048      # forward slices are multiples of this many voxels
-STEP_PAIRS = 4.0e10       # point-face pairs of work per scheduler step (adjoint pairs weighted)
+# Point-face pairs of work per scheduler step (adjoint pairs weighted).  A slice of a request costs its
+# mesh's own pass again, which the boundary path made the larger part: with 4e10 a burst of 64
+# requests took 487 ms and the median request 388 ms, with 4e11 237 and 55; a mesh that takes the
+# all-pairs sum holds a step for 0.3 s at most.
+STEP_PAIRS = 4.0e11
 POLICY = "edf"            # "edf": earliest deadline first; "fair": equal shares; "age": shares grow with age
 AGE_TAU = 0.25            # seconds of waiting that double a request's share under "age"
 ADJOINT_COST = 2.8        # cost of one adjoint (point, face) pair in forward pairs
