@@ -42,6 +42,16 @@
  *  - Limits: nV, nF < 2^31; nQ <= 2^31 - 1.
  *  - Results are deterministic: the same inputs give bit-identical outputs, on
  *    the same GPU model, independent of launch tuning and of what else runs.
+ *  - Which sum is formed depends on sizes, the workspace given and the mesh.  From 3e7
+ *    (point, face) pairs on (7e7 with a strip order, 1.5e8 for a point list; at least 128
+ *    faces) W is the winding number of the closed surface made of the mesh and caps over
+ *    its boundary, less the caps' solid angles.  Points closer to a face than 2e-4 of its
+ *    extent, points whose W is within 1e-5 of the threshold, and points on the slope of a
+ *    steep sigmoid (k > 10, |W - tau| < min(10 / k, 1 / 4)) take the sum over all faces;
+ *    so the occupancy mode can change W by that sum's rounding at such points.  Meshes
+ *    that do not suit take the sum over all faces at every point: coordinates that are not
+ *    finite or above 1e9, more boundary edges than faces or than 2^20, edges whose uses do
+ *    not leave one, a strip order that does not name each face once.
  */
 #ifndef WN_H
 #define WN_H
@@ -214,7 +224,10 @@ WN_API wn_status wn_backward(const float *V, int64_t nV, const int32_t *F, int64
  *          running sums at the shared edge's two vertices (12 instead of 18 per pair and
  *          split, fewer operations per point), so the sums per vertex stay exact up to
  *          rounding but those per corner do not; dLdT must then be NULL at WN_BWD_END
- *          (also without pairs, where the flag changes nothing else);
+ *          (also without pairs).  On a grid of at least 2e7 (point, face) pairs dL/dV
+ *          is then the sum over the mesh's boundary edges, where the mesh suits and the
+ *          workspace has the room that wn_workspace_size asks for: inner edges cancel,
+ *          a closed mesh has no gradient;
  *   ws:    wn_workspace_size(WN_OP_BACKWARD, nV, nF, nQ) bytes, holding the running sums.
  * A range of at least S tiles keeps every split busy (about nF / 256 x S workgroups).
  * Argument errors return WN_ERR_INVALID_ARG before any launch.
