@@ -446,6 +446,8 @@ wn_status run_backward(const float *V, int64_t nV, const int32_t *F, int64_t nF,
     char *table = ws + p.off_keys2;
     const size_t with_edges = edge_total(p, nV, nF, nQ);
     const CycState *st = nullptr;
+    CycBlocks blocks{};
+    EdgeBlocks eb{};
     if ((flags & kBwdVertexSums) && !naive && with_edges > 0 && ws_bytes >= with_edges && ps.Q == nullptr &&
         grid_ok(ps, nQ)) {
         CycMesh m{};
@@ -455,6 +457,10 @@ wn_status run_backward(const float *V, int64_t nV, const int32_t *F, int64_t nF,
         m.nF = nF;
         m.ps = ps;
         m.n0 = (int32_t)(nQ / ((int64_t)ps.n1 * ps.n2));
+        const int32_t cells[3] = {m.n0, m.ps.n1, m.ps.n2};
+        blocks = cyc_blocks(cells, nF);
+        eb = edge_blocks(blocks, nF, nQ, ws + p.off_part, p.off_T - p.off_part);
+        m.grid = blocks;
         cyc_place(m, table + kCycTable);
         st = m.st;
         if (flags & kBwdBegin) {
@@ -464,6 +470,8 @@ wn_status run_backward(const float *V, int64_t nV, const int32_t *F, int64_t nF,
             cyc_units(m, h);
             if (launch_cyc_begin(m, h, table, s) != hipSuccess || launch_cyc_edges(h, table, s) != hipSuccess)
                 return WN_ERR_HIP;
+            if (eb.splits > 0 && !((flags & kBwdEnd) && n == nQ))  // points that no range covers have no weight
+                k_fill_i32<<<blocks_for(nQ), kBlock, 0, s>>>(reinterpret_cast<int32_t *>(eb.kept), nQ, 0);
         }
     }
     WsHeader *hdr = reinterpret_cast<WsHeader *>(ws);
@@ -498,7 +506,15 @@ wn_status run_backward(const float *V, int64_t nV, const int32_t *F, int64_t nF,
     if (n > 0 && nV > 0 && nF > 0) {
         const int64_t t0 = p0 / kPointTile, t1 = (p0 + n + kPointTile - 1) / kPointTile;
         const int64_t rows = min((int64_t)S, t1 - t0);
-        if (st && launch_edge_bwd(table, nQ, t0, t1, dLdW, state, s) != hipSuccess) return WN_ERR_HIP;
+        const bool whole = (flags & kBwdBegin) && (flags & kBwdEnd) && n == nQ;
+        if (st && eb.splits == 0 && launch_edge_bwd(table, nQ, t0, t1, dLdW, state, s) != hipSuccess) return WN_ERR_HIP;
+        if (st && eb.splits > 0) {
+            if (whole)
+                e = launch_edge_blocks(table, blocks, dLdW, eb, s);
+            else
+                e = launch_edge_keep(table, dLdW, p0, n, eb, s);
+            if (e != hipSuccess) return WN_ERR_HIP;
+        }
         if (naive) {
             e = launch_naive_bwd(soup, (int32_t)nF, ps, nQ, p.split, t0, t1, (int32_t)rows, dLdW, state, s);
         } else if (use_pairs) {
@@ -539,7 +555,9 @@ wn_status run_backward(const float *V, int64_t nV, const int32_t *F, int64_t nF,
     if (st) {
         // the edges' gradients lie behind T (9 nF floats), in the sort's first two arrays (6 nF)
         float *G = reinterpret_cast<float *>(keys);
-        if (launch_edge_reduce(table, nQ, state, G, s) != hipSuccess ||
+        const bool whole = (flags & kBwdBegin) && n == nQ;
+        if (eb.splits > 0 && !whole && launch_edge_blocks(table, blocks, eb.kept, eb, s) != hipSuccess) return WN_ERR_HIP;
+        if (launch_edge_reduce(table, nQ, eb.splits, state, G, s) != hipSuccess ||
             launch_edge_gather(table, nV, G, T, dLdV, s) != hipSuccess)
             return WN_ERR_HIP;
         return WN_OK;

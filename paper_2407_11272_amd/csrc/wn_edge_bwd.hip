@@ -18,10 +18,12 @@
 //
 // The all-pairs adjoint is bound by its arithmetic over all faces; here the arithmetic of 42 VALU
 // instructions and 3 transcendentals per (edge, point) bounds the point kernel.  Measured, whole
-// adjoint: 7706 faces with 1154 boundary edges on 96 x 88 x 97 points, 10.0 -> 1.08 ms (point kernel
-// 1.02 ms); 9140 faces, 2.6 % of them missing, on 43 x 32 x 17 points, 519 -> 118 us.  The error
+// adjoint: 7706 faces with 1154 boundary edges on 96 x 88 x 97 points, 10.0 -> 1.08 ms point by point,
+// 0.73 ms with nodes (k_edge_blocks); 9140 faces, 2.6 % of them missing, on 43 x 32 x 17 points, 519 -> 118 us.  The error
 // against 64 bits falls too (1.3e-6 -> 1e-7 in the first): fewer terms, and none that cancel.
-#include "wn_cycle.hpp"
+#include <algorithm>
+
+#include "wn_blocks.hpp"
 
 namespace wn {
 
@@ -29,6 +31,7 @@ namespace {
 
 constexpr int kEdgeWaves = 16384;  // one-wave workgroups of the point kernel
 constexpr int kTile = kBwdTile;
+constexpr int64_t kEdgeBlockPoints = 1 << 19;  // 64^3: 208 us with and without the nodes, too few blocks
 
 // Splits of B edges over the tiles of the points, a pure function of the sizes: about
 // kEdgeWaves waves of (64 edges, split), all with the same number of tiles.
@@ -37,6 +40,45 @@ __device__ __forceinline__ int edge_splits(int B, int tiles) {
     const int per = max((int)((tiles * blocks + kEdgeWaves - 1) / kEdgeWaves), (tiles + 4095) / 4096);
     return max(1, (tiles + per - 1) / max(1, per));
 }
+
+// A boundary edge from u to v, and its sums over points.
+struct Edge {
+    float ux, uy, uz, Ex, Ey, Ez, L2, L, tiny, Fx, Fy, Fz;
+
+    __device__ __forceinline__ Edge(const CycMesh &m, const int2 id) {
+        const float *pu = m.V + 3 * (int64_t)id.x, *pv = m.V + 3 * (int64_t)id.y;
+        ux = pu[0], uy = pu[1], uz = pu[2];
+        const double ex = (double)pv[0] - ux, ey = (double)pv[1] - uy, ez = (double)pv[2] - uz;
+        const double l2 = ex * ex + ey * ey + ez * ez, inv = l2 > 0.0 ? 1.0 / l2 : 0.0;
+        Ex = (float)ex, Ey = (float)ey, Ez = (float)ez, L2 = (float)l2, L = (float)sqrt(l2);
+        tiny = (float)(1.0e-24 * l2 * l2);
+        Fx = (float)(ex * inv), Fy = (float)(ey * inv), Fz = (float)(ez * inv);  // E / |E|^2
+    }
+    // Adds g J P at the n points (x, y, z, g) for either end.
+    __device__ __forceinline__ void add(const float4 *pts, int n, float (&su)[3], float (&sv)[3]) const {
+#pragma unroll 4
+        for (int i = 0; i < n; ++i) {
+            const float4 q = pts[i];
+            const float x = ux - q.x, y = uy - q.y, z = uz - q.z;
+            const float a = x * Fx + y * Fy + z * Fz;  // A = a E + P
+            const float px = x - a * Ex, py = y - a * Ey, pz = z - a * Ez;
+            const float d2 = px * px + py * py + pz * pz;
+            const float ul = a * L, vl = ul + L;
+            const float A2 = ul * ul + d2, B2 = vl * vl + d2, AB = ul * vl + d2;
+            // (no point is at a vertex: such a mesh took the all-pairs sum)
+            const float ia = __builtin_amdgcn_rsqf(A2), ib = __builtin_amdgcn_rsqf(B2);
+            const float mn = (A2 * ia) * (B2 * ib) + __builtin_fabsf(AB);
+            // 1 / (|A| |B| + A . B); between the ends, where that cancels, through
+            // (|A| |B|)^2 - (A . B)^2 = |P|^2 |E|^2 (on the edge itself P = 0 and so is the term)
+            const bool between = AB < 0.0f;
+            const float den = between ? __builtin_fmaf(d2, L2, tiny) : mn;
+            const float k = (between ? mn * q.w : q.w) * __builtin_amdgcn_rcpf(den);
+            const float ku = k * ia, kv = k * ib;
+            su[0] += ku * px, su[1] += ku * py, su[2] += ku * pz;
+            sv[0] += kv * px, sv[1] += kv * py, sv[2] += kv * pz;
+        }
+    }
+};
 
 // state: float2 (sum, compensation) [S][6][B].  Grid: waves; wave w takes edge block
 // w mod blocks of the split w / blocks.  dL/dW that is not finite is noted (with
@@ -62,13 +104,7 @@ __global__ __launch_bounds__(64) void k_edge_bwd(const char *table, int64_t nQ, 
         const int e = block * 64 + lane;
         const bool live = e < B;
         const int2 id = B > 0 ? m.edge[live ? e : B - 1] : make_int2(0, 0);
-        const float *pu = m.V + 3 * (int64_t)id.x, *pv = m.V + 3 * (int64_t)id.y;
-        const float ux = pu[0], uy = pu[1], uz = pu[2];
-        const double ex = (double)pv[0] - ux, ey = (double)pv[1] - uy, ez = (double)pv[2] - uz;
-        const double l2 = ex * ex + ey * ey + ez * ez, inv = l2 > 0.0 ? 1.0 / l2 : 0.0;
-        const float Ex = (float)ex, Ey = (float)ey, Ez = (float)ez, L2 = (float)l2, L = (float)sqrt(l2);
-        const float tiny = (float)(1.0e-24 * l2 * l2);
-        const float Fx = (float)(ex * inv), Fy = (float)(ey * inv), Fz = (float)(ez * inv);  // E / |E|^2
+        const Edge edge(m, id);
         for (; t < (int)t1; t += S) {
             const int q0 = t * kTile;
             const int nt = (int)min((int64_t)kTile, nQ - q0);
@@ -85,27 +121,7 @@ __global__ __launch_bounds__(64) void k_edge_bwd(const char *table, int64_t nQ, 
             __syncthreads();
             if (B == 0) continue;
             float su[3] = {0.0f, 0.0f, 0.0f}, sv[3] = {0.0f, 0.0f, 0.0f};
-#pragma unroll 4
-            for (int i = 0; i < kTile; ++i) {
-                const float4 q = pts[i];
-                const float x = ux - q.x, y = uy - q.y, z = uz - q.z;
-                const float a = x * Fx + y * Fy + z * Fz;  // A = a E + P
-                const float px = x - a * Ex, py = y - a * Ey, pz = z - a * Ez;
-                const float d2 = px * px + py * py + pz * pz;
-                const float ul = a * L, vl = ul + L;
-                const float A2 = ul * ul + d2, B2 = vl * vl + d2, AB = ul * vl + d2;
-                // (no point is at a vertex: such a mesh took the all-pairs sum)
-                const float ia = __builtin_amdgcn_rsqf(A2), ib = __builtin_amdgcn_rsqf(B2);
-                const float mn = (A2 * ia) * (B2 * ib) + __builtin_fabsf(AB);
-                // 1 / (|A| |B| + A . B); between the ends, where that cancels, through
-                // (|A| |B|)^2 - (A . B)^2 = |P|^2 |E|^2 (on the edge itself P = 0 and so is the term)
-                const bool between = AB < 0.0f;
-                const float den = between ? __builtin_fmaf(d2, L2, tiny) : mn;
-                const float k = (between ? mn * q.w : q.w) * __builtin_amdgcn_rcpf(den);
-                const float ku = k * ia, kv = k * ib;
-                su[0] += ku * px, su[1] += ku * py, su[2] += ku * pz;
-                sv[0] += kv * px, sv[1] += kv * py, sv[2] += kv * pz;
-            }
+            edge.add(pts, kTile, su, sv);
             if (live) {
                 float2 *row = state + (int64_t)s * 6 * B + e;
                 const float ts[6] = {su[0], su[1], su[2], sv[0], sv[1], sv[2]};
@@ -123,13 +139,180 @@ __global__ __launch_bounds__(64) void k_edge_bwd(const char *table, int64_t nQ, 
     if (__builtin_amdgcn_ballot_w64(odd) && lane == 0) atomicOr(&m.st->odd, 1);
 }
 
-// One wave per edge: its six sums over the splits (lane l the splits l, l + 64, ... in
-// order, then the lanes in pairs), and the gradients of its two ends.
-__global__ __launch_bounds__(kBlock) void k_edge_reduce(const char *table, int64_t nQ, const float2 *__restrict__ state,
-                                                        float *__restrict__ G) {
+// Large grids.  An edge's J P is smooth away from it, so a block of voxels acts on a far edge
+// through its nodes: the block's dL/dW, weighted with what each node gives to each voxel, summed
+// per node (the transpose of the caps' interpolation).  The errors allowed are a tenth of the
+// field's: they are relative to a gradient here.
+constexpr float kEdgeTight = 0.1f;
+constexpr int kParts = 8;
+
+// Node sums of dL/dW, a workgroup per block: [block][coarse, fine].
+__global__ __launch_bounds__(kBlock) void k_edge_nodes(const char *table, const float *__restrict__ dLdW,
+                                                       float *__restrict__ node) {
+    static_assert(kBlock == kBlockSide * kBlockSide, "a thread per (y, z)");
+    __shared__ float T[3][kBlockSide][kFine], C[3][kFine][kCoarse];
+    __shared__ float Y[kFine][kBlockSide][kBlockSide], Z[kFine][kFine][kBlockSide], S[kFine][kFine][kFine];
     const CycMesh &m = *reinterpret_cast<const CycMesh *>(table + reinterpret_cast<const CycHead *>(table)->meshes);
     if (m.st->go) return;
-    const int64_t B = m.st->n_rec, S = edge_splits((int)B, (int)((nQ + kTile - 1) / kTile));
+    const CycBlocks &g = m.grid;
+    const int tid = threadIdx.x, ty = tid / kBlockSide, tz = tid % kBlockSide;
+    for (int e = tid; e < 3 * kBlockSide * kFine; e += kBlock) {
+        const int d = e / (kBlockSide * kFine), i = e / kFine % kBlockSide, j = e % kFine;
+        T[d][i][j] = i < g.size[d] && j < g.fine[d] ? node_weight(kFine, g.size[d], (float)i, j) : 0.0f;
+    }
+    if (tid < 3 * kFine * kCoarse) {
+        const int d = tid / (kFine * kCoarse), i = tid / kCoarse % kFine, j = tid % kCoarse;
+        C[d][i][j] = i < g.fine[d] && j < g.coarse[d]
+                         ? node_weight(kCoarse, g.size[d], node_at(kFine, g.size[d], i), j)
+                         : 0.0f;
+    }
+    __syncthreads();
+    int i0[3];
+    block_origin(m, blockIdx.x, i0);
+    const int iy = i0[1] + ty, iz = i0[2] + tz;
+    const bool in = ty < g.size[1] && tz < g.size[2] && iy < m.ps.n1 && iz < m.ps.n2;
+    float v[kFine];
+#pragma unroll
+    for (int j = 0; j < kFine; ++j) v[j] = 0.0f;
+    bool odd = false;
+    for (int x = 0; x < g.size[0] && i0[0] + x < m.n0; ++x) {
+        const float w = in ? dLdW[((int64_t)(i0[0] + x) * m.ps.n1 + iy) * m.ps.n2 + iz] : 0.0f;
+        odd = odd || !(__builtin_fabsf(w) < INFINITY);
+#pragma unroll
+        for (int j = 0; j < kFine; ++j) v[j] = __builtin_fmaf(T[0][x][j], w, v[j]);
+    }
+    if (__builtin_amdgcn_ballot_w64(odd) && (tid & 63) == 0) atomicOr(&m.st->odd, 1);
+#pragma unroll
+    for (int j = 0; j < kFine; ++j) Y[j][ty][tz] = v[j];
+    __syncthreads();
+    for (int e = tid; e < kFine * kFine * kBlockSide; e += kBlock) {
+        const int j0 = e / (kFine * kBlockSide), j1 = e / kBlockSide % kFine, z = e % kBlockSide;
+        float a = 0.0f;
+        for (int y = 0; y < kBlockSide; ++y) a = __builtin_fmaf(Y[j0][y][z], T[1][y][j1], a);
+        Z[j0][j1][z] = a;
+    }
+    __syncthreads();
+    const int nc = g.coarse[0] * g.coarse[1] * g.coarse[2], nf = g.fine[0] * g.fine[1] * g.fine[2];
+    float *out = node + (int64_t)blockIdx.x * (nc + nf);
+    for (int e = tid; e < kFine * kFine * kFine; e += kBlock) {
+        const int j0 = e / (kFine * kFine), j1 = e / kFine % kFine, j2 = e % kFine;
+        float a = 0.0f;
+        for (int z = 0; z < kBlockSide; ++z) a = __builtin_fmaf(Z[j0][j1][z], T[2][z][j2], a);
+        S[j0][j1][j2] = a;
+        if (j0 < g.fine[0] && j1 < g.fine[1] && j2 < g.fine[2]) out[nc + (j0 * g.fine[1] + j1) * g.fine[2] + j2] = a;
+    }
+    __syncthreads();
+    if (tid < nc) {
+        const int k0 = tid / (g.coarse[1] * g.coarse[2]), r = tid % (g.coarse[1] * g.coarse[2]);
+        const int k1 = r / g.coarse[2], k2 = r % g.coarse[2];
+        float a = 0.0f;
+        for (int j0 = 0; j0 < kFine; ++j0) {
+            float a0 = 0.0f;
+            for (int j1 = 0; j1 < kFine; ++j1) {
+                float a1 = 0.0f;
+                for (int j2 = 0; j2 < kFine; ++j2) a1 = __builtin_fmaf(S[j0][j1][j2], C[2][j2][k2], a1);
+                a0 = __builtin_fmaf(a1, C[1][j1][k1], a0);
+            }
+            a = __builtin_fmaf(a0, C[0][j0][k0], a);
+        }
+        out[tid] = a;
+    }
+}
+
+// A wave per 64 edges and split; split s takes the parts s, s + S, ... of the blocks (an eighth of the fine
+// nodes and of the voxels each, all coarse nodes in one of them): far edges at the coarse or
+// the fine nodes, near ones at the voxels (lanes without such an edge wait).  With whole blocks
+// the waves that had near edges took 864 us.
+// state: float2 [S][6][B].  42 VALU and 3 transcendentals per (edge, point) bound it: 1154 edges on
+// 96 x 88 x 97 voxels take 621 us, all points one by one 1024.
+__global__ __launch_bounds__(64) void k_edge_blocks(const char *table, const float *__restrict__ dLdW,
+                                                    const float *__restrict__ node, int S, float2 *__restrict__ state) {
+    __shared__ float4 pts[kTile];
+    const CycMesh &m = *reinterpret_cast<const CycMesh *>(table + reinterpret_cast<const CycHead *>(table)->meshes);
+    if (m.st->go) return;
+    const int B = __builtin_amdgcn_readfirstlane(m.st->n_rec), groups = (B + 63) / 64;
+    const CycBlocks &g = m.grid;
+    const int nc = g.coarse[0] * g.coarse[1] * g.coarse[2], nf = g.fine[0] * g.fine[1] * g.fine[2];
+    const int voxels = g.size[0] * g.size[1] * g.size[2], blocks = g.n[0] * g.n[1] * g.n[2];
+    const int lane = threadIdx.x;
+    for (int64_t w = blockIdx.x; w < (int64_t)groups * S; w += gridDim.x) {
+        const int split = (int)(w / groups), e = (int)(w - (int64_t)split * groups) * 64 + lane;
+        const bool live = e < B;
+        const Edge edge(m, m.edge[live ? e : B - 1]);
+        float s[6], c[6];
+#pragma unroll
+        for (int i = 0; i < 6; ++i) s[i] = c[i] = 0.0f;
+        for (int x = split; x < blocks * kParts; x += S) {
+            const int b = x / kParts, part = x - b * kParts;
+            int i0[3];
+            block_origin(m, b, i0);
+            const Block box(m, i0);
+            const int kind = live ? box.kind(make_float4(edge.ux, edge.uy, edge.uz, kFar * kFar * edge.L2), kEdgeTight) : 0;
+            const float *at = node + (int64_t)b * (nc + nf);
+#pragma unroll 1
+            for (int want = 2; want >= -1; --want) {
+                if (want == 0 || !__builtin_amdgcn_ballot_w64(kind == want)) continue;
+                const int n = want == 2 ? nc : want == 1 ? nf : voxels, order = want == 2 ? kCoarse : kFine;
+                const int *side = want == 2 ? g.coarse : want == 1 ? g.fine : g.size;
+                // (the coarse nodes are few: one part has them all)
+                const int first = want == 2 ? (part == b % kParts ? 0 : n) : n * part / kParts;
+                const int end = want == 2 ? n : n * (part + 1) / kParts;
+                for (int t0 = first; t0 < end; t0 += kTile) {
+                    const int here = min(kTile, end - t0);
+                    __syncthreads();
+#pragma unroll 1
+                    for (int k = lane; k < here; k += 64) {
+                        const int x = t0 + k, a = x / (side[1] * side[2]), r = x - a * side[1] * side[2];
+                        const int j = r / side[2], l = r - j * side[2];
+                        if (want > 0) {
+                            pts[k] = make_float4(__builtin_fmaf(node_at(order, g.size[0], a), m.ps.h[0], box.lo[0]),
+                                                 __builtin_fmaf(node_at(order, g.size[1], j), m.ps.h[1], box.lo[1]),
+                                                 __builtin_fmaf(node_at(order, g.size[2], l), m.ps.h[2], box.lo[2]),
+                                                 at[(want == 2 ? 0 : nc) + x]);
+                        } else {
+                            const int ix = i0[0] + a, iy = i0[1] + j, iz = i0[2] + l;
+                            const bool in = ix < m.n0 && iy < m.ps.n1 && iz < m.ps.n2;
+                            // (beyond the grid: a voxel of it, without weight)
+                            pts[k] = make_float4(centre(m.ps, 0, min(ix, m.n0 - 1)), centre(m.ps, 1, min(iy, m.ps.n1 - 1)),
+                                                 centre(m.ps, 2, min(iz, m.ps.n2 - 1)),
+                                                 in ? dLdW[((int64_t)ix * m.ps.n1 + iy) * m.ps.n2 + iz] : 0.0f);
+                        }
+                    }
+                    __syncthreads();
+                    if (kind == want) {
+                        float su[3] = {0.0f, 0.0f, 0.0f}, sv[3] = {0.0f, 0.0f, 0.0f};
+                        edge.add(pts, here, su, sv);
+#pragma unroll
+                        for (int i = 0; i < 3; ++i) {
+                            neumaier_add(s[i], c[i], su[i]);
+                            neumaier_add(s[3 + i], c[3 + i], sv[i]);
+                        }
+                    }
+                }
+            }
+        }
+        if (live)
+#pragma unroll
+            for (int i = 0; i < 6; ++i) state[((int64_t)split * 6 + i) * B + e] = make_float2(s[i], c[i]);
+    }
+}
+
+// dL/dW of a point range, for the call that ends the sequence.
+__global__ __launch_bounds__(kBlock) void k_edge_keep(const char *table, const float *__restrict__ dLdW, int64_t n,
+                                                      float *__restrict__ kept) {
+    const CycMesh &m = *reinterpret_cast<const CycMesh *>(table + reinterpret_cast<const CycHead *>(table)->meshes);
+    if (m.st->go) return;  // (the all-pairs sums use that space)
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        kept[i] = dLdW[i];
+}
+
+// One wave per edge: its six sums over the splits (lane l the splits l, l + 64, ... in
+// order, then the lanes in pairs), and the gradients of its two ends.
+__global__ __launch_bounds__(kBlock) void k_edge_reduce(const char *table, int64_t nQ, int splits,
+                                                        const float2 *__restrict__ state, float *__restrict__ G) {
+    const CycMesh &m = *reinterpret_cast<const CycMesh *>(table + reinterpret_cast<const CycHead *>(table)->meshes);
+    if (m.st->go) return;
+    const int64_t B = m.st->n_rec, S = splits > 0 ? splits : edge_splits((int)B, (int)((nQ + kTile - 1) / kTile));
     const int lane = threadIdx.x & 63;
     uint32_t bits = 0;
     for (int64_t e = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6); e < B;
@@ -262,8 +445,41 @@ hipError_t launch_edge_bwd(const char *table, int64_t nQ, int64_t t0, int64_t t1
     return hipGetLastError();
 }
 
-hipError_t launch_edge_reduce(const char *table, int64_t nQ, const float2 *state, float *G, hipStream_t s) {
-    k_edge_reduce<<<1024, kBlock, 0, s>>>(table, nQ, state, G);
+EdgeBlocks edge_blocks(const CycBlocks &g, int64_t nF, int64_t nQ, char *space, size_t bytes) {
+    EdgeBlocks e{};
+    if (g.order == 0 || nQ < kEdgeBlockPoints) return e;
+    const int64_t blocks = (int64_t)g.n[0] * g.n[1] * g.n[2];
+    const size_t node = align_up(4 * (size_t)cyc_node_floats(CycBlocks{g.order, {g.size[0], g.size[1], g.size[2]},
+                                                                       {g.n[0], g.n[1], g.n[2]},
+                                                                       {g.coarse[0], g.coarse[1], g.coarse[2]},
+                                                                       {g.fine[0], g.fine[1], g.fine[2]}, 1},
+                                                             g.n[0]));
+    const size_t kept = align_up(4 * (size_t)nQ);
+    if (node + kept >= bytes) return e;
+    const int64_t splits = std::min<int64_t>(blocks, (int64_t)((bytes - node - kept) / (48 * (size_t)nF)));
+    if (splits < std::min<int64_t>(blocks, 64)) return e;
+    e.splits = (int)splits;
+    e.state = reinterpret_cast<float2 *>(space);
+    e.kept = reinterpret_cast<float *>(space + bytes / 256 * 256 - kept);
+    e.node = reinterpret_cast<float *>(reinterpret_cast<char *>(e.kept) - node);
+    return e;
+}
+
+hipError_t launch_edge_keep(const char *table, const float *dLdW, int64_t p0, int64_t n, const EdgeBlocks &e,
+                            hipStream_t s) {
+    k_edge_keep<<<1024, kBlock, 0, s>>>(table, dLdW + p0, n, e.kept + p0);
+    return hipGetLastError();
+}
+
+hipError_t launch_edge_blocks(const char *table, const CycBlocks &g, const float *dLdW, const EdgeBlocks &e,
+                              hipStream_t s) {
+    k_edge_nodes<<<(unsigned)(g.n[0] * g.n[1] * g.n[2]), kBlock, 0, s>>>(table, dLdW, e.node);
+    k_edge_blocks<<<kEdgeWaves, 64, 0, s>>>(table, dLdW, e.node, e.splits, e.state);
+    return hipGetLastError();
+}
+
+hipError_t launch_edge_reduce(const char *table, int64_t nQ, int splits, const float2 *state, float *G, hipStream_t s) {
+    k_edge_reduce<<<1024, kBlock, 0, s>>>(table, nQ, splits, state, G);
     return hipGetLastError();
 }
 

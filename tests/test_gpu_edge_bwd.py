@@ -160,3 +160,50 @@ def test_fitting_step_follows_the_all_pairs_field(dev):
     occ2 = wn.soft_occupancy(y, Ft, Q=Q, tau=0.5, k=50.0)
     (occ2 ** 2).mean().backward()
     assert float((x.grad - y.grad).norm()) <= 1e-4 * float(y.grad.norm())
+
+
+@pytest.mark.parametrize("n", [(84, 80, 82), (97, 61, 131), (230, 6, 400)])
+@pytest.mark.parametrize("kind", ["holes", "open end", "sheet"])
+def test_blocks_of_voxels(dev, kind, n):
+    """Grids of at least 2^19 voxels, where far edges take nodes: ragged last blocks and an axis with
+    fewer voxels than nodes, against the sum over the boundary edges in FP64, and point ranges
+    against one call, bit for bit.  The nodes are allowed 4e-9 of an edge's share per block (x 10),
+    and white noise for dL/dW adds up to 1e-2 of its terms: 1e-5."""
+    import torch
+    import wn_inputs as wi
+    import paper_2407_11272_amd as wn
+    V, F = _mesh(kind)
+    grid = wi.Grid((-0.5, -0.45, -0.5), (0.5, 0.5, 0.47), n)
+    assert grid.size >= 1 << 19 and len(F) * grid.size >= 1.5e9
+    Vt, Ft = _dev(V, F)
+    g = torch.as_tensor(np.random.default_rng(4).standard_normal(grid.size).astype(np.float32)).cuda() / grid.size
+    D = wn.wn_backward(Vt, Ft, g, grid=grid)
+    # dW/du = -(A x E) / (4 pi |A| (|A| |B| + A . B)) summed over the boundary edges in FP64
+    e = np.concatenate([F[:, [0, 1]], F[:, [1, 2]], F[:, [2, 0]]]).astype(np.int64)
+    code, back = e[:, 0] * len(V) + e[:, 1], e[:, 1] * len(V) + e[:, 0]
+    e = torch.as_tensor(e[~np.isin(code, back)]).cuda()
+    U, E = Vt.double()[e[:, 0]], Vt.double()[e[:, 1]] - Vt.double()[e[:, 0]]
+    A = torch.zeros(len(V), 3, dtype=torch.float64, device="cuda")
+    Q = torch.as_tensor(_centres(grid)).cuda()
+    su, sv = torch.zeros_like(U), torch.zeros_like(U)
+    for i in range(0, len(Q), 16384):
+        R = U[:, None] - Q[None, i:i + 16384].double()
+        S = R + E[:, None]
+        a, b = R.norm(dim=2), S.norm(dim=2)
+        w = g[i:i + 16384].double() / (a * b + (R * S).sum(2))
+        su += ((w / a)[..., None] * R).sum(1)
+        sv += ((w / b)[..., None] * R).sum(1)
+    A.index_add_(0, e[:, 0], torch.cross(su, E, dim=1) / (-4 * np.pi))
+    A.index_add_(0, e[:, 1], torch.cross(sv, E, dim=1) / (-4 * np.pi))
+    err = float((D - A).norm() / A.norm())
+    print(f"[{kind} {n}] relative difference {err:.2e}", flush=True)
+    assert err <= 1e-5
+    sb = wn.SlicedBackward(Vt, Ft, grid=grid, vertex_sums=True)
+    sb.begin()
+    at = [0, 256, 256 * 700, 256 * 701, grid.size]
+    for a, b in zip(at[:-1], at[1:]):
+        sb.points(a, b - a, g)
+    assert torch.equal(sb.end(), D)
+    bad = g.clone()
+    bad[grid.size // 2] = float("nan")
+    assert bool(torch.isnan(wn.wn_backward(Vt, Ft, bad, grid=grid)[Ft.long()]).all())
