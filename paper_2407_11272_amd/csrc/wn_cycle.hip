@@ -545,6 +545,8 @@ __device__ __forceinline__ int count_of(unsigned long long x, int kind) { return
 // otherwise become one loop of six); then an edge entering a vertex continues with the
 // leaving edge of the same rank there.  A loop starts at its lowest edge, so the cap stream
 // depends on F alone.  A loop of k edges becomes a strip of k records and k - 2 triangles.
+// Bound by the latency of its dependent loads and barriers: 39 us for 1364 edges, 288 for 11082
+// (58 and 437 with the chains' heads read from memory and the triangles formed here).
 __global__ __launch_bounds__(kCapThreads) void k_cyc_caps(const char *table) {
     __shared__ unsigned long long red[kCapThreads / 64];
     __shared__ int2 s_edge[kCapLds];
@@ -1202,6 +1204,7 @@ __global__ __launch_bounds__(kWaves * 64) void k_cyc_sum_split(const char *table
 // below kCoarseError with kCoarse nodes per axis, it takes those (most triangles do, so their errors
 // add up: 4e-9 gave 6e-7 of W over 46000 faces with 8 % missing, the all-pairs sum's own error;
 // 1e-9 gives 2.4e-7).
+//
 // One wave per split of the triangles and 64 nodes of a block: the coarse ones, or 64 of the
 // fine ones.
 __global__ __launch_bounds__(64) void k_cyc_nodes(const char *table) {
@@ -1263,6 +1266,7 @@ __global__ __launch_bounds__(64) void k_cyc_nodes(const char *table) {
 // Both are bound by their arithmetic (38 VALU with 4 transcendentals per node, 30 per near point) and by
 // the latency of few waves.  19000 faces with 5 % missing on 128^3: one by one 1956 us, here 203 +
 // 234; 46000 faces with 8 % missing on 141 x 117 x 131: 7600 us, here 884 + 551.
+//
 // One workgroup per block and kBlockRows of its planes along x; a thread takes one (y, z) and
 // the planes' points there.
 __global__ __launch_bounds__(kBlock) void k_cyc_blocks(const char *table) {
