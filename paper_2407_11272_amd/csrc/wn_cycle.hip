@@ -77,7 +77,10 @@ __device__ void clear_unit(const CycMesh &m, int64_t u) {
             m.bin[i] = -1;
             m.bin_n[i] = 0;
         }
-        if (!m.W && i < m.nV) m.used[i] = 0;
+        if (!m.W && i < m.nV) {
+            m.used[i] = 0;
+            m.most[i] = 0u;
+        }
         if (!m.W && i < 3 * m.nV) m.grad[i] = 0;
         if (i == 0) *m.st = CycState{};
     }
@@ -1666,6 +1669,7 @@ void cyc_arrays(CycMesh &m, int64_t nodes, Fn &&take) {
     take(m.edge, 8 * nF);
     if (m.P == 0) {
         take(m.used, 4 * nV);
+        take(m.most, 4 * nV);
         take(m.grad, 24 * nV);
         return;
     }

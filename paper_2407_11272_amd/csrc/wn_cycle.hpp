@@ -54,7 +54,6 @@ struct CycState {
     int32_t n_near;     // points on the list of direct sums
     int32_t odd;        // adjoint: dL/dW holds a value that is not finite
     uint32_t max_bits;  // bits of the largest |coordinate| of a face corner
-    uint32_t grad_bits; // adjoint: bits of the largest |term|
     unsigned long long n_slab;  // entries asked of the raster list
     uint32_t box[6];    // point lists: largest x, y, z and -x, -y, -z of the vertices, as ordered integers
 };
@@ -84,6 +83,7 @@ struct CycMesh {
     int64_t buckets;      // a power of two
     int32_t *hout, *hin;  // [nV] first boundary edge leaving / entering a vertex
     int32_t *used;        // [nV] adjoint: 1 for a vertex of a face
+    uint32_t *most;       // [nV] adjoint: bits of the vertex's largest |term|
     int64_t *grad;        // [nV][3] adjoint: sums of its terms
     int32_t *count;       // [nF] times the stream names a face
     int32_t *list, *blk;  // boundary half-edges of each unit, and their number and offset

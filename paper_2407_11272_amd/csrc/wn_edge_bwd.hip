@@ -306,6 +306,14 @@ __global__ __launch_bounds__(kBlock) void k_edge_keep(const char *table, const f
         kept[i] = dLdW[i];
 }
 
+// Notes a term of vertex v (three floats) in the largest of its terms.
+__device__ __forceinline__ void note_term(const CycMesh &m, int32_t v, const float *x) {
+    uint32_t bits = 0;
+    for (int d = 0; d < 3; ++d)
+        if (__builtin_fabsf(x[d]) < INFINITY) bits = max(bits, __float_as_uint(__builtin_fabsf(x[d])));
+    if (bits) atomicMax(&m.most[v], bits);
+}
+
 // One wave per edge: its six sums over the splits (lane l the splits l, l + 64, ... in
 // order, then the lanes in pairs), and the gradients of its two ends.
 __global__ __launch_bounds__(kBlock) void k_edge_reduce(const char *table, int64_t nQ, int splits,
@@ -314,7 +322,6 @@ __global__ __launch_bounds__(kBlock) void k_edge_reduce(const char *table, int64
     if (m.st->go) return;
     const int64_t B = m.st->n_rec, S = splits > 0 ? splits : edge_splits((int)B, (int)((nQ + kTile - 1) / kTile));
     const int lane = threadIdx.x & 63;
-    uint32_t bits = 0;
     for (int64_t e = (int64_t)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6); e < B;
          e += (int64_t)gridDim.x * (kBlock / 64)) {
         float s[6], c[6];
@@ -354,21 +361,17 @@ __global__ __launch_bounds__(kBlock) void k_edge_reduce(const char *table, int64
                 G[6 * e + 3 * end + 0] = (float)(f * (P[1] * E[2] - P[2] * E[1]));
                 G[6 * e + 3 * end + 1] = (float)(f * (P[2] * E[0] - P[0] * E[2]));
                 G[6 * e + 3 * end + 2] = (float)(f * (P[0] * E[1] - P[1] * E[0]));
-                for (int d = 0; d < 3; ++d) {
-                    const float x = __builtin_fabsf(G[6 * e + 3 * end + d]);
-                    if (x < INFINITY) bits = max(bits, __float_as_uint(x));
-                }
+                note_term(m, end ? id.y : id.x, G + 6 * e + 3 * end);
             }
         }
     }
-    if (lane == 0 && bits) atomicMax(&m.st->grad_bits, bits);
 }
 
 // The terms of dL/dV: the two ends of each boundary edge (G), or, for a mesh that took the
-// all-pairs sum, every corner (T).  They are added per vertex as 64-bit integers on one
-// scale, so that the sum does not depend on the order: with n terms of at most 2^e the
-// unit is 2^(e - 61) n, rounded up to a power of two, 1e-13 of the largest term for 1e5
-// terms.
+// all-pairs sum, every corner (T).  They are added per vertex as 64-bit integers, so that the sum
+// does not depend on the order, on a scale of the vertex's own: with n terms in all and the vertex's of at
+// most 2^e the unit is 2^(e - 61) n, rounded up to a power of two, 1e-13 of its largest term for 1e5
+// terms (on one scale for the mesh a vertex beside one whose terms are 1e13 times larger got 0).
 struct Terms {
     const float *x;  // three floats per term
     int64_t n;
@@ -380,41 +383,39 @@ __device__ __forceinline__ Terms terms_of(const CycMesh &m, const float *G, cons
     return Terms{G, 2 * (int64_t)m.st->n_rec, true};
 }
 
-// Power of two that a term is multiplied by.
-__device__ __forceinline__ int term_shift(const CycMesh &m, int64_t n) {
+// Power of two that a term of vertex v is multiplied by.
+__device__ __forceinline__ int term_shift(const CycMesh &m, int64_t n, int64_t v) {
     int bits = 0;
     while (bits < 40 && ((int64_t)1 << bits) < n) ++bits;
-    int e = (int)(m.st->grad_bits >> 23) - 126;  // |term| < 2^e
+    const int e = (int)(m.most[v] >> 23) - 126;  // |term| < 2^e
     return 61 - bits - e;
 }
 
-// Largest corner gradient (the edges' is noted as they are formed).
+// The vertex of term i.
+__device__ __forceinline__ int32_t term_vertex(const CycMesh &m, bool edges, int64_t i) {
+    if (edges) {
+        const int2 e = m.edge[i >> 1];
+        return (i & 1) ? e.y : e.x;
+    }
+    const int32_t v = m.F[i];
+    return (v < 0 || (int64_t)v >= m.nV) ? 0 : v;
+}
+
+// Largest corner gradients (the edges' are noted as they are formed).
 __global__ __launch_bounds__(kBlock) void k_corner_max(const char *table, const float *__restrict__ T) {
     const CycMesh &m = *reinterpret_cast<const CycMesh *>(table + reinterpret_cast<const CycHead *>(table)->meshes);
     if (m.st->go == 0) return;
-    uint32_t bits = 0;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < 9 * m.nF; i += (int64_t)gridDim.x * blockDim.x) {
-        const float x = __builtin_fabsf(T[i]);
-        if (x < INFINITY) bits = max(bits, __float_as_uint(x));
-    }
-    for (int o = 32; o > 0; o >>= 1) bits = max(bits, (uint32_t)__shfl_xor((int)bits, o));
-    if ((threadIdx.x & 63) == 0 && bits) atomicMax(&m.st->grad_bits, bits);
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < 3 * m.nF; i += (int64_t)gridDim.x * blockDim.x)
+        note_term(m, term_vertex(m, false, i), T + 3 * i);
 }
 
 __global__ __launch_bounds__(kBlock) void k_add_terms(const char *table, const float *__restrict__ G,
                                                       const float *__restrict__ T) {
     const CycMesh &m = *reinterpret_cast<const CycMesh *>(table + reinterpret_cast<const CycHead *>(table)->meshes);
     const Terms t = terms_of(m, G, T);
-    const int shift = term_shift(m, t.n);
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < t.n; i += (int64_t)gridDim.x * blockDim.x) {
-        int32_t v;
-        if (t.edges) {
-            const int2 e = m.edge[i >> 1];
-            v = (i & 1) ? e.y : e.x;
-        } else {
-            v = m.F[i];
-            if (v < 0 || (int64_t)v >= m.nV) v = 0;
-        }
+        const int32_t v = term_vertex(m, t.edges, i);
+        const int shift = term_shift(m, t.n, v);
         for (int d = 0; d < 3; ++d) {
             const float x = t.x[3 * i + d];
             if (__builtin_fabsf(x) < INFINITY)
@@ -431,7 +432,7 @@ __global__ __launch_bounds__(kBlock) void k_write_grad(const char *table, float 
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= 3 * m.nV) return;
     const int32_t used = m.used[i / 3];
-    const int shift = term_shift(m, m.st->go ? 3 * m.nF : 2 * (int64_t)m.st->n_rec);
+    const int shift = term_shift(m, m.st->go ? 3 * m.nF : 2 * (int64_t)m.st->n_rec, i / 3);
     // dL/dW that is not finite reaches every vertex of a face
     const bool odd = used == 2 || (used == 1 && m.st->go == 0 && m.st->odd);
     dLdV[i] = odd ? NAN : (float)ldexp((double)m.grad[i], -shift);

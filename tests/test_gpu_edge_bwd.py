@@ -207,3 +207,26 @@ def test_blocks_of_voxels(dev, kind, n):
     bad = g.clone()
     bad[grid.size // 2] = float("nan")
     assert bool(torch.isnan(wn.wn_backward(Vt, Ft, bad, grid=grid)[Ft.long()]).all())
+
+
+@pytest.mark.parametrize("kind", ["closed", "reversed faces"])
+def test_small_terms_beside_large_ones(dev, orc, kind):
+    """A triangle 4e5 away, whose gradient is some 1e-15 of that of a triangle with a vertex 1e-7 from a
+    voxel centre.  From the boundary edges: 1e-5 of its largest component, as alone (FP32 terms).  With
+    edges that do not suit the path: its corner terms, which are its vertices', up to a rounding."""
+    import paper_2407_11272_amd as wn
+    V, F = _mesh(kind)
+    V = np.asarray(V, np.float32)
+    base, q = len(V), _centres(GRID)[5000]
+    A = np.float32([q + [1e-7, 0, 0], q + [0.1, 0.2, 0.1], q + [-0.1, 0.1, 0.2]])
+    B = np.float32([[4e5, 3e5, 1e5], [4e5 + 20, 3e5, 1e5 - 10], [4e5, 3e5 + 10, 1e5 + 20]])
+    Vt, Ft = _dev(np.concatenate([V, A, B]), np.concatenate([F, [[base, base + 1, base + 2], [base + 3, base + 4, base + 5]]]))
+    g = _weights(GRID.size)
+    D = wn.wn_backward(Vt, Ft, g, grid=GRID).cpu().numpy().astype(np.float64)
+    T = wn.wn_backward(Vt, Ft, g, grid=GRID, want_dLdT=True)[1][-1].cpu().numpy().astype(np.float64)
+    _, Dr = orc.grad(B.astype(np.float64), np.arange(3)[None], _centres(GRID).astype(np.float64),
+                     g.cpu().numpy().astype(np.float64))
+    far, ref, tol = D[-3:], (Dr if kind == "closed" else T), (1e-5 if kind == "closed" else 2.0 ** -23)
+    print(f"[{kind}] largest {np.abs(D).max():.1e}, far {np.abs(ref).max():.1e}, off by {np.abs(far - ref).max():.1e}", flush=True)
+    assert 0 < np.abs(ref).max() < 1e-13 * np.abs(D).max()
+    assert np.abs(far - ref).max() <= tol * np.abs(ref).max()
