@@ -227,7 +227,8 @@ WN_API wn_status wn_backward(const float *V, int64_t nV, const int32_t *F, int64
  *          (also without pairs).  On a grid of at least 2e7 (point, face) pairs dL/dV
  *          is then the sum over the mesh's boundary edges, where the mesh suits and the
  *          workspace has the room that wn_workspace_size asks for: inner edges cancel,
- *          a closed mesh has no gradient;
+ *          a closed mesh has no gradient, and of a boundary edge through q that edge's
+ *          own term is 0, not its whole face's;
  *   ws:    wn_workspace_size(WN_OP_BACKWARD, nV, nF, nQ) bytes, holding the running sums.
  * A range of at least S tiles keeps every split busy (about nF / 256 x S workgroups).
  * Argument errors return WN_ERR_INVALID_ARG before any launch.

@@ -75,9 +75,10 @@ struct Block {
     }
 };
 
-__device__ __forceinline__ void block_origin(const CycMesh &m, int64_t b, int (&i0)[3]) {
+template <typename Int>
+__device__ __forceinline__ void block_origin(const CycMesh &m, Int b, int (&i0)[3]) {
     const int yz = m.grid.n[1] * m.grid.n[2];
-    const int bx = (int)(b / yz), r = (int)(b - (int64_t)bx * yz), by = r / m.grid.n[2];
+    const int bx = (int)(b / yz), r = (int)(b - (Int)bx * yz), by = r / m.grid.n[2];
     i0[0] = (m.xb0 + bx) * m.grid.size[0];
     i0[1] = by * m.grid.size[1];
     i0[2] = (r - by * m.grid.n[2]) * m.grid.size[2];

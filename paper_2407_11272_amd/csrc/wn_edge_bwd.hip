@@ -12,11 +12,11 @@
 // that it vanishes).
 //
 // One lane owns an edge and keeps six sums, sum(g J P) for either end: A x E = P x E with P the
-// part of A at right angles to E, so the cross product waits until the sums are complete.  Points come
+// part of A at right angles to E and J the rest, so the cross product waits until the sums are complete.  Points come
 // through LDS, 256 to a tile, tiles dealt to S splits in turn, as in the all-pairs adjoint (the same
 // calls on point ranges give the same bits as one call).
 //
-// The all-pairs adjoint is bound by its arithmetic over all faces; here the arithmetic of 42 VALU
+// The all-pairs adjoint is bound by its arithmetic over all faces; here the arithmetic of 40 VALU
 // instructions and 3 transcendentals per (edge, point) bounds the point kernel.  Measured, whole
 // adjoint: 7706 faces with 1154 boundary edges on 96 x 88 x 97 points, 10.0 -> 1.08 ms point by point,
 // 0.73 ms with nodes (k_edge_blocks); 9140 faces, 2.6 % of them missing, on 43 x 32 x 17 points, 519 -> 118 us.  The error
@@ -41,43 +41,134 @@ __device__ __forceinline__ int edge_splits(int B, int tiles) {
     return max(1, (tiles + per - 1) / max(1, per));
 }
 
-// A boundary edge from u to v, and its sums over points.
+// A boundary edge from u to v, and its sums over points, in units of about its length: lengths
+// are multiplied by `s`, a power of two that brings |E| to [1, 2).  A coordinate times s is exact, so
+// u - q in these units is one multiply-add, and no product depends on the mesh's scale.  (An edge
+// shorter than 2^-30 of the distances to the points is taken in units of that, or the squares of
+// the distances would leave FP32's range.)
 struct Edge {
-    float ux, uy, uz, Ex, Ey, Ez, L2, L, tiny, Fx, Fy, Fz;
+    float s, u[3], v[3], E[3], f[3], l, L2;  // f = E / |E|^2, l = |E|; L2 = |E|^2 in the mesh's units
 
     __device__ __forceinline__ Edge(const CycMesh &m, const int2 id) {
         const float *pu = m.V + 3 * (int64_t)id.x, *pv = m.V + 3 * (int64_t)id.y;
-        ux = pu[0], uy = pu[1], uz = pu[2];
-        const double ex = (double)pv[0] - ux, ey = (double)pv[1] - uy, ez = (double)pv[2] - uz;
-        const double l2 = ex * ex + ey * ey + ez * ez, inv = l2 > 0.0 ? 1.0 / l2 : 0.0;
-        Ex = (float)ex, Ey = (float)ey, Ez = (float)ez, L2 = (float)l2, L = (float)sqrt(l2);
-        tiny = (float)(1.0e-24 * l2 * l2);
-        Fx = (float)(ex * inv), Fy = (float)(ey * inv), Fz = (float)(ez * inv);  // E / |E|^2
+        double x[3], l2 = 0.0, far = 0.0;
+        const int n[3] = {m.n0, m.ps.n1, m.ps.n2};
+        for (int d = 0; d < 3; ++d) {
+            x[d] = (double)pv[d] - pu[d];
+            l2 += x[d] * x[d];
+            const double a = (double)m.ps.lo[d] - pu[d];
+            far += fmax(fabs(a), fabs(a + (double)n[d] * m.ps.h[d]));
+        }
+        const double len = sqrt(l2);
+        s = (float)ldexp(1.0, -min(max(ilogb(fmax(len, 0x1p-30 * far)), -100), 100));
+        for (int d = 0; d < 3; ++d) {
+            u[d] = s * pu[d];
+            v[d] = s * pv[d];
+            E[d] = (float)(x[d] * s);
+            f[d] = l2 > 0.0 ? (float)(x[d] / (l2 * s)) : 0.0f;
+        }
+        l = (float)(len * s);
+        L2 = (float)l2;
     }
-    // Adds g J P at the n points (x, y, z, g) for either end.
+    // Its start in the mesh's units, and the square of the distance from which it may be far (wn_blocks.hpp).
+    __device__ __forceinline__ float4 start() const {
+        const float x = 1.0f / s;
+        return make_float4(x * u[0], x * u[1], x * u[2], kFar * kFar * L2);
+    }
+    // What a point adds: k J P for either end (ku, kv the factors of P).
+    struct Term {
+        float p[3], ku, kv;
+    };
+    // A point close to either end or to the edge's line.  |B| and P are formed from the nearer end,
+    // as they vanish with the distance to it.  The term is left out where the point is a vertex, or is on
+    // the edge up to the rounding of P (at most 4 x 2^-24 of the distance to the end that it is formed from:
+    // R, E and P are rounded; what a rounds to is along E).
+    __device__ __forceinline__ Term near_term(const float4 q) const {
+        float a[3], b[3];
+        for (int d = 0; d < 3; ++d) {
+            const float x = d == 0 ? q.x : d == 1 ? q.y : q.z;
+            a[d] = __builtin_fmaf(-x, s, u[d]);
+            b[d] = __builtin_fmaf(-x, s, v[d]);
+        }
+        const bool from_v = dot3(b[0], b[1], b[2], b[0], b[1], b[2]) < dot3(a[0], a[1], a[2], a[0], a[1], a[2]);
+        Term t;
+        for (int d = 0; d < 3; ++d) a[d] = from_v ? b[d] : a[d];
+        const float x = dot3(a[0], a[1], a[2], f[0], f[1], f[2]);
+        for (int d = 0; d < 3; ++d) t.p[d] = __builtin_fmaf(-x, E[d], a[d]);
+        const float d2 = dot3(t.p[0], t.p[1], t.p[2], t.p[0], t.p[1], t.p[2]);
+        const float ul = from_v ? x * l - l : x * l, vl = from_v ? x * l : x * l + l;
+        const float A2 = __builtin_fmaf(ul, ul, d2), B2 = __builtin_fmaf(vl, vl, d2), AB = __builtin_fmaf(ul, vl, d2);
+        const float ia = __builtin_amdgcn_rsqf(A2), ib = __builtin_amdgcn_rsqf(B2);
+        const float mn = (A2 * ia) * (B2 * ib) + __builtin_fabsf(AB);
+        const bool between = AB < 0.0f;
+        const float den = between ? d2 * (l * l) : mn;
+        const bool ok = fminf(fminf(A2, B2), den) >= kFltMin && !(between && d2 <= 0x1p-44f * (from_v ? B2 : A2));
+        const float k = (between ? mn * q.w : q.w) * __builtin_amdgcn_rcpf(den);
+        t.ku = ok ? k * ia : 0.0f;
+        t.kv = ok ? k * ib : 0.0f;
+        return t;
+    }
+    // Any other point's; where `den` comes out below kNear it is near_term's to form.
+    __device__ __forceinline__ Term term(const float4 q, float &den) const {
+        const float x = __builtin_fmaf(-q.x, s, u[0]), y = __builtin_fmaf(-q.y, s, u[1]), z = __builtin_fmaf(-q.z, s, u[2]);
+        const float a = dot3(x, y, z, f[0], f[1], f[2]);  // A = a E + P
+        const float px = __builtin_fmaf(-a, E[0], x), py = __builtin_fmaf(-a, E[1], y), pz = __builtin_fmaf(-a, E[2], z);
+        // (1e-37 keeps the squares of the distances from 0)
+        const float d2 = __builtin_fmaf(pz, pz, __builtin_fmaf(py, py, __builtin_fmaf(px, px, 1.0e-37f)));
+        const float ul = a * l, vl = ul + l;
+        const float A2 = __builtin_fmaf(ul, ul, d2), B2 = __builtin_fmaf(vl, vl, d2), AB = __builtin_fmaf(ul, vl, d2);
+        const float ia = __builtin_amdgcn_rsqf(A2), ib = __builtin_amdgcn_rsqf(B2);
+        const float mn = (A2 * ia) * (B2 * ib) + __builtin_fabsf(AB);
+        // 1 / (|A| |B| + A . B); between the ends, where that cancels, through
+        // (|A| |B|)^2 - (A . B)^2 = |P|^2 |E|^2
+        const bool between = AB < 0.0f;
+        den = between ? d2 * (l * l) : mn;
+        const float k = (between ? mn * q.w : q.w) * __builtin_amdgcn_rcpf(den);
+        return Term{{px, py, pz}, k * ia, k * ib};
+    }
+    // Adds g J P at the n points (x, y, z, g) for either end, four at a time; those up to the next
+    // multiple of four are there, without weight.  A group of eight with a point that is close to the edge of
+    // any lane is added again by near_term, which holds for every point: a minimum per point and a
+    // copy of the sums per group for the others.  (Eight, so that the sums before the group cost few
+    // registers: keeping four terms until the test took 116 instead of 95 and 4 % of a whole adjoint.)
     __device__ __forceinline__ void add(const float4 *pts, int n, float (&su)[3], float (&sv)[3]) const {
-#pragma unroll 4
-        for (int i = 0; i < n; ++i) {
-            const float4 q = pts[i];
-            const float x = ux - q.x, y = uy - q.y, z = uz - q.z;
-            const float a = x * Fx + y * Fy + z * Fz;  // A = a E + P
-            const float px = x - a * Ex, py = y - a * Ey, pz = z - a * Ez;
-            const float d2 = px * px + py * py + pz * pz;
-            const float ul = a * L, vl = ul + L;
-            const float A2 = ul * ul + d2, B2 = vl * vl + d2, AB = ul * vl + d2;
-            // (no point is at a vertex: such a mesh took the all-pairs sum)
-            const float ia = __builtin_amdgcn_rsqf(A2), ib = __builtin_amdgcn_rsqf(B2);
-            const float mn = (A2 * ia) * (B2 * ib) + __builtin_fabsf(AB);
-            // 1 / (|A| |B| + A . B); between the ends, where that cancels, through
-            // (|A| |B|)^2 - (A . B)^2 = |P|^2 |E|^2 (on the edge itself P = 0 and so is the term)
-            const bool between = AB < 0.0f;
-            const float den = between ? __builtin_fmaf(d2, L2, tiny) : mn;
-            const float k = (between ? mn * q.w : q.w) * __builtin_amdgcn_rcpf(den);
-            const float ku = k * ia, kv = k * ib;
-            su[0] += ku * px, su[1] += ku * py, su[2] += ku * pz;
-            sv[0] += kv * px, sv[1] += kv * py, sv[2] += kv * pz;
+        constexpr int kGroup = 8;
+#pragma unroll 1
+        for (int i0 = 0; i0 < n; i0 += kGroup) {
+            const int i1 = min(n, i0 + kGroup);
+            float bu[3], bv[3], least = INFINITY;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) bu[d] = su[d], bv[d] = sv[d];
+#pragma unroll 1
+            for (int i = i0; i < i1; i += 4)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    float den;
+                    const Term t = term(pts[i + j], den);
+                    least = fminf(least, den);
+                    add_term(t, su, sv);
+                }
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(least < kNear) == 0ull, 1)) continue;
+#pragma unroll
+            for (int d = 0; d < 3; ++d) su[d] = bu[d], sv[d] = bv[d];
+#pragma unroll 1
+            for (int i = i0; i < i1; ++i) {
+                const float4 q = pts[i];
+                const Term t = near_term(q);
+                add_term(t, su, sv);
+            }
         }
     }
+    static __device__ __forceinline__ void add_term(const Term &t, float (&su)[3], float (&sv)[3]) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            su[d] = __builtin_fmaf(t.ku, t.p[d], su[d]);
+            sv[d] = __builtin_fmaf(t.kv, t.p[d], sv[d]);
+        }
+    }
+    // Points within 1/128 (and up to 1/64, by direction) of the edge's length of an end, or 1/8 of it of the
+    // edge between them: beyond, |B| is off by at most 3e-5, and 1e-6 from a tenth of the length on.
+    static constexpr float kNear = 0x1p-6f;
 };
 
 // state: float2 (sum, compensation) [S][6][B].  Grid: waves; wave w takes edge block
@@ -145,6 +236,11 @@ __global__ __launch_bounds__(64) void k_edge_bwd(const char *table, int64_t nQ, 
 // field's: they are relative to a gradient here.
 constexpr float kEdgeTight = 0.1f;
 constexpr int kParts = 8;
+
+// A value that is the same in every lane, as a scalar.
+__device__ __forceinline__ float uniform(float x) {
+    return __uint_as_float((unsigned)__builtin_amdgcn_readfirstlane((int)__float_as_uint(x)));
+}
 
 // Node sums of dL/dW, a workgroup per block: [block][coarse, fine].
 __global__ __launch_bounds__(kBlock) void k_edge_nodes(const char *table, const float *__restrict__ dLdW,
@@ -223,7 +319,7 @@ __global__ __launch_bounds__(kBlock) void k_edge_nodes(const char *table, const 
 // nodes and of the voxels each, all coarse nodes in one of them): far edges at the coarse or
 // the fine nodes, near ones at the voxels (lanes without such an edge wait).  With whole blocks
 // the waves that had near edges took 864 us.
-// state: float2 [S][6][B].  42 VALU and 3 transcendentals per (edge, point) bound it: 1154 edges on
+// state: float2 [S][6][B].  40 VALU and 3 transcendentals per (edge, point) bound it: 1154 edges on
 // 96 x 88 x 97 voxels take 621 us, all points one by one 1024.
 __global__ __launch_bounds__(64) void k_edge_blocks(const char *table, const float *__restrict__ dLdW,
                                                     const float *__restrict__ node, int S, float2 *__restrict__ state) {
@@ -238,7 +334,8 @@ __global__ __launch_bounds__(64) void k_edge_blocks(const char *table, const flo
     for (int64_t w = blockIdx.x; w < (int64_t)groups * S; w += gridDim.x) {
         const int split = (int)(w / groups), e = (int)(w - (int64_t)split * groups) * 64 + lane;
         const bool live = e < B;
-        const Edge edge(m, m.edge[live ? e : B - 1]);
+        const int2 id = m.edge[live ? e : B - 1];
+        const Edge edge(m, id);
         float s[6], c[6];
 #pragma unroll
         for (int i = 0; i < 6; ++i) s[i] = c[i] = 0.0f;
@@ -246,8 +343,9 @@ __global__ __launch_bounds__(64) void k_edge_blocks(const char *table, const flo
             const int b = x / kParts, part = x - b * kParts;
             int i0[3];
             block_origin(m, b, i0);
-            const Block box(m, i0);
-            const int kind = live ? box.kind(make_float4(edge.ux, edge.uy, edge.uz, kFar * kFar * edge.L2), kEdgeTight) : 0;
+            Block box(m, i0);
+            for (int d = 0; d < 3; ++d) box.lo[d] = uniform(box.lo[d]);  // (three registers less)
+            const int kind = live ? box.kind(edge.start(), kEdgeTight) : 0;
             const float *at = node + (int64_t)b * (nc + nf);
 #pragma unroll 1
             for (int want = 2; want >= -1; --want) {
@@ -261,17 +359,17 @@ __global__ __launch_bounds__(64) void k_edge_blocks(const char *table, const flo
                     const int here = min(kTile, end - t0);
                     __syncthreads();
 #pragma unroll 1
-                    for (int k = lane; k < here; k += 64) {
-                        const int x = t0 + k, a = x / (side[1] * side[2]), r = x - a * side[1] * side[2];
+                    for (int k = lane; k < (here + 3) / 4 * 4; k += 64) {
+                        const int x = t0 + min(k, here - 1), a = x / (side[1] * side[2]), r = x - a * side[1] * side[2];
                         const int j = r / side[2], l = r - j * side[2];
                         if (want > 0) {
                             pts[k] = make_float4(__builtin_fmaf(node_at(order, g.size[0], a), m.ps.h[0], box.lo[0]),
                                                  __builtin_fmaf(node_at(order, g.size[1], j), m.ps.h[1], box.lo[1]),
                                                  __builtin_fmaf(node_at(order, g.size[2], l), m.ps.h[2], box.lo[2]),
-                                                 at[(want == 2 ? 0 : nc) + x]);
+                                                 k < here ? at[(want == 2 ? 0 : nc) + x] : 0.0f);
                         } else {
                             const int ix = i0[0] + a, iy = i0[1] + j, iz = i0[2] + l;
-                            const bool in = ix < m.n0 && iy < m.ps.n1 && iz < m.ps.n2;
+                            const bool in = k < here && ix < m.n0 && iy < m.ps.n1 && iz < m.ps.n2;
                             // (beyond the grid: a voxel of it, without weight)
                             pts[k] = make_float4(centre(m.ps, 0, min(ix, m.n0 - 1)), centre(m.ps, 1, min(iy, m.ps.n1 - 1)),
                                                  centre(m.ps, 2, min(iz, m.ps.n2 - 1)),
@@ -353,7 +451,8 @@ __global__ __launch_bounds__(kBlock) void k_edge_reduce(const char *table, int64
             const int2 id = m.edge[e];
             const float *pu = m.V + 3 * (int64_t)id.x, *pv = m.V + 3 * (int64_t)id.y;
             const double E[3] = {(double)pv[0] - pu[0], (double)pv[1] - pu[1], (double)pv[2] - pu[2]};
-            const double f = -0.07957747154594767;  // -1 / (4 pi)
+            const float scale = Edge(m, id).s;
+            const double f = -0.07957747154594767 * scale * scale;  // -1 / (4 pi), and P J is in the edge's units
 #pragma unroll
             for (int end = 0; end < 2; ++end) {
                 const double P[3] = {(double)s[3 * end] + c[3 * end], (double)s[3 * end + 1] + c[3 * end + 1],

@@ -230,3 +230,122 @@ def test_small_terms_beside_large_ones(dev, orc, kind):
     print(f"[{kind}] largest {np.abs(D).max():.1e}, far {np.abs(ref).max():.1e}, off by {np.abs(far - ref).max():.1e}", flush=True)
     assert 0 < np.abs(ref).max() < 1e-13 * np.abs(D).max()
     assert np.abs(far - ref).max() <= tol * np.abs(ref).max()
+
+
+def _edge_sums64(V, F, Q, g):
+    """The sum over the boundary edges in FP64, without the terms of points on an edge (P up to 1e-6 of the
+    distance to the nearer end) or so close to an end that FP32 squares of the distance are 0; and the sum of its edges' absolute values."""
+    import torch
+    V, Q, g = (torch.as_tensor(np.asarray(x, np.float64)).cuda() for x in (V, Q, g))
+    e = np.concatenate([F[:, [0, 1]], F[:, [1, 2]], F[:, [2, 0]]]).astype(np.int64)
+    n = int(F.max()) + 1
+    e = torch.as_tensor(e[~np.isin(e[:, 0] * n + e[:, 1], e[:, 1] * n + e[:, 0])]).cuda()
+    out, scale = torch.zeros_like(V), torch.zeros_like(V)
+    for i in range(0, len(e), 8):
+        u, v = V[e[i:i + 8, 0]][:, None], V[e[i:i + 8, 1]][:, None]
+        E, A, B = v - u, u - Q, v - Q
+        L = E.norm(dim=2)
+        a, b, AB = A.norm(dim=2), B.norm(dim=2), (A * B).sum(2)
+        near = torch.where((b < a)[..., None], B, A)
+        P = near - (near * E).sum(2, keepdim=True) / (L ** 2)[..., None] * E
+        on = ((AB < 0) & (P.norm(dim=2) <= 1e-6 * torch.minimum(a, b))) | (torch.minimum(a, b) < 1e-20 * L)
+        den = torch.where(AB < 0, (P * P).sum(2) * L ** 2 / (a * b - AB), a * b + AB)
+        k = torch.where(on, 0.0, g / den)
+        k = torch.nan_to_num(k, nan=0.0)
+        su, sv = ((torch.nan_to_num(k / x, nan=0.0)[..., None] * P).sum(1) for x in (a, b))
+        for end, x in ((0, su), (1, sv)):
+            x = torch.linalg.cross(x, E[:, 0]) / (-4 * np.pi)
+            out.index_add_(0, e[i:i + 8, end], x)
+            scale.index_add_(0, e[i:i + 8, end], x.abs())
+    return out.cpu().numpy(), scale.cpu().numpy()
+
+
+LATTICE = wi.Grid((-0.5 - 1 / 64,) * 3, (0.5 - 1 / 64,) * 3, (32, 32, 32))   # voxel centres at multiples of 1/32
+
+
+@pytest.mark.parametrize("scale", [0, -10, -33, 20])
+def test_rim_through_voxel_centres(dev, scale):
+    """A sheet in a layer of voxel centres, its rim through the middle of each of its edges there: the
+    terms on the rim are left out, at every scale of the mesh (2^scale) alike."""
+    import torch
+    import paper_2407_11272_amd as wn
+    n, h = 25, 1 / 32
+    x = (np.arange(n) - n // 2 + 0.5) * h
+    X, Y = np.meshgrid(x, (np.arange(n) - n // 2) * h, indexing="ij")
+    V = np.stack([X, Y, np.full_like(X, 3 * h)], -1).reshape(-1, 3)
+    a = (np.arange(n - 1)[:, None] * n + np.arange(n - 1)[None]).reshape(-1)
+    F = np.concatenate([np.stack([a, a + n, a + n + 1], -1), np.stack([a, a + n + 1, a + 1], -1)])
+    assert len(F) * LATTICE.size >= 2.0e7
+    f = 2.0 ** scale
+    grid = wi.Grid(tuple(f * np.array(LATTICE.lo)), tuple(f * np.array(LATTICE.hi)), LATTICE.n)
+    g = _weights(grid.size)
+    Vt, Ft = _dev(V * f, F)
+    D = wn.wn_backward(Vt, Ft, g, grid=grid).cpu().numpy().astype(np.float64) * f
+    Dr, _ = _edge_sums64(V, F, _centres(LATTICE), g.cpu().numpy())
+    print(f"[rim 2^{scale}] |d dL/dV| {np.abs(D - Dr).max():.2e} of {np.abs(Dr).max():.2e}", flush=True)
+    assert np.abs(D - Dr).max() <= 1e-5 * np.abs(Dr).max()
+
+
+@pytest.mark.parametrize("n", [(25, 23, 27), (84, 80, 82)])
+@pytest.mark.parametrize("kind", ["holes", "open end"])
+def test_scale_of_the_mesh(dev, kind, n):
+    """Powers of two scale every product exactly, so the gradient's bits do not depend on them."""
+    import torch
+    import paper_2407_11272_amd as wn
+    V, F = _mesh(kind)
+    grid = wi.Grid(GRID.lo, GRID.hi, n)
+    g = _weights(grid.size)
+    Vt, Ft = _dev(V, F)
+    D = wn.wn_backward(Vt, Ft, g, grid=grid)
+    assert D.any()
+    for e in (-33, -10, 20):
+        f = 2.0 ** e
+        gs = wi.Grid(tuple(float(np.float32(x)) * f for x in grid.lo), tuple(float(np.float32(x)) * f for x in grid.hi), n)
+        assert torch.equal(wn.wn_backward(Vt * f, Ft, g, grid=gs) * f, D)
+
+
+def test_edges_within_rounding_of_a_voxel_centre(dev):
+    """Vertices that differ from a voxel centre by less than the rounding of u - q (whose terms grow as
+    1 / distance), and edges through one: FP32 terms, so 1e-4 of a vertex's largest edge (two edges of the
+    thin triangle here cancel to 4e-4 of either at the vertex between them)."""
+    import torch
+    import paper_2407_11272_amd as wn
+    V, F = _mesh("closed")
+    q = np.array([0.125, -0.25, 0.0625])
+    d = np.array([0.36, 0.48, 0.8])
+    extra = np.array([
+        [0.37, 0, 0], [6.1e-17, 0, 0], [0.2, 0.1, 0.3],             # an end
+        [0.25, 0, 0.01], [0.25, 6e-24, 0.3125], [0.1, -0.4, 0.2],   # beside an end
+        q - 5e-5 * d, q + 7e-5 * d, [0.3, 0.3, -0.2],               # through the centre
+        [-0.25, 0.125, 0.124], [-0.25, 0.125, 0.126], [-0.2, 0, 0.1]])   # the centre is the middle of an edge
+    base = len(V)
+    V = np.concatenate([V, extra]).astype(np.float32)
+    F = np.concatenate([F, base + np.arange(12).reshape(4, 3)])
+    g = _weights(LATTICE.size)
+    Vt, Ft = _dev(V, F)
+    D = wn.wn_backward(Vt, Ft, g, grid=LATTICE).cpu().numpy().astype(np.float64)
+    Dr, terms = _edge_sums64(V, F, _centres(LATTICE), g.cpu().numpy())
+    assert np.isfinite(D).all() and not D[:base].any()
+    rel = np.abs(D - Dr)[base:].max(1) / terms[base:].max(1)
+    print("[near a centre] relative differences", " ".join(f"{x:.1e}" for x in rel), flush=True)
+    assert rel.max() <= 1e-4
+
+
+@pytest.mark.parametrize("distance", [1e-2, 1e-4, 1e-6])
+def test_a_voxel_close_to_a_vertex(dev, distance):
+    """The gradient that one voxel sends to a triangle whose vertex is `distance` of its edges away: R and
+    P are formed from that vertex, so they keep their digits (2^-24 each, some ten of them)."""
+    import torch
+    import paper_2407_11272_amd as wn
+    V, F = _mesh("closed")
+    base = len(V)
+    off = distance * 0.25 * np.array([0.48, -0.6, 0.64])
+    V = np.concatenate([V, [np.array([0, 0.03125, 0]) + off, [0.21, 0.13, 0.05], [-0.11, 0.19, 0.12]]]).astype(np.float32)
+    Vt, Ft = _dev(V, np.concatenate([F, [[base, base + 1, base + 2]]]))
+    g = torch.zeros(LATTICE.n, device="cuda")
+    g[16, 17, 16] = 1.0     # the centre (0, 1/32, 0)
+    D = wn.wn_backward(Vt, Ft, g.reshape(-1), grid=LATTICE).cpu().numpy().astype(np.float64)
+    Dr, _ = _edge_sums64(V, base + np.arange(3)[None], _centres(LATTICE), g.cpu().numpy().reshape(-1))
+    rel = np.abs(D - Dr)[base:].max(1) / np.abs(Dr)[base:].max(1)
+    print(f"[{distance:g} of an edge away] relative differences", " ".join(f"{x:.1e}" for x in rel), flush=True)
+    assert rel.max() <= 1e-5
