@@ -27,7 +27,7 @@ namespace wn {
 namespace {
 
 constexpr int kChainLimit = 1024;   // half-edges looked at per chain before giving up
-constexpr int kDegreeLimit = 1024;  // boundary edges looked at per vertex
+constexpr int kDegreeLimit = 1024;  // boundary edges looked at per vertex; fewer for long boundaries (degree_limit)
 constexpr float kCoordMax = 1.0e9f; // coordinates beyond this (or not finite) go direct
 
 __device__ __forceinline__ const CycMesh *meshes_of(const char *table) {
@@ -539,6 +539,12 @@ __device__ __forceinline__ unsigned long long block_scan(unsigned long long x, u
 // Place of a loop's vertex r (of k) in its zigzag strip p0, p1, p(k-1), p2, p(k-2), ...
 __device__ __forceinline__ int zigzag(int r, int k) { return r == 0 ? 0 : (r <= k / 2 ? 2 * r - 1 : 2 * (k - r)); }
 
+// Boundary edges that an edge looks at before the mesh goes direct: with B edges on one workgroup, at most
+// 2^25 / 1024 dependent loads per thread and search.
+__device__ __forceinline__ int degree_limit(int B) { return min(kDegreeLimit, max(16, (1 << 25) / B)); }
+
+constexpr int kWalk = 32;  // edges of a loop that each of its edges walks; longer loops are doubled
+
 // Loops by kind: triangles, other short loops, long loops; three counts of 21 bits.
 __device__ __forceinline__ int loop_kind(int k) { return k == 3 ? 0 : k <= kCycShortLoop ? 1 : 2; }
 __device__ __forceinline__ int count_of(unsigned long long x, int kind) { return (int)(x >> (21 * kind)) & 0x1fffff; }
@@ -621,6 +627,7 @@ __global__ __launch_bounds__(kCapThreads) void k_cyc_caps(const char *table) {
                 into[i] = m.hin[e.y];
             }
             __syncthreads();
+            const int limit = degree_limit(B);
             // the lowest triangle (by its edges in increasing order) that edge i is part of
             auto triangle = [&](int i, int &to) -> unsigned long long {
                 const int2 e = edge[i];
@@ -628,7 +635,7 @@ __global__ __launch_bounds__(kCapThreads) void k_cyc_caps(const char *table) {
                 int steps = 0;
                 for (int j = succ[i]; j >= 0; j = nout[j])
                     for (int k = succ[j]; k >= 0; k = nout[k]) {
-                        if (++steps > kDegreeLimit) {
+                        if (++steps > limit) {
                             s_bad = 1;
                             return best;
                         }
@@ -643,6 +650,7 @@ __global__ __launch_bounds__(kCapThreads) void k_cyc_caps(const char *table) {
                 return best;
             };
             for (int i = tid; i < B; i += kCapThreads) {
+                if (*(volatile int32_t *)&s_bad) break;
                 int j = -1, k = -1, x = -1;
                 const unsigned long long id = triangle(i, j);
                 // a loop if its other two edges choose it as well
@@ -652,11 +660,11 @@ __global__ __launch_bounds__(kCapThreads) void k_cyc_caps(const char *table) {
             __syncthreads();
             for (int i = tid; i < B; i += kCapThreads) {
                 int ro = 0, ri = 0, steps = 0;
-                for (int k = same[i]; k >= 0 && steps < kDegreeLimit; k = nout[k], ++steps)
+                for (int k = same[i]; k >= 0 && steps < limit; k = nout[k], ++steps)
                     ro += k < i && next[k] < 0;
-                for (int k = into[i]; k >= 0 && steps < kDegreeLimit; k = nin[k], ++steps)
+                for (int k = into[i]; k >= 0 && steps < limit; k = nin[k], ++steps)
                     ri += k < i && next[k] < 0;
-                if (steps >= kDegreeLimit) s_bad = 1;
+                if (steps >= limit) s_bad = 1;
                 rank[i] = ro | (ri << 16);
             }
             __syncthreads();
@@ -666,7 +674,7 @@ __global__ __launch_bounds__(kCapThreads) void k_cyc_caps(const char *table) {
                 if (to < 0) {
                     const int want = rank[i] >> 16;
                     int steps = 0;
-                    for (int k = succ[i]; k >= 0 && steps < kDegreeLimit; k = nout[k], ++steps)
+                    for (int k = succ[i]; k >= 0 && steps < limit; k = nout[k], ++steps)
                         if (next[k] < 0 && (rank[k] & 0xffff) == want) to = k;
                     if (to < 0) s_bad = 1;
                 }
@@ -676,24 +684,88 @@ __global__ __launch_bounds__(kCapThreads) void k_cyc_caps(const char *table) {
             for (int i = tid; i < B; i += kCapThreads) next[i] = len[i];
             __syncthreads();
             if (s_bad) return -1;
-            // a loop's length at its lowest edge, 0 at the others
-            int32_t *off = rank;
+            // each edge's loop (its lowest edge) and place in it, counted from there; the loop's length at its
+            // lowest edge
+            int32_t *lead = into, *place = nin, *size = nout;
+            bool any_long = false;
             for (int i = tid; i < B; i += kCapThreads) {
-                int n = 1;
-                for (int j = next[i]; j != i; j = next[j]) {
-                    if (j < i || n >= B) {
-                        n = 0;
-                        break;
+                int n = 1, lo = i, at = 0, j = next[i];
+                for (; j != i && n < kWalk; j = next[j], ++n)
+                    if (j < lo) {
+                        lo = j;
+                        at = n;
                     }
-                    ++n;
-                }
-                len[i] = n;
+                const bool closed = j == i;
+                any_long = any_long || !closed;
+                lead[i] = lo;
+                place[i] = closed ? (at == 0 ? 0 : n - at) : -1;
+                size[i] = n;
             }
-            __syncthreads();
+            // Long loops by doubling: log2 of the length rounds over their edges (each edge walking to a
+            // lower one was quadratic, 1.2e6 dependent loads for a ribbon of 1e5 faces).
+            if (__syncthreads_or(any_long)) {
+                // x[0] the edge 2^k further on and x[1] the lowest edge before that.  Where a round
+                // changes no minimum, each is its loop's: it is the same after 2^k steps, and so after
+                // gcd(2^k, length), and the 2^k edges that it covers come to every such rest.
+                int32_t *x[2] = {succ, same}, *y[2] = {rank, size};
+                auto rounds = [&](auto step) {
+                    for (int k = 0; k < 21; ++k) {
+                        bool more = false;
+                        for (int i = tid; i < B; i += kCapThreads)
+                            if (place[i] < 0) more = step(i) || more;
+                        more = __syncthreads_or(more);
+                        for (int d = 0; d < 2; ++d) {
+                            int32_t *const z = x[d];
+                            x[d] = y[d];
+                            y[d] = z;
+                        }
+                        if (!more) break;
+                    }
+                };
+                for (int i = tid; i < B; i += kCapThreads)
+                    if (place[i] < 0) {
+                        x[0][i] = next[i];
+                        x[1][i] = i;
+                    }
+                __syncthreads();
+                rounds([&](int i) {
+                    const int j = x[0][i], a = x[1][i], b = x[1][j];
+                    y[0][i] = x[0][j];
+                    y[1][i] = min(a, b);
+                    return b < a;
+                });
+                for (int i = tid; i < B; i += kCapThreads)
+                    if (place[i] < 0) lead[i] = x[1][i];
+                __syncthreads();
+                // x[0] an edge further on, the last of the loop in the end, and x[1] the steps to it
+                for (int i = tid; i < B; i += kCapThreads)
+                    if (place[i] < 0) {
+                        const bool end = next[i] == lead[i];
+                        x[0][i] = end ? i : next[i];
+                        x[1][i] = !end;
+                    }
+                __syncthreads();
+                rounds([&](int i) {
+                    const int j = x[0][i], to = x[0][j];
+                    y[0][i] = to;
+                    y[1][i] = x[1][i] + x[1][j];
+                    return to != j;
+                });
+                for (int i = tid; i < B; i += kCapThreads)
+                    if (place[i] < 0) next[i] = x[1][lead[i]] - x[1][i];
+                __syncthreads();
+                for (int i = tid; i < B; i += kCapThreads)
+                    if (place[i] < 0) {
+                        if (lead[i] == i) size[i] = x[1][i] + 1;
+                        place[i] = next[i];
+                    }
+                __syncthreads();
+            }
+            int32_t *off = rank;
             unsigned long long done = 0;  // records of each kind
             for (int i0 = 0; i0 < B; i0 += kCapThreads) {
                 const int i = i0 + tid;
-                const int n = i < B ? len[i] : 0, kind = loop_kind(n);
+                const int n = i < B && lead[i] == i ? size[i] : 0, kind = loop_kind(n);
                 unsigned long long all;
                 const unsigned long long at = done + block_scan((unsigned long long)n << (21 * kind), red, all);
                 if (n) off[i] = count_of(at, kind);
@@ -701,17 +773,11 @@ __global__ __launch_bounds__(kCapThreads) void k_cyc_caps(const char *table) {
             }
             const int first[3] = {0, count_of(done, 0), count_of(done, 0) + count_of(done, 1)};
             if (first[2] + count_of(done, 2) != B) return -1;  // not a permutation (cannot be)
+            __syncthreads();
             for (int i = tid; i < B; i += kCapThreads) {
-                const int k = len[i];
-                if (k == 0) continue;
-                const int at = off[i] + first[loop_kind(k)];
-                int j = i;
-                for (int r = 0; r < k; ++r) {
-                    const int pos = zigzag(r, k);
-                    m.cvid[at + pos] = edge[j].x;
-                    m.cpos[at + pos] = pos;
-                    j = next[j];
-                }
+                const int k = size[lead[i]], pos = zigzag(place[i], k), at = off[lead[i]] + first[loop_kind(k)] + pos;
+                m.cvid[at] = edge[i].x;
+                m.cpos[at] = pos;
             }
             n_tri = first[1] / 3;
             n_short = first[2];

@@ -1,0 +1,97 @@
+"""Boundaries that are long loops (ribbons, tubes, sheets): the forward joins them by walking short
+loops and by doubling long ones, in LDS up to 4096 edges and in global memory beyond.
+
+Against the FP64 oracle, |dW| <= 1e-4 off the guard band as for every forward; a face order does not
+change the loops, only where they start, so shuffled faces are held to the same."""
+import numpy as np
+import pytest
+
+import wn_inputs as wi
+from .test_gpu_cycle import _centres, _dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dev():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_2407_11272_amd as wn
+    wn.wn_version()
+    return torch.device("cuda", 0)
+
+
+def ribbon(n, w):
+    """n quads along a winding band, w across: one loop of 2 (n + w) edges, faces in order along it."""
+    t, y = np.meshgrid(np.linspace(0, 1, n + 1), np.linspace(-1, 1, w + 1), indexing="ij")
+    a, r = 11 * np.pi * t, 0.12 + 0.3 * t
+    V = np.stack([r * np.cos(a), r * np.sin(a), 0.07 * y + 0.05 * np.sin(3 * a)], -1).reshape(-1, 3)
+    a = (np.arange(n)[:, None] * (w + 1) + np.arange(w)[None]).reshape(-1)
+    b = a + w + 1
+    return V, np.stack([np.stack([a, b, b + 1], -1), np.stack([a, b + 1, a + 1], -1)], 1).reshape(-1, 3)
+
+
+def tubes(lengths, h=6):
+    """Open tubes side by side with loops of the given lengths at both ends, and the other way round inside
+    one another in pairs."""
+    V, F, base = [], [], 0
+    for i, n in enumerate(lengths):
+        a = 2 * np.pi * np.arange(n) / n
+        for k in range(h + 1):
+            V.append(np.stack([0.04 * np.cos(a) + 0.11 * (i % 8) - 0.39, 0.04 * np.sin(a) + 0.21 * (i // 8) - 0.3,
+                               np.full(n, -0.4 + 0.7 * k / h)], -1))
+        p = (np.arange(h)[:, None] * n + np.arange(n)[None]).reshape(-1)
+        q = (np.arange(h)[:, None] * n + (np.arange(n)[None] + 1) % n).reshape(-1)
+        f = np.concatenate([np.stack([p, q, q + n], -1), np.stack([p, q + n, p + n], -1)]) + base
+        F.append(f if i % 2 == 0 else f[:, ::-1])
+        base += (h + 1) * n
+    return np.concatenate(V), np.concatenate(F)
+
+
+MESHES = {"ribbon of 3004 edges": lambda: ribbon(1500, 2), "ribbon of 12004 edges": lambda: ribbon(6000, 2),
+          "tubes, 3 to 8": lambda: tubes([3, 4, 5, 6, 7, 8] * 4),
+          "tubes about the walk's length": lambda: tubes([31, 32, 33, 34, 63, 64, 65, 66, 7, 100]),
+          "tubes, more edges than LDS holds": lambda: tubes([5, 33, 900, 3, 700, 64, 1025, 6])}
+
+
+@pytest.mark.parametrize("shuffled", [False, True])
+@pytest.mark.parametrize("kind", list(MESHES))
+def test_long_loops(dev, orc, kind, shuffled):
+    import paper_2407_11272_amd as wn
+    V, F = MESHES[kind]()
+    if shuffled:
+        F = F[np.random.default_rng(4).permutation(len(F))]
+    n = max(16, int(np.ceil((3.2e7 / len(F)) ** (1 / 3))))
+    grid = wi.Grid((-0.5, -0.48, -0.5), (0.5, 0.52, 0.47), (n, n + 1, n + 2))
+    assert len(F) * grid.size >= 3.0e7
+    Vt, Ft = _dev(V, F)
+    W = wn.wn_voxelize(Vt, Ft, grid=grid).cpu().numpy().reshape(-1)
+    Q = _centres(grid).astype(np.float64)
+    pick = np.random.default_rng(5).choice(grid.size, min(grid.size, 3000), replace=False)
+    V64 = np.asarray(V, np.float32).astype(np.float64)
+    Wr = orc.winding(V64, F, Q[pick])
+    guard = orc.guard_mask(V64, F, Q[pick])
+    err = np.abs(W[pick] - Wr)[~guard]
+    print(f"[{kind}] {len(F)} faces, max |dW| {err.max():.2e}", flush=True)
+    assert err.max() <= 1e-4
+
+
+def test_an_ordered_ribbon_of_1e5_faces_takes_milliseconds(dev):
+    """50 004 boundary edges in one loop, numbered along it: about 34 rounds of 49 edges per thread.  Walks
+    to the next lower edge were 1.2e6 loads in a row, 0.4 s at 300 ns each; the bar is a quarter of that."""
+    import time
+    import torch
+    import paper_2407_11272_amd as wn
+    V, F = ribbon(25000, 2)
+    Vt, Ft = _dev(V, F)
+    grid = wn.Grid((-0.5,) * 3, (0.5,) * 3, (8, 8, 5))
+    assert len(F) * grid.size >= 3.0e7
+    wn.wn_voxelize(Vt, Ft, grid=grid)
+    torch.cuda.synchronize()
+    t = time.perf_counter()
+    wn.wn_voxelize(Vt, Ft, grid=grid)
+    torch.cuda.synchronize()
+    t = time.perf_counter() - t
+    print(f"{1e3 * t:.2f} ms", flush=True)
+    assert t < 0.1
