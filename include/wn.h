@@ -51,7 +51,8 @@
  *    so the occupancy mode can change W by that sum's rounding at such points.  Meshes
  *    that do not suit take the sum over all faces at every point: coordinates that are not
  *    finite or above 1e9, more boundary edges than faces or than 2^20, edges whose uses do
- *    not leave one, a strip order that does not name each face once.
+ *    not leave one, a boundary whose caps would take longer than the faces (mostly one long
+ *    loop), a strip order that does not name each face once.
  */
 #ifndef WN_H
 #define WN_H

@@ -543,6 +543,59 @@ __device__ __forceinline__ int zigzag(int r, int k) { return r == 0 ? 0 : (r <= 
 // 2^25 / 1024 dependent loads per thread and search.
 __device__ __forceinline__ int degree_limit(int B) { return min(kDegreeLimit, max(16, (1 << 25) / B)); }
 
+// What the path and the all-pairs sum take, in units of 0.01 ps per voxel, measured on open sheets, ribbons, fans
+// and patches: a face of the all-pairs sum without and with a strip order; a cap record summed one by one, of a
+// triangle, of another short loop, of a long one (in FP64); in blocks one that is far (as those of short loops
+// mostly are), and what one of a long loop adds where it is close (a workgroup takes it for 1024 voxels, so few
+// workgroups leave the chip idle); and joining, per edge and call.  Where the caps cost more the mesh goes
+// direct: a fan of 5000 faces (5000 edges in one loop) on 64^3 takes 3.37 ms by its boundary and 1.63 by its
+// faces, a ribbon of 10000 faces two quads wide 5.7 and 3.1; the ribbon on 128^3 13.0 and 25, 1000 patches of
+// eight faces on 64^3 1.7 and 2.5.
+constexpr double kFaceCost = 122.0, kStripCost = 88.0, kJoinCost = 3.0e6;
+constexpr int kTriCost = 70, kShortCost = 110, kLongCost = 260, kFarCost = 4, kCloseCost = 380;
+constexpr int kBusyBlocks = 1024;
+
+__device__ __forceinline__ int64_t all_points(const CycMesh &m) {
+    return m.bins ? m.P : (int64_t)m.n0 * m.ps.n1 * m.ps.n2;  // (of a slice its grid's, so that slices decide alike)
+}
+
+// Whether caps of this cost per voxel, over B edges, make the all-pairs sum the cheaper one.
+__device__ __forceinline__ bool caps_cost_more(const CycMesh &m, int64_t B, double cost) {
+    const double P = (double)all_points(m);
+    return P * cost + kJoinCost * (double)B > P * (double)m.nF * (m.strips ? kStripCost : kFaceCost);
+}
+
+// What a triangle of a long loop adds in blocks: close to it are the voxels within twice its edges (and a quarter of a
+// block) of its first vertex.
+struct CloseCost {
+    float lo[3], hi[3], a, scale;  // the grid's box; a quarter of a block; the cost of a triangle close to all, over its volume
+
+    __device__ __forceinline__ explicit CloseCost(const CycMesh &m) {
+        const CycBlocks &g = m.grid;
+        const int n[3] = {m.n0, m.ps.n1, m.ps.n2};
+        const int units = g.n[0] * g.n[1] * g.n[2] * ((g.size[0] + kBlockRows - 1) / kBlockRows);
+        a = 0.0f;
+        scale = (float)kCloseCost * fmaxf((float)kBusyBlocks / (float)units, 1.0f);
+        for (int d = 0; d < 3; ++d) {
+            const float w = (float)n[d] * m.ps.h[d];
+            lo[d] = m.ps.lo[d];
+            hi[d] = lo[d] + w;
+            scale /= w;
+            a = fmaxf(a, 0.25f * (float)g.size[d] * m.ps.h[d]);
+        }
+    }
+    __device__ __forceinline__ int operator()(const float (&p)[3][3]) const {
+        float e2 = 0.0f, x = scale;
+        for (int k = 1; k < 3; ++k) {
+            const float dx = p[k][0] - p[0][0], dy = p[k][1] - p[0][1], dz = p[k][2] - p[0][2];
+            e2 = fmaxf(e2, dx * dx + dy * dy + dz * dz);
+        }
+        const float r = 2.0f * fast_sqrt(e2) + a;
+        for (int d = 0; d < 3; ++d) x *= fmaxf(fminf(p[0][d] + r, hi[d]) - fmaxf(p[0][d] - r, lo[d]), 0.0f);
+        return (int)x;
+    }
+};
+
 constexpr int kWalk = 32;  // edges of a loop that each of its edges walks; longer loops are doubled
 
 // Loops by kind: triangles, other short loops, long loops; three counts of 21 bits.
@@ -579,8 +632,9 @@ __global__ __launch_bounds__(kCapThreads) void k_cyc_caps(const char *table) {
             B64 += all;
         }
         const bool range = m.st->max_bits > __float_as_uint(kCoordMax);  // NaN bits are larger still
-        if (m.st->go || range || (int64_t)B64 > m.nF ||
-            (int64_t)B64 > kCycMaxEdges) {
+        const int least = m.grid.order ? kFarCost : kTriCost;
+        if (m.st->go || range || (int64_t)B64 > m.nF || (int64_t)B64 > kCycMaxEdges ||
+            (m.W && caps_cost_more(m, (int64_t)B64, (double)B64 * least))) {
             if (tid == 0) atomicMax(&m.st->go, 2);
             continue;
         }
@@ -688,6 +742,7 @@ __global__ __launch_bounds__(kCapThreads) void k_cyc_caps(const char *table) {
             // lowest edge
             int32_t *lead = into, *place = nin, *size = nout;
             bool any_long = false;
+            unsigned long long kinds = 0;  // edges of each kind of loop
             for (int i = tid; i < B; i += kCapThreads) {
                 int n = 1, lo = i, at = 0, j = next[i];
                 for (; j != i && n < kWalk; j = next[j], ++n)
@@ -697,9 +752,16 @@ __global__ __launch_bounds__(kCapThreads) void k_cyc_caps(const char *table) {
                     }
                 const bool closed = j == i;
                 any_long = any_long || !closed;
+                kinds += 1ull << (21 * loop_kind(n));
                 lead[i] = lo;
                 place[i] = closed ? (at == 0 ? 0 : n - at) : -1;
                 size[i] = n;
+            }
+            if (!m.grid.order) {
+                block_scan(kinds, red, kinds);
+                if (caps_cost_more(m, B, (double)count_of(kinds, 0) * kTriCost + (double)count_of(kinds, 1) * kShortCost +
+                                             (double)count_of(kinds, 2) * kLongCost))
+                    return -1;
             }
             // Long loops by doubling: log2 of the length rounds over their edges (each edge walking to a
             // lower one was quadratic, 1.2e6 dependent loads for a ribbon of 1e5 faces).
@@ -792,10 +854,19 @@ __global__ __launch_bounds__(kCapThreads) void k_cyc_caps(const char *table) {
         }
         __syncthreads();
         // triangles over many columns go on the raster list; k_cyc_slabs takes the others one by one
+        unsigned long long cost = 0;
+        const float *V = m.V;
+        int32_t *cvid = m.cvid, *cpos = m.cpos;
+        const bool blocks = m.grid.order != 0 && n_short < B;
+        const CloseCost close(m);
         for (int x = tid; x < B; x += kCapThreads) {
-            if (m.cpos[x] < 2) continue;
-            const float *p[3] = {m.V + 3 * (int64_t)m.cvid[x - 2], m.V + 3 * (int64_t)m.cvid[x - 1],
-                                 m.V + 3 * (int64_t)m.cvid[x]};
+            if (cpos[x] < 2) continue;
+            float p[3][3];
+            for (int k = 0; k < 3; ++k) {
+                const int64_t v = 3 * (int64_t)cvid[x - 2 + k];
+                for (int d = 0; d < 3; ++d) p[k][d] = V[v + d];
+            }
+            if (blocks && x >= n_short) cost += close(p);
             double area = 1.0;
             for (int d = 0; d < 2; ++d) {
                 const float l = fminf(fminf(p[0][d], p[1][d]), p[2][d]), u = fmaxf(fmaxf(p[0][d], p[1][d]), p[2][d]);
@@ -803,11 +874,14 @@ __global__ __launch_bounds__(kCapThreads) void k_cyc_caps(const char *table) {
             }
             if (area > (double)kWaveColumns) {
                 RasterFace f;
-                if (set_cap(m, x, f) && add_slabs(m, (int32_t)(m.nF + x), f.columns())) m.cpos[x] |= kCapListed;
+                if (set_cap(m, x, f) && add_slabs(m, (int32_t)(m.nF + x), f.columns())) cpos[x] |= kCapListed;
             }
         }
+        if (blocks) block_scan(cost, red, cost);
         __syncthreads();
-        if (tid == 0) {
+        if (blocks && caps_cost_more(m, B, (double)cost + (double)B * kFarCost)) {
+            if (tid == 0) atomicMax(&m.st->go, 2);
+        } else if (tid == 0) {
             m.st->n_rec = B;
             m.st->n_tri = n_tri;
             m.st->n_short = n_short;

@@ -49,7 +49,7 @@ def tubes(lengths, h=6):
     return np.concatenate(V), np.concatenate(F)
 
 
-MESHES = {"ribbon of 3004 edges": lambda: ribbon(1500, 2), "ribbon of 12004 edges": lambda: ribbon(6000, 2),
+MESHES = {"ribbon of 3016 edges": lambda: ribbon(1500, 8), "ribbon of 12016 edges": lambda: ribbon(6000, 8),
           "tubes, 3 to 8": lambda: tubes([3, 4, 5, 6, 7, 8] * 4),
           "tubes about the walk's length": lambda: tubes([31, 32, 33, 34, 63, 64, 65, 66, 7, 100]),
           "tubes, more edges than LDS holds": lambda: tubes([5, 33, 900, 3, 700, 64, 1025, 6])}
@@ -58,15 +58,17 @@ MESHES = {"ribbon of 3004 edges": lambda: ribbon(1500, 2), "ribbon of 12004 edge
 @pytest.mark.parametrize("shuffled", [False, True])
 @pytest.mark.parametrize("kind", list(MESHES))
 def test_long_loops(dev, orc, kind, shuffled):
+    import torch
     import paper_2407_11272_amd as wn
     V, F = MESHES[kind]()
     if shuffled:
         F = F[np.random.default_rng(4).permutation(len(F))]
-    n = max(16, int(np.ceil((3.2e7 / len(F)) ** (1 / 3))))
-    grid = wi.Grid((-0.5, -0.48, -0.5), (0.5, 0.52, 0.47), (n, n + 1, n + 2))
+    grid = wi.Grid((-0.5, -0.48, -0.5), (0.5, 0.52, 0.47), (40, 41, 42))
     assert len(F) * grid.size >= 3.0e7
     Vt, Ft = _dev(V, F)
-    W = wn.wn_voxelize(Vt, Ft, grid=grid).cpu().numpy().reshape(-1)
+    W = wn.wn_voxelize(Vt, Ft, grid=grid)
+    assert not torch.equal(W, all_pairs(Vt, Ft, wn.Grid.of(grid)))  # (the path was taken)
+    W = W.cpu().numpy().reshape(-1)
     Q = _centres(grid).astype(np.float64)
     pick = np.random.default_rng(5).choice(grid.size, min(grid.size, 3000), replace=False)
     V64 = np.asarray(V, np.float32).astype(np.float64)
@@ -77,17 +79,17 @@ def test_long_loops(dev, orc, kind, shuffled):
     assert err.max() <= 1e-4
 
 
-def test_an_ordered_ribbon_of_1e5_faces_takes_milliseconds(dev):
-    """50 004 boundary edges in one loop, numbered along it: about 34 rounds of 49 edges per thread.  Walks
-    to the next lower edge were 1.2e6 loads in a row, 0.4 s at 300 ns each; the bar is a quarter of that."""
+def test_an_ordered_ribbon_takes_milliseconds(dev):
+    """5e5 faces and 50 020 boundary edges in one loop, numbered along it: about 34 rounds of 49 edges per
+    thread.  Walks to the next lower edge were 1.2e6 loads in a row, 0.4 s at 300 ns each; the bar is a
+    quarter of that."""
     import time
     import torch
     import paper_2407_11272_amd as wn
-    V, F = ribbon(25000, 2)
+    V, F = ribbon(25000, 10)
     Vt, Ft = _dev(V, F)
-    grid = wn.Grid((-0.5,) * 3, (0.5,) * 3, (8, 8, 5))
-    assert len(F) * grid.size >= 3.0e7
-    wn.wn_voxelize(Vt, Ft, grid=grid)
+    grid = wn.Grid((-0.5,) * 3, (0.5,) * 3, (32, 32, 32))
+    assert not torch.equal(wn.wn_voxelize(Vt, Ft, grid=grid), all_pairs(Vt, Ft, grid))  # (the path was taken)
     torch.cuda.synchronize()
     t = time.perf_counter()
     wn.wn_voxelize(Vt, Ft, grid=grid)
@@ -95,3 +97,45 @@ def test_an_ordered_ribbon_of_1e5_faces_takes_milliseconds(dev):
     t = time.perf_counter() - t
     print(f"{1e3 * t:.2f} ms", flush=True)
     assert t < 0.1
+
+
+def all_pairs(V, F, grid, strips=None, occupancy=0, tau=0.5, k=50.0):
+    """The C entry point with a byte less than the boundary path asks for: the all-pairs kernels alone."""
+    import ctypes
+    import torch
+    import paper_2407_11272_amd as wn
+    from paper_2407_11272_amd import _lib as L
+    lib, p = L.load(), ctypes.c_void_p
+    n = wn.wn_workspace_size(L.WN_OP_VOXELIZE, V.shape[0], F.shape[0], grid.size) - 1
+    ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+    W = torch.empty(tuple(grid.n), device="cuda")
+    occ = torch.empty(tuple(grid.n), dtype=torch.float32 if occupancy == L.WN_OCC_SIGMOID else torch.uint8, device="cuda")
+    R = () if strips is None else (p(strips.data_ptr()), strips.shape[0])
+    st = (lib.wn_voxelize if strips is None else lib.wn_voxelize_strips)(
+        p(V.data_ptr()), V.shape[0], p(F.data_ptr()), F.shape[0], *R, ctypes.byref(grid.to_c()), p(0), 0,
+        p(W.data_ptr()), occupancy, tau, k, p(occ.data_ptr()) if occupancy else p(0), p(ws.data_ptr()), n,
+        p(torch.cuda.current_stream().cuda_stream))
+    assert st == 0
+    torch.cuda.synchronize()
+    return (W, occ) if occupancy else W
+
+
+def fan(n):
+    a = 2 * np.pi * np.arange(n) / n
+    V = np.concatenate([[[0, 0, 0.1]], np.stack([0.4 * np.cos(a), 0.4 * np.sin(a), 0.05 * np.sin(5 * a)], -1)])
+    return V, np.stack([np.zeros(n, int), 1 + np.arange(n), 1 + (np.arange(n) + 1) % n], -1)
+
+
+@pytest.mark.parametrize("mesh,n", [("fan", 40), ("fan", 128), ("ribbon", 32), ("ribbon", 64)])
+def test_caps_that_cost_more_than_the_faces(dev, mesh, n):
+    """As many boundary edges as faces, or half as many in one long loop: the caps would take more than the
+    faces, below the line of the blocks and above, so the mesh goes direct (the all-pairs bits)."""
+    import torch
+    import paper_2407_11272_amd as wn
+    V, F = fan(3000) if mesh == "fan" else ribbon(2500, 2)
+    Vt, Ft = _dev(V, F)
+    grid = wn.Grid((-0.5,) * 3, (0.5,) * 3, (n, n, n + 1))
+    assert len(F) * grid.size >= 7.0e7
+    R = torch.as_tensor(wn.wn_build_strips(np.ascontiguousarray(F), len(V))).cuda()
+    assert torch.equal(wn.wn_voxelize(Vt, Ft, grid=grid), all_pairs(Vt, Ft, grid))
+    assert torch.equal(wn.wn_voxelize_strips(Vt, Ft, R, grid=grid), all_pairs(Vt, Ft, grid, R))
