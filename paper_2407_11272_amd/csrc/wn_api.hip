@@ -164,7 +164,7 @@ wn_status voxelize_impl(const float *V, int64_t nV, const int32_t *F, int64_t nF
     const bool cyc = !all_pairs && extra > 0 && need + extra <= ws_bytes && fits && suits;
     if (!cyc) {
         hipError_t e = launch_pack_records(V, nV, F, nF, R, nR, recs, hdr, s);
-        if (e == hipSuccess) e = launch_fwd(recs, nR, ps, P, split, W, partials, op, cfg.ppl, cfg.depth, nullptr, nullptr, s);
+        if (e == hipSuccess) e = launch_fwd(recs, nR, ps, P, split, W, partials, op, cfg.ppl, cfg.depth, nullptr, nullptr, nullptr, s);
         return hip_status(e);
     }
     char *table = base + need;
@@ -195,7 +195,8 @@ wn_status voxelize_impl(const float *V, int64_t nV, const int32_t *F, int64_t nF
     if (e == hipSuccess && Q) e = launch_cyc_bins(m, table, s);
     if (e == hipSuccess) e = launch_cyc(h, table, false, Q ? 0 : nR, s);
     if (e == hipSuccess)
-        e = launch_fwd(recs, nR, ps, P, split, W, partials, op, cfg.ppl, cfg.depth, m.st, m.mark, s);
+        e = launch_fwd(recs, nR, ps, P, split, W, partials, op, cfg.ppl, cfg.depth, m.st, m.mark,
+                       &reinterpret_cast<CycHead *>(table)->cursor, s);
     if (e == hipSuccess) e = launch_cyc_near(table, s);
     return hip_status(e);
 }

@@ -510,10 +510,10 @@ hipError_t launch_pack(const float *V, int64_t nV, const int32_t *F, int64_t nF,
 // where the stream does not stand for F.
 hipError_t launch_pack_records(const float *V, int64_t nV, const int32_t *F, int64_t nF, const int32_t *R,
                                int64_t nR, VRec *recs, WsHeader *hdr, hipStream_t s);
-// st, mark (optional, device; wn_cycle.hpp): the launch does what the state asks for.
+// st, mark, cursor (optional, device; wn_cycle.hpp): the launch does what the state asks for; the cursor starts at 0.
 hipError_t launch_fwd(const VRec *recs, int64_t nR, const PointSrc &ps, int64_t nQ, int split,
                       float *W, float *partials, const OccParams &occ, int ppl, int depth, const struct CycState *st,
-                      const uint32_t *mark, hipStream_t s);
+                      const uint32_t *mark, unsigned long long *cursor, hipStream_t s);
 // Order-free checksum (sum of the bit patterns) of n floats into hdr->checksum.
 hipError_t launch_checksum(const float *x, int64_t n, WsHeader *hdr, bool reset, hipStream_t s);
 hipError_t launch_occ(const float *W, int64_t n, const OccParams &occ, hipStream_t s);
