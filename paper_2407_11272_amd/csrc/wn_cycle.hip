@@ -266,37 +266,43 @@ struct RasterFace {
     }
 };
 
-// Columns that a face's own lanes take; more are left to the slab list, 64 per entry.
+// Columns that a face's own lanes take; more are left to the raster list, 64 per entry or as many more as the
+// triangle's share of the list asks for: the list has room for a share for each, so it never overflows.
 constexpr int kOwnColumns = 64;
+constexpr int kListShare = 32768;  // entries for the faces beyond one each, and entries for the caps
 
-// Room for the columns on the raster list; false where there is none.  Called by the lanes of a
-// wave together (any of them): one atomic for all, since thousands queue up at its address (the
-// caps of 1364 boundary edges took 58 us with one each, 55 with one per wave).
-__device__ __forceinline__ bool add_slabs(const CycMesh &m, int32_t id, int64_t columns) {
-    const int64_t n = (columns + 63) / 64;
-    const bool fits = n <= m.slab_cap;
+__device__ __forceinline__ int face_share(const CycMesh &m) { return 1 + kListShare / (int)m.nF; }
+
+// Entries of a triangle with so many columns (more than 0), and the columns of each.
+__device__ __forceinline__ int list_entries(int64_t columns, int share) { return (int)min((columns + 63) / 64, (int64_t)share); }
+__device__ __forceinline__ int64_t list_columns(int64_t columns, int share) {
+    const int n = list_entries(columns, share);
+    return (columns + 64 * (int64_t)n - 1) / (64 * n) * 64;
+}
+
+// Puts a triangle on the raster list.  Called by the lanes of a wave together (any of them): one atomic for
+// all, since thousands queue up at its address (the caps of 1364 boundary edges took 58 us with one
+// each, 55 with one per wave).  Returns how many entries of 64 columns were asked for before (the counter's upper
+// half; it may wrap).
+__device__ __forceinline__ unsigned add_slabs(const CycMesh &m, int32_t id, int64_t columns, int share) {
+    const int n = list_entries(columns, share);
+    const int wide = (int)min((columns + 63) / 64, (int64_t)1 << 20);
     const int lane = threadIdx.x & 63;
-    unsigned long long asking = __builtin_amdgcn_ballot_w64(fits && n > 0);
-    if (!asking) return fits;
+    unsigned long long asking = __builtin_amdgcn_ballot_w64(true);
     const int leader = __builtin_ctzll(asking);
-    unsigned long long before = 0, total = 0;
+    unsigned before = 0, total = 0, total_wide = 0;
     for (; asking; asking &= asking - 1ull) {
         const int l = __builtin_ctzll(asking);
-        const unsigned x = (unsigned)__builtin_amdgcn_readlane((int)n, l);
+        const unsigned x = (unsigned)__builtin_amdgcn_readlane(n, l);
         if (l < lane) before += x;
         total += x;
+        total_wide += (unsigned)__builtin_amdgcn_readlane(wide, l);
     }
     unsigned long long at = 0;
-    if (lane == leader) at = atomicAdd(&m.st->n_slab, total);
-    at = ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((int)(at >> 32), leader) << 32 |
-          (unsigned)__builtin_amdgcn_readlane((int)(unsigned)at, leader)) + before;
-    if (!fits || n == 0) return fits;
-    if (at + n > (unsigned long long)m.slab_cap) {
-        for (int64_t k = at; k < m.slab_cap; ++k) m.slab[k] = make_int2(-1, 0);  // what was left of it
-        return false;
-    }
-    for (int32_t k = 0; k < (int32_t)n; ++k) m.slab[at + k] = make_int2(id, k);
-    return true;
+    if (lane == leader) at = atomicAdd(&m.st->n_slab, (unsigned long long)total_wide << 32 | total);
+    const unsigned first = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)at, leader) + before;
+    for (int k = 0; k < n; ++k) m.slab[first + k] = make_int2(id, k);
+    return (unsigned)__builtin_amdgcn_readlane((int)(at >> 32), leader);
 }
 
 // The bucket of an undirected edge (l < u): a multiplicative hash.
@@ -411,16 +417,11 @@ __global__ __launch_bounds__(kCycUnit) void k_cyc_faces(const char *table) {
                 RasterFace r;
                 r.set(m, p[0], p[1], p[2]);
                 const int64_t n = r.columns();
-                int own = n <= kOwnColumns;
-                if (!own) {
-                    if (part == 0) own = !add_slabs(m, (int32_t)f, n);
-                    own = __shfl(own, (threadIdx.x & 63) - part);
-                    if (own && m.bins) {  // many large faces
+                if (n > kOwnColumns) {
+                    // (many large faces on a list of points are better summed)
+                    if (part == 0 && add_slabs(m, (int32_t)f, n, face_share(m)) > (unsigned)m.slab_cap && m.bins)
                         atomicMax(&m.st->go, 2);
-                        own = 0;
-                    }
-                }
-                if (own) {
+                } else {
                     const int nj = r.j1 - r.j0 + 1;
                     for (int c = part; c < (int)n; c += kCycFaceLanes) {
                         const int i = c / nj;
@@ -547,11 +548,11 @@ __device__ __forceinline__ int degree_limit(int B) { return min(kDegreeLimit, ma
 // and patches: a face of the all-pairs sum without and with a strip order; a cap record summed one by one, of a
 // triangle, of another short loop, of a long one (in FP64); in blocks one that is far (as those of short loops
 // mostly are), and what one of a long loop adds where it is close (a workgroup takes it for 1024 voxels, so few
-// workgroups leave the chip idle); and joining, per edge and call.  Where the caps cost more the mesh goes
-// direct: a fan of 5000 faces (5000 edges in one loop) on 64^3 takes 3.37 ms by its boundary and 1.63 by its
-// faces, a ribbon of 10000 faces two quads wide 5.7 and 3.1; the ribbon on 128^3 13.0 and 25, 1000 patches of
-// eight faces on 64^3 1.7 and 2.5.
-constexpr double kFaceCost = 122.0, kStripCost = 88.0, kJoinCost = 3.0e6;
+// workgroups leave the chip idle); joining, per edge and call; a column that a cap triangle may meet.  Where
+// the caps cost more the mesh goes direct: a fan of 5000 faces (5000 edges in one loop) on 64^3 takes 3.37 ms by
+// its boundary and 1.63 by its faces, a ribbon of 10000 faces two quads wide 5.7 and 3.1; the ribbon on 128^3
+// 13.0 and 25, 1000 patches of eight faces on 64^3 1.7 and 2.5.
+constexpr double kFaceCost = 122.0, kStripCost = 88.0, kJoinCost = 3.0e6, kColumnCost = 700.0;
 constexpr int kTriCost = 70, kShortCost = 110, kLongCost = 260, kFarCost = 4, kCloseCost = 380;
 constexpr int kBusyBlocks = 1024;
 
@@ -559,10 +560,14 @@ __device__ __forceinline__ int64_t all_points(const CycMesh &m) {
     return m.bins ? m.P : (int64_t)m.n0 * m.ps.n1 * m.ps.n2;  // (of a slice its grid's, so that slices decide alike)
 }
 
-// Whether caps of this cost per voxel, over B edges, make the all-pairs sum the cheaper one.
-__device__ __forceinline__ bool caps_cost_more(const CycMesh &m, int64_t B, double cost) {
+// Whether caps of this cost per voxel, over B edges and so many columns, make the all-pairs sum the cheaper one.
+__device__ __forceinline__ bool caps_cost_more(const CycMesh &m, int64_t B, double cost, double columns = 0.0) {
     const double P = (double)all_points(m);
-    return P * cost + kJoinCost * (double)B > P * (double)m.nF * (m.strips ? kStripCost : kFaceCost);
+    return P * cost + kJoinCost * (double)B + kColumnCost * columns > P * (double)m.nF * (m.strips ? kStripCost : kFaceCost);
+}
+
+__device__ __forceinline__ double plain_cost(int tri, int other, int lng) {
+    return (double)tri * kTriCost + (double)other * kShortCost + (double)lng * kLongCost;
 }
 
 // What a triangle of a long loop adds in blocks: close to it are the voxels within twice its edges (and a quarter of a
@@ -759,9 +764,7 @@ __global__ __launch_bounds__(kCapThreads) void k_cyc_caps(const char *table) {
             }
             if (!m.grid.order) {
                 block_scan(kinds, red, kinds);
-                if (caps_cost_more(m, B, (double)count_of(kinds, 0) * kTriCost + (double)count_of(kinds, 1) * kShortCost +
-                                             (double)count_of(kinds, 2) * kLongCost))
-                    return -1;
+                if (caps_cost_more(m, B, plain_cost(count_of(kinds, 0), count_of(kinds, 1), count_of(kinds, 2)))) return -1;
             }
             // Long loops by doubling: log2 of the length rounds over their edges (each edge walking to a
             // lower one was quadratic, 1.2e6 dependent loads for a ribbon of 1e5 faces).
@@ -854,11 +857,13 @@ __global__ __launch_bounds__(kCapThreads) void k_cyc_caps(const char *table) {
         }
         __syncthreads();
         // triangles over many columns go on the raster list; k_cyc_slabs takes the others one by one
-        unsigned long long cost = 0;
+        unsigned long long cost = 0, columns = 0;
         const float *V = m.V;
         int32_t *cvid = m.cvid, *cpos = m.cpos;
+        const int share = kListShare / B;
         const bool blocks = m.grid.order != 0 && n_short < B;
         const CloseCost close(m);
+        const double limit = m.bins ? (double)m.bins * m.bins : (double)m.n0 * m.ps.n1;
         for (int x = tid; x < B; x += kCapThreads) {
             if (cpos[x] < 2) continue;
             float p[3][3];
@@ -872,14 +877,18 @@ __global__ __launch_bounds__(kCapThreads) void k_cyc_caps(const char *table) {
                 const float l = fminf(fminf(p[0][d], p[1][d]), p[2][d]), u = fmaxf(fmaxf(p[0][d], p[1][d]), p[2][d]);
                 area *= ((double)u - l) * (m.bins ? Bins(m).inv[d] : m.inv_h[d]) + 1.0;
             }
+            columns += (unsigned long long)fmin(area, limit);
             if (area > (double)kWaveColumns) {
                 RasterFace f;
-                if (set_cap(m, x, f) && add_slabs(m, (int32_t)(m.nF + x), f.columns())) cpos[x] |= kCapListed;
+                if (share > 0 && set_cap(m, x, f) && f.columns() > 0) {
+                    add_slabs(m, (int32_t)(m.nF + x), f.columns(), share);
+                    cpos[x] |= kCapListed;
+                }
             }
         }
         if (blocks) block_scan(cost, red, cost);
-        __syncthreads();
-        if (blocks && caps_cost_more(m, B, (double)cost + (double)B * kFarCost)) {
+        block_scan(columns, red, columns);
+        if (caps_cost_more(m, B, m.grid.order ? (double)cost + (double)B * kFarCost : plain_cost(3 * n_tri, n_short - 3 * n_tri, B - n_short), (double)columns)) {
             if (tid == 0) atomicMax(&m.st->go, 2);
         } else if (tid == 0) {
             m.st->n_rec = B;
@@ -901,8 +910,7 @@ __global__ __launch_bounds__(kCycUnit) void k_cyc_slabs(const char *table) {
     int64_t before = 0;
     for (int mi = 0; mi < h->n; ++mi) {
         const CycMesh &m = meshes[mi];
-        const unsigned long long asked = m.st->n_slab;
-        const int64_t n = asked < (unsigned long long)m.slab_cap ? (int64_t)asked : m.slab_cap;
+        const int64_t n = (unsigned)m.st->n_slab;
         if (m.st->go) continue;
         const int n_tri = m.st->n_tri, n_rec = m.st->n_rec;
         for (int64_t x = (wave + waves - before % waves) % waves; x < n + n_rec; x += waves) {
@@ -934,17 +942,20 @@ __global__ __launch_bounds__(kCycUnit) void k_cyc_slabs(const char *table) {
                 sign = -1;
             } else {
                 const int2 e = m.slab[x];
-                if (e.x < 0) continue;
+                int share;
                 if (e.x >= m.nF) {
                     set_cap(m, (int)(e.x - m.nF), r);
+                    share = kListShare / n_rec;
                     sign = -1;
                 } else {
                     const int64_t f = e.x;
+                    share = face_share(m);
                     r.set(m, m.V + 3 * (int64_t)face_vertex(m, 3 * f), m.V + 3 * (int64_t)face_vertex(m, 3 * f + 1),
                           m.V + 3 * (int64_t)face_vertex(m, 3 * f + 2));
                 }
-                first = (int64_t)e.y * 64;
-                end = min(first + 64, r.columns());
+                const int64_t per = list_columns(r.columns(), share);
+                first = e.y * per;
+                end = min(first + per, r.columns());
             }
             const int64_t nj = r.j1 - r.j0 + 1;
             for (int64_t c = first + lane; c < end; c += 64)
@@ -954,15 +965,22 @@ __global__ __launch_bounds__(kCycUnit) void k_cyc_slabs(const char *table) {
     }
 }
 
-__device__ __forceinline__ void list_near(const CycMesh &m, int64_t idx) {
+// Puts a voxel on the list, with one atomic on its length for the lanes that come here together.  `go`: of the
+// state, as the kernel found it; a list that is full by then is not counted on.  (4e5 voxels beyond its end took
+// 6 ms one by one.)
+__device__ __forceinline__ void list_near(const CycMesh &m, int64_t idx, int go) {
     const int32_t x = (int32_t)(idx - m.p0);
     const uint32_t bit = 1u << (x & 31);
-    if (atomicOr(&m.mark[x >> 5], bit) & bit) return;
-    const int32_t at = atomicAdd(&m.st->n_near, 1);
-    if (at < m.near_cap)
-        m.near[at] = x;
-    else
-        atomicMax(&m.st->go, 1);
+    if ((atomicOr(&m.mark[x >> 5], bit) & bit) || go) return;
+    const unsigned long long all = __builtin_amdgcn_ballot_w64(true);
+    const int leader = __builtin_ctzll(all), lane = threadIdx.x & 63, n = __popcll(all);
+    int32_t at = 0;
+    if (lane == leader) {
+        at = atomicAdd(&m.st->n_near, n);
+        if (at + n > m.near_cap) atomicMax(&m.st->go, 1);
+    }
+    at = __builtin_amdgcn_readlane(at, leader) + __popcll(all & ((1ull << lane) - 1ull));
+    if (at < m.near_cap) m.near[at] = x;
 }
 
 // Where the occupancy map amplifies the rounding of W: within rounding of a threshold, and
@@ -994,37 +1012,42 @@ __device__ __forceinline__ void write_weights(const CycMesh &m) {
     }
 }
 
-// One wave per column, from the top: W is the sum of the crossings at and above a voxel.
+// One wave per column, or for as many short ones as it has lanes for, from the top: W is the sum of the crossings
+// at and above a voxel.  (A wave for each column of one voxel took 1.56 ms for 2000 x 2000 x 1.)
 __global__ __launch_bounds__(kCycColumns * 64) void k_cyc_columns(const char *table) {
     const CycHead *h = reinterpret_cast<const CycHead *>(table);
     const int lane = threadIdx.x & 63;
     for (int64_t u = blockIdx.x; u < h->u_col; u += gridDim.x) {
         const CycMesh &m = *find_mesh<&CycMesh::u_col>(table, u);
         if (u == m.u_col && m.grid.order) write_weights(m);
+        const int go = m.st->go, n_rec = m.st->n_rec;
+        if (go >= 2) continue;  // (the all-pairs kernels write every voxel)
+        const bool last = n_rec == 0;  // no caps to add
         if (m.bins) {
             const int64_t idx = (u - m.u_col) * (kCycColumns * 64) + threadIdx.x;
             if (idx >= m.P) continue;
             const uint32_t x = reinterpret_cast<const uint32_t *>(m.W)[idx];
             const float w = (float)((int)(x & ~kCloseBit) - (int)kCountBias);
             m.W[idx] = w;
-            if (m.st->n_rec == 0) write_occ(m.occ, idx, w);
-            if ((x & kCloseBit) || (m.st->n_rec == 0 && near_threshold(m.occ, w))) list_near(m, idx);
+            if (last) write_occ(m.occ, idx, w);
+            if ((x & kCloseBit) || (last && near_threshold(m.occ, w))) list_near(m, idx, go);
             continue;
         }
-        const int n2 = m.ps.n2;
-        const int64_t base = (m.p0 / n2 + (u - m.u_col) * kCycColumns + (threadIdx.x >> 6)) * n2;
+        const int n2 = m.ps.n2, per = m.per, n = per * n2;
+        const int64_t base = (m.p0 / n2 + ((u - m.u_col) * kCycColumns + (threadIdx.x >> 6)) * per) * n2;
         const int64_t lo = base > m.p0 ? base : m.p0;
-        const int64_t hi = base + n2 < m.p0 + m.P ? base + n2 : m.p0 + m.P;
-        const bool last = m.st->n_rec == 0;  // no caps to add
+        const int64_t hi = base + n < m.p0 + m.P ? base + n : m.p0 + m.P;
+        int below = lane;  // voxels of its column that this pass has above the lane's
+        if (per > 1) below = lane % n2;
         int carry = 0;
-        for (int64_t top = hi; top > lo; top -= 64) {
+        for (int64_t top = per > 1 ? base + n : hi; top > lo; top -= 64) {
             const int64_t idx = top - 1 - lane;  // lane 0 is the highest voxel
-            const bool live = idx >= lo;
+            const bool live = idx >= lo && idx < hi;
             const uint32_t x = live ? reinterpret_cast<const uint32_t *>(m.W)[idx] : kCountBias;
             int s = (int)(x & ~kCloseBit) - (int)kCountBias;
             for (int o = 1; o < 64; o <<= 1) {
                 const int y = __shfl_up(s, o);
-                if (lane >= o) s += y;
+                if (below >= o) s += y;
             }
             s += carry;
             carry = __shfl(s, 63);
@@ -1036,7 +1059,7 @@ __global__ __launch_bounds__(kCycColumns * 64) void k_cyc_columns(const char *ta
                 write_occ(m.occ, idx, w);
                 near = near || near_threshold(m.occ, w);
             }
-            if (near) list_near(m, idx);
+            if (near) list_near(m, idx, go);
         }
     }
 }
@@ -1212,11 +1235,11 @@ __device__ __forceinline__ T *uniform(T *p) {
     return reinterpret_cast<T *>((uint64_t)hi << 32 | lo);
 }
 
-__device__ __forceinline__ void add_caps(const CycMesh &m, int64_t at, float sum) {
+__device__ __forceinline__ void add_caps(const CycMesh &m, int64_t at, float sum, int go) {
     const float w = m.W[at] + sum * kInv2Pi;
     m.W[at] = w;
     write_occ(m.occ, at, w);
-    if (near_threshold(m.occ, w)) list_near(m, at);
+    if (near_threshold(m.occ, w)) list_near(m, at, go);
 }
 
 template <int PPL>
@@ -1255,7 +1278,7 @@ __global__ __launch_bounds__(kBlock) void k_cyc_sum(const char *table) {
             for (int p = 0; p < PPL; ++p) {
                 const int64_t idx = base + (int64_t)p * kBlock;
                 if (idx >= m.P) continue;
-                add_caps(m, m.p0 + idx, s[p] + c[p]);
+                add_caps(m, m.p0 + idx, s[p] + c[p], s_go);
             }
         }
         if (units <= gridDim.x) break;
@@ -1330,7 +1353,7 @@ __global__ __launch_bounds__(kWaves * 64) void k_cyc_sum_split(const char *table
                 for (int k = 0; k < b1; ++k) neumaier_add(s, c, s_block[k][lane]);
             __syncthreads();
         }
-        if (wave == 0 && idx < m.P) add_caps(m, m.p0 + idx, s + c);
+        if (wave == 0 && idx < m.P) add_caps(m, m.p0 + idx, s + c, s_go);
     }
 }
 
@@ -1426,6 +1449,7 @@ __global__ __launch_bounds__(kBlock) void k_cyc_blocks(const char *table) {
     for (int64_t u = blockIdx.x; u < units; u += gridDim.x) {
         const CycMesh &m = *uniform(find_mesh<&CycMesh::u_blk>(table, u));
         const int n_tri = uniform(m.st->n_tri), n_short = uniform(m.st->n_short), n = uniform(m.st->n_rec) - 2 * n_tri;
+        const int go = uniform(m.st->go);
         if (n == 0) continue;  // (go is 2 with no caps, and 1 leaves them to be added)
         const CycBlocks &g = m.grid;
         const int parts = (g.size[0] + kBlockRows - 1) / kBlockRows;
@@ -1566,7 +1590,7 @@ __global__ __launch_bounds__(kBlock) void k_cyc_blocks(const char *table) {
             for (int p = 0; p < kBlockRows; ++p) {
                 if (x0 + p >= g.size[0] || i0[0] + x0 + p >= m.n0) break;
                 const int64_t at = ((int64_t)(i0[0] + x0 + p) * m.ps.n1 + iy) * m.ps.n2 + iz;
-                if (at >= m.p0 && at < m.p0 + m.P) add_caps(m, at, s[p] + c[p]);
+                if (at >= m.p0 && at < m.p0 + m.P) add_caps(m, at, s[p] + c[p], go);
             }
         }
     }
@@ -1786,7 +1810,7 @@ int64_t edge_buckets(int64_t nF) {
     return b;
 }
 
-int64_t slab_capacity(int64_t nF) { return nF + 65536; }
+int64_t slab_capacity(int64_t nF) { return nF + 2 * kListShare; }
 
 // Bins per side for so many points (0: too many): about three to a bin.
 int64_t bin_side(int64_t points) {
@@ -1875,8 +1899,10 @@ void cyc_place(CycMesh &m, char *base) {
 
 void cyc_units(CycMesh &m, CycHead &h) {
     auto units = [](int64_t n, int64_t per) { return (n + per - 1) / per; };
+    m.per = !m.bins && m.ps.n2 <= 32 ? 64 / m.ps.n2 : 1;
     // (a list's units hold as many points as a grid's hold columns' lanes)
-    const int64_t columns = m.bins ? (m.P + 63) / 64 : (m.p0 + m.P - 1) / m.ps.n2 - m.p0 / m.ps.n2 + 1;
+    const int64_t columns = m.bins ? (m.P + 63) / 64
+                                   : units((m.p0 + m.P - 1) / m.ps.n2 - m.p0 / m.ps.n2 + 1, m.per);
     m.u_clear = h.u_clear;
     m.u_face = h.u_face;
     m.u_half = h.u_half;

@@ -21,7 +21,7 @@ namespace wn {
 
 constexpr int kCycUnit = 256;        // half-edges per workgroup unit
 constexpr int kCycFaceLanes = 8;     // lanes per face
-constexpr int kCycColumns = 4;       // columns of voxels per workgroup unit (one per wave)
+constexpr int kCycColumns = 4;       // waves of columns of voxels per workgroup unit
 constexpr int kCycClear = 2048;      // words cleared per workgroup unit
 constexpr int kCycNear = 65536;      // points that may take the direct sum one by one
 constexpr int kCycShortLoop = 6;     // longest loop whose caps are evaluated in FP32
@@ -54,7 +54,7 @@ struct CycState {
     int32_t n_near;     // points on the list of direct sums
     int32_t odd;        // adjoint: dL/dW holds a value that is not finite
     uint32_t max_bits;  // bits of the largest |coordinate| of a face corner
-    unsigned long long n_slab;  // entries asked of the raster list
+    unsigned long long n_slab;  // entries of the raster list; in the upper half those of 64 columns asked for
     uint32_t box[6];    // point lists: largest x, y, z and -x, -y, -z of the vertices, as ordered integers
 };
 
@@ -72,6 +72,7 @@ struct CycMesh {
     PointSrc ps;
     int32_t n0;           // cells along x
     int32_t strips;       // the stream has to name every face once
+    int32_t per;          // columns of voxels that a wave takes at once
     int64_t p0, P;        // the voxels [p0, p0 + P)
     int32_t i_first, i_last;  // their range along x
     float *W;             // null: the boundary edges alone (the adjoint)
@@ -102,7 +103,7 @@ struct CycMesh {
     int32_t bins;
     int32_t *bin, *bin_n; // [bins^2] first point of a bin, and their number
     int32_t *after;       // [P] the next point of its bin
-    int2 *slab;           // raster list: (face, or nF + cap record; 64 columns of its range)
+    int2 *slab;           // raster list: (face, or nF + cap record; which part of its columns)
     int32_t *near;        // voxels for the direct sum, counted from p0
     uint32_t *mark;       // a bit for each such voxel, also those that the list had no room for
     int32_t near_cap, slab_cap;
