@@ -470,8 +470,6 @@ wn_status run_backward(const float *V, int64_t nV, const int32_t *F, int64_t nF,
             cyc_units(m, h);
             if (launch_cyc_begin(m, h, table, s) != hipSuccess || launch_cyc_edges(h, table, s) != hipSuccess)
                 return WN_ERR_HIP;
-            if (eb.splits > 0 && !((flags & kBwdEnd) && n == nQ))  // points that no range covers have no weight
-                k_fill_i32<<<blocks_for(nQ), kBlock, 0, s>>>(reinterpret_cast<int32_t *>(eb.kept), nQ, 0);
         }
     }
     WsHeader *hdr = reinterpret_cast<WsHeader *>(ws);
@@ -506,13 +504,11 @@ wn_status run_backward(const float *V, int64_t nV, const int32_t *F, int64_t nF,
     if (n > 0 && nV > 0 && nF > 0) {
         const int64_t t0 = p0 / kPointTile, t1 = (p0 + n + kPointTile - 1) / kPointTile;
         const int64_t rows = min((int64_t)S, t1 - t0);
-        const bool whole = (flags & kBwdBegin) && (flags & kBwdEnd) && n == nQ;
         if (st && eb.splits == 0 && launch_edge_bwd(table, nQ, t0, t1, dLdW, state, s) != hipSuccess) return WN_ERR_HIP;
         if (st && eb.splits > 0) {
-            if (whole)
-                e = launch_edge_blocks(table, blocks, dLdW, eb, s);
-            else
-                e = launch_edge_keep(table, dLdW, p0, n, eb, s);
+            const int64_t plane = (int64_t)ps.n1 * ps.n2;
+            if (n < nQ) e = launch_edge_keep(table, dLdW, p0, n, eb, s);
+            if (e == hipSuccess) e = launch_edge_blocks(table, blocks, plane, p0, p0 + n, nQ, n < nQ ? eb.kept : dLdW, eb, s);
             if (e != hipSuccess) return WN_ERR_HIP;
         }
         if (naive) {
@@ -555,8 +551,6 @@ wn_status run_backward(const float *V, int64_t nV, const int32_t *F, int64_t nF,
     if (st) {
         // the edges' gradients lie behind T (9 nF floats), in the sort's first two arrays (6 nF)
         float *G = reinterpret_cast<float *>(keys);
-        const bool whole = (flags & kBwdBegin) && n == nQ;
-        if (eb.splits > 0 && !whole && launch_edge_blocks(table, blocks, eb.kept, eb, s) != hipSuccess) return WN_ERR_HIP;
         if (launch_edge_reduce(table, nQ, eb.splits, state, G, s) != hipSuccess ||
             launch_edge_gather(table, nV, G, T, dLdV, s) != hipSuccess)
             return WN_ERR_HIP;

@@ -159,8 +159,8 @@ hipError_t launch_cyc_edges(const CycHead &h, char *table, hipStream_t s);
 // state: as much as the all-pairs adjoint's.
 hipError_t launch_edge_bwd(const char *table, int64_t nQ, int64_t t0, int64_t t1, const float *dLdW, float2 *state,
                            hipStream_t s);
-// With `splits` > 0 the state comes from the blocks of a large grid, which take the whole dL/dW at the
-// end of a sequence of ranges (kept from each range, unless one call has it all).
+// With `splits` > 0 the state comes from the blocks of a large grid: each call of a sequence takes those that
+// its points complete, from the dL/dW kept of all ranges so far (unless one call has it all).
 struct EdgeBlocks {
     int splits;
     float2 *state;
@@ -169,8 +169,8 @@ struct EdgeBlocks {
 EdgeBlocks edge_blocks(const CycBlocks &g, int64_t nF, int64_t nQ, char *space, size_t bytes);
 hipError_t launch_edge_keep(const char *table, const float *dLdW, int64_t p0, int64_t n, const EdgeBlocks &e,
                             hipStream_t s);
-hipError_t launch_edge_blocks(const char *table, const CycBlocks &g, const float *dLdW, const EdgeBlocks &e,
-                              hipStream_t s);
+hipError_t launch_edge_blocks(const char *table, const CycBlocks &g, int64_t plane, int64_t p0, int64_t p1, int64_t nQ,
+                              const float *dLdW, const EdgeBlocks &e, hipStream_t s);
 hipError_t launch_edge_reduce(const char *table, int64_t nQ, int splits, const float2 *state, float *G, hipStream_t s);
 hipError_t launch_edge_gather(const char *table, int64_t nV, const float *G, const float *T, float *dLdV,
                               hipStream_t s);

@@ -242,8 +242,8 @@ __device__ __forceinline__ float uniform(float x) {
     return __uint_as_float((unsigned)__builtin_amdgcn_readfirstlane((int)__float_as_uint(x)));
 }
 
-// Node sums of dL/dW, a workgroup per block: [block][coarse, fine].
-__global__ __launch_bounds__(kBlock) void k_edge_nodes(const char *table, const float *__restrict__ dLdW,
+// Node sums of dL/dW, a workgroup per block from `first` on: [block][coarse, fine].
+__global__ __launch_bounds__(kBlock) void k_edge_nodes(const char *table, int first, const float *__restrict__ dLdW,
                                                        float *__restrict__ node) {
     static_assert(kBlock == kBlockSide * kBlockSide, "a thread per (y, z)");
     __shared__ float T[3][kBlockSide][kFine], C[3][kFine][kCoarse];
@@ -264,7 +264,8 @@ __global__ __launch_bounds__(kBlock) void k_edge_nodes(const char *table, const 
     }
     __syncthreads();
     int i0[3];
-    block_origin(m, blockIdx.x, i0);
+    const int b = first + (int)blockIdx.x;
+    block_origin(m, b, i0);
     const int iy = i0[1] + ty, iz = i0[2] + tz;
     const bool in = ty < g.size[1] && tz < g.size[2] && iy < m.ps.n1 && iz < m.ps.n2;
     float v[kFine];
@@ -289,7 +290,7 @@ __global__ __launch_bounds__(kBlock) void k_edge_nodes(const char *table, const 
     }
     __syncthreads();
     const int nc = g.coarse[0] * g.coarse[1] * g.coarse[2], nf = g.fine[0] * g.fine[1] * g.fine[2];
-    float *out = node + (int64_t)blockIdx.x * (nc + nf);
+    float *out = node + (int64_t)b * (nc + nf);
     for (int e = tid; e < kFine * kFine * kFine; e += kBlock) {
         const int j0 = e / (kFine * kFine), j1 = e / kFine % kFine, j2 = e % kFine;
         float a = 0.0f;
@@ -319,10 +320,14 @@ __global__ __launch_bounds__(kBlock) void k_edge_nodes(const char *table, const 
 // nodes and of the voxels each, all coarse nodes in one of them): far edges at the coarse or
 // the fine nodes, near ones at the voxels (lanes without such an edge wait).  With whole blocks
 // the waves that had near edges took 864 us.
+// kRange: the call takes the parts [x0, x1) of a sequence, and a split goes on from its sums in `state`; else all
+// of them (an instance of its own: 1.5 % of the adjoint).
 // state: float2 [S][6][B].  40 VALU and 3 transcendentals per (edge, point) bound it: 1154 edges on
 // 96 x 88 x 97 voxels take 621 us, all points one by one 1024.
+template <bool kRange>
 __global__ __launch_bounds__(64) void k_edge_blocks(const char *table, const float *__restrict__ dLdW,
-                                                    const float *__restrict__ node, int S, float2 *__restrict__ state) {
+                                                    const float *__restrict__ node, int S, int x0, int x1,
+                                                    float2 *__restrict__ state) {
     __shared__ float4 pts[kTile];
     const CycMesh &m = *reinterpret_cast<const CycMesh *>(table + reinterpret_cast<const CycHead *>(table)->meshes);
     if (m.st->go) return;
@@ -333,13 +338,21 @@ __global__ __launch_bounds__(64) void k_edge_blocks(const char *table, const flo
     const int lane = threadIdx.x;
     for (int64_t w = blockIdx.x; w < (int64_t)groups * S; w += gridDim.x) {
         const int split = (int)(w / groups), e = (int)(w - (int64_t)split * groups) * 64 + lane;
+        const int first = kRange && split < x0 ? split + (x0 - split + S - 1) / S * S : split;
+        if (kRange && first >= x1) continue;
         const bool live = e < B;
         const int2 id = m.edge[live ? e : B - 1];
         const Edge edge(m, id);
         float s[6], c[6];
 #pragma unroll
         for (int i = 0; i < 6; ++i) s[i] = c[i] = 0.0f;
-        for (int x = split; x < blocks * kParts; x += S) {
+        if (kRange && split < x0 && live)
+#pragma unroll
+            for (int i = 0; i < 6; ++i) {
+                const float2 x = state[((int64_t)split * 6 + i) * B + e];
+                s[i] = x.x, c[i] = x.y;
+            }
+        for (int x = first; x < (kRange ? x1 : blocks * kParts); x += S) {
             const int b = x / kParts, part = x - b * kParts;
             int i0[3];
             block_origin(m, b, i0);
@@ -395,7 +408,7 @@ __global__ __launch_bounds__(64) void k_edge_blocks(const char *table, const flo
     }
 }
 
-// dL/dW of a point range, for the call that ends the sequence.
+// dL/dW of a point range, for the calls that complete its blocks.
 __global__ __launch_bounds__(kBlock) void k_edge_keep(const char *table, const float *__restrict__ dLdW, int64_t n,
                                                       float *__restrict__ kept) {
     const CycMesh &m = *reinterpret_cast<const CycMesh *>(table + reinterpret_cast<const CycHead *>(table)->meshes);
@@ -571,10 +584,15 @@ hipError_t launch_edge_keep(const char *table, const float *dLdW, int64_t p0, in
     return hipGetLastError();
 }
 
-hipError_t launch_edge_blocks(const char *table, const CycBlocks &g, const float *dLdW, const EdgeBlocks &e,
-                              hipStream_t s) {
-    k_edge_nodes<<<(unsigned)(g.n[0] * g.n[1] * g.n[2]), kBlock, 0, s>>>(table, dLdW, e.node);
-    k_edge_blocks<<<kEdgeWaves, 64, 0, s>>>(table, dLdW, e.node, e.splits, e.state);
+hipError_t launch_edge_blocks(const char *table, const CycBlocks &g, int64_t plane, int64_t p0, int64_t p1, int64_t nQ,
+                              const float *dLdW, const EdgeBlocks &e, hipStream_t s) {
+    // layers of blocks along x that are complete with so many points
+    auto complete = [&](int64_t points) { return points >= nQ ? g.n[0] : (int)(points / (plane * g.size[0])); };
+    const int layer = g.n[1] * g.n[2], b0 = complete(p0) * layer, b1 = complete(p1) * layer;
+    if (b1 == b0) return hipSuccess;
+    k_edge_nodes<<<(unsigned)(b1 - b0), kBlock, 0, s>>>(table, b0, dLdW, e.node);
+    (p1 - p0 < nQ ? k_edge_blocks<true> : k_edge_blocks<false>)<<<kEdgeWaves, 64, 0, s>>>(
+        table, dLdW, e.node, e.splits, b0 * kParts, b1 * kParts, e.state);
     return hipGetLastError();
 }
 

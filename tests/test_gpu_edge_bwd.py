@@ -349,3 +349,35 @@ def test_a_voxel_close_to_a_vertex(dev, distance):
     rel = np.abs(D - Dr)[base:].max(1) / np.abs(Dr)[base:].max(1)
     print(f"[{distance:g} of an edge away] relative differences", " ".join(f"{x:.1e}" for x in rel), flush=True)
     assert rel.max() <= 1e-5
+
+
+def test_ranges_share_the_work_of_large_grids(dev):
+    """On grids that take blocks each range does the blocks that it completes, so none takes much more than
+    its share of one call: the last of eight a quarter and the launches at most (it took all of it)."""
+    import time
+    import torch
+    import paper_2407_11272_amd as wn
+    V, F, _ = wi.ellipsoid_union(np.random.default_rng(1), 4, 4000)
+    F = wi.delete_faces(F, 1600, np.random.default_rng(2))
+    Vt, Ft = _dev(V, F)
+    grid = wn.Grid((-0.5,) * 3, (0.5,) * 3, (128, 128, 128))
+    g = _weights(grid.size)
+
+    def timed(f):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        out = f()
+        torch.cuda.synchronize()
+        return out, time.perf_counter() - t
+    wn.wn_backward(Vt, Ft, g, grid=grid)
+    D, whole = timed(lambda: wn.wn_backward(Vt, Ft, g, grid=grid))
+    sb = wn.SlicedBackward(Vt, Ft, grid=grid, vertex_sums=True)
+    for _ in range(2):
+        took = [timed(sb.begin)[1]]
+        for i in range(8):
+            took.append(timed(lambda: sb.points(i * grid.size // 8, grid.size // 8, g))[1])
+        E, last = timed(sb.end)
+        took.append(last)
+    assert torch.equal(E, D)
+    print(f"whole {1e3 * whole:.2f} ms, begin, ranges and end " + " ".join(f"{1e3 * t:.2f}" for t in took), flush=True)
+    assert max(took[:-2]) <= 0.25 * whole + 2e-4 and took[-2] + took[-1] <= 0.25 * whole + 4e-4
