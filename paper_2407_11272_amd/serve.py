@@ -35,6 +35,7 @@ an executor object; tests drive it with a simulated executor on the CPU.
 from __future__ import annotations
 
 import collections
+import ctypes
 import math
 import time
 from dataclasses import dataclass
@@ -134,13 +135,28 @@ def adjoint_unit(nF: int, P: int) -> int:
     return S * L.WN_BWD_TILE
 
 
+def _batch_bytes(req: ServeRequest, slice_points: int) -> int:
+    """Bytes of the batched workspace that a slice of the request's forward takes, as the library sizes them
+    (records and partial sums, and the boundary path's scratch), with the most strip records.  A slice may begin
+    inside a layer of voxel blocks (16 along x), so it is counted with one more."""
+    from . import _lib as L
+    nF, P, n = len(req.F), req.points, req.grid.n
+    d = L.WnMeshDesc()
+    some = 256   # (any pointer: only sizes are read)
+    d.V, d.nV, d.F, d.nF, d.W, d.occ, d.occ_mode = some, len(req.V), some, nF, some, some, L.WN_OCC_THRESHOLD
+    d.grid = L.WnGrid((ctypes.c_float * 3)(*req.grid.lo), (ctypes.c_float * 3)(*req.grid.hi), (ctypes.c_int32 * 3)(*n))
+    d.point_count = min(P, int(slice_points) + 16 * int(n[1]) * int(n[2]))
+    if nF:
+        d.strips, d.n_strip_records = some, 3 * nF
+    return int(_lib().wn_workspace_size_batched((L.WnMeshDesc * 1)(d), 1))
+
+
 def footprint_bytes(req: ServeRequest, slice_points: int) -> int:
     """Device bytes a request holds while admitted: mesh, outputs, gradient buffers,
-    and its share of the batched workspace (face records and chunk partials)."""
+    and its share of the batched workspace."""
     nV, nF, P = len(req.V), len(req.F), req.points
     b = 12 * nV + 12 * nF + 4 * P + (4 if req.occupancy == "sigmoid" else 1) * P
-    chunks = max(1, -(-nF // 4096))
-    b += 48 * nF + (4 * chunks * min(P, slice_points) if chunks > 1 else 0)
+    b += 24 * nF + _batch_bytes(req, slice_points)   # (the strip order, 8 B a record, stays with the mesh)
     if req.wants_grad:
         # target, dL/dW, dL/dV, the face-pair list (at most 2 int32 per face), and the
         # adjoint's own workspace (face or pair records, the splits' running corner sums,

@@ -315,3 +315,25 @@ def test_adjoint_unit_of_a_huge_grid():
     P = 1024 ** 3
     u = adjoint_unit(100000, P)
     assert u % 256 == 0 and 256 <= u <= 4096 * 256
+
+
+@pytest.mark.parametrize("faces,res,share", [(60000, 256, 1.0), (60000, 256, 0.1), (20000, 128, 1.0), (2000, 64, 0.5),
+                                             (1000, 16, 1.0)])
+def test_footprint_holds_the_library_s_workspace(faces, res, share):
+    """The workspace that the library asks for a request's slice, wherever it begins, with a strip order."""
+    import ctypes
+    from paper_2407_11272_amd import _lib as L
+    lib = L.load()
+    r = _req(0, faces, res, 0.0)
+    n = max(2048, int(r.points * share) // 2048 * 2048)
+    d = (L.WnMeshDesc * 1)()
+    d[0].V = d[0].F = d[0].W = d[0].occ = d[0].strips = 256
+    d[0].nV, d[0].nF, d[0].n_strip_records, d[0].occ_mode = len(r.V), faces, faces * 5 // 4, L.WN_OCC_THRESHOLD
+    d[0].grid = Grid.cube(res).to_c() if hasattr(Grid.cube(res), "to_c") else L.WnGrid(
+        (ctypes.c_float * 3)(*r.grid.lo), (ctypes.c_float * 3)(*r.grid.hi), (ctypes.c_int32 * 3)(*r.grid.n))
+    held = 12 * len(r.V) + 12 * faces + 8 * d[0].n_strip_records + 5 * r.points
+    for begin in {0, 2048, r.points // 2 // 2048 * 2048, r.points - n}:
+        if 0 <= begin < r.points:
+            d[0].point_begin, d[0].point_count = begin, min(n, r.points - begin)
+            ws = lib.wn_workspace_size_batched(d, 1)
+            assert ws > 0 and footprint_bytes(r, n) >= held + ws
