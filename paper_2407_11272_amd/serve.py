@@ -137,8 +137,9 @@ def adjoint_unit(nF: int, P: int) -> int:
 
 def _batch_bytes(req: ServeRequest, slice_points: int) -> int:
     """Bytes of the batched workspace that a slice of the request's forward takes, as the library sizes them
-    (records and partial sums, and the boundary path's scratch), with the most strip records.  A slice may begin
-    inside a layer of voxel blocks (16 along x), so it is counted with one more."""
+    (records and partial sums, and the boundary path's scratch), with 1.5 strip records per face (strips have 1.1
+    to 1.25; the 3 of separate faces would double the partial sums).  A slice may begin inside a layer of voxel
+    blocks (16 along x), so it is counted with one more."""
     from . import _lib as L
     nF, P, n = len(req.F), req.points, req.grid.n
     d = L.WnMeshDesc()
@@ -147,7 +148,7 @@ def _batch_bytes(req: ServeRequest, slice_points: int) -> int:
     d.grid = L.WnGrid((ctypes.c_float * 3)(*req.grid.lo), (ctypes.c_float * 3)(*req.grid.hi), (ctypes.c_int32 * 3)(*n))
     d.point_count = min(P, int(slice_points) + 16 * int(n[1]) * int(n[2]))
     if nF:
-        d.strips, d.n_strip_records = some, 3 * nF
+        d.strips, d.n_strip_records = some, 3 * nF // 2
     return int(_lib().wn_workspace_size_batched((L.WnMeshDesc * 1)(d), 1))
 
 
@@ -156,7 +157,7 @@ def footprint_bytes(req: ServeRequest, slice_points: int) -> int:
     and its share of the batched workspace."""
     nV, nF, P = len(req.V), len(req.F), req.points
     b = 12 * nV + 12 * nF + 4 * P + (4 if req.occupancy == "sigmoid" else 1) * P
-    b += 24 * nF + _batch_bytes(req, slice_points)   # (the strip order, 8 B a record, stays with the mesh)
+    b += 12 * nF + _batch_bytes(req, slice_points)   # (the strip order, 8 B a record, stays with the mesh)
     if req.wants_grad:
         # target, dL/dW, dL/dV, the face-pair list (at most 2 int32 per face), and the
         # adjoint's own workspace (face or pair records, the splits' running corner sums,
