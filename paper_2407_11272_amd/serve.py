@@ -43,11 +43,12 @@ from dataclasses import dataclass
 import numpy as np
 
 POINT_QUANTUM = 2048      # forward slices are multiples of this many voxels
-# Point-face pairs of work per scheduler step (adjoint pairs weighted).  A slice of a request costs its
-# mesh's own pass again, which the boundary path made the larger part: with 4e10 a burst of 64
-# requests took 487 ms and the median request 388 ms, with 4e11 237 and 55; a mesh that takes the
-# all-pairs sum holds a step for 0.3 s at most.
-STEP_PAIRS = 4.0e11
+STEP_PAIRS = 4.0e10       # point-face pairs of work per scheduler step (adjoint pairs weighted): 30 ms of all pairs
+# What a pair counts of a mesh that is expected to take the boundary path (16 to 100 times faster).  A
+# slice costs such a mesh its own pass again, so its requests are not to be cut small: with every mesh counted
+# in full a burst of 64 requests took 588 ms, with this 180 (plain FIFO 170).  (More in a step also
+# means gigabytes for the partial sums that a mesh may fall back to.)
+BOUNDARY_COST = 0.05
 POLICY = "edf"            # "edf": earliest deadline first; "fair": equal shares; "age": shares grow with age
 AGE_TAU = 0.25            # seconds of waiting that double a request's share under "age"
 ADJOINT_COST = 2.8        # cost of one adjoint (point, face) pair in forward pairs
@@ -107,6 +108,7 @@ class _Active:
     res: ServeResult
     footprint: int
     adj_unit: int = 0           # adjoint: points per unit granule (one round over its splits)
+    scale: float = 1.0          # what one of its pairs counts (BOUNDARY_COST)
     deadline: float = 0.0
     state: object = None        # executor-owned per-request state
     next_point: int = 0         # forward: next voxel to launch
@@ -133,6 +135,18 @@ def adjoint_unit(nF: int, P: int) -> int:
     if S < 1:
         raise ValueError("sizes out of range for the adjoint")
     return S * L.WN_BWD_TILE
+
+
+def boundary_sizes(req: ServeRequest) -> bool:
+    """Whether the request is large enough for the boundary path (by a strip order)."""
+    nF, P = len(req.F), req.points
+    return nF >= 128 and nF * P >= 7.0e7
+
+
+def boundary_expected(req: ServeRequest, n_strip_records: int) -> bool:
+    """Whether its mesh is also expected to suit that path: strips of at most 1.5 records per face, so that most
+    faces share edges (separate faces have 3, separate quads 2)."""
+    return boundary_sizes(req) and 2 * n_strip_records <= 3 * len(req.F)
 
 
 def _batch_bytes(req: ServeRequest, slice_points: int) -> int:
@@ -236,7 +250,8 @@ class Server:
         return res
 
     def _max_slice_points(self, req: ServeRequest) -> int:
-        per = self.quantum / max(1, len(req.F))
+        """The largest slice that any plan may give it (its footprint holds one)."""
+        per = self.quantum / max(1, len(req.F)) / (BOUNDARY_COST if boundary_sizes(req) else 1.0)
         pts = max(POINT_QUANTUM, int(per) // POINT_QUANTUM * POINT_QUANTUM)
         return min(pts, req.points)
 
@@ -260,6 +275,9 @@ class Server:
             admitted += 1
             a.res.admitted = now
             a.state = self.ex.admit(a.req)
+            records = a.state.get("n_strip_records") if isinstance(a.state, dict) else None
+            if records is not None and boundary_expected(a.req, records):
+                a.scale = BOUNDARY_COST
             self.active.append(a)
             self.in_use += a.footprint
             self.peak_in_use = max(self.peak_in_use, self.in_use)
@@ -291,7 +309,7 @@ class Server:
             if budgets is None and b <= 0:
                 break
             must = budgets is not None or i == 0   # the head (or every share) always progresses
-            nF, P = max(1, len(a.req.F)), a.req.points
+            nF, P = max(1, len(a.req.F)) * a.scale, a.req.points   # (what a point costs)
             spent = 0.0
             if not a.launched_all:
                 pts = int(b / nF) // POINT_QUANTUM * POINT_QUANTUM
@@ -440,7 +458,15 @@ class GpuExecutor:
         if self.strips and len(req.F):
             self.strip_jobs[req.rid] = self.pool.submit(wn.wn_build_strips, req.F, len(req.V))
         if self.face_pairs and req.wants_grad and len(req.F):
-            self.pair_jobs[req.rid] = self.pool.submit(wn.wn_build_face_pairs, req.F, len(req.V))
+            self.pair_jobs[req.rid] = self.pool.submit(self._face_pairs, req, self.strip_jobs.get(req.rid))
+
+    def _face_pairs(self, req: ServeRequest, strips):
+        """Face pairs, or None where dL/dV is expected to come from the boundary edges (the strip order, which the
+        pool began before, says so): building them took half as long again as the strips."""
+        import paper_2407_11272_amd as wn
+        if strips is not None and not self.keep_dLdT and boundary_expected(req, len(strips.result())):
+            return None
+        return wn.wn_build_face_pairs(req.F, len(req.V))
 
     def start(self, t0: float):
         torch = self.torch
@@ -467,6 +493,7 @@ class GpuExecutor:
                 Rh = torch.from_numpy(rec).pin_memory()
                 R = Rh.to(self.dev, non_blocking=True)
                 st["hold_strips"] = Rh
+                st["n_strip_records"] = len(rec)
             job = wn.MeshJob(st["V"], st["F"], wn.Grid.of(req.grid), req.occupancy, req.tau, req.k, strips=R)
             job.prepare()
             st["job"] = job
@@ -479,9 +506,10 @@ class GpuExecutor:
                 if self.face_pairs and len(req.F):
                     pj = self.pair_jobs.pop(req.rid, None)
                     ph = pj.result() if pj is not None else wn.wn_build_face_pairs(req.F, len(req.V))
-                    Ph = torch.from_numpy(ph).pin_memory()
-                    pairs = Ph.to(self.dev, non_blocking=True)
-                    st["hold_pairs"] = Ph
+                    if ph is not None:
+                        Ph = torch.from_numpy(ph).pin_memory()
+                        pairs = Ph.to(self.dev, non_blocking=True)
+                        st["hold_pairs"] = Ph
                 st["adj"] = wn.SlicedBackward(st["V"], st["F"], grid=job.grid, pairs=pairs,
                                               vertex_sums=not self.keep_dLdT)
                 if self.keep_dLdT:

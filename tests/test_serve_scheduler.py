@@ -337,3 +337,44 @@ def test_footprint_holds_the_library_s_workspace(faces, res, share):
             d[0].point_begin, d[0].point_count = begin, min(n, r.points - begin)
             ws = lib.wn_workspace_size_batched(d, 1)
             assert ws > 0 and footprint_bytes(r, n) >= held + ws
+
+
+def _slices_by_default(faces, res, records_per_face, monkeypatch=None):
+    class Executor(FakeExecutor):
+        def admit(self, req):
+            return dict(super().admit(req), n_strip_records=int(records_per_face * len(req.F)))
+    clock = VClock()
+    ex = Executor(clock)
+    out = Server(ex, clock=clock).run_trace([_req(0, faces, res, 0.0)], idle_sleep=1e-3)
+    assert np.isfinite(out[0].done)
+    return [n for _, n, _ in ex.slices[0]]
+
+
+def test_steps_of_meshes_that_take_all_pairs_stay_short():
+    """A mesh of separate faces (3 strip records each) holds a step for at most 4e10 pairs, 30 ms at 1.4e12 a
+    second; one whose faces share edges, which is expected to take the boundary path, is not cut for less than
+    twenty times that."""
+    faces, res = 40000, 256
+    soup = _slices_by_default(faces, res, 3.0)
+    assert max(soup) * faces <= 4.0e10 and len(soup) >= res ** 3 * faces / 4.0e10
+    shared = _slices_by_default(faces, res, 1.2)
+    assert len(shared) == 1
+    assert len(_slices_by_default(100000, res, 1.2)) == 3
+    # below the path's line a pair counts in full whatever the strips
+    assert len(_slices_by_default(100, 128, 1.2)) == len(_slices_by_default(100, 128, 3.0))
+
+
+def test_face_pairs_are_left_out_where_the_boundary_edges_give_the_gradient():
+    import concurrent.futures
+    from paper_2407_11272_amd.serve import GpuExecutor
+    import wn_inputs as wi
+    V, F = wi.icosphere(3)
+    r = ServeRequest(0, V.astype(np.float32), F.astype(np.int32), Grid.cube(64), 0.0, "sigmoid",
+                     np.zeros(64 ** 3, np.float32))
+    ex = GpuExecutor.__new__(GpuExecutor)
+    with concurrent.futures.ThreadPoolExecutor(1) as pool:
+        for records, keep, wanted in ((1.2, False, False), (3.0, False, True), (1.2, True, True)):
+            ex.keep_dLdT = keep
+            strips = pool.submit(lambda: np.zeros((int(records * len(F)), 2), np.int32))
+            assert (ex._face_pairs(r, strips) is not None) == wanted
+        assert ex._face_pairs(r, None) is not None
