@@ -10,7 +10,8 @@ same meshes launched one per call (the plain kernel) are timed beside it.
 
 Rows measured in the same run (``rows``; a compact ``summary`` closes the line):
   * forward_c2: the 19 000-face non-watertight union at 128^3, one mesh per launch;
-  * adjoint: forward + sigmoid-MSE loss + wn_backward on the 5120-face icosphere at 64^3;
+  * adjoint: forward + sigmoid-MSE loss + wn_backward on the 5120-face icosphere with 5 % of its faces
+    missing at 64^3;
   * served: continuous batching of a seeded Poisson trace, p50/p99 latency vs the
     plain one-mesh-per-launch loop at several offered loads;
   * naive (Eq. 4), eval (Section 3's evaluation chain), morph (Section 2.4), flip
@@ -36,6 +37,7 @@ METRIC = "point-triangle evals/s (FP32) vs FP32 peak; p50/p99 latency served vs 
 UNIT = "point-triangle evals/s"
 FLOP_FWD = 86    # algorithmic FLOPs per forward (point, face) pair
 FLOP_BWD = 182   # algorithmic FLOPs per adjoint pair
+FLOP_EDGE = 70   # FLOPs per (boundary edge, point) of the adjoint by the mesh's boundary
 PEAK_FP32 = 157.3e12   # MI355X FP32 vector peak (256 CU x 2.4 GHz x 256 FLOP/clk)
 PEAK_HBM = 8.0e12
 
@@ -44,7 +46,9 @@ PEAK_HBM = 8.0e12
 KERNEL_SOURCES = {"k_wn_fwd": ("wn_internal.hpp", "wn_fwd.hip"),
                   "k_batched_persistent": ("wn_internal.hpp", "wn_batched.hip"),
                   "k_wn_bwd": ("wn_internal.hpp", "wn_bwd.hip"),
-                  "k_wn_bwd_pairs": ("wn_internal.hpp", "wn_bwd_pairs.hip")}
+                  "k_wn_bwd_pairs": ("wn_internal.hpp", "wn_bwd_pairs.hip"),
+                  "k_cyc_nodes + k_cyc_blocks": ("wn_internal.hpp", "wn_cycle.hpp", "wn_blocks.hpp", "wn_cycle.hip"),
+                  "k_edge_bwd": ("wn_internal.hpp", "wn_cycle.hpp", "wn_blocks.hpp", "wn_edge_bwd.hip")}
 
 
 def source_hash(kernel: str = "k_wn_fwd") -> str:
@@ -149,7 +153,7 @@ def bench_forward(steps, warmup, autotune=True, compare=True):
         "strip_records_per_face": len(Rh) / len(c.F),
         "strip_build_ms_host": strip_ms,
         "autotune": tune["chosen"] if tune else None,
-        "roofline": roofline("k_wn_fwd", "c2", pairs, dev_s / steps, FLOP_FWD),
+        "roofline": roofline("k_cyc_nodes + k_cyc_blocks", "c2", pairs, dev_s / steps, FLOP_FWD),
     }
     if compare:
         n = max(2, steps // 2)
@@ -159,12 +163,15 @@ def bench_forward(steps, warmup, autotune=True, compare=True):
 
 
 def bench_adjoint(steps, warmup):
+    import numpy as np
     import torch
     import paper_2407_11272_amd as wn
     import wn_inputs as wi
-    c = wi.config3_differentiable()
+    c = wi.config3_differentiable(open_variant=True)   # (a closed mesh has no gradient, and no work)
     V, F = wn.as_mesh(torch.as_tensor(c.V), torch.as_tensor(c.F))
     grid = wn.Grid.of(c.grid)
+    e = np.concatenate([c.F[:, [0, 1]], c.F[:, [1, 2]], c.F[:, [2, 0]]]).astype(np.int64)
+    edges = int((~np.isin(e[:, 0] * len(c.V) + e[:, 1], e[:, 1] * len(c.V) + e[:, 0])).sum())
     T = torch.as_tensor(c.target).cuda()
     W = torch.empty(grid.size, dtype=torch.float32, device="cuda")
     loss = torch.empty(1, dtype=torch.float32, device="cuda")
@@ -192,7 +199,11 @@ def bench_adjoint(steps, warmup):
     npairs = grid.size * len(c.F)
     bwd_s = max(s_s - f_s, 1e-12) / n
     out = {
-        "workload": "icosphere-s4-5120f-64cube sigmoid(k=50) MSE, forward+loss+adjoint (two faces per lane, sums shared per vertex)",
+        "workload": f"icosphere-s4 with 5 % of its 5120 faces missing, 64cube, sigmoid(k=50) MSE, forward+loss+adjoint "
+                    f"(dL/dV from the {edges} boundary edges)",
+        "boundary_edges": edges,
+        "edge_points_per_s": edges * grid.size / (a_s / n),
+        "edge_points_frac_fp32_peak": edges * grid.size / (a_s / n) * FLOP_EDGE / PEAK_FP32,
         "pairs_per_pass": npairs,
         "ms_per_step": s_s / n * 1e3,
         "fwd_ms": f_s / n * 1e3,
@@ -200,10 +211,11 @@ def bench_adjoint(steps, warmup):
         "adjoint_pairs_per_s": npairs / bwd_s,
         "adjoint_frac_fp32_peak": npairs / bwd_s * FLOP_BWD / PEAK_FP32,
         "step_pairs_per_s": 2 * npairs / (s_s / n),
-        # the adjoint call alone (pack, the two-faces-per-lane kernel, split reduction, per-vertex gather)
+        # the adjoint call alone (boundary edges, their sums over the points, per-vertex gather); pairs are those of
+        # the all-pairs sum that it stands for
         "adjoint_call_ms": a_s / n * 1e3,
         "adjoint_call_pairs_per_s": npairs / (a_s / n),
-        "roofline": roofline("k_wn_bwd_pairs", "c3", npairs, a_s / n, FLOP_BWD),
+        "roofline": roofline("k_edge_bwd", "c3", npairs, a_s / n, FLOP_BWD),
     }
     return out
 
@@ -659,7 +671,7 @@ def main():
             "derived_as": "res^3 x faces / time of the paper's own method at 128^3 (appendix table), "
                           "over its meshes",
         },
-        "roofline": roofline("k_batched_persistent", "c4", pairs, launch_s, FLOP_FWD),
+        "roofline": roofline("k_cyc_nodes + k_cyc_blocks", "c4", pairs, launch_s, FLOP_FWD),
     }
     want = set() if args.no_rows else {r.strip() for r in args.rows.split(",") if r.strip()}
     rows = {}
@@ -717,6 +729,7 @@ def summary(out) -> dict:
         # step difference (step minus a separately timed forward) is kept beside it
         s["adjoint_c3"] = {"pairs_per_s": a["adjoint_call_pairs_per_s"],
                            "frac": round(a["roofline"]["frac"], 4), "ms": round(a["adjoint_call_ms"], 3),
+                           "edge_frac": round(a["edge_points_frac_fp32_peak"], 4),
                            "step_diff_frac": round(a["adjoint_frac_fp32_peak"], 4)}
         if "hw_frac" in a["roofline"]:
             s["adjoint_c3"]["hw_frac"] = round(a["roofline"]["hw_frac"], 4)
