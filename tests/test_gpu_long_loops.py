@@ -100,22 +100,29 @@ def test_an_ordered_ribbon_takes_milliseconds(dev):
 
 
 def all_pairs(V, F, grid, strips=None, occupancy=0, tau=0.5, k=50.0):
-    """The C entry point with a byte less than the boundary path asks for: the all-pairs kernels alone."""
+    """The C entry point with the smallest workspace that it accepts, found by bisection: without room for the
+    boundary path, so the all-pairs kernels alone."""
     import ctypes
     import torch
     import paper_2407_11272_amd as wn
     from paper_2407_11272_amd import _lib as L
-    lib, p = L.load(), ctypes.c_void_p
-    n = wn.wn_workspace_size(L.WN_OP_VOXELIZE, V.shape[0], F.shape[0], grid.size) - 1
-    ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+    lib, p, grid = L.load(), ctypes.c_void_p, wn.Grid.of(grid)
+    full = wn.wn_workspace_size(L.WN_OP_VOXELIZE, V.shape[0], F.shape[0], grid.size)
+    ws = torch.empty(full, dtype=torch.uint8, device="cuda")
     W = torch.empty(tuple(grid.n), device="cuda")
     occ = torch.empty(tuple(grid.n), dtype=torch.float32 if occupancy == L.WN_OCC_SIGMOID else torch.uint8, device="cuda")
     R = () if strips is None else (p(strips.data_ptr()), strips.shape[0])
-    st = (lib.wn_voxelize if strips is None else lib.wn_voxelize_strips)(
-        p(V.data_ptr()), V.shape[0], p(F.data_ptr()), F.shape[0], *R, ctypes.byref(grid.to_c()), p(0), 0,
-        p(W.data_ptr()), occupancy, tau, k, p(occ.data_ptr()) if occupancy else p(0), p(ws.data_ptr()), n,
-        p(torch.cuda.current_stream().cuda_stream))
-    assert st == 0
+
+    def call(n):
+        return (lib.wn_voxelize if strips is None else lib.wn_voxelize_strips)(
+            p(V.data_ptr()), V.shape[0], p(F.data_ptr()), F.shape[0], *R, ctypes.byref(grid.to_c()), p(0), 0,
+            p(W.data_ptr()), occupancy, tau, k, p(occ.data_ptr()) if occupancy else p(0), p(ws.data_ptr()), n,
+            p(torch.cuda.current_stream().cuda_stream))
+    lo, hi = 0, full
+    while hi - lo > 256:    # (sizes are multiples of 256 bytes)
+        mid = (lo + hi) // 512 * 256
+        lo, hi = (lo, mid) if call(mid) == L.WN_OK else (mid, hi)
+    assert call(hi) == L.WN_OK and call(hi - 256) == L.WN_ERR_WORKSPACE
     torch.cuda.synchronize()
     return (W, occ) if occupancy else W
 
