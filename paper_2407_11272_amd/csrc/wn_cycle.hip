@@ -131,6 +131,10 @@ __device__ __forceinline__ float axis_centre(const PointSrc &ps, int d, int i) {
     return __builtin_fmaf((float)i + 0.5f, ps.h[d], ps.lo[d]);
 }
 
+// Cells whose centres may be a coordinate: more (a grid whose cells are far below the rounding of its place) are
+// not looked at one by one.
+constexpr int kCentreCells = 1024;
+
 // Cells [a, b] of an axis whose centres may lie in [lo, hi] (all of them, and perhaps a
 // neighbour: the slack covers the rounding of the centres), within [first, last].
 __device__ __forceinline__ void cell_range(const CycMesh &m, int d, double lo, double hi, int first, int last, int &a,
@@ -402,14 +406,14 @@ __global__ __launch_bounds__(kCycUnit) void k_cyc_faces(const char *table) {
                 if (part < 3) {
                     const int32_t v = part == 0 ? id[0] : part == 1 ? id[1] : id[2];
                     m.used[v] = 1;
-                    bool same = true;
-                    for (int d = 0; d < 3; ++d) {
+                    bool same = bits <= __float_as_uint(kCoordMax);  // else the mesh goes direct
+                    for (int d = 0; d < 3 && same; ++d) {
                         const float x = part == 0 ? p[0][d] : part == 1 ? p[1][d] : p[2][d];
                         int a, b;
                         cell_range(m, d, x, x, 0, (d == 0 ? m.n0 : d == 1 ? m.ps.n1 : m.ps.n2) - 1, a, b);
-                        bool hit = false;
-                        for (int k = a - 1; k <= b + 1; ++k) hit = hit || axis_centre(m.ps, d, k) == x;
-                        same = same && hit;
+                        bool hit = b - a > kCentreCells;
+                        for (int k = a - 1; k <= b + 1 && !hit; ++k) hit = axis_centre(m.ps, d, k) == x;
+                        same = hit;
                     }
                     if (same) atomicMax(&m.st->go, 2);
                 }

@@ -381,3 +381,30 @@ def test_ranges_share_the_work_of_large_grids(dev):
     assert torch.equal(E, D)
     print(f"whole {1e3 * whole:.2f} ms, begin, ranges and end " + " ".join(f"{1e3 * t:.2f}" for t in took), flush=True)
     assert max(took[:-2]) <= 0.25 * whole + 2e-4 and took[-2] + took[-1] <= 0.25 * whole + 4e-4
+
+
+def test_a_coordinate_that_is_not_finite_on_a_long_axis(dev):
+    """The cells that hold a vertex are looked up within the rounding of their centres; a NaN has none (it went
+    through all 4e6 cells of the axis, one by one)."""
+    import time
+    import torch
+    import paper_2407_11272_amd as wn
+    V, F = _mesh("holes")
+    V = np.asarray(V, np.float32).copy()
+    V[5, 0] = np.nan
+    Vt, Ft = _dev(V, F)
+    grid = wn.Grid((-0.5,) * 3, (0.5,) * 3, (1 << 22, 1, 1))
+    g = torch.zeros(grid.size, device="cuda")
+    few = wn.Grid((-0.5,) * 3, (0.5,) * 3, (1 << 14, 16, 16))   # as many points, short axes
+
+    def timed(gr):
+        wn.wn_backward(Vt, Ft, g, grid=gr)
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        D = wn.wn_backward(Vt, Ft, g, grid=gr)
+        torch.cuda.synchronize()
+        return D, time.perf_counter() - t
+    D, t = timed(grid)
+    _, t0 = timed(few)
+    assert torch.isnan(D[5]).any()
+    assert t <= 1.5 * t0 + 1e-3
