@@ -127,16 +127,37 @@ struct Edge {
         return Term{{px, py, pz}, k * ia, k * ib};
     }
     // Adds g J P at the n points (x, y, z, g) for either end, four at a time; those up to the next
-    // multiple of four are there, without weight.  A group of eight with a point that is close to the edge of
-    // any lane is added again by near_term, which holds for every point: a minimum per point and a
-    // copy of the sums per group for the others.  (Eight, so that the sums before the group cost few
-    // registers: keeping four terms until the test took 116 instead of 95 and 4 % of a whole adjoint.)
+    // multiple of four are there, without weight.  Points that are close to the edge of any lane are taken by
+    // near_term: with kHold the four terms wait for the test (107 registers), else they are added as they
+    // come and a group of eight with such a point is taken again by near_term, which holds for every point.
+    // k_edge_bwd holds them: adjoints of 1000 to 5000 faces below 2^19 voxels take 0 to 7 % less than without,
+    // 326 us for 351 at 4983 faces of 72 x 38 x 76.  k_edge_blocks, which has a block's state to keep as well,
+    // needs 95 registers without and 116 with it, and is no faster with it.
+    template <bool kHold>
     __device__ __forceinline__ void add(const float4 *pts, int n, float (&su)[3], float (&sv)[3]) const {
-        constexpr int kGroup = 8;
+        constexpr int kGroup = kHold ? 4 : 8;
 #pragma unroll 1
         for (int i0 = 0; i0 < n; i0 += kGroup) {
+            float least = INFINITY;
+            if constexpr (kHold) {
+                Term t[4];
+                float den[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    t[j] = term(pts[i0 + j], den[j]);
+                    least = fminf(least, den[j]);
+                }
+                if (__builtin_expect(__builtin_amdgcn_ballot_w64(least < kNear) != 0ull, 0)) {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        if (den[j] < kNear) t[j] = near_term(pts[i0 + j]);
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) add_term(t[j], su, sv);
+                continue;
+            }
             const int i1 = min(n, i0 + kGroup);
-            float bu[3], bv[3], least = INFINITY;
+            float bu[3], bv[3];
 #pragma unroll
             for (int d = 0; d < 3; ++d) bu[d] = su[d], bv[d] = sv[d];
 #pragma unroll 1
@@ -152,11 +173,7 @@ struct Edge {
 #pragma unroll
             for (int d = 0; d < 3; ++d) su[d] = bu[d], sv[d] = bv[d];
 #pragma unroll 1
-            for (int i = i0; i < i1; ++i) {
-                const float4 q = pts[i];
-                const Term t = near_term(q);
-                add_term(t, su, sv);
-            }
+            for (int i = i0; i < i1; ++i) add_term(near_term(pts[i]), su, sv);
         }
     }
     static __device__ __forceinline__ void add_term(const Term &t, float (&su)[3], float (&sv)[3]) {
@@ -212,7 +229,7 @@ __global__ __launch_bounds__(64) void k_edge_bwd(const char *table, int64_t nQ, 
             __syncthreads();
             if (B == 0) continue;
             float su[3] = {0.0f, 0.0f, 0.0f}, sv[3] = {0.0f, 0.0f, 0.0f};
-            edge.add(pts, kTile, su, sv);
+            edge.add<true>(pts, kTile, su, sv);
             if (live) {
                 float2 *row = state + (int64_t)s * 6 * B + e;
                 const float ts[6] = {su[0], su[1], su[2], sv[0], sv[1], sv[2]};
@@ -392,7 +409,7 @@ __global__ __launch_bounds__(64) void k_edge_blocks(const char *table, const flo
                     __syncthreads();
                     if (kind == want) {
                         float su[3] = {0.0f, 0.0f, 0.0f}, sv[3] = {0.0f, 0.0f, 0.0f};
-                        edge.add(pts, here, su, sv);
+                        edge.add<false>(pts, here, su, sv);
 #pragma unroll
                         for (int i = 0; i < 3; ++i) {
                             neumaier_add(s[i], c[i], su[i]);
