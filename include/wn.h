@@ -146,6 +146,9 @@ WN_API wn_status wn_build_strips(const int32_t *F, int64_t nF, int64_t nV, int32
  * for a given stream.  Face ids in the stream must be < nF and vertex ids < nV (out of
  * range entries are replaced and recorded, as for F).  The workspace is
  * wn_workspace_size(WN_OP_VOXELIZE, nV, nF, nQ) for any stream of at most 3 nF records.
+ * A call that wn_voxelize_strips_noalloc takes, but without room in its array for the
+ * faster path's workspace, sums over all faces, so that the two agree bit for bit (on a
+ * 128^3 grid from about 350000 to 2.6 million faces); wn_voxelize has no such line.
  */
 WN_API wn_status wn_voxelize_strips(const float *V, int64_t nV, const int32_t *F, int64_t nF,
                                     const int32_t *strips, int64_t n_records,

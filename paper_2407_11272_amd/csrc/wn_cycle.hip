@@ -13,9 +13,10 @@
 //   sum     solid angles of the caps at every voxel, W and occupancy;
 //   near    the direct sum at the listed voxels.
 // A mesh that the path does not suit (an edge used three times the same way, a
-// boundary longer than the face count, coordinates out of range, a strip stream that
-// does not name every face once) sets `go` and the all-pairs kernels, launched after
-// `sum`, run for it; otherwise they leave at once.  More voxels than the list holds are
+// boundary longer than the face count or with too many edges at a vertex, caps that cost
+// more than the faces, coordinates out of range, a strip stream that does not name every
+// face once) sets `go` and the all-pairs kernels, launched after `sum`, run for it;
+// otherwise they leave at once.  More voxels than the list holds are
 // marked, and the all-pairs kernels run for the marked ones.
 #include "wn_blocks.hpp"
 
@@ -616,7 +617,7 @@ __device__ __forceinline__ int count_of(unsigned long long x, int kind) { return
 // otherwise become one loop of six); then an edge entering a vertex continues with the
 // leaving edge of the same rank there.  A loop starts at its lowest edge, so the cap stream
 // depends on F alone.  A loop of k edges becomes a strip of k records and k - 2 triangles.
-// Bound by the latency of its dependent loads and barriers: 39 us for 1364 edges, 288 for 11082
+// Bound by the latency of its dependent loads and barriers: 36 us for 1364 edges, 300 for 11082
 // (58 and 437 with the chains' heads read from memory and the triangles formed here).
 __global__ __launch_bounds__(kCapThreads) void k_cyc_caps(const char *table) {
     __shared__ unsigned long long red[kCapThreads / 64];
@@ -1433,9 +1434,10 @@ __global__ __launch_bounds__(64) void k_cyc_nodes(const char *table) {
     }
 }
 
-// Both are bound by their arithmetic (38 VALU with 4 transcendentals per node, 30 per near point) and by
-// the latency of few waves.  19000 faces with 5 % missing on 128^3: one by one 1956 us, here 203 +
-// 234; 46000 faces with 8 % missing on 141 x 117 x 131: 7600 us, here 884 + 551.
+// 38 VALU with 4 transcendentals per node, 30 per near point.  Counted, the nodes issue 0.90 VALU per CU and
+// clock and the blocks 0.48, where the all-pairs kernel reaches 1.6: the rest is waits, for the triangles'
+// scalar loads and, at the end, for few waves.  19000 faces with 5 % missing on 128^3: one by one 1956 us, here
+// 204 + 221; 46000 faces with 8 % missing on 141 x 117 x 131: 7600 us, here 876 + 541.
 //
 // One workgroup per block and kBlockRows of its planes along x; a thread takes one (y, z) and
 // the planes' points there.

@@ -16,10 +16,11 @@
 // through LDS, 256 to a tile, tiles dealt to S splits in turn, as in the all-pairs adjoint (the same
 // calls on point ranges give the same bits as one call).
 //
-// The all-pairs adjoint is bound by its arithmetic over all faces; here the arithmetic of 40 VALU
-// instructions and 3 transcendentals per (edge, point) bounds the point kernel.  Measured, whole
+// The all-pairs adjoint is bound by its arithmetic over all faces; here it is 40 VALU instructions and 3
+// transcendentals per (edge, point), issued at 1.1 VALU per CU and clock in the point kernel and 0.73 over blocks
+// (the all-pairs kernels: 1.5): few waves and idle lanes are the rest.  Measured, whole
 // adjoint: 7706 faces with 1154 boundary edges on 96 x 88 x 97 points, 10.0 -> 1.08 ms point by point,
-// 0.73 ms with nodes (k_edge_blocks); 9140 faces, 2.6 % of them missing, on 43 x 32 x 17 points, 519 -> 118 us.  The error
+// 0.72 ms with nodes (k_edge_blocks); 9140 faces, 2.6 % of them missing, on 43 x 32 x 17 points, 519 -> 118 us.  The error
 // against 64 bits falls too (1.3e-6 -> 1e-7 in the first): fewer terms, and none that cancel.
 #include <algorithm>
 
@@ -339,8 +340,8 @@ __global__ __launch_bounds__(kBlock) void k_edge_nodes(const char *table, int fi
 // the waves that had near edges took 864 us.
 // kRange: the call takes the parts [x0, x1) of a sequence, and a split goes on from its sums in `state`; else all
 // of them (an instance of its own: 1.5 % of the adjoint).
-// state: float2 [S][6][B].  40 VALU and 3 transcendentals per (edge, point) bound it: 1154 edges on
-// 96 x 88 x 97 voxels take 621 us, all points one by one 1024.
+// state: float2 [S][6][B].  Bound by 40 VALU and 3 transcendentals per (edge, point), a part of them in lanes that
+// wait: 1154 edges on 96 x 88 x 97 voxels take 621 to 700 us, all points one by one 1024.
 template <bool kRange>
 __global__ __launch_bounds__(64) void k_edge_blocks(const char *table, const float *__restrict__ dLdW,
                                                     const float *__restrict__ node, int S, int x0, int x1,

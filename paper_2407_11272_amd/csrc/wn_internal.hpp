@@ -506,8 +506,6 @@ hipError_t launch_pack(const float *V, int64_t nV, const int32_t *F, int64_t nF,
                        WsHeader *hdr, hipStream_t s);
 // Vertex records from (V, F) and an optional strip stream R ([nR][2] = vertex, face or
 // -1); with R == nullptr the stream is three records per face (nR = 3 nF).
-// counts / go (optional): the times a strip stream names each face, and a flag raised to 2
-// where the stream does not stand for F.
 hipError_t launch_pack_records(const float *V, int64_t nV, const int32_t *F, int64_t nF, const int32_t *R,
                                int64_t nR, VRec *recs, WsHeader *hdr, hipStream_t s);
 // st, mark, cursor (optional, device; wn_cycle.hpp): the launch does what the state asks for; the cursor starts at 0.
